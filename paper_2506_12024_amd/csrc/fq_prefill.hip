@@ -11,7 +11,7 @@
 //
 // Operand path.  Both slabs of a step -- x: 128 rows x 128 bytes, packed weights: 256 rows x
 // 32 / 64 / 128 bytes for 4-bit / 8-bit / fp16 -- go from global memory straight into LDS
-// (global_load_lds_dwordx4: no staging registers, a wavefront fetches whole rows), three
+// (buffer_load_dwordx4 ... lds: no staging registers, a wavefront fetches whole rows), three
 // stages deep (two for fp16 weights), one wait and one barrier per step.  Rows are stored 128 bytes apart (two 64-byte
 // or four 32-byte weight rows share such a line) with the 16-byte slots of a line XOR-ed by
 // (line >> 1) & 7, so that a 128-bit operand read of 16 consecutive rows touches every bank
@@ -40,17 +40,9 @@
 #include <type_traits>
 
 #include "fq_internal.h"
+#include "fq_mfma.h"
 
 namespace {
-
-#define FQ_GLOBAL __attribute__((address_space(1)))
-#define FQ_LDS __attribute__((address_space(3)))
-
-typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
-typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
-typedef float float16_t __attribute__((ext_vector_type(16)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int THREADS = 512;
 constexpr int WAVES = THREADS / 64;
@@ -109,35 +101,21 @@ constexpr int dma_loads()
 // PART = -1: all the loads of the slab; PART = p (0 .. 3): quarter p of them (those with index i,
 // i * 4 / LOADS = p), so that a step can issue its loads in four portions.
 template <int ROWS, int RB, int PART = -1>
-__device__ __forceinline__ void dma_slab(const uint8_t *tile, const DmaLane &L, int last_row, uint32_t pitch,
-                                         uint8_t *slab)
+__device__ __forceinline__ void dma_slab(__amdgpu_buffer_rsrc_t tile, uint32_t at, const DmaLane &L, int last_row,
+                                         uint32_t pitch, uint8_t *slab)
 {
-    const int wave = RB == 16 ? (threadIdx.x >> 6) & 3 : threadIdx.x >> 6;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = RB == 16 ? wv & 3 : wv;
     constexpr int LOADS = dma_loads<ROWS, RB>();
 #pragma unroll
     for (int i = 0; i < LOADS; i++) {
         if (PART >= 0 && (LOADS >= 4 ? i * 4 / LOADS : (LOADS == 2 ? 2 * i : 0)) != PART)
             continue;
         const uint32_t off = (uint32_t)min(L.r0 + i * L.rstep, last_row) * pitch + L.byte0;
-        __builtin_amdgcn_global_load_lds((const FQ_GLOBAL void *)(tile + off),
-                                         (FQ_LDS void *)(slab + (i * WAVES + wave) * 1024), 16, 0, 0);
+        load_to_lds<16>(tile, slab + (i * WAVES + wave) * 1024, off, at);
     }
 }
 
-// (a + b) * s, each operation rounded to half; a + b is the exact integer q - z
-__device__ __forceinline__ uint32_t deq(uint32_t a, uint32_t b, half2_t s)
-{
-    return __builtin_bit_cast(uint32_t, (__builtin_bit_cast(half2_t, a) + __builtin_bit_cast(half2_t, b)) * s);
-}
-
 __device__ __forceinline__ float as_float_global(const float *p) { return *(const FQ_GLOBAL float *)p; }
-
-__device__ __forceinline__ float16_t mfma32(const u32x4 a, const uint32_t (&b)[4], float16_t c)
-{
-    const u32x4 bv = {b[0], b[1], b[2], b[3]};
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8_t, a),
-                                                  __builtin_bit_cast(half8_t, bv), c, 0, 0, 0);
-}
 
 // Which 8 k of the 64-k step lane (row, c) supplies in k16-step i, as the index of the
 // 16-byte chunk of 8 halves in an x row:
@@ -201,7 +179,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const float *scales = BITS == 2 ? d.scales2 : BITS == 4 ? d.scales4 : d.scales8;
     const uint8_t *zeros = BITS == 2 ? d.zeros2 : BITS == 4 ? d.zeros4 : d.zeros8;
 
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int l32 = lane & 31, c = lane >> 5;
     const int wm = (wave & 1) * WM, wn = (wave >> 1) * WN;
 
@@ -243,6 +221,9 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const uint8_t *w_tile = codes + (size_t)n0 * w_pitch;
     const float *scales_tile = BITS == 16 ? nullptr : scales + (size_t)n0 * G;
     const uint8_t *zeros_tile = BITS == 16 ? nullptr : zeros + (size_t)n0 * G;
+    const uint32_t x_rows = (uint32_t)(min(x_last, BM - 1) + 1), w_rows = (uint32_t)(min(w_last, BN - 1) + 1);
+    const __amdgpu_buffer_rsrc_t xbuf = buffer_of(x_tile, x_rows * K * 2), wbuf = buffer_of(w_tile, w_rows * w_pitch);
+    const __amdgpu_buffer_rsrc_t sbuf = buffer_of(scales_tile, w_rows * G * 4), zbuf = buffer_of(zeros_tile, w_rows * G);
     // Scales and zero points of one quantization group for the tile's 256 weight rows also
     // come in through direct-to-LDS loads (a dword resp. a byte per lane; either lands in the
     // lane's dword slot, the byte zero-extended): wavefronts 0-3 fetch 64 scales each,
@@ -263,19 +244,15 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
                 if ((g & 3) != 0)
                     return; // (requested with the first group of its four)
                 if (wave < 4)
-                    __builtin_amdgcn_global_load_lds((const FQ_GLOBAL void *)(scales_tile + g + row),
-                                                     (FQ_LDS void *)(smeta + (wave & 3) * 256), 16, 0, 0);
+                    load_to_lds<16>(sbuf, smeta + (wave & 3) * 256, row * 4, g * 4);
                 else
-                    __builtin_amdgcn_global_load_lds((const FQ_GLOBAL void *)(zeros_tile + g + row),
-                                                     (FQ_LDS void *)(zmeta + (wave & 3) * 64), 4, 0, 0);
+                    load_to_lds<4>(zbuf, zmeta + (wave & 3) * 64, row, g);
                 return;
             }
             if (wave < 4)
-                __builtin_amdgcn_global_load_lds((const FQ_GLOBAL void *)(scales_tile + g + row),
-                                                 (FQ_LDS void *)(smeta + (wave & 3) * 64), 4, 0, 0);
+                load_to_lds<4>(sbuf, smeta + (wave & 3) * 64, row * 4, g * 4);
             else
-                __builtin_amdgcn_global_load_lds((const FQ_GLOBAL void *)(zeros_tile + g + row),
-                                                 (FQ_LDS void *)(zmeta + (wave & 3) * 64), 1, 0, 0);
+                load_to_lds<1>(zbuf, zmeta + (wave & 3) * 64, row, g);
         }
     };
 
@@ -321,15 +298,15 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
     };
     auto fetch = [&](int sf, auto st) { // step sf (clamped: always issued) into stage st
         const int sn = min(sf, nsteps - 1);
-        dma_slab<BM, XRB>(x_tile + sn * XRB, xl, x_last, K * 2, stage_x(st));
-        dma_slab<BN, WRB>(w_tile + sn * WRB, wl, w_last, w_pitch, stage_w(st));
+        dma_slab<BM, XRB>(xbuf, sn * XRB, xl, x_last, K * 2, stage_x(st));
+        dma_slab<BN, WRB>(wbuf, sn * WRB, wl, w_last, w_pitch, stage_w(st));
     };
     // the same in four portions (x: a load each; weights: one, two or four loads dealt over them)
     auto fetch_part = [&](int sf, auto st, auto part) {
         constexpr int P = decltype(part)::value;
         const int sn = min(sf, nsteps - 1);
-        dma_slab<BM, XRB, P>(x_tile + sn * XRB, xl, x_last, K * 2, stage_x(st));
-        dma_slab<BN, WRB, P>(w_tile + sn * WRB, wl, w_last, w_pitch, stage_w(st));
+        dma_slab<BM, XRB, P>(xbuf, sn * XRB, xl, x_last, K * 2, stage_x(st));
+        dma_slab<BN, WRB, P>(wbuf, sn * WRB, wl, w_last, w_pitch, stage_w(st));
     };
     fetch(0, std::integral_constant<int, 0>());
     if (NST == 3)

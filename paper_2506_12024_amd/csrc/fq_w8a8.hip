@@ -28,7 +28,7 @@
 // 128 tokens (2 x 2 tiles per wavefront) serves the launches whose tile count fits the chip
 // better that way.  One step = one
 // quantization group: both operand slabs of a step (192 and 256 rows x 128 bytes) are fetched
-// straight into LDS by global_load_lds_dwordx4 -- no staging registers, nothing for the
+// straight into LDS by buffer_load_dwordx4 ... lds -- no staging registers, nothing for the
 // register allocator to juggle -- double buffered, one wait and one barrier per step.
 // int8 doubles the MFMA rate and halves the bytes per operand element against the fp16
 // kernel, so the tile has to be this large to keep the L2 traffic per MFMA down.
@@ -37,10 +37,10 @@
 #include <type_traits>
 
 #include "fq_internal.h"
+#include "fq_mfma.h"
 
 namespace {
 
-#define FQ_GLOBAL __attribute__((address_space(1)))
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef int v4i __attribute__((ext_vector_type(4)));
@@ -168,18 +168,14 @@ __device__ __forceinline__ DmaLane dma_lane()
 // first k of the step) and is the same for the whole workgroup; rows past `last_row` (relative
 // to the tile) are clamped to it.  Every thread issues ROWS / 64 loads of 16 bytes.
 template <int ROWS>
-__device__ __forceinline__ void dma_slab(const uint8_t *tile, const DmaLane &L, int last_row, int K,
+__device__ __forceinline__ void dma_slab(__amdgpu_buffer_rsrc_t tile, uint32_t at, const DmaLane &L, int last_row, int K,
                                          uint8_t *slab)
 {
-    const int wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 #pragma unroll
     for (int i = 0; i < ROWS * 8 / THREADS; i++) {
-        // 32-bit offset from a scalar base: the load then takes the scalar-base form instead of
-        // needing a 64-bit address pair per chunk
         const uint32_t off = (uint32_t)min(L.r0 + i * (WAVES * 8), last_row) * (uint32_t)K + L.p16;
-        __builtin_amdgcn_global_load_lds((const FQ_GLOBAL void *)(tile + off),
-                                         (__attribute__((address_space(3))) void *)(slab + (i * WAVES + wave) * 1024),
-                                         16, 0, 0);
+        load_to_lds<16>(tile, slab + (i * WAVES + wave) * 1024, off, at);
     }
 }
 
@@ -194,10 +190,10 @@ __device__ __forceinline__ void dma_slab(const uint8_t *tile, const DmaLane &L, 
 // from there on.
 constexpr int MB = 8; // groups per block of metadata
 
-__device__ __forceinline__ void dma_meta(const float *scales_tile, const uint8_t *zeros_tile, uint32_t G, int w_last,
-                                         int block, float *sm, uint32_t *zm)
+__device__ __forceinline__ void dma_meta(__amdgpu_buffer_rsrc_t scales_tile, __amdgpu_buffer_rsrc_t zeros_tile, uint32_t G,
+                                         int w_last, int block, float *sm, uint32_t *zm)
 {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
 #pragma unroll
     for (int j = 0; j < 8; j++) {
         const int q = wave * 8 + j;
@@ -205,11 +201,9 @@ __device__ __forceinline__ void dma_meta(const float *scales_tile, const uint8_t
         const uint32_t g = min((uint32_t)(block * MB + gi), G - 1); // (past the last group: fetched again, never read)
         const uint32_t idx = (uint32_t)min(rb * 64 + lane, w_last) * G + g;
         if (q < 32)
-            __builtin_amdgcn_global_load_lds((const FQ_GLOBAL void *)(scales_tile + idx),
-                                             (__attribute__((address_space(3))) void *)(sm + gi * BN + rb * 64), 4, 0, 0);
+            load_to_lds<4>(scales_tile, sm + gi * BN + rb * 64, idx * 4, 0);
         else
-            __builtin_amdgcn_global_load_lds((const FQ_GLOBAL void *)(zeros_tile + idx),
-                                             (__attribute__((address_space(3))) void *)(zm + gi * BN + rb * 64), 1, 0, 0);
+            load_to_lds<1>(zeros_tile, zm + gi * BN + rb * 64, idx, 0);
     }
 }
 
@@ -240,7 +234,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
         return;
     const int m0 = (logical % m_tiles) * BM, n0 = (logical / m_tiles) * BN;
 
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int l32 = lane & 31, c = lane >> 5;
     const int wm = (wave & 1) * (MT * 32); // first token of this wavefront inside the tile
     const int wn = (wave >> 1) * WN;   // first weight row
@@ -266,15 +260,16 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const int nsteps = d.K / BKB;
     const DmaLane dl = dma_lane();
     const int x_last = d.M - 1 - m0, w_last = d.N - 1 - n0;
-    const uint8_t *x_tile = (const uint8_t *)d.xq + (size_t)m0 * d.K;
-    const uint8_t *w_tile = d.codes + (size_t)n0 * d.K;
+    const uint32_t x_rows = (uint32_t)(min(x_last, BM - 1) + 1), w_rows = (uint32_t)(min(w_last, BN - 1) + 1);
+    const __amdgpu_buffer_rsrc_t x_tile = buffer_of(d.xq + (size_t)m0 * d.K, x_rows * (uint32_t)d.K);
+    const __amdgpu_buffer_rsrc_t w_tile = buffer_of(d.codes + (size_t)n0 * d.K, w_rows * (uint32_t)d.K);
     const uint32_t G = (uint32_t)d.K >> 7;
     const uint32_t tok = (uint32_t)min((int)min(threadIdx.x, (unsigned)BM - 1), d.M - 1 - m0); // the thread's token (group sums)
-    const float *scales_tile = d.scales + (size_t)n0 * G;
-    const uint8_t *zeros_tile = d.zeros + (size_t)n0 * G;
+    const __amdgpu_buffer_rsrc_t scales_tile = buffer_of(d.scales + (size_t)n0 * G, w_rows * G * 4);
+    const __amdgpu_buffer_rsrc_t zeros_tile = buffer_of(d.zeros + (size_t)n0 * G, w_rows * G);
     const int32_t *xsum_tile = d.xsum + m0;
-    dma_slab<BM>(x_tile, dl, x_last, d.K, xs0);
-    dma_slab<BN>(w_tile, dl, w_last, d.K, ws0);
+    dma_slab<BM>(x_tile, 0, dl, x_last, d.K, xs0);
+    dma_slab<BN>(w_tile, 0, dl, w_last, d.K, ws0);
     dma_meta(scales_tile, zeros_tile, G, w_last, 0, sm[0], zm[0]);
     int sum_next = ((const FQ_GLOBAL int32_t *)xsum_tile)[tok];
     if (threadIdx.x < BM)
@@ -310,8 +305,8 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
             cur_z[j] = zm[(s >> 3) & 1][(s & (MB - 1)) * BN + wn + j * 32 + l32];
         }
         const int sn = min(s + 1, nsteps - 1); // always issued: the last step refetches itself
-        dma_slab<BM>(x_tile + sn * BKB, dl, x_last, d.K, ODD ? xs0 : xs1); // last read in step s-1: a barrier has passed
-        dma_slab<BN>(w_tile + sn * BKB, dl, w_last, d.K, ODD ? ws0 : ws1);
+        dma_slab<BM>(x_tile, sn * BKB, dl, x_last, d.K, ODD ? xs0 : xs1); // last read in step s-1: a barrier has passed
+        dma_slab<BN>(w_tile, sn * BKB, dl, w_last, d.K, ODD ? ws0 : ws1);
         if ((s & (MB - 1)) == 0) // the next block of scales and zero points; its buffer was last read a block ago
             dma_meta(scales_tile, zeros_tile, G, w_last, (s >> 3) + 1, sm[((s >> 3) + 1) & 1], zm[((s >> 3) + 1) & 1]);
         sum_next = ((const FQ_GLOBAL int32_t *)(xsum_tile + (size_t)sn * (size_t)d.M))[tok];
@@ -471,7 +466,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
     if (m0 >= d.M)
         return; // the second half of a last, partly filled tile
 
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int l32 = lane & 31, c = lane >> 5;
     const int wm = (wave & 1) * (RMT * 32);
     const int wn = (wave >> 1) * WN;
@@ -494,10 +489,11 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const int nsteps = d.K / BKB;
     const DmaLane dl = dma_lane();
     const int x_last = d.M - 1 - m0, w_last = d.N - 1 - n0;
-    const uint8_t *x_tile = (const uint8_t *)d.xq + (size_t)m0 * d.K;
-    const uint8_t *w_tile = d.codes + (size_t)n0 * d.K;
-    dma_slab<RBM>(x_tile, dl, x_last, d.K, xs0);
-    dma_slab<BN>(w_tile, dl, w_last, d.K, ws0);
+    const uint32_t x_rows = (uint32_t)(min(x_last, RBM - 1) + 1), w_rows = (uint32_t)(min(w_last, BN - 1) + 1);
+    const __amdgpu_buffer_rsrc_t x_tile = buffer_of(d.xq + (size_t)m0 * d.K, x_rows * (uint32_t)d.K);
+    const __amdgpu_buffer_rsrc_t w_tile = buffer_of(d.codes + (size_t)n0 * d.K, w_rows * (uint32_t)d.K);
+    dma_slab<RBM>(x_tile, 0, dl, x_last, d.K, xs0);
+    dma_slab<BN>(w_tile, 0, dl, w_last, d.K, ws0);
     // the tokens' sums over the whole row: the sum of their group sums
     if (threadIdx.x < RBM) {
         const int tok = min((int)threadIdx.x, d.M - 1 - m0);
@@ -512,8 +508,8 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
     auto step = [&](int s, auto odd) {
         constexpr bool ODD = decltype(odd)::value;
         const int sn = min(s + 1, nsteps - 1); // always issued: the last step refetches itself
-        dma_slab<RBM>(x_tile + sn * BKB, dl, x_last, d.K, ODD ? xs0 : xs1); // last read in step s-1: a barrier has passed
-        dma_slab<BN>(w_tile + sn * BKB, dl, w_last, d.K, ODD ? ws0 : ws1);
+        dma_slab<RBM>(x_tile, sn * BKB, dl, x_last, d.K, ODD ? xs0 : xs1); // last read in step s-1: a barrier has passed
+        dma_slab<BN>(w_tile, sn * BKB, dl, w_last, d.K, ODD ? ws0 : ws1);
         // The requests stay here, ahead of the step's arithmetic: left to itself the scheduler sinks them to
         // the end of the step, just before the wait for them (1.49 instead of 1.74 POP/s).
         __builtin_amdgcn_sched_barrier(0);
