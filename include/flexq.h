@@ -79,6 +79,7 @@ typedef struct fq_plan fq_plan;   /* opaque: a list of linears run by one launch
 #define FQ_MAX_DECODE_M 32 /* rows of x served by the skinny (decode) kernels */
 #define FQ_MAX_DECODE_K 32768 /* longest row they take (a row of x stays in LDS at M = 1) */
 #define FQ_MAX_LM_HEAD_M 4 /* rows of x served by fq_lm_head_entropy */
+#define FQ_PART_STREAMS 4 /* streams per device with an array for the partial sums of products split along K */
 #define FQ_SCRATCH_BANKS 16 /* streams per device with a copy of their own of the library's static
                                scratch (fq_entropy_kl over a few rows, fq_lm_head_entropy) */
 
@@ -167,6 +168,10 @@ int fq_layer_destroy(fq_layer *layer);
  * kernels; anything else (prefill-shaped, any M >= 1) runs the MFMA dequant-GEMM -- but for
  * bits = 3, which the GEMM does not unpack: there the small-batch kernel runs the call in slabs of
  * FQ_MAX_DECODE_M rows of x, one launch per slab, reading the weights once per slab.
+ * GEMM calls with too few output tiles for the chip split K and add the parts, in binary32 and in a fixed
+ * order, through a static device array of the library (16 MiB for each of the first FQ_PART_STREAMS streams of a
+ * device that make such a call).  Calls on further streams, on hipStreamPerThread and under stream capture use no such
+ * array: they take longer and give the same bits, so any of these calls may overlap.
  */
 int fq_linear(const fq_layer *layer, int bits, const void *x_fp16, int M,
               void *y_fp16, void *stream);

@@ -30,6 +30,8 @@ struct DeviceFacts {
     size_t raised_to[MAX_KERNEL_FACTS];
     int n_banks;
     hipStream_t bank_stream[FQ_BANKS]; // the stream that bank i of the static scratch arrays belongs to
+    int n_part_banks;
+    hipStream_t part_stream[FQ_PART_BANKS]; // the same for the partial sums of products split along K
 };
 
 std::mutex g_lock;
@@ -82,19 +84,30 @@ int fq_workgroups_per_cu(const void *func, int threads, size_t lds, int fallback
     return per_cu;
 }
 
+// The index of `stream` in a table of at most `most` streams, entered if there is room; -1 if not.
+static int bank_of(hipStream_t *table, int &n, int most, hipStream_t stream)
+{
+    for (int i = 0; i < n; i++)
+        if (table[i] == stream)
+            return i;
+    if (n == most)
+        return -1;
+    table[n] = stream;
+    return n++;
+}
+
 int fq_stream_bank(hipStream_t stream)
 {
     std::lock_guard<std::mutex> hold(g_lock);
     DeviceFacts *d = current();
-    if (!d)
-        return -1;
-    for (int i = 0; i < d->n_banks; i++)
-        if (d->bank_stream[i] == stream)
-            return i;
-    if (d->n_banks == FQ_BANKS)
-        return -1;
-    d->bank_stream[d->n_banks] = stream;
-    return d->n_banks++;
+    return d ? bank_of(d->bank_stream, d->n_banks, FQ_BANKS, stream) : -1;
+}
+
+int fq_part_bank(hipStream_t stream)
+{
+    std::lock_guard<std::mutex> hold(g_lock);
+    DeviceFacts *d = current();
+    return d && stream != hipStreamPerThread ? bank_of(d->part_stream, d->n_part_banks, FQ_PART_BANKS, stream) : -1;
 }
 
 hipError_t fq_raise_dynamic_lds(const void *func, size_t bytes)

@@ -59,6 +59,10 @@ hipError_t fq_raise_dynamic_lds(const void *func, size_t bytes);
 // current device (the first FQ_BANKS distinct streams get one each), or -1 if none is left.
 constexpr int FQ_BANKS = 16; // FQ_SCRATCH_BANKS of the public header
 int fq_stream_bank(hipStream_t stream);
+// The same for the partial sums of products split along K, whose copies are larger and fewer; -1 also for
+// hipStreamPerThread, one handle for as many streams as there are threads.
+constexpr int FQ_PART_BANKS = 4;
+int fq_part_bank(hipStream_t stream);
 
 hipError_t fq_launch_quantize(const void *w, long long n_groups, int bits, bool symmetric, void *codes,
                               void *scales, void *zeros, hipStream_t stream);
@@ -135,9 +139,18 @@ hipError_t fq_launch_sched_step(FqSchedState *s, const float *entropy, hipStream
 hipError_t fq_launch_rank_ascending(const float *values, int n, int m, int32_t *order,
                                     hipStream_t stream);
 
-// Prefill-shaped dequant-GEMM on MFMA.
+// Prefill-shaped dequant-GEMM on MFMA (hands the call to fq_launch_prompt where that is expected to be faster).
 hipError_t fq_launch_prefill(const FqLinearDesc &d, int bits, int M, hipStream_t stream);
 
+
+// The same product on smaller tiles and segments of K: 32 * mt tokens x 128 rows, `segments` of K; mt = 0: the
+// large tiles serve this shape better.  The plan depends on the shape and the device only, and the result
+// on the plan only.
+struct FqPromptPlan {
+    int mt, segments;
+};
+FqPromptPlan fq_prompt_plan(int N, int K, int bits, int M, int cus);
+hipError_t fq_launch_prompt(const FqLinearDesc &d, int bits, int M, FqPromptPlan plan, hipStream_t stream);
 
 // W8A8 prefill: per-token symmetric 8-bit activation quantization (also writes the per-group
 // code sums, [K/128][M]) and the int8 MFMA GEMM against the resident 8-bit copy.

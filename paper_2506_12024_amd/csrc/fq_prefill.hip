@@ -509,6 +509,10 @@ static hipError_t launch_prefill(const FqLinearDesc &d, int bits, int M, int m_t
 
 hipError_t fq_launch_prefill(const FqLinearDesc &d, int bits, int M, hipStream_t stream)
 {
+    const int cus = fq_device_cus();
+    const FqPromptPlan plan = fq_prompt_plan(d.N, d.K, bits, M, cus);
+    if (plan.mt > 0)
+        return fq_launch_prompt(d, bits, M, plan, stream);
     const int m_tiles = (M + BM_FULL - 1) / BM_FULL, n_tiles = (d.N + BN - 1) / BN;
     const long long total = (long long)m_tiles * n_tiles;
     if (total > 0x3fffffffLL)
@@ -518,7 +522,6 @@ hipError_t fq_launch_prefill(const FqLinearDesc &d, int bits, int M, hipStream_t
     // count.  What is left for the last round, if it would fill at most half the CUs, runs as half
     // tiles in a second launch (2048 x 28672: 112 tiles per XCD = 3 rounds of 32 + 16 tiles, which
     // then take half a round instead of a whole one).
-    const int cus = fq_device_cus();
     const int per_round = cus / 8 > 0 ? cus / 8 : 1;
     const int rest = per_xcd % per_round;
     const int tail = rest > 0 && 2 * rest <= per_round ? rest : 0;

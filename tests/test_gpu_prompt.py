@@ -1,0 +1,64 @@
+"""fq_linear for prompts of some tens to some hundreds of rows (csrc/fq_prompt.hip): tokens at the edges of
+its blocks of 32 and of its tiles, rows at the edges of 128, one to many groups of K (its scales come
+eight groups at a time, its steps three to a turn), one and several segments of K, against the oracle; and
+that the result is the same bits wherever the partial sums of the segments are kept."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+import paper_2506_12024_amd as fq
+from gpu_util import DEV, gpu_linear, make_layer, rel_err, to_dev
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(33, 127, 128), (64, 129, 256), (65, 1, 1152), (96, 640, 2176), (97, 300, 1024), (128, 512, 8192),
+          (129, 257, 1280), (200, 384, 4224), (333, 1000, 2048), (40, 2048, 5504)]
+
+
+@pytest.mark.parametrize("bits", [2, 4, 8, 16])
+@pytest.mark.parametrize("M,N,K", SHAPES)
+def test_prompt_matches_oracle(M, N, K, bits):
+    name = "prompt/%dx%dx%d" % (M, N, K)
+    w = synth.weight(11, name + "/w", N, K, 0.02, outlier_p=0.001)
+    w[N // 2, :128] = 0.0  # an all-zero group: scale 1
+    x = synth.activations(11, name + "/x", M, K)
+    layer, packed = make_layer(w, (bits,))
+    y = gpu_linear(layer, bits, x)
+    if bits == 16:
+        ref = oracle.linear(x, w, None, None, 16)
+    else:
+        c, s, z = (t.cpu().numpy() for t in packed[bits])
+        ref = oracle.linear(x, c, s, z, bits)
+    assert np.isfinite(y.astype(np.float32)).all()
+    # the operand is rounded to half twice, 2^-11 relative each (csrc/fq_prefill.hip): 2e-3 of the largest output
+    assert rel_err(y, ref) <= 2e-3
+
+
+def test_same_bits_with_and_without_partial_sums():
+    """The default stream and some others own an array for the segments' sums; further streams and
+    captured calls add the segments inside one workgroup, in the same order."""
+    M, N, K = 100, 512, 8192
+    layer, _ = make_layer(synth.weight(11, "prompt/banks/w", N, K, 0.02), (4,))
+    x = to_dev(synth.activations(11, "prompt/banks/x", M, K))
+    want = torch.empty((M, N), dtype=torch.float16, device=DEV)
+    fq.fq_linear(layer, 4, x, M, want)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(6)]
+    ys = [torch.full((M, N), float("nan"), dtype=torch.float16, device=DEV) for _ in streams]
+    for _ in range(4):  # overlapping calls
+        for st, y in zip(streams, ys):
+            fq.fq_linear(layer, 4, x, M, y, stream=st)
+    torch.cuda.synchronize()
+    for y in ys:
+        assert torch.equal(y, want)
+    graph, y = torch.cuda.CUDAGraph(), torch.full((M, N), float("nan"), dtype=torch.float16, device=DEV)
+    with torch.cuda.graph(graph):
+        fq.fq_linear(layer, 4, x, M, y)
+    for _ in range(3):
+        y.fill_(float("nan"))
+        graph.replay()
+        fq.fq_linear(layer, 4, x, M, ys[0])
+        torch.cuda.synchronize()
+        assert torch.equal(y, want) and torch.equal(ys[0], want)
