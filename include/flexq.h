@@ -289,7 +289,7 @@ int fq_stream_read(const void *src, size_t bytes, uint32_t *sink, void *stream);
  * the sum over g is one term: the whole row is summed exactly in int32 and scaled once,
  * y[m][n] = fp16( s_x[m] * (s[n] * float( sum_k xq[m][k] (q[n][k] - z[n]) )) ).
  *   y_fp16  device, fp16 [M][N], 2-byte aligned             (written)
- * M >= 1.
+ * M >= 1.  Calls with few output tiles split K, as fq_linear's GEMM calls do.
  */
 int fq_quantize_act(const void *x_fp16, int M, int K, void *xq, float *sx, int32_t *xsum,
                     void *stream);

@@ -63,6 +63,10 @@ int fq_stream_bank(hipStream_t stream);
 // hipStreamPerThread, one handle for as many streams as there are threads.
 constexpr int FQ_PART_BANKS = 4;
 int fq_part_bank(hipStream_t stream);
+// The stream's array for such sums (FQ_PART_FLOATS words), null if it has none or is being captured: the caller
+// then adds the parts inside one workgroup, in the same order.
+constexpr size_t FQ_PART_FLOATS = (size_t)4 << 20; // 16 MiB: 256 workgroups' tiles of 128 x 128
+hipError_t fq_part_array(hipStream_t stream, float **part);
 
 hipError_t fq_launch_quantize(const void *w, long long n_groups, int bits, bool symmetric, void *codes,
                               void *scales, void *zeros, hipStream_t stream);
@@ -159,6 +163,12 @@ hipError_t fq_launch_quantize_act(const void *x, int M, int K, void *xq, float *
 // per_row: the 8-bit copy has one scale and zero point per weight row (group = K) instead of per 128 inputs
 hipError_t fq_launch_w8a8(const FqLinearDesc &d, const void *xq, const float *sx, const int32_t *xsum,
                           int M, bool per_row, hipStream_t stream);
+
+// The same on smaller tiles and segments of K (mt: 64-token blocks of a tile; 0: the large tiles, of 64 * large_mt
+// tokens for groups of 128, serve the shape better).
+FqPromptPlan fq_w8a8_prompt_plan(int N, int K, int M, bool per_row, int large_mt, int cus);
+hipError_t fq_launch_w8a8_prompt(const FqLinearDesc &d, const void *xq, const float *sx, const int32_t *xsum, int M,
+                                 bool per_row, FqPromptPlan plan, hipStream_t stream);
 
 // Output layer (fp16 weight [V][K], 1 <= M <= 4 rows of x) fused with entropy and argmax of its logits.
 hipError_t fq_launch_lm_head_entropy(const void *x, const void *w, int M, int V, int K, float *logits, float *H,

@@ -116,4 +116,44 @@ __device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t r, void *lds,
         __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (FQ_LDS void *)lds, 1, (int)lane_off, (int)off, 0, 0);
 }
 
+// Byte offset of 16-byte piece `ch` of row `r` of a slab with RB bytes per row.  The pieces of a 256-byte line
+// are permuted so that a read of one piece of 16 consecutive rows touches every bank once, rows 0 .. 7 in one half
+// of the bank row and rows 8 .. 15 in the other.
+template <int RB>
+__device__ __forceinline__ int w_offset(int r, int ch)
+{
+    const int blk = r >> 4, q = r & 15;
+    if (RB == 256)
+        return r * 256 + ((ch ^ q) << 4);
+    if (RB == 128)
+        return blk * 2048 + (q & 7) * 256 + (((q >> 3) * 8 + (ch ^ (q & 7))) << 4);
+    if (RB == 64)
+        return blk * 1024 + ((q >> 1) & 3) * 256 + ((((q >> 3) * 2 + (q & 1)) * 4 + (ch ^ ((q >> 1) & 3))) << 4);
+    return (r >> 3) * 256 + (((r & 7) * 2 + (ch ^ ((r >> 3) & 1))) << 4); // 32
+}
+
+// The inverse: the row and the byte inside the row that lane `lane` of the load fetches that fills bytes ld * 1024
+// .. + 1023 of the slab, 16 per lane.
+template <int RB>
+__device__ __forceinline__ void w_piece(int ld, int lane, int &row, int &byte)
+{
+    const int line = lane >> 4, slot = lane & 15;
+    if (RB == 256) {
+        row = ld * 4 + line;
+        byte = (slot ^ (row & 15)) << 4;
+    } else if (RB == 128) {
+        const int l = (ld & 1) * 4 + line;
+        row = (ld >> 1) * 16 + (slot >> 3) * 8 + l;
+        byte = ((slot & 7) ^ l) << 4;
+    } else if (RB == 64) {
+        const int q = slot >> 2;
+        row = ld * 16 + (q >> 1) * 8 + line * 2 + (q & 1);
+        byte = ((slot & 3) ^ line) << 4;
+    } else {
+        const int l8 = ld * 4 + line;
+        row = l8 * 8 + (slot >> 1);
+        byte = ((slot & 1) ^ (l8 & 1)) << 4;
+    }
+}
+
 #endif

@@ -44,7 +44,7 @@ constexpr int MAX_SEGMENTS = 16;
 // different streams may overlap); any other call -- a further stream, one being captured, whose graph may
 // be replayed beside anything -- walks its segments inside one workgroup, adding them in the same order:
 // slower, the same bits, no array.
-constexpr size_t PART_FLOATS = (size_t)4 << 20; // 16 MiB: 256 workgroups' tiles of 128 x 128
+constexpr size_t PART_FLOATS = FQ_PART_FLOATS;
 __device__ __attribute__((aligned(256))) float g_part[FQ_PART_BANKS][PART_FLOATS];
 
 // Which 8 k of its 64-k half lane (row, c) supplies in k16-step i, as the index of a 16-byte piece of x.  A lane
@@ -54,44 +54,6 @@ template <int BITS>
 __device__ __forceinline__ int x_chunk(int i, int c)
 {
     return BITS == 4 || BITS == 2 ? 4 * c + i : BITS == 8 ? 4 * (i >> 1) + 2 * c + (i & 1) : 2 * i + c;
-}
-
-// Byte offset of 16-byte chunk `ch` of row `r` of a slab of packed weights with RB bytes per row.
-template <int RB>
-__device__ __forceinline__ int w_offset(int r, int ch)
-{
-    const int blk = r >> 4, q = r & 15;
-    if (RB == 256)
-        return r * 256 + ((ch ^ q) << 4);
-    if (RB == 128)
-        return blk * 2048 + (q & 7) * 256 + (((q >> 3) * 8 + (ch ^ (q & 7))) << 4);
-    if (RB == 64)
-        return blk * 1024 + ((q >> 1) & 3) * 256 + ((((q >> 3) * 2 + (q & 1)) * 4 + (ch ^ ((q >> 1) & 3))) << 4);
-    return (r >> 3) * 256 + (((r & 7) * 2 + (ch ^ ((r >> 3) & 1))) << 4); // 32
-}
-
-// The inverse for load `i` of wavefront `w`: the row and the byte inside the row that lane `lane` of
-// it fetches (the load fills bytes (i * WAVES + w) * 1024 .. + 1023 of the slab, 16 per lane).
-template <int RB>
-__device__ __forceinline__ void w_piece(int i, int w, int lane, int &row, int &byte)
-{
-    const int ld = i * WAVES + w, line = lane >> 4, slot = lane & 15;
-    if (RB == 256) {
-        row = ld * 4 + line;
-        byte = (slot ^ (row & 15)) << 4;
-    } else if (RB == 128) {
-        const int l = (ld & 1) * 4 + line;
-        row = (ld >> 1) * 16 + (slot >> 3) * 8 + l;
-        byte = ((slot & 7) ^ l) << 4;
-    } else if (RB == 64) {
-        const int q = slot >> 2;
-        row = ld * 16 + (q >> 1) * 8 + line * 2 + (q & 1);
-        byte = ((slot & 3) ^ line) << 4;
-    } else {
-        const int l8 = ld * 4 + line;
-        row = l8 * 8 + (slot >> 1);
-        byte = ((slot & 1) ^ (l8 & 1)) << 4;
-    }
 }
 
 // MT: blocks of 32 tokens of a tile.
@@ -170,7 +132,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 #pragma unroll
     for (int i = 0; i < T::WL; i++) {
         int r, b;
-        w_piece<T::WRB>(i, wwave, lane, r, b);
+        w_piece<T::WRB>(i * WAVES + wwave, lane, r, b);
         woff[i] = (uint32_t)min(r, w_last) * w_pitch + b;
     }
     // Scales and zero points, MB groups at a time: load i of wavefront w covers rows (i * 8 + w) * 8 .. + 7,
@@ -545,20 +507,27 @@ FqPromptPlan fq_prompt_plan(int N, int K, int bits, int M, int cus)
     return best;
 }
 
+hipError_t fq_part_array(hipStream_t stream, float **part)
+{
+    *part = nullptr;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone)
+        return hipSuccess;
+    const int bank = fq_part_bank(stream);
+    if (bank < 0)
+        return hipSuccess;
+    hipError_t e = hipGetSymbolAddress((void **)part, HIP_SYMBOL(g_part));
+    if (e == hipSuccess)
+        *part += (size_t)bank * PART_FLOATS;
+    return e;
+}
+
 hipError_t fq_launch_prompt(const FqLinearDesc &d, int bits, int M, FqPromptPlan plan, hipStream_t stream)
 {
     float *part = nullptr;
-    if (plan.segments > 1) {
-        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        const bool eager = hipStreamIsCapturing(stream, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone;
-        const int bank = eager ? fq_part_bank(stream) : -1;
-        if (bank >= 0) {
-            hipError_t e = hipGetSymbolAddress((void **)&part, HIP_SYMBOL(g_part));
-            if (e != hipSuccess)
-                return e;
-            part += (size_t)bank * PART_FLOATS;
-        }
-    }
+    if (plan.segments > 1)
+        if (const hipError_t e = fq_part_array(stream, &part))
+            return e;
     return bits == 2   ? launch_mt<2>(d, M, plan.mt, plan.segments, part, stream)
            : bits == 4 ? launch_mt<4>(d, M, plan.mt, plan.segments, part, stream)
            : bits == 8 ? launch_mt<8>(d, M, plan.mt, plan.segments, part, stream)

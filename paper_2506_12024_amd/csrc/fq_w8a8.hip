@@ -619,6 +619,9 @@ hipError_t fq_launch_w8a8(const FqLinearDesc &l, const void *xq, const float *sx
         if (((t2 + c - 1) / c) * 2 * 8 < ((t3 + c - 1) / c) * 3 * 7)
             mt = 2;
     }
+    const FqPromptPlan plan = fq_w8a8_prompt_plan(l.N, l.K, M, per_row, mt, cus > 0 ? cus : 1);
+    if (plan.mt > 0)
+        return fq_launch_w8a8_prompt(l, xq, sx, xsum, M, per_row, plan, stream);
     const int bm = per_row ? RBM_FULL : 2 * mt * 32;
     const int m_tiles = (M + bm - 1) / bm;
     const long long total = (long long)m_tiles * n_tiles;

@@ -1,7 +1,8 @@
 """fq_linear for prompts of some tens to some hundreds of rows (csrc/fq_prompt.hip): tokens at the edges of
 its blocks of 32 and of its tiles, rows at the edges of 128, one to many groups of K (its scales come
 eight groups at a time, its steps three to a turn), one and several segments of K, against the oracle; and
-that the result is the same bits wherever the partial sums of the segments are kept."""
+that the result is the same bits wherever the partial sums of the segments are kept.  The same for the W8A8
+product (csrc/fq_w8a8_prompt.hip) with groups of 128 and with one scale per row."""
 import numpy as np
 import pytest
 import torch
@@ -34,6 +35,27 @@ def test_prompt_matches_oracle(M, N, K, bits):
     assert np.isfinite(y.astype(np.float32)).all()
     # the operand is rounded to half twice, 2^-11 relative each (csrc/fq_prefill.hip): 2e-3 of the largest output
     assert rel_err(y, ref) <= 2e-3
+
+
+@pytest.mark.parametrize("per_row", [False, True])
+@pytest.mark.parametrize("M,N,K", SHAPES + [(1, 640, 1152), (192, 384, 2816), (193, 128, 896)])
+def test_w8a8_prompt_matches_oracle(M, N, K, per_row):
+    name = "prompt8/%dx%dx%d" % (M, N, K)
+    group = K if per_row else 128
+    w = synth.weight(12, name + "/w", N, K, 0.02, outlier_p=0.001)
+    x = synth.activations(12, name + "/x", M, K)
+    layer, packed = make_layer(w, (8,), group)
+    xq, sx, xsum = (torch.empty(s, dtype=t, device=DEV) for s, t in
+                    (((M, K), torch.int8), ((M,), torch.float32), ((K // 128, M), torch.int32)))
+    y = torch.full((M, N), float("nan"), dtype=torch.float16, device=DEV)
+    fq.fq_quantize_act(to_dev(x), M, K, xq, sx, xsum)
+    fq.fq_linear_w8a8(layer, xq, sx, xsum, M, y)
+    torch.cuda.synchronize()
+    c, s, z = (t.cpu().numpy() for t in packed[8])
+    ref = oracle.linear_w8a8(xq.cpu().numpy(), sx.cpu().numpy(), c.reshape(N, K), s.reshape(N, -1), z.reshape(N, -1), group)
+    # exact integers inside a group, binary32 sums of groups: the rounding of the result to fp16, 2^-11, and the
+    # W8A8 tests' bound of 2e-3
+    assert rel_err(y.cpu().numpy(), ref) <= 2e-3
 
 
 def test_same_bits_with_and_without_partial_sums():
