@@ -300,6 +300,12 @@ int fq_linear(const fq_layer *layer, int bits, const void *x_fp16, int M, void *
             e = fq_launch_skinny(&d, bits, nullptr, nullptr, 1, tiles, rows, m, true, nullptr, nullptr, (hipStream_t)stream);
         }
     } else if (M <= FQ_MAX_DECODE_M && layer->K <= MAX_DECODE_K) {
+        if (M > 1 && bits != 2 && bits != 3) { // (the packings of 2 and 3 bits: the register-fed kernel)
+            e = fq_launch_batch(&d, bits, nullptr, nullptr, 1, (layer->N + 15) / 16, M, nullptr, (hipStream_t)stream);
+            if (e != hipSuccess)
+                return hip_fail(e, "fq_linear launch");
+            return FQ_OK;
+        }
         int rows = M == 1 ? fq_decode_tile_rows(layer->N, layer->K, M) : fq_skinny_tile_rows(layer->N, M);
         if (M > 1 && bits == 2 && rows == 16) // the K-split kernel takes 3, 4, 8 and 16 bits
             rows = 64;
@@ -419,6 +425,9 @@ int fq_plan_layout(const char *who, int count, const fq_layer *const *layers, co
     // token, runs on the register-fed kernel
     if (M > 1 && has3 && rows == 256)
         rows = 128;
+    geom->batch = M > 1 && rows != 256 && !has2 && !has3 && fq_batch_serves(count, total_rows) ? 1 : 0;
+    if (geom->batch)
+        rows = 16;
     long long tiles = 0;
     for (int i = 0; i < count; i++) {
         fill_desc(table[i], layers[i], xs[i], ys[i]);
@@ -442,6 +451,9 @@ static_assert(FQ_BANKS == FQ_SCRATCH_BANKS && FQ_PART_BANKS == FQ_PART_STREAMS,
 hipError_t fq_plan_launch(const FqPlanGeom &g, const FqLinearDesc *table_dev, int *queue_dev, void *order_dev,
                           const int32_t *bits_dev, hipStream_t stream)
 {
+    if (g.batch)
+        return fq_launch_batch(nullptr, 0, table_dev, bits_dev, g.count, g.total_tiles, g.M, queue_dev ? queue_dev + FQ_Q_FLAGS : nullptr,
+                               stream);
     hipError_t e = g.M == 1
         ? fq_launch_decode(nullptr, 0, table_dev, bits_dev, g.count, g.total_tiles, g.tile_rows, g.max_K, g.M,
                            queue_dev ? queue_dev + FQ_Q_FLAGS : nullptr, stream)

@@ -1,0 +1,380 @@
+// Decode-phase weight-only quantized linear for small batches (2 <= M <= 32): single calls and plans of the
+// size a decoder's stages have (q/k/v, o, gate/up, down of one layer; up to 64 entries), 4, 8 and 16 bits; y[M][N] =
+// x[M][K] . dequant(W[N][K])^T, dequant = Sec. 2.2 Eq. (3).  Bound by the weight stream (Sec. 4.1) on paper; a launch of
+// 10 to 90 MB lasts 8 to 25 us, so that its start, its end and an even division count as much.
+//
+// Work split.  One workgroup (8 wavefronts) per compute unit.  The launch's tiles of 16 weight rows are divided
+// among them by cost (tile_cost), a contiguous run each; every workgroup works the division out from the
+// entries' shapes and the bit-widths it finds in device memory, one entry per lane.  Within a tile the wavefronts
+// split K: wavefront w takes the 128-byte lines w, w + 8, ... of all 16 rows, so that a step of the workgroup reads
+// 1 KiB of each row, and their sums meet in LDS at the end, added in the wavefronts' order.
+//
+// x sits in LDS, 128 KiB of it at a time (4096 inputs of 16 batch rows, 2048 of 32), brought by direct-to-LDS loads
+// in slabs of 64 inputs whose 16-byte pieces are permuted (w_offset) so that operand reads are conflict free; the
+// 11008 x 4096 projections stay in one panel, and entries that share x (q, k, v) do not fetch it again.  Scales and
+// zero points of the run's tiles are laid beside it.  Weights go straight to registers: lane (n, c) takes 16 bytes of
+// each half line of row n, the operand layout of v_mfma_f32_16x16x32_f16 up to a permutation of the inputs that x
+// shares, RD lines ahead.
+//
+// Measured (us at 16 batch rows, 4 / 8 / 16 bits, cold weights; before: the register-fed kernel with K split between four
+// wavefronts below 8192 rows and 64-row tiles above): 4096 x 4096 9.1 / 11.3 / 14.2 -> 8.5 / 9.5 / 11.3; 11008 rows x 4096
+// 17.3 / 26.3 / 36.4 -> 11.0 / 14.9 / 20.8; 4096 rows x 11008 17.7 / 24.1 / 30.8 -> 14.4 / 19.1 / 25.8; 22016 rows x 4096
+// 23.8 / 34.8 / 47.0 -> 16.7 / 24.2 / 39.5.  What was found on the way: requests past a run's end must cost nothing (as
+// re-reads of the last line, 8 ahead, they made 4096 x 4096 cost 12 us: the loads' line accesses, not HBM, were the
+// limit) -- they ask beyond the buffer's end; two lines ahead are as fast as eight (19.6 against 23.8 us at 22016 rows);
+// sixteen wavefronts the same as eight; without the arithmetic 16.6 instead of 19.3 us, without x 1.1 us less.  What
+// bounds it now: 4.3 us of launch, division and end, the ramp of the first request, and tiles that do not
+// divide evenly (22016 rows are 5.4 per workgroup).
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+#include <type_traits>
+
+#include "fq_internal.h"
+#include "fq_mfma.h"
+
+namespace {
+
+constexpr int THREADS = 512;
+constexpr int WAVES = 8;
+constexpr int XBYTES = 128 * 1024; // x of a panel
+constexpr int NB = 6;              // tiles of 16 rows a workgroup takes at a time
+constexpr int RD = 2;              // 128-byte lines of each row a wavefront has in flight
+constexpr int MAX_ENTRIES = 64;
+
+__device__ __forceinline__ float4_t mfma16(const u32x4 a, const uint32_t (&b)[4], float4_t c)
+{
+    const u32x4 bv = {b[0], b[1], b[2], b[3]};
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a), __builtin_bit_cast(half8_t, bv), c, 0, 0, 0);
+}
+
+__device__ __forceinline__ uint32_t pk_add(uint32_t a, uint32_t b)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, a) + __builtin_bit_cast(half2_t, b));
+}
+
+struct Lds {
+    __attribute__((aligned(1024))) uint8_t x[XBYTES];
+    float s[NB * 16 * 33];
+    uint8_t z[NB * 16 * 33];
+    float4_t red[2 * WAVES * 64];
+};
+
+// The tiles [t0, t0 + nt) of one entry.
+template <int BITS, int MB>
+__device__ __forceinline__ void run_batch(Lds &L, const uint8_t *codes, const float *scales, const uint8_t *zeros,
+                                          const uint16_t *x, uint16_t *y, int N, int K, int M, int t0, int nt, bool x_there)
+{
+    constexpr int KP = XBYTES / (32 * MB); // inputs of a panel: 4096 or 2048
+    constexpr int GP = KP / 128, GS = GP + 1; // groups of a panel; their stride in LDS
+    constexpr int KL = 1024 / BITS;        // inputs of a line: 256 / 128 / 64
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int n = lane & 15, c = lane >> 4;
+    const uint32_t row_bytes = (uint32_t)K * BITS / 8;
+    const int G = K >> 7;
+    const int n0 = t0 * 16;
+    float4_t sum[NB][MB];
+#pragma unroll
+    for (int t = 0; t < NB; t++)
+#pragma unroll
+        for (int mb = 0; mb < MB; mb++)
+            sum[t][mb] = float4_t{0.f, 0.f, 0.f, 0.f};
+    const __amdgpu_buffer_rsrc_t xbuf = buffer_of(x, (uint32_t)M * (uint32_t)K * 2);
+    const __amdgpu_buffer_rsrc_t wbuf = buffer_of(codes + (size_t)n0 * row_bytes, (uint32_t)min(nt * 16, N - n0) * row_bytes);
+    const uint32_t lane_off = (uint32_t)n * row_bytes + c * 16;
+    // x operand reads: piece p of batch row n in a slab of 64 inputs
+    uint32_t xat[8];
+#pragma unroll
+    for (int i = 0; i < 8; i++)
+        xat[i] = BITS == 4   ? (uint32_t)((c >> 1) * 2048 * MB + w_offset<128>(n, 4 * (c & 1) + (i & 3)))
+                 : BITS == 8 ? (uint32_t)w_offset<128>(n, 2 * c + (i & 1))
+                             : (uint32_t)w_offset<128>(n, 4 * (i & 1) + c);
+    DeqMagic<BITS> mg;
+    mg.pin();
+
+    for (int k0 = 0; k0 < K; k0 += KP) {
+        const int kp = min(KP, K - k0), gp = kp >> 7, g0 = k0 >> 7;
+        if (k0 > 0 || !x_there) {
+            if (k0 > 0)
+                __syncthreads(); // every wavefront is done with the panel before
+            const int loads = kp / 64 * 2 * MB;
+            // (every workgroup reads this x: each starts somewhere else in it, or they would all ask the same
+            // L2 channel at the same time)
+            const int first = (int)((blockIdx.x >> 3) * 37u % 32u) * (loads >> 5);
+            for (int j0 = wave; j0 < loads; j0 += WAVES) {
+                const int j = j0 + first < loads ? j0 + first : j0 + first - loads;
+                int r, b;
+                w_piece<128>(j & 1, lane, r, b);
+                const int mb = MB == 2 ? (j >> 1) & 1 : 0, slab = j / (2 * MB);
+                load_to_lds<16>(xbuf, L.x + j * 1024, (uint32_t)min(mb * 16 + r, M - 1) * (uint32_t)K * 2 + b,
+                                (uint32_t)(k0 + slab * 64) * 2);
+            }
+        }
+        // lines of this panel; a wavefront takes every eighth, tile after tile
+        const int lines = (kp + KL - 1) / KL, mine = (lines - wave + WAVES - 1) / WAVES;
+        const int items = max(mine, 0) * nt;
+        u32x4 w[RD][2];
+        int it = 0, il = wave; // the next request: tile and line
+        const uint32_t line0 = (uint32_t)k0 * BITS / 8;
+        auto issue = [&](u32x4 (&to)[2]) {
+            // Past the last line the lanes ask beyond the buffer's end, which costs no access.  (An odd number of
+            // groups at 4 bits: the second half of a row's last line is the next row's, and not used.)
+            const uint32_t at = it < nt ? lane_off : 0xffffff00u;
+            const uint32_t off = (uint32_t)it * 16 * row_bytes + line0 + (uint32_t)il * 128;
+            to[0] = __builtin_amdgcn_raw_buffer_load_b128(wbuf, (int)at, (int)off, 0);
+            to[1] = __builtin_amdgcn_raw_buffer_load_b128(wbuf, (int)at, (int)(off + 64), 0);
+            il += WAVES;
+            if (il >= lines) {
+                il = wave;
+                it++;
+            }
+        };
+        if (items > 0) {
+#pragma unroll
+            for (int j = 0; j < RD; j++)
+                issue(w[j]);
+        }
+        if (BITS != 16) {
+            // scales and zero points of the batch's tiles for the panel's groups: [tile][row][group]
+            const int rows = nt * 16;
+            for (int i = threadIdx.x; i < rows * GP; i += THREADS) {
+                const int r = i / GP, g = i % GP;
+                const size_t at = (size_t)min(n0 + r, N - 1) * G + min(g0 + g, G - 1);
+                L.s[r * GS + g] = ((const FQ_GLOBAL float *)scales)[at];
+                L.z[r * GS + g] = ((const FQ_GLOBAL uint8_t *)zeros)[at];
+            }
+        }
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+
+        float4_t out[MB];
+#pragma unroll
+        for (int mb = 0; mb < MB; mb++)
+            out[mb] = float4_t{0.f, 0.f, 0.f, 0.f};
+        int ct = 0, cl = wave;
+        auto compute = [&](const u32x4 (&v)[2]) {
+            if (BITS == 4) {
+                const int g = cl * 2;
+                const uint8_t *xs = L.x + (size_t)g * 4096 * MB;
+#pragma unroll
+                for (int h = 0; h < 2; h++) {
+                    if (h == 1 && g + 1 >= gp)
+                        break;
+                    const float s = L.s[(ct * 16 + n) * GS + g + h];
+                    const uint32_t z = L.z[(ct * 16 + n) * GS + g + h];
+                    const uint32_t nz = (z | 0xE400u) | (((z << 4) | 0xD400u) << 16);
+                    float4_t acc[MB];
+#pragma unroll
+                    for (int mb = 0; mb < MB; mb++)
+                        acc[mb] = float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int i = 0; i < 4; i++) {
+                        uint32_t b[4];
+                        const uint32_t q = v[h][i];
+                        b[0] = pk_add((__builtin_amdgcn_perm(0u, q, 0x0c000c00u) & mg.m0) | mg.e0, nz);
+                        b[1] = pk_add((__builtin_amdgcn_perm(0u, q, 0x0c010c01u) & mg.m0) | mg.e0, nz);
+                        b[2] = pk_add((__builtin_amdgcn_perm(0u, q, 0x0c020c02u) & mg.m0) | mg.e0, nz);
+                        b[3] = pk_add((__builtin_amdgcn_perm(0u, q, 0x0c030c03u) & mg.m0) | mg.e0, nz);
+#pragma unroll
+                        for (int mb = 0; mb < MB; mb++)
+                            acc[mb] = mfma16(*reinterpret_cast<const u32x4 *>(xs + h * 4096 * MB + mb * 2048 + xat[i]), b, acc[mb]);
+                    }
+#pragma unroll
+                    for (int mb = 0; mb < MB; mb++)
+                        out[mb] += s * acc[mb];
+                }
+            } else if (BITS == 8) {
+                const uint8_t *xs = L.x + (size_t)cl * 4096 * MB;
+                const float s = L.s[(ct * 16 + n) * GS + cl];
+                const uint32_t z = L.z[(ct * 16 + n) * GS + cl], nz = (z | (z << 16)) | 0xE400E400u;
+                float4_t acc[MB];
+#pragma unroll
+                for (int mb = 0; mb < MB; mb++)
+                    acc[mb] = float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    const uint32_t q0 = v[i >> 1][2 * (i & 1)], q1 = v[i >> 1][2 * (i & 1) + 1];
+                    uint32_t b[4];
+                    b[0] = pk_add(__builtin_amdgcn_perm(mg.e0, q0, 0x04010400u), nz);
+                    b[1] = pk_add(__builtin_amdgcn_perm(mg.e0, q0, 0x04030402u), nz);
+                    b[2] = pk_add(__builtin_amdgcn_perm(mg.e0, q1, 0x04010400u), nz);
+                    b[3] = pk_add(__builtin_amdgcn_perm(mg.e0, q1, 0x04030402u), nz);
+#pragma unroll
+                    for (int mb = 0; mb < MB; mb++)
+                        acc[mb] = mfma16(*reinterpret_cast<const u32x4 *>(xs + ((i >> 1) * MB + mb) * 2048 + xat[i & 1]), b, acc[mb]);
+                }
+#pragma unroll
+                for (int mb = 0; mb < MB; mb++)
+                    out[mb] += s * acc[mb];
+            } else {
+                const uint8_t *xs = L.x + (size_t)cl * 2048 * MB;
+#pragma unroll
+                for (int i = 0; i < 2; i++) {
+                    const uint32_t b[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
+#pragma unroll
+                    for (int mb = 0; mb < MB; mb++)
+                        out[mb] = mfma16(*reinterpret_cast<const u32x4 *>(xs + mb * 2048 + xat[i]), b, out[mb]);
+                }
+            }
+            cl += WAVES;
+            if (cl >= lines) { // the tile's last line in this panel
+                cl = wave;
+#pragma unroll
+                for (int t = 0; t < NB; t++)
+                    if (t == ct) {
+#pragma unroll
+                        for (int mb = 0; mb < MB; mb++)
+                            sum[t][mb] += out[mb];
+                    }
+#pragma unroll
+                for (int mb = 0; mb < MB; mb++)
+                    out[mb] = float4_t{0.f, 0.f, 0.f, 0.f};
+                ct++;
+            }
+        };
+        for (int i = 0; i < items; i += RD) {
+#pragma unroll
+            for (int j = 0; j < RD; j++) {
+                if (i + j < items)
+                    compute(w[j]);
+                issue(w[j]);
+            }
+        }
+    }
+    // the wavefronts' sums, added in their order: two blocks of 16 x 16 outputs at a time (MB = 1: two tiles)
+#pragma unroll
+    for (int t = 0; t < NB * MB; t += 2) {
+        if (t >= nt * MB)
+            break;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 2; u++)
+            L.red[(u * WAVES + wave) * 64 + lane] = sum[(t + u) / MB][(t + u) % MB];
+        __syncthreads();
+        // D layout of the 16x16 MFMA: lane holds column n (weight row), rows (batch) 4 * c + r
+        const int u = threadIdx.x >> 8, m16 = (threadIdx.x >> 4) & 15, nn = threadIdx.x & 15;
+        const float *p = reinterpret_cast<const float *>(L.red + u * WAVES * 64) + ((m16 >> 2) * 16 + nn) * 4 + (m16 & 3);
+        float v = p[0];
+#pragma unroll
+        for (int q = 1; q < WAVES; q++)
+            v += p[q * 256];
+        const int tile = (t + u) / MB, row = n0 + tile * 16 + nn, m = (t + u) % MB * 16 + m16;
+        if (tile < nt && m < M && row < N)
+            ((FQ_GLOBAL uint16_t *)y)[(size_t)m * N + row] = __builtin_bit_cast(uint16_t, (_Float16)v);
+    }
+}
+
+// What a tile costs, in thirds of a 128-byte line of its 16 rows (29 ns): its lines, and per input what
+// unpacking, folding and adding up cost whatever the width (22016 rows of 4096 inputs at 16 batch rows: 2.0 / 3.4 /
+// 6.2 us a tile at 4 / 8 / 16 bits).  An entry's first tile also pays for the start on it: x, scales, the ramp.
+__device__ __forceinline__ int tile_cost(int K, int bits) { return (K >> 7) * (3 * bits + 5) / 8 + 1; }
+constexpr uint32_t START_COST = 50;
+
+template <bool SINGLE, int MB>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_batch_kernel(
+    const FqLinearDesc single, int bits_host, const FqLinearDesc *__restrict__ table, const int32_t *__restrict__ bits_dev,
+    int count, int M, int *flags)
+{
+    __shared__ Lds L;
+    const int lane = threadIdx.x & 63;
+    // Every wavefront works out the same division of the launch's cost: lane e holds entry e, all of it, so that
+    // one trip to memory serves the whole table.
+    int e_bits = 0, e_tiles = 0, e_cost = 0, e_N = 0, e_K = 0;
+    const void *e_codes = nullptr, *e_scales = nullptr, *e_zeros = nullptr, *e_x = nullptr;
+    void *e_y = nullptr;
+    if (SINGLE ? lane == 0 : lane < count) {
+        const FqLinearDesc *d = SINGLE ? &single : &table[lane];
+        e_bits = SINGLE ? bits_host : bits_dev[lane];
+        const void *c4 = d->codes4, *c8 = d->codes8, *c16 = d->w16, *s4 = d->scales4, *s8 = d->scales8, *z4 = d->zeros4,
+                   *z8 = d->zeros8;
+        e_x = d->x, e_y = d->y, e_N = d->N, e_K = d->K;
+        e_codes = e_bits == 4 ? c4 : e_bits == 8 ? c8 : e_bits == 16 ? c16 : nullptr;
+        e_scales = e_bits == 4 ? s4 : s8;
+        e_zeros = e_bits == 4 ? z4 : z8;
+        if (e_codes) {
+            e_tiles = (e_N + 15) >> 4;
+            e_cost = tile_cost(e_K, e_bits);
+        } else if (flags && blockIdx.x == 0 && threadIdx.x < 64) {
+            *flags = 1; // no such width here, or no copy of it: nobody runs this entry
+        }
+    }
+    auto of = [](const void *p, int e) -> const void * { // lane e's pointer
+        const uint64_t v = reinterpret_cast<uint64_t>(p);
+        const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)v, e), hi = __builtin_amdgcn_readlane((uint32_t)(v >> 32), e);
+        return reinterpret_cast<const void *>((uint64_t)hi << 32 | lo);
+    };
+    const uint32_t e_all = e_tiles > 0 ? (uint32_t)e_tiles * e_cost + START_COST : 0u;
+    uint32_t upto = e_all; // inclusive prefix
+    if (!SINGLE) {
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t o = __shfl_up(upto, off, 64);
+            if (lane >= off)
+                upto += o;
+        }
+    }
+    const uint32_t all = SINGLE ? __builtin_amdgcn_readfirstlane(upto) : __builtin_amdgcn_readlane(upto, 63);
+    const uint32_t before = upto - e_all + START_COST;
+    // this workgroup's share [lo, hi) of the cost; a tile belongs to the share its first unit lies in
+    const uint32_t each = all / gridDim.x, rest = all % gridDim.x;
+    const uint32_t lo = each * blockIdx.x + rest * blockIdx.x / gridDim.x;
+    const uint32_t hi = each * (blockIdx.x + 1) + rest * (blockIdx.x + 1) / gridDim.x;
+    int t_lo = 0, t_hi = 0;
+    if (e_tiles > 0) {
+        t_lo = lo <= before ? 0 : (int)min((uint32_t)e_tiles, (lo - before + e_cost - 1) / e_cost);
+        t_hi = hi <= before ? 0 : (int)min((uint32_t)e_tiles, (hi - before + e_cost - 1) / e_cost);
+    }
+    unsigned long long todo = __ballot(t_hi > t_lo);
+    const uint16_t *x_in = nullptr; // whose first panel is in LDS (all of it: one panel)
+    int x_K = 0;
+    while (todo) {
+        const int e = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        const int bits = __builtin_amdgcn_readlane(e_bits, e);
+        const int tb = __builtin_amdgcn_readlane(t_lo, e), te = __builtin_amdgcn_readlane(t_hi, e);
+        const int N = __builtin_amdgcn_readlane(e_N, e), K = __builtin_amdgcn_readlane(e_K, e);
+        const uint8_t *codes = (const uint8_t *)of(e_codes, e), *zeros = (const uint8_t *)of(e_zeros, e);
+        const float *scales = (const float *)of(e_scales, e);
+        const uint16_t *x = (const uint16_t *)of(e_x, e);
+        uint16_t *y = (uint16_t *)const_cast<void *>(of(e_y, e));
+        for (int t = tb; t < te; t += NB) {
+            const bool there = x == x_in && K == x_K && K <= XBYTES / (32 * MB);
+            if (t > tb || x_in)
+                __syncthreads(); // LDS is free again
+            const int nt = min(NB, te - t);
+            if (bits == 4)
+                run_batch<4, MB>(L, codes, scales, zeros, x, y, N, K, M, t, nt, there);
+            else if (bits == 8)
+                run_batch<8, MB>(L, codes, scales, zeros, x, y, N, K, M, t, nt, there);
+            else
+                run_batch<16, MB>(L, codes, nullptr, nullptr, x, y, N, K, M, t, nt, there);
+            x_in = x;
+            x_K = K;
+        }
+    }
+}
+
+} // namespace
+
+// Up to 24 tiles per compute unit (two 7B-shaped layers): there the plans of mixed widths are 10 to 35 % faster than on
+// the register-fed kernel's round-robin tiles; at four layers {4, 8} 195 against 216 us, but {4, 8, 16} 296 against 265
+// and all widths at 32 batch rows slower, since each run of NB tiles starts anew.
+bool fq_batch_serves(int count, long long rows) { return count <= MAX_ENTRIES && rows <= 384LL * fq_device_cus(); }
+
+hipError_t fq_launch_batch(const FqLinearDesc *single, int bits_host, const FqLinearDesc *descs_dev, const int32_t *bits_dev,
+                           int count, long long tiles, int M, int *flags, hipStream_t stream)
+{
+    const int cus = fq_device_cus();
+    const unsigned grid = (unsigned)(tiles < cus ? tiles : cus);
+    FqLinearDesc none = {};
+    if (single) {
+        if (M <= 16)
+            decode_batch_kernel<true, 1><<<grid, THREADS, 0, stream>>>(*single, bits_host, nullptr, nullptr, 1, M, nullptr);
+        else
+            decode_batch_kernel<true, 2><<<grid, THREADS, 0, stream>>>(*single, bits_host, nullptr, nullptr, 1, M, nullptr);
+    } else if (M <= 16) {
+        decode_batch_kernel<false, 1><<<grid, THREADS, 0, stream>>>(none, 0, descs_dev, bits_dev, count, M, flags);
+    } else {
+        decode_batch_kernel<false, 2><<<grid, THREADS, 0, stream>>>(none, 0, descs_dev, bits_dev, count, M, flags);
+    }
+    return hipGetLastError();
+}

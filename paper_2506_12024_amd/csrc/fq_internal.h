@@ -34,6 +34,7 @@ struct FqLinearDesc {
 struct FqPlanGeom {
     int count, M, total_tiles, tile_rows, max_K;
     int has3; // some layer of the plan holds a 3-bit copy
+    int batch; // served by fq_launch_batch
 };
 struct fq_layer;
 // Records a message for fq_last_error() on the calling thread and returns `code`.
@@ -110,6 +111,11 @@ hipError_t fq_launch_skinny(const FqLinearDesc *single, int bits_host,
                             int total_tiles, int tile_rows, int M, bool with3, int *queue, void *order,
                             hipStream_t stream);
 int fq_skinny_tile_rows(long long total_rows, int M);
+// Single calls and small plans (up to 64 entries) at 2 <= M <= 32 and 4, 8 or 16 bits (fq_batch.hip); `tiles`: tiles of
+// 16 rows in all.
+bool fq_batch_serves(int count, long long rows);
+hipError_t fq_launch_batch(const FqLinearDesc *single, int bits_host, const FqLinearDesc *descs_dev, const int32_t *bits_dev,
+                           int count, long long tiles, int M, int *flags, hipStream_t stream);
 // Streaming variant for plan launches with 2 <= M <= 32 and tiles of 256 rows (fq_launch_skinny
 // hands those to it).
 hipError_t fq_launch_skinny_stream(const FqLinearDesc *descs_dev, const int32_t *bits_dev, int count,

@@ -1,0 +1,62 @@
+"""The small-batch kernel of single calls and stage-sized plans (csrc/fq_batch.hip) at its edges: rows around its
+tiles of 16, batch rows around 16, inputs of one group, an odd number of groups, and more than one
+panel of x in LDS (4096 inputs up to 16 batch rows, 2048 above), runs longer than the six tiles a workgroup
+holds at a time, entries that share x and entries that do not, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+import paper_2506_12024_amd as fq
+from gpu_util import DEV, gpu_linear, make_layer, rel_err, to_dev
+
+pytestmark = pytest.mark.gpu
+
+TOL = 2e-3  # exact integers times fp16 in binary32: what shows is the result's rounding to fp16, 2^-11
+
+
+def _ref(w, packed, bits, x):
+    if bits == 16:
+        return oracle.linear(x, w, None, None, 16)
+    c, s, z = (t.cpu().numpy() for t in packed[bits])
+    return oracle.linear(x, c, s, z, bits)
+
+
+@pytest.mark.parametrize("bits", [4, 8, 16])
+@pytest.mark.parametrize("M,N,K", [(2, 1, 128), (16, 17, 384), (17, 15, 1152), (32, 48, 2048), (31, 33, 2176), (16, 40, 4096),
+                                   (15, 64, 4224), (5, 16, 11008), (18, 256, 4480)])
+def test_single_call(M, N, K, bits):
+    name = "batch/%dx%dx%d" % (M, N, K)
+    w = synth.weight(13, name + "/w", N, K, 0.02, outlier_p=0.001)
+    x = synth.activations(13, name + "/x", M, K)
+    layer, packed = make_layer(w, (bits,))
+    assert rel_err(gpu_linear(layer, bits, x), _ref(w, packed, bits, x)) <= TOL
+
+
+@pytest.mark.parametrize("M", [3, 16, 32])
+def test_plan_of_mixed_entries(M):
+    # 30000 rows are seven tiles of 16 per workgroup on 256 compute units; the rest are slivers beside them
+    shapes = [(30000, 256), (48, 256), (17, 384), (300, 2304), (5, 256)]
+    bits = [4, 16, 8, 4, 8]
+    shared = {1: 0, 4: 0}  # entries that read entry 0's x
+    layers, xs, ys, ws, packs = [], [], [], [], []
+    for i, (N, K) in enumerate(shapes):
+        w = synth.weight(13, "batch/plan/w%d" % i, N, K, 0.02)
+        layer, packed = make_layer(w, (4, 8, 16))
+        x = xs[shared[i]] if i in shared else to_dev(synth.activations(13, "batch/plan/x%d/%d" % (i, M), M, K))
+        layers.append(layer), xs.append(x), ws.append(w), packs.append(packed)
+        ys.append(torch.full((M, N), float("nan"), dtype=torch.float16, device=DEV))
+    wsp = torch.empty(fq.Plan.workspace_bytes(len(shapes)), dtype=torch.uint8, device=DEV)
+    plan = fq.Plan(layers, xs, ys, M, wsp)
+    plan.run(torch.tensor(bits, dtype=torch.int32, device=DEV))
+    torch.cuda.synchronize()
+    for i in range(len(shapes)):
+        ref = _ref(ws[i], packs[i], bits[i], xs[i].cpu().numpy())
+        assert rel_err(ys[i].cpu().numpy(), ref) <= TOL, i
+    assert plan.status() == (0, 0)
+    # a width that is not served leaves the entry's y alone and is reported
+    before = ys[2].clone()
+    plan.run(torch.tensor([8, 4, 2, 16, 4], dtype=torch.int32, device=DEV))
+    assert plan.status() == (0, 1) and torch.equal(ys[2], before)
+    assert rel_err(ys[3].cpu().numpy(), _ref(ws[3], packs[3], 16, xs[3].cpu().numpy())) <= TOL
