@@ -3,38 +3,28 @@
 //
 // One 16-lane segment of a wavefront owns one group of 128 consecutive k of
 // one row: every lane loads 8 halves (one 128-bit load, fully coalesced: a
-// wavefront reads 1 KiB = 4 groups), the segment reduces min/max with DPP
-// row shifts, every lane then derives the same s and z and writes its 8 codes
+// wavefront reads 1 KiB = 4 groups; two such loads per lane), the segment reduces min/max with DPP
+// row rotations, every lane then derives the same s and z and writes its 8 codes
 // with one 16-bit (2-bit codes), 32-bit (4-bit codes) or 64-bit (8-bit codes) store (3-bit
 // codes: four lanes put a block of three words together).
 //
 // The arithmetic is pinned so that codes, scales and zeros are bit-exact
 // against a binary32 evaluation with one rounding per operation: IEEE
-// division, no fused multiply-add, round-half-to-even.
+// division, no fused multiply-add, round-half-to-even.  (The weights are divided by their group's scale
+// through its reciprocal and one correction, fq_div.h, which gives the same codes.)
+//
+// Bound by the vector ALUs as long as every weight was divided in full (9 divisions of ten instructions for 8
+// weights), now nearly by HBM: 11008 x 4096, 114 MB at 4 bits, 33.5 -> 25.1 us.  Two groups per lane or one
+// or four: the same.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "fq_div.h"
 #include "fq_internal.h"
 
 namespace {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
-
-// min/max over the 16 lanes of a DPP row (lanes 16j .. 16j+15), result in all 16.
-__device__ __forceinline__ float seg16_min(float v)
-{
-#pragma unroll
-    for (int off = 8; off >= 1; off >>= 1)
-        v = fminf(v, __shfl_xor(v, off, 64));
-    return v;
-}
-__device__ __forceinline__ float seg16_max(float v)
-{
-#pragma unroll
-    for (int off = 8; off >= 1; off >>= 1)
-        v = fmaxf(v, __shfl_xor(v, off, 64));
-    return v;
-}
 
 // Scale, zero point and code limits of a group from its range (every lane of the segment
 // computes the same).  Asymmetric: the range always contains 0.  Symmetric: max |w| on the last of
@@ -42,33 +32,33 @@ __device__ __forceinline__ float seg16_max(float v)
 // stored zero point, so that Eq. (3) applies unchanged.
 struct GroupParams {
     float s, z, qlo, qhi;
+    Divisor by; // s
 };
 template <bool SYM>
 __device__ __forceinline__ GroupParams group_params(float lo, float hi, int bits)
 {
 #pragma clang fp contract(off)
-    GroupParams p;
+    GroupParams p{0.f, 0.f, 0.f, 0.f, Divisor(1.0f)};
     if (SYM) {
         const float amax = fmaxf(-lo, hi);
         const float lim = (float)((1 << (bits - 1)) - 1);
         p.s = amax == 0.0f ? 1.0f : __fdiv_rn(__fadd_rn(amax, amax), (float)((1 << bits) - 2));
+        p.by = Divisor(p.s);
         p.z = 0.0f;
         p.qlo = -lim;
         p.qhi = lim;
     } else {
         const float qmax = (float)((1 << bits) - 1);
-        if (hi == lo) { // all-zero group
-            p.s = 1.0f;
-            p.z = 0.0f;
-        } else {
-            p.s = __fdiv_rn(__fsub_rn(hi, lo), qmax);
-            p.z = fminf(fmaxf(rintf(__fdiv_rn(-lo, p.s)), 0.0f), qmax);
-        }
+        p.s = hi == lo ? 1.0f : __fdiv_rn(__fsub_rn(hi, lo), qmax); // an all-zero group: s = 1, z = 0
+        p.by = Divisor(p.s);
+        p.z = fminf(fmaxf(rintf(p.by.of(-lo)), 0.0f), qmax);
         p.qlo = 0.0f;
         p.qhi = qmax;
     }
     return p;
 }
+
+constexpr int QG = 2; // groups a lane works on, both requested before the first is used
 
 template <int BITS, bool SYM>
 __global__ __launch_bounds__(256) void quantize_kernel(const half8 *__restrict__ w,
@@ -78,85 +68,93 @@ __global__ __launch_bounds__(256) void quantize_kernel(const half8 *__restrict__
                                                        uint8_t *__restrict__ zeros)
 {
 #pragma clang fp contract(off)
-    const long long seg = ((long long)blockIdx.x * 256 + threadIdx.x) >> 4; // group index
     const int sub = threadIdx.x & 15;
-    // Whole 16-lane segments are in or out together, so the shuffles below never
-    // read an inactive lane of their own segment.
-    if (seg >= n_groups)
-        return;
-    const half8 v = w[seg * 16 + sub];
-    float f[8];
-    float lo = 0.0f, hi = 0.0f; // the range always contains 0
+    const long long seg0 = (long long)blockIdx.x * (16 * QG) + (threadIdx.x >> 4); // first group
+    half8 vs[QG];
 #pragma unroll
-    for (int i = 0; i < 8; i++) {
-        f[i] = (float)v[i];
-        lo = fminf(lo, f[i]);
-        hi = fmaxf(hi, f[i]);
-    }
-    lo = seg16_min(lo);
-    hi = seg16_max(hi);
+    for (int u = 0; u < QG; u++)
+        vs[u] = w[min(seg0 + 16 * u, n_groups - 1) * 16 + sub];
+#pragma unroll
+    for (int u = 0; u < QG; u++) {
+        const long long seg = seg0 + 16 * u;
+        // Whole 16-lane segments are in or out together, so the row operations below never
+        // read an inactive lane of their own segment.
+        if (seg >= n_groups)
+            return;
+        const half8 v = vs[u];
+        float f[8];
+        float lo = 0.0f, hi = 0.0f; // the range always contains 0
+#pragma unroll
+        for (int i = 0; i < 8; i++) {
+            f[i] = (float)v[i];
+            lo = fminf(lo, f[i]);
+            hi = fmaxf(hi, f[i]);
+        }
+        lo = row_min(lo);
+        hi = row_max(hi);
 
-    const GroupParams p = group_params<SYM>(lo, hi, BITS);
-    const float s = p.s;
-    const float z = SYM ? (float)(1 << (BITS - 1)) : p.z; // what is stored
-    uint32_t q[8];
+        const GroupParams p = group_params<SYM>(lo, hi, BITS);
+        const float s = p.s;
+        const float z = SYM ? (float)(1 << (BITS - 1)) : p.z; // what is stored
+        uint32_t q[8];
 #pragma unroll
-    for (int i = 0; i < 8; i++) {
-        float t = rintf(__fadd_rn(__fdiv_rn(f[i], s), p.z));
-        t = fminf(fmaxf(t, p.qlo), p.qhi);
-        q[i] = (uint32_t)(int)(SYM ? t + z : t);
-    }
-    if (BITS == 2) {
-        uint32_t word = 0;
+        for (int i = 0; i < 8; i++) {
+            float t = rintf(__fadd_rn(p.by.of(f[i]), p.z));
+            t = fminf(fmaxf(t, p.qlo), p.qhi);
+            q[i] = (uint32_t)(int)(SYM ? t + z : t);
+        }
+        if (BITS == 2) {
+            uint32_t word = 0;
 #pragma unroll
-        for (int i = 0; i < 8; i++)
-            word |= q[i] << (2 * i); // byte j = code(4j) | code(4j+1) << 2 | code(4j+2) << 4 | code(4j+3) << 6
-        reinterpret_cast<uint16_t *>(codes)[seg * 16 + sub] = (uint16_t)word;
-    } else if (BITS == 3) {
-        // A block of 12 bytes = three words holds 32 codes: word j the codes 10 j .. 10 j + 9 whole
-        // (code 10 j + 5 h + p in bits 16 h + 3 p .. + 2), the words' bits 15 and 31 the three bits
-        // of codes 30 and 31.  The four lanes of a block place their eight codes each, the words
-        // are OR-ed across the four, and lane t < 3 stores word t.
-        const int t = sub & 3;
-        uint32_t c[3] = {0u, 0u, 0u};
+            for (int i = 0; i < 8; i++)
+                word |= q[i] << (2 * i); // byte j = code(4j) | code(4j+1) << 2 | code(4j+2) << 4 | code(4j+3) << 6
+            reinterpret_cast<uint16_t *>(codes)[seg * 16 + sub] = (uint16_t)word;
+        } else if (BITS == 3) {
+            // A block of 12 bytes = three words holds 32 codes: word j the codes 10 j .. 10 j + 9 whole
+            // (code 10 j + 5 h + p in bits 16 h + 3 p .. + 2), the words' bits 15 and 31 the three bits
+            // of codes 30 and 31.  The four lanes of a block place their eight codes each, the words
+            // are OR-ed across the four, and lane t < 3 stores word t.
+            const int t = sub & 3;
+            uint32_t c[3] = {0u, 0u, 0u};
 #pragma unroll
-        for (int e = 0; e < 8; e++) {
-            const int i = 8 * t + e;
-            if (i < 30) {
-                const int j = i / 10, r = i - 10 * j;
-                const uint32_t v = q[e] << (r >= 5 ? 16 + 3 * (r - 5) : 3 * r);
+            for (int e = 0; e < 8; e++) {
+                const int i = 8 * t + e;
+                if (i < 30) {
+                    const int j = i / 10, r = i - 10 * j;
+                    const uint32_t v = q[e] << (r >= 5 ? 16 + 3 * (r - 5) : 3 * r);
 #pragma unroll
-                for (int jj = 0; jj < 3; jj++)
-                    c[jj] |= j == jj ? v : 0u;
-            } else {
-                const int sh = 15 + 16 * (i - 30);
+                    for (int jj = 0; jj < 3; jj++)
+                        c[jj] |= j == jj ? v : 0u;
+                } else {
+                    const int sh = 15 + 16 * (i - 30);
 #pragma unroll
-                for (int jj = 0; jj < 3; jj++)
-                    c[jj] |= ((q[e] >> jj) & 1u) << sh;
+                    for (int jj = 0; jj < 3; jj++)
+                        c[jj] |= ((q[e] >> jj) & 1u) << sh;
+                }
             }
-        }
 #pragma unroll
-        for (int jj = 0; jj < 3; jj++) {
-            c[jj] |= (uint32_t)__shfl_xor((int)c[jj], 1, 64);
-            c[jj] |= (uint32_t)__shfl_xor((int)c[jj], 2, 64);
-        }
-        if (t < 3)
-            reinterpret_cast<uint32_t *>(codes)[(seg * 4 + (sub >> 2)) * 3 + t] = t == 0 ? c[0] : t == 1 ? c[1] : c[2];
-    } else if (BITS == 4) {
-        uint32_t word = 0;
+            for (int jj = 0; jj < 3; jj++) {
+                c[jj] |= (uint32_t)__shfl_xor((int)c[jj], 1, 64);
+                c[jj] |= (uint32_t)__shfl_xor((int)c[jj], 2, 64);
+            }
+            if (t < 3)
+                reinterpret_cast<uint32_t *>(codes)[(seg * 4 + (sub >> 2)) * 3 + t] = t == 0 ? c[0] : t == 1 ? c[1] : c[2];
+        } else if (BITS == 4) {
+            uint32_t word = 0;
 #pragma unroll
-        for (int i = 0; i < 8; i++)
-            word |= q[i] << (4 * i); // code k in nibble k: byte j = code(2j) | code(2j+1) << 4
-        reinterpret_cast<uint32_t *>(codes)[seg * 16 + sub] = word;
-    } else {
-        uint2 word;
-        word.x = q[0] | (q[1] << 8) | (q[2] << 16) | (q[3] << 24);
-        word.y = q[4] | (q[5] << 8) | (q[6] << 16) | (q[7] << 24);
-        reinterpret_cast<uint2 *>(codes)[seg * 16 + sub] = word;
-    }
-    if (sub == 0) {
-        scales[seg] = s;
-        zeros[seg] = (uint8_t)z;
+            for (int i = 0; i < 8; i++)
+                word |= q[i] << (4 * i); // code k in nibble k: byte j = code(2j) | code(2j+1) << 4
+            reinterpret_cast<uint32_t *>(codes)[seg * 16 + sub] = word;
+        } else {
+            uint2 word;
+            word.x = q[0] | (q[1] << 8) | (q[2] << 16) | (q[3] << 24);
+            word.y = q[4] | (q[5] << 8) | (q[6] << 16) | (q[7] << 24);
+            reinterpret_cast<uint2 *>(codes)[seg * 16 + sub] = word;
+        }
+        if (sub == 0) {
+            scales[seg] = s;
+            zeros[seg] = (uint8_t)z;
+        }
     }
 }
 
@@ -180,13 +178,13 @@ __global__ __launch_bounds__(256) void fake_quantize_kernel(const half8 *w, long
         lo = fminf(lo, f[i]);
         hi = fmaxf(hi, f[i]);
     }
-    lo = seg16_min(lo);
-    hi = seg16_max(hi);
+    lo = row_min(lo);
+    hi = row_max(hi);
     const GroupParams p = group_params<SYM>(lo, hi, bits);
     half8 out;
 #pragma unroll
     for (int i = 0; i < 8; i++) {
-        float t = rintf(__fadd_rn(__fdiv_rn(f[i], p.s), p.z));
+        float t = rintf(__fadd_rn(p.by.of(f[i]), p.z));
         t = fminf(fmaxf(t, p.qlo), p.qhi);
         const float code = (float)(int)t; // the stored code is an integer: -0 becomes 0
         float d = __fmul_rn(__fsub_rn(code, p.z), p.s);
@@ -240,7 +238,7 @@ __global__ __launch_bounds__(256) void quantize_row8_kernel(const half8 *__restr
         uint32_t q[8];
 #pragma unroll
         for (int j = 0; j < 8; j++) {
-            float c = rintf(__fadd_rn(__fdiv_rn((float)v[j], p.s), p.z));
+            float c = rintf(__fadd_rn(p.by.of((float)v[j]), p.z));
             c = fminf(fmaxf(c, p.qlo), p.qhi);
             q[j] = (uint32_t)(int)(SYM ? c + z : c);
         }
@@ -260,8 +258,7 @@ __global__ __launch_bounds__(256) void quantize_row8_kernel(const half8 *__restr
 hipError_t fq_launch_quantize(const void *w, long long n_groups, int bits, bool symmetric, void *codes,
                               void *scales, void *zeros, hipStream_t stream)
 {
-    const long long threads = n_groups * 16;
-    const unsigned blocks = (unsigned)((threads + 255) / 256);
+    const unsigned blocks = (unsigned)((n_groups + 16 * QG - 1) / (16 * QG));
     if (blocks == 0)
         return hipSuccess;
     const half8 *wp = (const half8 *)w;

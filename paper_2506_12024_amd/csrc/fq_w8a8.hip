@@ -36,6 +36,7 @@
 #include <stdint.h>
 #include <type_traits>
 
+#include "fq_div.h"
 #include "fq_internal.h"
 #include "fq_mfma.h"
 
@@ -87,6 +88,7 @@ __global__ __launch_bounds__(QA_THREADS) void quantize_act_kernel(const half8 *_
         amax = fmaxf(amax, s_max[w]);
 
     const float s = amax > 0.0f ? __fdiv_rn(__fadd_rn(amax, amax), 254.0f) : 1.0f;
+    const Divisor by(s);
     if (t == 0)
         sx[m] = s;
 
@@ -97,7 +99,7 @@ __global__ __launch_bounds__(QA_THREADS) void quantize_act_kernel(const half8 *_
         int q[8], sum = 0;
 #pragma unroll
         for (int j = 0; j < 8; j++) {
-            float r = rintf(__fdiv_rn((float)v[j], s));
+            float r = rintf(by.of((float)v[j]));
             r = fminf(fmaxf(r, -127.0f), 127.0f);
             q[j] = (int)r;
             sum += q[j];
@@ -106,9 +108,7 @@ __global__ __launch_bounds__(QA_THREADS) void quantize_act_kernel(const half8 *_
         word.x = (q[0] & 255) | ((q[1] & 255) << 8) | ((q[2] & 255) << 16) | ((uint32_t)(q[3] & 255) << 24);
         word.y = (q[4] & 255) | ((q[5] & 255) << 8) | ((q[6] & 255) << 16) | ((uint32_t)(q[7] & 255) << 24);
         reinterpret_cast<uint2 *>(xq + (size_t)m * K)[i] = word;
-#pragma unroll
-        for (int off = 8; off >= 1; off >>= 1)
-            sum += __shfl_xor(sum, off, 64);
+        sum = row_sum(sum);
         if ((t & 15) == 0)
             xsum[(size_t)(i >> 4) * M + m] = sum;
     }
