@@ -4,8 +4,8 @@
 // the dequantization of Sec. 2.2 Eq. (3) fused into the operand path.
 //
 // Tiling.  A workgroup (8 wavefronts, two per SIMD) owns a 256 (tokens) x 256 (weight rows)
-// tile of y and walks K in steps of 64.  A wavefront owns 128 tokens x 64 rows = 4 x 2 tiles
-// of v_mfma_f32_32x32x16_f16 (A = x: 32 tokens x 16 k, B = weights: 16 k x 32 rows; 128
+// tile of y and walks K in steps of 64.  A wavefront owns 256 tokens x 32 rows (2 and 4 bits) or 128 tokens x 64
+// rows (8 bits, fp16): 8 x 1 or 4 x 2 tiles of v_mfma_f32_32x32x16_f16 (A = x: 32 tokens x 16 k, B = weights: 16 k x 32 rows; 128
 // binary32 accumulator registers).  The large shared tile keeps the bytes fetched per MFMA
 // low enough that one step of compute covers the latency of the next stage's fetch.
 //
@@ -47,7 +47,6 @@ namespace {
 constexpr int THREADS = 512;
 constexpr int WAVES = THREADS / 64;
 constexpr int BM_FULL = 256, BN = 256, BK = 64;
-constexpr int WN = 64;             // weight rows per wavefront (2 MFMA tiles)
 constexpr int XRB = BK * 2;        // bytes of an x row per step (128)
 
 // Byte offset of 16-byte chunk `ch` of row `r` in a slab whose rows are RB bytes long:
@@ -128,14 +127,7 @@ __device__ __forceinline__ int x_chunk(int i, int c)
     return BITS == 4 || BITS == 2 ? 4 * c + i : 2 * i + c;
 }
 
-// Scale and zero point of a lane's two weight rows for one quantization group.
-struct Meta {
-    float s[2];
-    uint32_t z[2];
-};
-
-// HALF: the workgroup takes half a tile, 128 tokens x 256 weight rows (a wavefront 64 tokens x 64
-// rows): the tiles left over after the last full round of workgroups are cut in two, so that they
+// HALF: the workgroup takes half a tile, 128 tokens x 256 weight rows (a wavefront half the tokens): the tiles left over after the last full round of workgroups are cut in two, so that they
 // keep twice as many CUs busy for half as long.  `skip`: first tile of this launch inside an XCD's
 // run of `per_xcd` tiles.
 template <int BITS, bool HALF>
@@ -143,7 +135,12 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const FqLinearDesc d, int M, int m_tiles, int n_tiles, int per_xcd, int skip)
 {
     constexpr int BM = HALF ? BM_FULL / 2 : BM_FULL; // tokens per workgroup
-    constexpr int WM = BM / 2;                       // tokens per wavefront
+    // MFMA tiles of a wavefront along the weight rows.  One, the wavefront taking all of the tile's tokens: every weight
+    // is unpacked by one wavefront (with two tiles, by two, but x is read from LDS half as often), worth it where the
+    // unpacking is 16 instructions per operand: 2048 x 8192 x 28672 at 4 bits 872 -> 838 us, 2 bits 900 -> 881; at 8 bits
+    // 864 -> 860 but 803 -> 822 with the sizes exchanged; fp16 weights, nothing to unpack, 833 -> 868.
+    constexpr int NT = BITS == 2 || BITS == 4 ? 1 : 2, WN = 32 * NT;
+    constexpr int WM = BM / NT;                      // tokens per wavefront
     constexpr int MTL = WM / 32;                     // MFMA tiles of a wavefront along the tokens (4 or 2)
     constexpr int XSLAB = BM * XRB;                  // 32 or 16 KiB
     constexpr int WRB = BK * BITS / 8;  // bytes of a packed weight row per step
@@ -181,13 +178,13 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int l32 = lane & 31, c = lane >> 5;
-    const int wm = (wave & 1) * WM, wn = (wave >> 1) * WN;
+    const int wm = NT == 1 ? 0 : (wave & 1) * WM, wn = NT == 1 ? wave * WN : (wave >> 1) * WN;
 
-    float16_t acc[MTL][2];
+    float16_t acc[MTL][NT];
 #pragma unroll
     for (int i = 0; i < MTL; i++)
 #pragma unroll
-        for (int j = 0; j < 2; j++)
+        for (int j = 0; j < NT; j++)
 #pragma unroll
             for (int v = 0; v < 16; v++)
                 acc[i][j][v] = 0.f;
@@ -206,12 +203,12 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
     int bofs[4];
 #pragma unroll
     for (int i = 0; i < 4; i++)
-        bofs[i] = BITS == 2 ? slab_offset<WRB_>(wn + (i & 1) * 32 + l32, 0) + 8 * c
-                : BITS == 4 ? slab_offset<WRB_>(wn + (i & 1) * 32 + l32, c)
+        bofs[i] = BITS == 2 ? slab_offset<WRB_>(wn + (NT == 2 ? (i & 1) * 32 : 0) + l32, 0) + 8 * c
+                : BITS == 4 ? slab_offset<WRB_>(wn + (NT == 2 ? (i & 1) * 32 : 0) + l32, c)
                 : BITS == 8 ? slab_offset<WRB_>(wn + l32, i) + 8 * c
                             : slab_offset<WRB_>(wn + l32, 2 * i + c);
-    constexpr int BJ = 32 * WRB_; // bytes from n-tile 0 to n-tile 1 (8-bit, fp16)
 
+    constexpr int BJ = 32 * WRB_; // bytes from n-tile 0 to n-tile 1 (8-bit, fp16)
     const uint32_t K = (uint32_t)d.K, G = K >> 7;
     const int nsteps = d.K / BK;
     const DmaLane xl = dma_lane<XRB>(), wl = dma_lane<WRB>();
@@ -256,16 +253,18 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
         }
     };
 
-    Meta cur;
+    DeqConst dc[NT];
+    DeqMagic<BITS> mg;
+    mg.pin();
     // The operand carries the group's scale as a half: a scale below 2^-14 would lose bits there and
     // one below 2^-25 the whole group.  Every weight row therefore gets a power of two, taken from
     // two of its scales (the first group's and the middle one's), that brings them to about 2^-4 --
     // halves then hold scales 2^10 times smaller and 2^12 times larger than those exactly as well --
     // and the row's sums are multiplied by its inverse at the end.
-    int ex[2] = {0, 0};
+    int ex[NT] = {};
     if (BITS != 16) {
 #pragma unroll
-        for (int j = 0; j < 2; j++) {
+        for (int j = 0; j < NT; j++) {
             const float *srow = scales_tile + (size_t)min(wn + j * 32 + l32, w_last) * G;
             const float m = fmaxf(as_float_global(srow), as_float_global(srow + (G >> 1)));
             ex[j] = -3 - __builtin_amdgcn_frexp_expf(m);
@@ -326,10 +325,10 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
             // first step of a group: its scales and zero points landed during the previous step
             // (nothing is writing smeta / zmeta now: the next request goes out a step later)
 #pragma unroll
-            for (int j = 0; j < 2; j++) {
+            for (int j = 0; j < NT; j++) {
                 const int row = wn + j * 32 + l32, g4 = (s >> 1) & 3;
-                cur.s[j] = __builtin_ldexpf(meta4 ? smeta[row * 4 + g4] : smeta[row], ex[j]);
-                cur.z[j] = meta4 ? (zmeta[row] >> (8 * g4)) & 255u : zmeta[row];
+                dc[j] = deq_const<BITS>(__builtin_ldexpf(meta4 ? smeta[row * 4 + g4] : smeta[row], ex[j]),
+                                        meta4 ? (zmeta[row] >> (8 * g4)) & 255u : zmeta[row]);
             }
         }
         if (ODD && (!meta4 || (s >> 1) + 1 < (int)G)) // (four groups at a time: nothing to request past the last)
@@ -346,31 +345,15 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
         for (int i = 0; i < 4; i++)
             asm volatile("" : "+v"(aofs[i]), "+v"(bofs[i]));
 
-        // constants of the group for the two n-tiles
-        half2_t sh[2];
-        uint32_t nz[2], nz2[2];
+        u32x4 w4[NT]; // 4-bit: the lane's 32 codes of the step, per n-tile; 2-bit: the same in 8 bytes
 #pragma unroll
-        for (int j = 0; j < 2; j++) {
-            if (BITS != 16) {
-                sh[j] = half2_t{(_Float16)cur.s[j], (_Float16)cur.s[j]};
-                const uint32_t z = cur.z[j];
-                nz[j] = BITS == 8 ? ((z | (z << 16)) | 0xE400E400u)               // -(1024 + z) twice
-                      : BITS == 4 ? ((z | 0xE400u) | (((z << 4) | 0xD400u) << 16)) // -(1024 + z), -(64 + z)
-                                  : ((z | 0xE400u) | (((z << 2) | 0xDC00u) << 16)); // -(1024 + z), -(256 + z)
-                nz2[j] = ((z << 4) | 0xD400u) | (((z << 6) | 0xCC00u) << 16);     // 2 bits: -(64 + z), -(16 + z)
-            }
-        }
-        u32x4 w4[2]; // 4-bit: the lane's 32 codes of the step, per n-tile
-        if (BITS == 4) {
-#pragma unroll
-            for (int j = 0; j < 2; j++)
+        for (int j = 0; j < NT; j++) {
+            if (BITS == 4)
                 w4[j] = *reinterpret_cast<const u32x4 *>(wc + bofs[j]);
-        }
-        u32x2 w2[2]; // 2-bit: the same 32 codes in 8 bytes
-        if (BITS == 2) {
-#pragma unroll
-            for (int j = 0; j < 2; j++)
-                w2[j] = *reinterpret_cast<const u32x2 *>(wc + bofs[j]);
+            if (BITS == 2) {
+                const u32x2 q = *reinterpret_cast<const u32x2 *>(wc + bofs[j]);
+                w4[j].x = q.x, w4[j].y = q.y;
+            }
         }
 #pragma unroll
         for (int i = 0; i < 4; i++) {
@@ -379,40 +362,18 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
             for (int mt = 0; mt < MTL; mt++)
                 a[mt] = *reinterpret_cast<const u32x4 *>(xc + (wm + mt * 32) * XRB + aofs[i]);
 #pragma unroll
-            for (int j = 0; j < 2; j++) {
+            for (int j = 0; j < NT; j++) {
                 uint32_t b[4];
-                if (BITS == 2) {
-                    // half-word i: fields q0 .. q7 of k = 32 c + 8 i .., byte t holds q(4t) .. q(4t+3).
-                    // The byte is copied under both halves; fields 0 and 1 (or 2 and 3) of it stay
-                    // where they are, one per half, each under the exponent that makes it offset + q
-                    const uint32_t v = i < 2 ? w2[j].x : w2[j].y;
-                    const uint32_t lo = __builtin_amdgcn_perm(0u, v, (i & 1) ? 0x0c020c02u : 0x0c000c00u);
-                    const uint32_t hi = __builtin_amdgcn_perm(0u, v, (i & 1) ? 0x0c030c03u : 0x0c010c01u);
-                    b[0] = deq((lo & 0x000C0003u) | 0x5C006400u, nz[j], sh[j]);  // q0, q1
-                    b[1] = deq((lo & 0x00C00030u) | 0x4C005400u, nz2[j], sh[j]); // q2, q3
-                    b[2] = deq((hi & 0x000C0003u) | 0x5C006400u, nz[j], sh[j]);  // q4, q5
-                    b[3] = deq((hi & 0x00C00030u) | 0x4C005400u, nz2[j], sh[j]); // q6, q7
-                } else if (BITS == 4) {
-                    // word i: nibbles q0 .. q7 of k = 32 c + 8 i ..; byte t holds (q(2t+1) q(2t)).
-                    // The byte is copied under both halves, the low nibble kept in the low half
-                    // (exponent 0x64: 1024 + q) and the high nibble in the high half (0x54: 64 + q)
-                    const uint32_t v = w4[j][i];
-                    b[0] = deq((__builtin_amdgcn_perm(0u, v, 0x0c000c00u) & 0x00F0000Fu) | 0x54006400u, nz[j], sh[j]);
-                    b[1] = deq((__builtin_amdgcn_perm(0u, v, 0x0c010c01u) & 0x00F0000Fu) | 0x54006400u, nz[j], sh[j]);
-                    b[2] = deq((__builtin_amdgcn_perm(0u, v, 0x0c020c02u) & 0x00F0000Fu) | 0x54006400u, nz[j], sh[j]);
-                    b[3] = deq((__builtin_amdgcn_perm(0u, v, 0x0c030c03u) & 0x00F0000Fu) | 0x54006400u, nz[j], sh[j]);
-                } else if (BITS == 8) {
+                if constexpr (BITS == 2) {
+                    deq8<2>(i < 2 ? w4[j].x : w4[j].y, 0u, i, dc[j], mg, b);
+                } else if constexpr (BITS == 4) {
+                    deq8<4>(w4[j][i], 0u, 0, dc[j], mg, b);
+                } else if constexpr (BITS == 8) {
                     const u32x2 q = *reinterpret_cast<const u32x2 *>(wc + j * BJ + bofs[i]); // k = 16 i + 8 c ..
-                    b[0] = deq(__builtin_amdgcn_perm(0x64646464u, q.x, 0x04010400u), nz[j], sh[j]);
-                    b[1] = deq(__builtin_amdgcn_perm(0x64646464u, q.x, 0x04030402u), nz[j], sh[j]);
-                    b[2] = deq(__builtin_amdgcn_perm(0x64646464u, q.y, 0x04010400u), nz[j], sh[j]);
-                    b[3] = deq(__builtin_amdgcn_perm(0x64646464u, q.y, 0x04030402u), nz[j], sh[j]);
+                    deq8<8>(q.x, q.y, 0, dc[j], mg, b);
                 } else {
                     const u32x4 q = *reinterpret_cast<const u32x4 *>(wc + j * BJ + bofs[i]);
-                    b[0] = q.x;
-                    b[1] = q.y;
-                    b[2] = q.z;
-                    b[3] = q.w;
+                    b[0] = q.x, b[1] = q.y, b[2] = q.z, b[3] = q.w;
                 }
 #pragma unroll
                 for (int mt = 0; mt < MTL; mt++)
@@ -475,14 +436,14 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 #pragma unroll
     for (int mt = 0; mt < MTL; mt++)
 #pragma unroll
-        for (int j = 0; j < 2; j++) {
+        for (int j = 0; j < NT; j++) {
             const int n = n0 + wn + j * 32 + l32;
 #pragma unroll
             for (int v = 0; v < 16; v++) {
                 const int m = m0 + wm + mt * 32 + 8 * (v >> 2) + 4 * c + (v & 3);
                 if (m < M && n < d.N)
-                    ((FQ_GLOBAL uint16_t *)d.y)[(size_t)m * d.N + n] =
-                        __builtin_bit_cast(uint16_t, (_Float16)(BITS == 16 ? acc[mt][j][v] : __builtin_ldexpf(acc[mt][j][v], -ex[j])));
+                    ((FQ_GLOBAL uint16_t *)d.y)[(size_t)m * d.N + n] = __builtin_bit_cast(
+                        uint16_t, (_Float16)(BITS == 16 ? acc[mt][j][v] : __builtin_ldexpf(acc[mt][j][v], -ex[j])));
             }
         }
 }
