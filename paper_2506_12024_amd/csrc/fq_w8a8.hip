@@ -494,20 +494,18 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const __amdgpu_buffer_rsrc_t w_tile = buffer_of(d.codes + (size_t)n0 * d.K, w_rows * (uint32_t)d.K);
     dma_slab<RBM>(x_tile, 0, dl, x_last, d.K, xs0);
     dma_slab<BN>(w_tile, 0, dl, w_last, d.K, ws0);
-    // the tokens' sums over the whole row: the sum of their group sums
-    if (threadIdx.x < RBM) {
-        const int tok = min((int)threadIdx.x, d.M - 1 - m0);
-        int t = 0;
-        for (int g = 0; g < nsteps; g++)
-            t += ((const FQ_GLOBAL int32_t *)(d.xsum + m0 + (size_t)g * (size_t)d.M))[tok];
-        xtot[threadIdx.x] = t;
-    }
+    // The tokens' sums over the whole row are the sums of their group sums: thread t adds up token t's, one a
+    // step, requested with the step's slabs.  (Added up ahead of the first step they were K / 128 loads that
+    // every workgroup started with: 2048 x 28672 -> 8192, one round of 256 workgroups, with the buffer loads 509 -> 492 us.)
+    const int32_t *xs_tok = d.xsum + m0 + min((int)min(threadIdx.x, (unsigned)RBM - 1), d.M - 1 - m0);
+    int xt = 0;
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
 
     auto step = [&](int s, auto odd) {
         constexpr bool ODD = decltype(odd)::value;
         const int sn = min(s + 1, nsteps - 1); // always issued: the last step refetches itself
+        const int group_sum = ((const FQ_GLOBAL int32_t *)xs_tok)[(size_t)s * (size_t)d.M];
         dma_slab<RBM>(x_tile, sn * BKB, dl, x_last, d.K, ODD ? xs0 : xs1); // last read in step s-1: a barrier has passed
         dma_slab<BN>(w_tile, sn * BKB, dl, w_last, d.K, ODD ? ws0 : ws1);
         // The requests stay here, ahead of the step's arithmetic: left to itself the scheduler sinks them to
@@ -537,6 +535,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
                 for (int j = 0; j < 2; j++)
                     acc[mt][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[mt][i], b[j][i], acc[mt][j], 0, 0, 0);
         __builtin_amdgcn_s_waitcnt(0); // this wavefront's direct-to-LDS loads have landed
+        xt += group_sum;
         __syncthreads();               // everyone's have; buffers of step s are free
     };
     int s = 0;
@@ -547,6 +546,9 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
     if (s < nsteps)
         step(s, std::false_type());
 
+    if (threadIdx.x < RBM)
+        xtot[threadIdx.x] = xt;
+    __syncthreads();
     // D layout of the 32x32 MFMA: lane holds column l32 (weight row), rows (tokens)
     // 8 * (v / 4) + 4 * (lane / 32) + v % 4.
     float sn_[2];
