@@ -10,16 +10,16 @@
 // 1 KiB of each row, and their sums meet in LDS at the end, added in the wavefronts' order.
 //
 // x sits in LDS, 128 KiB of it at a time (4096 inputs of 16 batch rows, 2048 of 32), brought by direct-to-LDS loads
-// in slabs of 64 inputs whose 16-byte pieces are permuted (w_offset) so that operand reads are conflict free; the
-// 11008 x 4096 projections stay in one panel, and entries that share x (q, k, v) do not fetch it again.  Scales and
+// in slabs of 64 inputs whose 16-byte pieces are permuted (w_offset) so that operand reads are conflict free; projections of
+// 4096 inputs are one panel, and entries that share x (q, k, v) do not fetch it again.  Scales and
 // zero points of the run's tiles are laid beside it.  Weights go straight to registers: lane (n, c) takes 16 bytes of
 // each half line of row n, the operand layout of v_mfma_f32_16x16x32_f16 up to a permutation of the inputs that x
 // shares, RD lines ahead.
 //
 // Measured (us at 16 batch rows, 4 / 8 / 16 bits, cold weights; before: the register-fed kernel with K split between four
-// wavefronts below 8192 rows and 64-row tiles above): 4096 x 4096 9.1 / 11.3 / 14.2 -> 8.5 / 9.5 / 11.3; 11008 rows x 4096
-// 17.3 / 26.3 / 36.4 -> 11.0 / 14.9 / 20.8; 4096 rows x 11008 17.7 / 24.1 / 30.8 -> 14.4 / 19.1 / 25.8; 22016 rows x 4096
-// 23.8 / 34.8 / 47.0 -> 16.7 / 24.2 / 39.5.  What was found on the way: requests past a run's end must cost nothing (as
+// wavefronts below 8192 rows and 64-row tiles above): 4096 x 4096 9.1 / 11.3 / 14.0 -> 8.2 / 9.8 / 11.9; 11008 rows x 4096
+// 17.2 / 26.0 / 36.1 -> 11.3 / 15.1 / 21.3; 4096 rows x 11008 17.7 / 23.9 / 30.7 -> 14.6 / 19.2 / 26.2; 22016 rows x 4096
+// 23.8 / 34.8 / 46.9 -> 17.0 / 24.6 / 40.6.  What was found on the way: requests past a run's end must cost nothing (as
 // re-reads of the last line, 8 ahead, they made 4096 x 4096 cost 12 us: the loads' line accesses, not HBM, were the
 // limit) -- they ask beyond the buffer's end; two lines ahead are as fast as eight (19.6 against 23.8 us at 22016 rows);
 // sixteen wavefronts the same as eight; without the arithmetic 16.6 instead of 19.3 us, without x 1.1 us less.  What
