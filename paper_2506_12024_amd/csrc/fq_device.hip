@@ -110,6 +110,12 @@ int fq_part_bank(hipStream_t stream)
     return d && stream != hipStreamPerThread ? bank_of(d->part_stream, d->n_part_banks, FQ_PART_BANKS, stream) : -1;
 }
 
+std::mutex &fq_part_mutex()
+{
+    static std::mutex m;
+    return m;
+}
+
 hipError_t fq_raise_dynamic_lds(const void *func, size_t bytes)
 {
     std::lock_guard<std::mutex> hold(g_lock);

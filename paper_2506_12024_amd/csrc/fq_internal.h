@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <mutex>
+
 // One linear of a launch: which resident copies exist and where x and y live.
 // Plain data, passed by value in the kernel arguments (single call) or read
 // from a device table (plan).
@@ -68,6 +70,9 @@ int fq_part_bank(hipStream_t stream);
 // then adds the parts inside one workgroup, in the same order.
 constexpr size_t FQ_PART_FLOATS = (size_t)4 << 20; // 16 MiB: 256 workgroups' tiles of 128 x 128
 hipError_t fq_part_array(hipStream_t stream, float **part);
+// Held while the two launches of such a call are enqueued: of two host threads that use one stream, neither may
+// put its product between the other's product and the sum of its parts.
+std::mutex &fq_part_mutex();
 
 hipError_t fq_launch_quantize(const void *w, long long n_groups, int bits, bool symmetric, void *codes,
                               void *scales, void *zeros, hipStream_t stream);

@@ -528,6 +528,9 @@ hipError_t fq_launch_prompt(const FqLinearDesc &d, int bits, int M, FqPromptPlan
     if (plan.segments > 1)
         if (const hipError_t e = fq_part_array(stream, &part))
             return e;
+    std::unique_lock<std::mutex> both(fq_part_mutex(), std::defer_lock);
+    if (part)
+        both.lock();
     return bits == 2   ? launch_mt<2>(d, M, plan.mt, plan.segments, part, stream)
            : bits == 4 ? launch_mt<4>(d, M, plan.mt, plan.segments, part, stream)
            : bits == 8 ? launch_mt<8>(d, M, plan.mt, plan.segments, part, stream)

@@ -450,6 +450,9 @@ hipError_t fq_launch_w8a8_prompt(const FqLinearDesc &l, const void *xq, const fl
     if (plan.segments > 1)
         if (const hipError_t e = fq_part_array(stream, &part))
             return e;
+    std::unique_lock<std::mutex> both(fq_part_mutex(), std::defer_lock);
+    if (part)
+        both.lock();
     const Args d = {l.codes8, l.scales8, l.zeros8, (const int8_t *)xq, sx, xsum, l.y, M, l.N, l.K};
     if (per_row)
         return plan.mt == 1   ? launch<1, true>(d, plan.segments, part, stream)

@@ -3,6 +3,8 @@ its blocks of 32 and of its tiles, rows at the edges of 128, one to many groups 
 eight groups at a time, its steps three to a turn), one and several segments of K, against the oracle; and
 that the result is the same bits wherever the partial sums of the segments are kept.  The same for the W8A8
 product (csrc/fq_w8a8_prompt.hip) with groups of 128 and with one scale per row."""
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -84,3 +86,31 @@ def test_same_bits_with_and_without_partial_sums():
         fq.fq_linear(layer, 4, x, M, ys[0])
         torch.cuda.synchronize()
         assert torch.equal(y, want) and torch.equal(ys[0], want)
+
+
+def test_threads_on_one_stream():
+    """Two host threads, one stream, products split along K: each thread's parts are added before the other's
+    product overwrites them."""
+    N, K, reps = 512, 8192, 60
+    jobs = []
+    for j, M in enumerate((100, 64)):
+        layer, _ = make_layer(synth.weight(11, "prompt/threads/w%d" % j, N, K, 0.02), (4,))
+        x = to_dev(synth.activations(11, "prompt/threads/x%d" % j, M, K))
+        want = torch.empty((M, N), dtype=torch.float16, device=DEV)
+        fq.fq_linear(layer, 4, x, M, want)
+        jobs.append((layer, x, M, want, [torch.empty_like(want) for _ in range(reps)]))
+    torch.cuda.synchronize()
+    stream = torch.cuda.current_stream().cuda_stream
+
+    def work(layer, x, M, want, ys):
+        for y in ys:
+            fq.fq_linear(layer, 4, x, M, y, stream=stream)
+
+    threads = [threading.Thread(target=work, args=job) for job in jobs]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    for _, _, _, want, ys in jobs:
+        assert all(torch.equal(y, want) for y in ys)
