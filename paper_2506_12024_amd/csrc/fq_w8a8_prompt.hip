@@ -412,7 +412,7 @@ float large_cost(int N, int K, int M, bool per_row, int mt, int cus)
         return 5.75f + (tiles + cus - 1) / cus * (6.08f + K / 128 * (0.592f + 0.458f * mt + 0.225f * full));
     const long long per_xcd = (tiles + 7) / 8, per_round = cus >= 8 ? cus / 8 : 1, rest = per_xcd % per_round;
     const float rounds = per_xcd / per_round + (rest == 0 ? 0.f : 2 * rest <= per_round ? 0.93f : 1.f);
-    return 26.1f + rounds * (-18.4f + K / 128 * (1.29f + 1.08f * full));
+    return 8.7f + rounds * (K / 128) * (1.36f + 0.75f * full);
 }
 
 } // namespace
@@ -425,7 +425,7 @@ FqPromptPlan fq_w8a8_prompt_plan(int N, int K, int M, bool per_row, int large_mt
     FqPromptPlan best = {0, 0};
     if ((unsigned long long)groups * (unsigned long long)M * 4 > 0x7fffffffULL) // the group sums' 32-bit offsets
         return best;
-    float least = 0.95f * large_cost(N, K, M, per_row, large_mt, cus); // (within 5 %: left to the large tiles)
+    float least = 0.9f * large_cost(N, K, M, per_row, large_mt, cus); // (within a tenth: left to the large tiles)
     for (int tm = 1; tm <= 3; tm++) {
         const long long tiles = ((long long)M + 64 * tm - 1) / (64 * tm) * n_tiles;
         if (tiles > 0x3ffffffLL)
