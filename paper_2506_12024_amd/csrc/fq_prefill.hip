@@ -127,19 +127,21 @@ __device__ __forceinline__ int x_chunk(int i, int c)
     return BITS == 4 || BITS == 2 ? 4 * c + i : 2 * i + c;
 }
 
+// NT: MFMA tiles of a wavefront along the weight rows.  One, the wavefront taking all of the tile's tokens: every
+// weight is unpacked by one wavefront (with two tiles, by two, but x is read from LDS half as often), worth it where
+// the unpacking is 16 instructions per operand: 2048 x 8192 x 28672 at 4 bits 872 -> 838 us, 2 bits 900 -> 881; at 8 bits
+// 864 -> 860 but 803 -> 822 with the sizes exchanged; fp16 weights, nothing to unpack, 833 -> 868.  Calls over fewer than
+// 2048 inputs are mostly the writing of y, whose lines one wavefront writes whole only with two: 633 x 512 -> 18304 at 2
+// bits 22.8 us against 25.0.
 // HALF: the workgroup takes half a tile, 128 tokens x 256 weight rows (a wavefront half the tokens): the tiles left over after the last full round of workgroups are cut in two, so that they
 // keep twice as many CUs busy for half as long.  `skip`: first tile of this launch inside an XCD's
 // run of `per_xcd` tiles.
-template <int BITS, bool HALF>
+template <int BITS, bool HALF, int NT>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void prefill_kernel(
     const FqLinearDesc d, int M, int m_tiles, int n_tiles, int per_xcd, int skip)
 {
     constexpr int BM = HALF ? BM_FULL / 2 : BM_FULL; // tokens per workgroup
-    // MFMA tiles of a wavefront along the weight rows.  One, the wavefront taking all of the tile's tokens: every weight
-    // is unpacked by one wavefront (with two tiles, by two, but x is read from LDS half as often), worth it where the
-    // unpacking is 16 instructions per operand: 2048 x 8192 x 28672 at 4 bits 872 -> 838 us, 2 bits 900 -> 881; at 8 bits
-    // 864 -> 860 but 803 -> 822 with the sizes exchanged; fp16 weights, nothing to unpack, 833 -> 868.
-    constexpr int NT = BITS == 2 || BITS == 4 ? 1 : 2, WN = 32 * NT;
+    constexpr int WN = 32 * NT;                      // weight rows per wavefront
     constexpr int WM = BM / NT;                      // tokens per wavefront
     constexpr int MTL = WM / 32;                     // MFMA tiles of a wavefront along the tokens (4 or 2)
     constexpr int XSLAB = BM * XRB;                  // 32 or 16 KiB
@@ -457,14 +459,19 @@ static hipError_t launch_prefill(const FqLinearDesc &d, int bits, int M, int m_t
     if (per_launch <= 0)
         return hipSuccess;
     const unsigned grid = (unsigned)per_launch * (HALF ? 16u : 8u);
-    if (bits == 2)
-        prefill_kernel<2, HALF><<<grid, THREADS, 0, stream>>>(d, M, m_tiles, n_tiles, per_xcd, skip);
+    const bool once = d.K >= 2048;
+    if (bits == 2 && once)
+        prefill_kernel<2, HALF, 1><<<grid, THREADS, 0, stream>>>(d, M, m_tiles, n_tiles, per_xcd, skip);
+    else if (bits == 2)
+        prefill_kernel<2, HALF, 2><<<grid, THREADS, 0, stream>>>(d, M, m_tiles, n_tiles, per_xcd, skip);
+    else if (bits == 4 && once)
+        prefill_kernel<4, HALF, 1><<<grid, THREADS, 0, stream>>>(d, M, m_tiles, n_tiles, per_xcd, skip);
     else if (bits == 4)
-        prefill_kernel<4, HALF><<<grid, THREADS, 0, stream>>>(d, M, m_tiles, n_tiles, per_xcd, skip);
+        prefill_kernel<4, HALF, 2><<<grid, THREADS, 0, stream>>>(d, M, m_tiles, n_tiles, per_xcd, skip);
     else if (bits == 8)
-        prefill_kernel<8, HALF><<<grid, THREADS, 0, stream>>>(d, M, m_tiles, n_tiles, per_xcd, skip);
+        prefill_kernel<8, HALF, 2><<<grid, THREADS, 0, stream>>>(d, M, m_tiles, n_tiles, per_xcd, skip);
     else
-        prefill_kernel<16, HALF><<<grid, THREADS, 0, stream>>>(d, M, m_tiles, n_tiles, per_xcd, skip);
+        prefill_kernel<16, HALF, 2><<<grid, THREADS, 0, stream>>>(d, M, m_tiles, n_tiles, per_xcd, skip);
     return hipGetLastError();
 }
 
