@@ -29,6 +29,7 @@
 #include <stdint.h>
 #include <type_traits>
 
+#include "fq_batch_at.h"
 #include "fq_internal.h"
 #include "fq_mfma.h"
 
@@ -79,8 +80,8 @@ __device__ __forceinline__ void run_batch(Lds &L, const uint8_t *codes, const fl
         for (int mb = 0; mb < MB; mb++)
             sum[t][mb] = float4_t{0.f, 0.f, 0.f, 0.f};
     const __amdgpu_buffer_rsrc_t xbuf = buffer_of(x, (uint32_t)M * (uint32_t)K * 2);
-    const __amdgpu_buffer_rsrc_t wbuf = buffer_of(codes + (size_t)n0 * row_bytes, (uint32_t)min(nt * 16, N - n0) * row_bytes);
-    const uint32_t lane_off = (uint32_t)n * row_bytes + c * 16;
+    const __amdgpu_buffer_rsrc_t wbuf = buffer_of(codes + (size_t)n0 * row_bytes, batch_run_bytes(row_bytes, nt, N - n0));
+    const uint32_t lane_off = batch_lane_offset(row_bytes, n, c);
     // x operand reads: piece p of batch row n in a slab of 64 inputs
     uint32_t xat[8];
 #pragma unroll
@@ -116,12 +117,11 @@ __device__ __forceinline__ void run_batch(Lds &L, const uint8_t *codes, const fl
         int it = 0, il = wave; // the next request: tile and line
         const uint32_t line0 = (uint32_t)k0 * BITS / 8;
         auto issue = [&](u32x4 (&to)[2]) {
-            // Past the last line the lanes ask beyond the buffer's end, which costs no access.  (An odd number of
-            // groups at 4 bits: the second half of a row's last line is the next row's, and not used.)
-            const uint32_t at = it < nt ? lane_off : 0xffffff00u;
-            const uint32_t off = (uint32_t)it * 16 * row_bytes + line0 + (uint32_t)il * 128;
-            to[0] = __builtin_amdgcn_raw_buffer_load_b128(wbuf, (int)at, (int)off, 0);
-            to[1] = __builtin_amdgcn_raw_buffer_load_b128(wbuf, (int)at, (int)(off + 64), 0);
+            // Past the last line the lanes ask beyond the buffer's end, which costs no access (fq_batch_at.h).  An odd
+            // number of groups at 4 bits: the second half of a row's last line is the next row's, and not used.
+            const uint32_t at = batch_request(row_bytes, lane_off, it, line0, il);
+            to[0] = __builtin_amdgcn_raw_buffer_load_b128(wbuf, (int)at, 0, 0);
+            to[1] = __builtin_amdgcn_raw_buffer_load_b128(wbuf, (int)(at + 64), 0, 0);
             il += WAVES;
             if (il >= lines) {
                 il = wave;

@@ -1,0 +1,98 @@
+"""Every weight request of the small-batch kernel (csrc/fq_batch.hip) stays inside the weight it reads (CPU only).
+
+The kernel's address rule is plain integer code (csrc/fq_batch_at.h).  It is compiled for the host here, and the
+requests of a run -- every wavefront, line, lane and half line, and the requests ahead past the last tile -- are
+walked as the kernel walks them.  A lane whose offset is below the descriptor's size reads 16 bytes at that
+offset; one whose offset is not reads nothing.  (The scalar offset is no part of the range check: the rule
+must hold without it, and the kernel passes none.)"""
+import ctypes
+import itertools
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2506_12024_amd", "csrc")
+
+DRIVER = r"""
+#include "fq_batch_at.h"
+// Walks one run of nt tiles from row n0 of an N x K weight at `bits`; panels of kp inputs.  Returns the number of
+// reads that leave the weight, and counts in *missing the 16-byte pieces of the run's rows that nobody read.
+extern "C" long walk(int N, int K, int bits, int n0, int nt, int kp_max, unsigned char *seen, long *missing)
+{
+    const uint32_t row_bytes = (uint32_t)((long)K * bits / 8);
+    const long whole = (long)N * row_bytes, base = (long)n0 * row_bytes;
+    const uint32_t records = batch_run_bytes(row_bytes, nt, N - n0);
+    const int KL = 1024 / bits, WAVES = 8, AHEAD = 2;
+    long bad = 0;
+    for (int k0 = 0; k0 < K; k0 += kp_max) {
+        const int kp = K - k0 < kp_max ? K - k0 : kp_max, lines = (kp + KL - 1) / KL;
+        const uint32_t line0 = (uint32_t)((long)k0 * bits / 8);
+        for (int wave = 0; wave < WAVES; wave++) {
+            if (lines <= wave)
+                continue; // no line of this panel: no request
+            const int items = (lines - wave + WAVES - 1) / WAVES * nt;
+            int it = 0, il = wave;
+            for (int i = 0; i < items + 2 * AHEAD; i++) {
+                for (int lane = 0; lane < 64; lane++)
+                    for (int half = 0; half < 2; half++) {
+                        const uint32_t at = batch_request(row_bytes, batch_lane_offset(row_bytes, lane & 15, lane >> 4), it,
+                                                          line0, il) + 64 * half;
+                        if (at >= records)
+                            continue;
+                        const long addr = base + (long)at;
+                        if (addr < 0 || addr + 16 > whole)
+                            bad++;
+                        else if (i < items)
+                            seen[addr / 16] = 1;
+                    }
+                il += WAVES;
+                if (il >= lines)
+                    il = wave, it++;
+            }
+        }
+    }
+    *missing = 0;
+    const long last = n0 + nt * 16 < N ? n0 + nt * 16 : N;
+    for (long p = base / 16; p < last * row_bytes / 16; p++)
+        *missing += !seen[p];
+    return bad;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def walk(tmp_path_factory):
+    d = tmp_path_factory.mktemp("batch_at")
+    src, lib = str(d / "walk.cpp"), str(d / "walk.so")
+    with open(src, "w") as f:
+        f.write(DRIVER)
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-Wall", "-shared", "-fPIC", "-I", CSRC, "-o", lib, src])
+    fn = ctypes.CDLL(lib).walk
+    fn.restype = ctypes.c_long
+    return fn
+
+
+@pytest.mark.parametrize("bits", [4, 8, 16])
+def test_requests_stay_inside_the_weight(walk, bits):
+    # whole and partial last tiles, alone and at the end of a run; one group, odd and even numbers of groups; several
+    # panels of x (4096 inputs up to 16 batch rows, 2048 above)
+    for (N, K, kp), nt in itertools.product([(16, 128, 4096), (1, 128, 4096), (33, 384, 4096), (37, 1152, 4096),
+                                             (95, 2176, 2048), (96, 2176, 2048), (100, 4224, 4096), (61, 11008, 2048)],
+                                            range(1, 7)):
+        tiles = (N + 15) // 16
+        for t0 in range(tiles):
+            if t0 + nt > tiles:
+                continue
+            seen = (ctypes.c_ubyte * (N * K * bits // 128 + 1))()
+            missing = ctypes.c_long()
+            bad = walk(N, K, bits, t0 * 16, nt, kp, seen, ctypes.byref(missing))
+            assert (bad, missing.value) == (0, 0), (N, K, t0, nt)
+
+
+def test_the_last_offsets_do_not_wrap(walk):
+    # the longest rows and runs the kernel takes: 6 tiles and two requests ahead of 65536-byte rows
+    seen = (ctypes.c_ubyte * (112 * 32768 * 16 // 128 + 1))()
+    missing = ctypes.c_long()
+    assert walk(112, 32768, 16, 16, 6, 2048, seen, ctypes.byref(missing)) == 0 and missing.value == 0

@@ -34,6 +34,21 @@ def test_single_call(M, N, K, bits):
     assert rel_err(gpu_linear(layer, bits, x), _ref(w, packed, bits, x)) <= TOL
 
 
+@pytest.mark.parametrize("bits", [4, 8, 16])
+@pytest.mark.parametrize("M,N,K", [(7, 11205, 384), (20, 8201, 1152)])
+def test_partial_tile_behind_others_of_its_run(M, N, K, bits):
+    # two or three tiles of 16 rows per workgroup on 256 compute units, the last one partly filled; odd numbers of
+    # groups (at 4 bits half a 128-byte line is left over); and the same bits from every call
+    name = "batch/ragged/%dx%d" % (N, K)
+    w = synth.weight(13, name + "/w", N, K, 0.02)
+    x = synth.activations(13, name + "/x", M, K)
+    layer, packed = make_layer(w, (bits,))
+    y = gpu_linear(layer, bits, x)
+    assert rel_err(y, _ref(w, packed, bits, x)) <= TOL
+    for _ in range(3):
+        assert np.array_equal(gpu_linear(layer, bits, x).view(np.uint16), y.view(np.uint16))
+
+
 @pytest.mark.parametrize("M", [3, 16, 32])
 def test_plan_of_mixed_entries(M):
     # 30000 rows are seven tiles of 16 per workgroup on 256 compute units; the rest are slivers beside them
