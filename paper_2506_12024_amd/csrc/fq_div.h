@@ -12,10 +12,12 @@
 // z: that can differ only next to the numbers n / 2 and n / 2 +- 2^-i at which the sum's rounding turns over, and for the
 // 11-bit w and 24-bit s all the pairs within 64 units of such a middle (1943 of them) were enumerated on the host:
 // every one rounds like the division; so do 5 10^9 random pairs.  For finite halves and scales of groups of halves
-// (2^-32 .. 2^17) nothing under- or overflows on the way.
+// (2^-32 .. 2^17) nothing under- or overflows on the way.  An infinite scale (a group that holds an infinity)
+// has y = 0 and would make the residual 0 * infinity: it is left out of the residual, so that finite numerators
+// divide to 0 and infinite ones to NaN.
 struct Divisor {
     float s, y;
-    __device__ __forceinline__ explicit Divisor(float d) : s(d), y(__fdiv_rn(1.0f, d)) {}
+    __device__ __forceinline__ explicit Divisor(float d) : s(d == __builtin_inff() ? 0.0f : d), y(__fdiv_rn(1.0f, d)) {}
     __device__ __forceinline__ float of(float w) const
     {
         const float q0 = __fmul_rn(w, y);
