@@ -512,7 +512,13 @@ hipError_t fq_part_array(hipStream_t stream, float **part)
 {
     *part = nullptr;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone)
+    if (hipStreamIsCapturing(stream, &capture) != hipSuccess) {
+        // (the null stream while a blocking stream is captured: the question fails, launches do not.  The failure
+        // is not left for the query after the launch to find.)
+        (void)hipGetLastError();
+        return hipSuccess;
+    }
+    if (capture != hipStreamCaptureStatusNone)
         return hipSuccess;
     const int bank = fq_part_bank(stream);
     if (bank < 0)

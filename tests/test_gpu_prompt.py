@@ -3,6 +3,7 @@ its blocks of 32 and of its tiles, rows at the edges of 128, one to many groups 
 eight groups at a time, its steps three to a turn), one and several segments of K, against the oracle; and
 that the result is the same bits wherever the partial sums of the segments are kept.  The same for the W8A8
 product (csrc/fq_w8a8_prompt.hip) with groups of 128 and with one scale per row."""
+import ctypes
 import threading
 
 import numpy as np
@@ -114,3 +115,36 @@ def test_threads_on_one_stream():
     torch.cuda.synchronize()
     for _, _, _, want, ys in jobs:
         assert all(torch.equal(y, want) for y in ys)
+
+
+def test_null_stream_beside_a_captured_blocking_stream():
+    """While a stream that synchronizes with the null stream is being captured, the runtime answers no question
+    about the null stream, but takes launches on it: the calls run, without partial sums in memory."""
+    with open("/proc/self/maps") as f:
+        hip = ctypes.CDLL([line.split()[-1] for line in f if "libamdhip64" in line][0])
+    M, N, K = 100, 512, 8192
+    layer, _ = make_layer(synth.weight(11, "prompt/null/w", N, K, 0.02), (4, 8))
+    x = to_dev(synth.activations(11, "prompt/null/x", M, K))
+    xq, sx, xsum = (torch.empty(s, dtype=t, device=DEV) for s, t in
+                    (((M, K), torch.int8), ((M,), torch.float32), ((K // 128, M), torch.int32)))
+    fq.fq_quantize_act(x, M, K, xq, sx, xsum, stream=0)
+    want, y = (torch.empty((2, M, N), dtype=torch.float16, device=DEV) for _ in range(2))
+
+    def calls(out):
+        fq.fq_linear(layer, 4, x, M, out[0], stream=0)
+        fq.fq_linear_w8a8(layer, xq, sx, xsum, M, out[1], stream=0)
+
+    calls(want)
+    torch.cuda.synchronize()
+    stream, graph = ctypes.c_void_p(), ctypes.c_void_p()
+    assert hip.hipStreamCreateWithFlags(ctypes.byref(stream), 0) == 0  # 0: blocking
+    try:
+        assert hip.hipStreamBeginCapture(stream, 2) == 0               # 2: relaxed
+        try:
+            calls(y)
+        finally:
+            assert hip.hipStreamEndCapture(stream, ctypes.byref(graph)) == 0
+    finally:
+        assert hip.hipStreamDestroy(stream) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(y, want)
