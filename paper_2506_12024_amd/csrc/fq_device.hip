@@ -103,17 +103,20 @@ int fq_stream_bank(hipStream_t stream)
     return d ? bank_of(d->bank_stream, d->n_banks, FQ_BANKS, stream) : -1;
 }
 
-int fq_part_bank(hipStream_t stream)
+int fq_part_bank(hipStream_t stream, int *device)
 {
     std::lock_guard<std::mutex> hold(g_lock);
     DeviceFacts *d = current();
-    return d && stream != hipStreamPerThread ? bank_of(d->part_stream, d->n_part_banks, FQ_PART_BANKS, stream) : -1;
+    if (!d || stream == hipStreamPerThread)
+        return -1;
+    *device = (int)(d - g_dev);
+    return bank_of(d->part_stream, d->n_part_banks, FQ_PART_BANKS, stream);
 }
 
-std::mutex &fq_part_mutex()
+std::mutex *fq_part_mutex(int device, int bank)
 {
-    static std::mutex m;
-    return m;
+    static std::mutex m[MAX_DEVICES][FQ_PART_BANKS];
+    return &m[device][bank];
 }
 
 hipError_t fq_raise_dynamic_lds(const void *func, size_t bytes)

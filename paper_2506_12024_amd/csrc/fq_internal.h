@@ -65,14 +65,15 @@ int fq_stream_bank(hipStream_t stream);
 // The same for the partial sums of products split along K, whose copies are larger and fewer; -1 also for
 // hipStreamPerThread, one handle for as many streams as there are threads.
 constexpr int FQ_PART_BANKS = 4;
-int fq_part_bank(hipStream_t stream);
+int fq_part_bank(hipStream_t stream, int *device);
 // The stream's array for such sums (FQ_PART_FLOATS words), null if it has none or is being captured: the caller
-// then adds the parts inside one workgroup, in the same order.
+// then adds the parts inside one workgroup, in the same order.  `both` is locked with the array's mutex and held
+// while the two launches of such a call are enqueued: of two host threads that use one stream, neither may
+// put its product between the other's product and the sum of its parts.  (A mutex for each array: calls on other
+// streams and devices do not wait for a launch that waits for room in its queue.)
 constexpr size_t FQ_PART_FLOATS = (size_t)4 << 20; // 16 MiB: 256 workgroups' tiles of 128 x 128
-hipError_t fq_part_array(hipStream_t stream, float **part);
-// Held while the two launches of such a call are enqueued: of two host threads that use one stream, neither may
-// put its product between the other's product and the sum of its parts.
-std::mutex &fq_part_mutex();
+hipError_t fq_part_array(hipStream_t stream, float **part, std::unique_lock<std::mutex> &both);
+std::mutex *fq_part_mutex(int device, int bank);
 
 hipError_t fq_launch_quantize(const void *w, long long n_groups, int bits, bool symmetric, void *codes,
                               void *scales, void *zeros, hipStream_t stream);

@@ -508,7 +508,7 @@ FqPromptPlan fq_prompt_plan(int N, int K, int bits, int M, int cus)
     return best;
 }
 
-hipError_t fq_part_array(hipStream_t stream, float **part)
+hipError_t fq_part_array(hipStream_t stream, float **part, std::unique_lock<std::mutex> &both)
 {
     *part = nullptr;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
@@ -520,24 +520,24 @@ hipError_t fq_part_array(hipStream_t stream, float **part)
     }
     if (capture != hipStreamCaptureStatusNone)
         return hipSuccess;
-    const int bank = fq_part_bank(stream);
+    int device = 0;
+    const int bank = fq_part_bank(stream, &device);
     if (bank < 0)
         return hipSuccess;
-    hipError_t e = hipGetSymbolAddress((void **)part, HIP_SYMBOL(g_part));
-    if (e == hipSuccess)
-        *part += (size_t)bank * PART_FLOATS;
-    return e;
+    if (const hipError_t e = hipGetSymbolAddress((void **)part, HIP_SYMBOL(g_part)))
+        return e;
+    *part += (size_t)bank * PART_FLOATS;
+    both = std::unique_lock<std::mutex>(*fq_part_mutex(device, bank));
+    return hipSuccess;
 }
 
 hipError_t fq_launch_prompt(const FqLinearDesc &d, int bits, int M, FqPromptPlan plan, hipStream_t stream)
 {
     float *part = nullptr;
+    std::unique_lock<std::mutex> both;
     if (plan.segments > 1)
-        if (const hipError_t e = fq_part_array(stream, &part))
+        if (const hipError_t e = fq_part_array(stream, &part, both))
             return e;
-    std::unique_lock<std::mutex> both(fq_part_mutex(), std::defer_lock);
-    if (part)
-        both.lock();
     return bits == 2   ? launch_mt<2>(d, M, plan.mt, plan.segments, part, stream)
            : bits == 4 ? launch_mt<4>(d, M, plan.mt, plan.segments, part, stream)
            : bits == 8 ? launch_mt<8>(d, M, plan.mt, plan.segments, part, stream)

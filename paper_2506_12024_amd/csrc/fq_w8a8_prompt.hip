@@ -447,12 +447,10 @@ hipError_t fq_launch_w8a8_prompt(const FqLinearDesc &l, const void *xq, const fl
                                  bool per_row, FqPromptPlan plan, hipStream_t stream)
 {
     float *part = nullptr;
+    std::unique_lock<std::mutex> both;
     if (plan.segments > 1)
-        if (const hipError_t e = fq_part_array(stream, &part))
+        if (const hipError_t e = fq_part_array(stream, &part, both))
             return e;
-    std::unique_lock<std::mutex> both(fq_part_mutex(), std::defer_lock);
-    if (part)
-        both.lock();
     const Args d = {l.codes8, l.scales8, l.zeros8, (const int8_t *)xq, sx, xsum, l.y, M, l.N, l.K};
     if (per_row)
         return plan.mt == 1   ? launch<1, true>(d, plan.segments, part, stream)
