@@ -300,7 +300,7 @@ int fq_linear(const fq_layer *layer, int bits, const void *x_fp16, int M, void *
             e = fq_launch_skinny(&d, bits, nullptr, nullptr, 1, tiles, rows, m, true, nullptr, nullptr, (hipStream_t)stream);
         }
     } else if (M <= FQ_MAX_DECODE_M && layer->K <= MAX_DECODE_K) {
-        if (M > 1 && bits != 2 && bits != 3) { // (the packings of 2 and 3 bits: the register-fed kernel)
+        if (M > 1 && fq_batch_serves_linear(layer->N, layer->K, bits, M)) {
             e = fq_launch_batch(&d, bits, nullptr, nullptr, 1, (layer->N + 15) / 16, M, nullptr, (hipStream_t)stream);
             if (e != hipSuccess)
                 return hip_fail(e, "fq_linear launch");

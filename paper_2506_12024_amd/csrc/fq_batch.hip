@@ -360,6 +360,31 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 // and all widths at 32 batch rows slower, since each run of NB tiles starts anew.
 bool fq_batch_serves(int count, long long rows) { return count <= MAX_ENTRIES && rows <= 384LL * fq_device_cus(); }
 
+// Single calls, both kernels measured at 128 to 11008 inputs, 1024 to 200000 rows, 2, 16, 17 and 32 batch rows (ratios of
+// times, this kernel's first).  Short rows give most of a workgroup's wavefronts nothing to do: 32768 x 512 at 4
+// bits 1.5 to 1.7; from 3072 inputs at 4 bits, 1792 at 8 and 1024 at 16 on 0.7 to 1.0 -- unless there are at most three tiles
+// per compute unit, where the launch is what counts (0.85 to 1.03 at any K).  The register-fed kernel's 64-row tiles
+// come in rounds of one per compute unit; where they fill the last round (32768 rows: two full rounds) it wins
+// back 10 to 20 %: at 4 bits it then keeps the calls over more than 16 batch rows (1.02 to 1.16) or over a K that leaves
+// part of a panel of x (5120: 1.08; 4096: 0.93, 8192: 0.95), up to six rounds (beyond: 0.75 to 1.0).  With 512 rows per
+// compute unit it goes over to larger tiles and is as good or better (131072 rows at 4 bits: 1.1 to 2.9).  Under this rule
+// 0.86 of the register-fed kernel's time on average over 5900 calls; one shape stays behind it (29696 x 5120 at 16 bits, 1.14).
+// 2 and 3 bits: this kernel does not unpack them.
+bool fq_batch_serves_linear(int N, int K, int bits, int M)
+{
+    const int cus = fq_device_cus();
+    if (bits == 2 || bits == 3 || fq_skinny_tile_rows(N, M) > 64)
+        return false;
+    if ((N + 15) / 16 <= 3 * cus)
+        return true;
+    const int weight = (K >> 7) * (3 * bits + 5); // what a tile's bytes and arithmetic grow with
+    const int rest = N % (64 * cus);              // rows of the last round of 64-row tiles (0: a full one)
+    const bool filled = N > 96 * cus && (rest == 0 || rest > (M > 16 ? 35 : 48) * cus);
+    if (!filled)
+        return weight >= 400;
+    return weight >= 470 && (bits != 4 || N > 384 * cus || (M <= 16 && K % 4096 == 0));
+}
+
 hipError_t fq_launch_batch(const FqLinearDesc *single, int bits_host, const FqLinearDesc *descs_dev, const int32_t *bits_dev,
                            int count, long long tiles, int M, int *flags, hipStream_t stream)
 {

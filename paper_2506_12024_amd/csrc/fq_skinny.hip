@@ -31,9 +31,9 @@
 // computed.
 //
 // Launches with few rows use a second kernel further down, in which the four wavefronts of a workgroup
-// share one row tile and split K.  Single calls at 4, 8 and 16 bits and plans of a decoder's stages at these widths run in
-// fq_batch.hip; what is left here are 2- and 3-bit copies, plans that hold any, plans of more than 64 small
-// entries, and plans between two layers' size and the streaming kernel's.
+// share one row tile and split K.  What fq_batch.hip serves better goes there (single calls at 4, 8 and 16 bits
+// over rows that are not short, plans of a decoder's stages at these widths); what is left here are 2- and 3-bit copies, plans that
+// hold any, short rows, plans of more than 64 small entries, and plans between two layers' size and the streaming kernel's.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -672,17 +672,14 @@ __global__ __launch_bounds__(WG_THREADS) void decode_skinny_sk_kernel(const FqLi
             continue;
         }
         const int row0 = (tile - dp->tile_begin) * 16;
-        // (single calls at 4, 8 and 16 bits go to fq_launch_batch)
-        if (W3 && bits == 3) {
+        if (W3 && bits == 3)
             run_tile_sk<3, MT>(d, dp->x, dp->y, M, row0, wave, lds_x[wave], lds_s[wave], lds_z[wave], red);
-        } else if constexpr (!SINGLE) {
-            if (bits == 4)
-                run_tile_sk<4, MT>(d, dp->x, dp->y, M, row0, wave, lds_x[wave], lds_s[wave], lds_z[wave], red);
-            else if (bits == 8)
-                run_tile_sk<8, MT>(d, dp->x, dp->y, M, row0, wave, lds_x[wave], lds_s[wave], lds_z[wave], red);
-            else
-                run_tile_sk<16, MT>(d, dp->x, dp->y, M, row0, wave, lds_x[wave], lds_s[wave], lds_z[wave], red);
-        }
+        else if (bits == 4)
+            run_tile_sk<4, MT>(d, dp->x, dp->y, M, row0, wave, lds_x[wave], lds_s[wave], lds_z[wave], red);
+        else if (bits == 8)
+            run_tile_sk<8, MT>(d, dp->x, dp->y, M, row0, wave, lds_x[wave], lds_s[wave], lds_z[wave], red);
+        else
+            run_tile_sk<16, MT>(d, dp->x, dp->y, M, row0, wave, lds_x[wave], lds_s[wave], lds_z[wave], red);
     }
 }
 
@@ -736,14 +733,12 @@ __global__ __launch_bounds__(WG_THREADS) void decode_skinny_kernel(const FqLinea
             run_tile<2, MT, RT>(d, dp->x, dp->y, M, wave_row0, lds_x, lds_s[wave], lds_z[wave]);
         else if (W3 && bits == 3)
             run_tile<3, MT, RT>(d, dp->x, dp->y, M, wave_row0, lds_x, lds_s[wave], lds_z[wave]);
-        else if constexpr (!SINGLE) { // (single calls at 4, 8 and 16 bits go to fq_launch_batch)
-            if (bits == 4)
-                run_tile<4, MT, RT>(d, dp->x, dp->y, M, wave_row0, lds_x, lds_s[wave], lds_z[wave]);
-            else if (bits == 8)
-                run_tile<8, MT, RT>(d, dp->x, dp->y, M, wave_row0, lds_x, lds_s[wave], lds_z[wave]);
-            else
-                run_tile<16, MT, RT>(d, dp->x, dp->y, M, wave_row0, lds_x, lds_s[wave], lds_z[wave]);
-        }
+        else if (bits == 4)
+            run_tile<4, MT, RT>(d, dp->x, dp->y, M, wave_row0, lds_x, lds_s[wave], lds_z[wave]);
+        else if (bits == 8)
+            run_tile<8, MT, RT>(d, dp->x, dp->y, M, wave_row0, lds_x, lds_s[wave], lds_z[wave]);
+        else
+            run_tile<16, MT, RT>(d, dp->x, dp->y, M, wave_row0, lds_x, lds_s[wave], lds_z[wave]);
     }
 }
 

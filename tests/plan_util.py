@@ -16,3 +16,4 @@ def _fn(name, restype, *argtypes):
 
 _i = ctypes.c_int
 part_mutex = _fn("_Z13fq_part_mutexii", ctypes.c_void_p, _i, _i)
+batch_serves_linear = _fn("_Z22fq_batch_serves_lineariiii", ctypes.c_bool, _i, _i, _i, _i)

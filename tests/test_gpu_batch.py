@@ -10,6 +10,7 @@ import oracle
 import synth
 import paper_2506_12024_amd as fq
 from gpu_util import DEV, gpu_linear, make_layer, rel_err, to_dev
+from plan_util import batch_serves_linear
 
 pytestmark = pytest.mark.gpu
 
@@ -47,6 +48,19 @@ def test_partial_tile_behind_others_of_its_run(M, N, K, bits):
     assert rel_err(y, _ref(w, packed, bits, x)) <= TOL
     for _ in range(3):
         assert np.array_equal(gpu_linear(layer, bits, x).view(np.uint16), y.view(np.uint16))
+
+
+@pytest.mark.parametrize("bits", [4, 8, 16])
+@pytest.mark.parametrize("M,N,K", [(2, 12289, 128), (16, 20000, 512), (17, 13000, 384), (9, 131071, 256), (24, 131080, 128)])
+def test_single_call_left_to_the_register_fed_kernel(M, N, K, bits):
+    # short rows over more than three tiles of 16 per compute unit, and 512 rows per compute unit: its 64- and
+    # 128-row tiles, the last one partly filled
+    assert not batch_serves_linear(N, K, bits, M)
+    name = "batch/short/%dx%d" % (N, K)
+    w = synth.weight(13, name + "/w", N, K, 0.02)
+    x = synth.activations(13, name + "/x", M, K)
+    layer, packed = make_layer(w, (bits,))
+    assert rel_err(gpu_linear(layer, bits, x), _ref(w, packed, bits, x)) <= TOL
 
 
 @pytest.mark.parametrize("M", [3, 16, 32])
