@@ -4,7 +4,7 @@
 // 10 to 90 MB lasts 8 to 25 us, so that its start, its end and an even division count as much.
 //
 // Work split.  One workgroup (8 wavefronts) per compute unit.  The launch's tiles of 16 weight rows are divided
-// among them by cost (tile_cost), a contiguous run each; every workgroup works the division out from the
+// among them by cost (batch_tile_cost), a contiguous run each; every workgroup works the division out from the
 // entries' shapes and the bit-widths it finds in device memory, one entry per lane.  Within a tile the wavefronts
 // split K: wavefront w takes the 128-byte lines w, w + 8, ... of all 16 rows, so that a step of the workgroup reads
 // 1 KiB of each row, and their sums meet in LDS at the end, added in the wavefronts' order.
@@ -263,12 +263,6 @@ __device__ __forceinline__ void run_batch(Lds &L, const uint8_t *codes, const fl
     }
 }
 
-// What a tile costs, in thirds of a 128-byte line of its 16 rows (29 ns): its lines, and per input what
-// unpacking, folding and adding up cost whatever the width (22016 rows of 4096 inputs at 16 batch rows: 2.0 / 3.4 /
-// 6.2 us a tile at 4 / 8 / 16 bits).  An entry's first tile also pays for the start on it: x, scales, the ramp.
-__device__ __forceinline__ int tile_cost(int K, int bits) { return (K >> 7) * (3 * bits + 5) / 8 + 1; }
-constexpr uint32_t START_COST = 50;
-
 template <bool SINGLE, int MB>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_batch_kernel(
     const FqLinearDesc single, int bits_host, const FqLinearDesc *__restrict__ table, const int32_t *__restrict__ bits_dev,
@@ -292,7 +286,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
         e_zeros = e_bits == 4 ? z4 : z8;
         if (e_codes) {
             e_tiles = (e_N + 15) >> 4;
-            e_cost = tile_cost(e_K, e_bits);
+            e_cost = batch_tile_cost(XBYTES / (32 * MB), e_K, e_bits);
         } else if (flags && blockIdx.x == 0 && threadIdx.x < 64) {
             *flags = 1; // no such width here, or no copy of it: nobody runs this entry
         }
@@ -302,7 +296,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
         const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)v, e), hi = __builtin_amdgcn_readlane((uint32_t)(v >> 32), e);
         return reinterpret_cast<const void *>((uint64_t)hi << 32 | lo);
     };
-    const uint32_t e_all = e_tiles > 0 ? (uint32_t)e_tiles * e_cost + START_COST : 0u;
+    const uint32_t e_all = e_tiles > 0 ? (uint32_t)e_tiles * e_cost + BATCH_START_COST : 0u;
     uint32_t upto = e_all; // inclusive prefix
     if (!SINGLE) {
 #pragma unroll
@@ -313,15 +307,11 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
         }
     }
     const uint32_t all = SINGLE ? __builtin_amdgcn_readfirstlane(upto) : __builtin_amdgcn_readlane(upto, 63);
-    const uint32_t before = upto - e_all + START_COST;
-    // this workgroup's share [lo, hi) of the cost; a tile belongs to the share its first unit lies in
-    const uint32_t each = all / gridDim.x, rest = all % gridDim.x;
-    const uint32_t lo = each * blockIdx.x + rest * blockIdx.x / gridDim.x;
-    const uint32_t hi = each * (blockIdx.x + 1) + rest * (blockIdx.x + 1) / gridDim.x;
+    // this workgroup's share of the cost; a tile belongs to the share its first unit lies in
     int t_lo = 0, t_hi = 0;
     if (e_tiles > 0) {
-        t_lo = lo <= before ? 0 : (int)min((uint32_t)e_tiles, (lo - before + e_cost - 1) / e_cost);
-        t_hi = hi <= before ? 0 : (int)min((uint32_t)e_tiles, (hi - before + e_cost - 1) / e_cost);
+        t_lo = batch_first_tile(batch_share(all, blockIdx.x, gridDim.x), upto - e_all, e_cost, e_tiles);
+        t_hi = batch_first_tile(batch_share(all, blockIdx.x + 1, gridDim.x), upto - e_all, e_cost, e_tiles);
     }
     unsigned long long todo = __ballot(t_hi > t_lo);
     const uint16_t *x_in = nullptr; // whose first panel is in LDS (all of it: one panel)

@@ -1,5 +1,5 @@
-// Where the weight requests of the small-batch kernel (fq_batch.hip) go: plain integer code, so that a host
-// program can check every request of a launch against the array it reads.
+// Where the weight requests of the small-batch kernel (fq_batch.hip) go and how it divides a launch: plain integer
+// code, so that a host program can check every request against the array it reads, and every division.
 //
 // A run of `rows` weight rows is read through a buffer descriptor of rows * row_bytes bytes.  Whether a request is
 // in range must not depend on the scalar offset of the instruction (compilers are free to leave it out of the
@@ -31,6 +31,33 @@ FQ_BATCH_FN uint32_t batch_lane_offset(uint32_t row_bytes, int n, int c) { retur
 FQ_BATCH_FN uint32_t batch_request(uint32_t row_bytes, uint32_t lane_offset, int tile, uint32_t line0, int line)
 {
     return lane_offset + ((uint32_t)tile * 16 * row_bytes + line0 + (uint32_t)line * 128);
+}
+
+// What a tile of 16 rows costs, in units of 10 ns, fitted to single calls of 128 to 11008 inputs and 1024 to 98304
+// rows: a part that does not depend on K (sums, stores, its share of a run's start), its bytes, its lines in turns of
+// the eight wavefronts -- a panel (4096 inputs up to 16 batch rows, 2048 above) that does not fill its last turn pays for all of
+// it -- and, for each panel after the first, its share of the wait for x and scales.  Without the first part
+// short rows look free beside long ones, and one workgroup gets hundreds of their tiles: rows 14848 x 5120, 12741 x
+// 512, 1408 x 5120, 21248 x 5120 at 16, 4, 8 and 4 bits, 4 batch rows, took 205 us against 71 on the register-fed kernel; now
+// 60.  An entry's first tile also pays for the start on it (100 to 200 units do the same; 50 are 1 % slower over 1200 plans).
+constexpr uint32_t BATCH_START_COST = 160;
+FQ_BATCH_FN int batch_tile_cost(int panel, int K, int bits)
+{
+    const int turns = K / panel * (panel / 1024 * bits / 8) + (((K % panel * bits + 1023) >> 10) + 7) / 8;
+    const int per_group = bits == 4 ? 54 : bits == 8 ? 75 : 142;
+    return (bits == 16 ? 40 : 66) + (K >> 7) * per_group / 10 + turns * (panel == 4096 ? 11 : 25) +
+           ((K + panel - 1) / panel - 1) * (panel == 4096 ? 55 : 30);
+}
+
+// Share i of n of a launch's cost begins here.
+FQ_BATCH_FN uint32_t batch_share(uint32_t all, uint32_t i, uint32_t n) { return all / n * i + all % n * i / n; }
+
+// The first tile of an entry that does not begin ahead of `at`; the entry begins at `begin`.
+FQ_BATCH_FN int batch_first_tile(uint32_t at, uint32_t begin, int cost, int tiles)
+{
+    const uint32_t first = begin + BATCH_START_COST;
+    const uint32_t t = at <= first ? 0 : (at - first + (uint32_t)cost - 1) / (uint32_t)cost;
+    return (int)(t < (uint32_t)tiles ? t : (uint32_t)tiles);
 }
 
 #endif

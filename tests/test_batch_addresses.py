@@ -1,6 +1,7 @@
-"""Every weight request of the small-batch kernel (csrc/fq_batch.hip) stays inside the weight it reads (CPU only).
+"""Every weight request of the small-batch kernel (csrc/fq_batch.hip) stays inside the weight it reads, and its
+division of a launch gives every tile to one workgroup and no workgroup far too many (CPU only).
 
-The kernel's address rule is plain integer code (csrc/fq_batch_at.h).  It is compiled for the host here, and the
+The kernel's address and division rules are plain integer code (csrc/fq_batch_at.h), compiled for the host here.  The
 requests of a run -- every wavefront, line, lane and half line, and the requests ahead past the last tile -- are
 walked as the kernel walks them.  A lane whose offset is below the descriptor's size reads 16 bytes at that
 offset; one whose offset is not reads nothing.  (The scalar offset is no part of the range check: the rule
@@ -59,19 +60,39 @@ extern "C" long walk(int N, int K, int bits, int n0, int nt, int kp_max, unsigne
         *missing += !seen[p];
     return bad;
 }
+// The tiles of each entry that share i of `shares` takes: out[2 * (i * count + e)] .. out[2 * (i * count + e) + 1].
+extern "C" void divide(int count, const int *N, const int *K, const int *bits, int panel, int shares, int *out)
+{
+    uint32_t all = 0;
+    for (int e = 0; e < count; e++)
+        all += (uint32_t)((N[e] + 15) / 16) * batch_tile_cost(panel, K[e], bits[e]) + BATCH_START_COST;
+    for (int i = 0; i < shares; i++) {
+        uint32_t begin = 0;
+        for (int e = 0; e < count; e++) {
+            const int tiles = (N[e] + 15) / 16, cost = batch_tile_cost(panel, K[e], bits[e]);
+            for (int h = 0; h < 2; h++)
+                out[2 * (i * count + e) + h] = batch_first_tile(batch_share(all, i + h, shares), begin, cost, tiles);
+            begin += (uint32_t)tiles * cost + BATCH_START_COST;
+        }
+    }
+}
 """
 
 
 @pytest.fixture(scope="module")
-def walk(tmp_path_factory):
+def lib(tmp_path_factory):
     d = tmp_path_factory.mktemp("batch_at")
     src, lib = str(d / "walk.cpp"), str(d / "walk.so")
     with open(src, "w") as f:
         f.write(DRIVER)
     subprocess.check_call(["g++", "-O2", "-std=c++17", "-Wall", "-shared", "-fPIC", "-I", CSRC, "-o", lib, src])
-    fn = ctypes.CDLL(lib).walk
-    fn.restype = ctypes.c_long
-    return fn
+    return ctypes.CDLL(lib)
+
+
+@pytest.fixture(scope="module")
+def walk(lib):
+    lib.walk.restype = ctypes.c_long
+    return lib.walk
 
 
 @pytest.mark.parametrize("bits", [4, 8, 16])
@@ -96,3 +117,32 @@ def test_the_last_offsets_do_not_wrap(walk):
     seen = (ctypes.c_ubyte * (112 * 32768 * 16 // 128 + 1))()
     missing = ctypes.c_long()
     assert walk(112, 32768, 16, 16, 6, 2048, seen, ctypes.byref(missing)) == 0 and missing.value == 0
+
+
+MIXES = [[(14848, 5120, 16), (12741, 512, 4), (1408, 5120, 8), (21248, 5120, 4)],
+         [(15360, 28288, 8), (5632, 512, 4), (9856, 11008, 8)],
+         [(5376, 8192, 4), (512, 8192, 4), (2304, 8192, 4), (14514, 8192, 4), (1379, 5248, 4), (23158, 8192, 4),
+          (11155, 768, 4), (14720, 8192, 4)],
+         [(4096, 4096, 8), (4096, 4096, 4), (4096, 4096, 8)], [(1, 128, 4)], [(11008, 4096, 16), (17, 32768, 4)],
+         [(98304, 32768, 16)]]
+
+
+@pytest.mark.parametrize("panel", [4096, 2048])
+@pytest.mark.parametrize("mix", MIXES)
+def test_division_of_a_launch(lib, mix, panel):
+    count = len(mix)
+    tiles = [(n + 15) // 16 for n, _, _ in mix]
+    shares = min(256, sum(tiles))
+    arr = [(ctypes.c_int * count)(*[m[j] for m in mix]) for j in range(3)]
+    out = (ctypes.c_int * (2 * shares * count))()
+    lib.divide(count, *arr, panel, shares, out)
+    most = 0
+    for e in range(count):
+        ranges = [(out[2 * (i * count + e)], out[2 * (i * count + e) + 1]) for i in range(shares)]
+        assert ranges[0][0] == 0 and ranges[-1][1] == tiles[e]
+        assert all(a <= b for a, b in ranges) and all(x[1] == y[0] for x, y in zip(ranges, ranges[1:]))
+        most = max(most, max(b - a for a, b in ranges))
+    # A tile takes half a microsecond however short its rows are, and the launch at least as long as its weights do at
+    # 6.5 TB/s: no workgroup may get so many short tiles that the launch waits for it.
+    stream_us = sum(n * k * b / 8 for n, k, b in mix) / 6.5e6
+    assert 0.5 * most <= 2 * stream_us + 2
