@@ -407,6 +407,7 @@ int fq_plan_layout(const char *who, int count, const fq_layer *const *layers, co
         if (!layers[i]->codes[0] && !layers[i]->codes[1] && !layers[i]->codes[2] && !layers[i]->codes[3] &&
             !layers[i]->codes[4])
             return fail(FQ_ERR_NOT_ATTACHED, "%s: entry %d has no copy attached", who, i);
+        fill_desc(table[i], layers[i], xs[i], ys[i]);
         total_rows += layers[i]->N;
         if (layers[i]->K > max_K)
             max_K = layers[i]->K;
@@ -425,12 +426,11 @@ int fq_plan_layout(const char *who, int count, const fq_layer *const *layers, co
     // token, runs on the register-fed kernel
     if (M > 1 && has3 && rows == 256)
         rows = 128;
-    geom->batch = M > 1 && rows != 256 && !has2 && !has3 && fq_batch_serves(count, total_rows) ? 1 : 0;
+    geom->batch = M > 1 && rows != 256 && !has2 && !has3 && fq_batch_serves(table, count, M) ? 1 : 0;
     if (geom->batch)
         rows = 16;
     long long tiles = 0;
     for (int i = 0; i < count; i++) {
-        fill_desc(table[i], layers[i], xs[i], ys[i]);
         table[i].tile_begin = (int)tiles;
         tiles += (layers[i]->N + rows - 1) / rows;
         if (tiles > 0x7fffffffLL)

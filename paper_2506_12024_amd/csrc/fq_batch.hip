@@ -345,10 +345,42 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 
 } // namespace
 
-// Up to 24 tiles per compute unit (two 7B-shaped layers): there the plans of mixed widths are 10 to 35 % faster than on
-// the register-fed kernel's round-robin tiles; at four layers {4, 8} 195 against 216 us, but {4, 8, 16} 296 against 265
-// and all widths at 32 batch rows slower, since each run of NB tiles starts anew.
-bool fq_batch_serves(int count, long long rows) { return count <= MAX_ENTRIES && rows <= 384LL * fq_device_cus(); }
+// Plans.  Up to 24 tiles per compute unit (two 7B-shaped layers): there the plans of mixed widths of the 7B, 13B and
+// 70B shapes take 0.58 to 0.90 of the time on the register-fed kernel's round-robin tiles; at four layers {4, 8} 195 against
+// 216 us, but {4, 8, 16} 296 against 265 and all widths at 32 batch rows slower, since each run of NB tiles starts anew.
+// Below that as for single calls, over 3740 plans: with more than two tiles per compute unit rows must not be short, the
+// mean over a plan's rows and copies (without: 4 x 16384 x 512 at {4, 8} 1.7, 3 x 24576 x 1024 at 4 bits 1.6), counted by the panels
+// of x they take (K = 5120 takes two and fills one and a quarter), and where the register-fed kernel's 64-row tiles fill
+// their rounds it keeps plans of 4-bit copies alone over more than 16 batch rows or over part panels (65536 x 5120: 1.15).
+// Under this rule 0.85 of its time on average; one plan in a hundred is 1.06 to 1.19, where a workgroup's tiles are
+// one more than full runs or a round of the other kernel is just full.
+bool fq_batch_serves(const FqLinearDesc *table, int count, int M)
+{
+    const int cus = fq_device_cus(), panel = M <= 16 ? 4096 : 2048;
+    long long rows = 0, tiles = 0;
+    double weight = 0, inputs = 0, padded = 0; // summed over the rows
+    bool four_alone = true;
+    for (int i = 0; i < count; i++) {
+        const FqLinearDesc &d = table[i];
+        const int copies = (d.codes4 != nullptr) + (d.codes8 != nullptr) + (d.w16 != nullptr);
+        const int per_group = (d.codes4 ? 17 : 0) + (d.codes8 ? 29 : 0) + (d.w16 ? 53 : 0); // 3 * bits + 5
+        four_alone = four_alone && !d.codes8 && !d.w16;
+        rows += d.N;
+        tiles += (d.N + 15) / 16;
+        weight += (double)d.N * (d.K >> 7) * per_group / (copies > 0 ? copies : 1);
+        inputs += (double)d.N * d.K;
+        padded += (double)d.N * ((d.K + panel - 1) / panel) * panel;
+    }
+    if (count > MAX_ENTRIES || rows > 384LL * cus)
+        return false;
+    if (tiles <= 2 * cus)
+        return true;
+    if (weight / rows * inputs / padded < 400)
+        return false;
+    const int rest = (int)(rows % (64 * cus));
+    const bool filled = rows > 96 * cus && (rest == 0 || rest > 48 * cus);
+    return !(filled && four_alone && (M > 16 || padded > inputs));
+}
 
 // Single calls, both kernels measured at 128 to 11008 inputs, 1024 to 200000 rows, 2, 16, 17 and 32 batch rows (ratios of
 // times, this kernel's first).  Short rows give most of a workgroup's wavefronts nothing to do: 32768 x 512 at 4

@@ -119,7 +119,7 @@ hipError_t fq_launch_skinny(const FqLinearDesc *single, int bits_host,
 int fq_skinny_tile_rows(long long total_rows, int M);
 // Single calls and small plans (up to 64 entries) at 2 <= M <= 32 and 4, 8 or 16 bits (fq_batch.hip); `tiles`: tiles of
 // 16 rows in all.
-bool fq_batch_serves(int count, long long rows);
+bool fq_batch_serves(const FqLinearDesc *table, int count, int M); // a plan (host table)
 bool fq_batch_serves_linear(int N, int K, int bits, int M);
 hipError_t fq_launch_batch(const FqLinearDesc *single, int bits_host, const FqLinearDesc *descs_dev, const int32_t *bits_dev,
                            int count, long long tiles, int M, int *flags, hipStream_t stream);

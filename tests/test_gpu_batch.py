@@ -10,7 +10,7 @@ import oracle
 import synth
 import paper_2506_12024_amd as fq
 from gpu_util import DEV, gpu_linear, make_layer, rel_err, to_dev
-from plan_util import batch_serves_linear
+from plan_util import batch_serves, batch_serves_linear
 
 pytestmark = pytest.mark.gpu
 
@@ -89,3 +89,35 @@ def test_plan_of_mixed_entries(M):
     plan.run(torch.tensor([8, 4, 2, 16, 4], dtype=torch.int32, device=DEV))
     assert plan.status() == (0, 1) and torch.equal(ys[2], before)
     assert rel_err(ys[3].cpu().numpy(), _ref(ws[3], packs[3], 16, xs[3].cpu().numpy())) <= TOL
+
+
+def test_plan_of_long_runs():
+    # as above over rows that are not short: seven tiles of 16 per workgroup and more, x in one panel and in several
+    shapes = [(30000, 4096), (48, 4096), (17, 384), (300, 8320), (5, 256)]
+    bits = [4, 16, 8, 4, 8]
+    layers, ws, packs = [], [], []
+    for i, (N, K) in enumerate(shapes):
+        w = synth.weight(13, "batch/long/w%d" % i, N, K, 0.02)
+        layer, packed = make_layer(w, (4, 8, 16))
+        layers.append(layer), ws.append(w), packs.append(packed)
+    for M in (3, 16, 32):
+        assert batch_serves([(N, K, (4, 8, 16)) for N, K in shapes], M)
+        xs = [to_dev(synth.activations(13, "batch/long/x%d/%d" % (i, M), M, K)) for i, (_, K) in enumerate(shapes)]
+        xs[1] = xs[0]
+        for pattern in (bits, [8, 4, 16, 8, 4]):
+            ys = [torch.full((M, N), float("nan"), dtype=torch.float16, device=DEV) for N, _ in shapes]
+            wsp = torch.empty(fq.Plan.workspace_bytes(len(shapes)), dtype=torch.uint8, device=DEV)
+            plan = fq.Plan(layers, xs, ys, M, wsp)
+            plan.run(torch.tensor(pattern, dtype=torch.int32, device=DEV))
+            torch.cuda.synchronize()
+            assert plan.status() == (0, 0)
+            for i, (N, K) in enumerate(shapes):
+                y, x = ys[i].cpu().numpy(), xs[i].cpu().numpy()
+                assert not np.isnan(y.astype(np.float32)).any()
+                for row0 in range(0, N, 3700):  # some rows out of every stretch
+                    n = min(60, N - row0)
+                    if pattern[i] == 16:
+                        ref = oracle.linear(x, ws[i], None, None, 16, row0=row0, rows=n)
+                    else:
+                        ref = oracle.linear(x, *(t.cpu().numpy() for t in packs[i][pattern[i]]), pattern[i], row0=row0, rows=n)
+                    assert rel_err(y[:, row0:row0 + n], ref) <= TOL, (M, i, row0)

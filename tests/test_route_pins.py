@@ -1,7 +1,7 @@
 """Host-side choices of the launch code that need no device (CPU only)."""
 import pytest
 
-from plan_util import batch_serves_linear, part_mutex
+from plan_util import batch_serves, batch_serves_linear, part_mutex
 
 
 def test_calls_on_different_streams_and_devices_share_no_lock():
@@ -20,3 +20,25 @@ def test_calls_on_different_streams_and_devices_share_no_lock():
 def test_single_calls_take_the_faster_small_batch_kernel(N, K, bits, M, batch):
     # (a host without a device counts 256 compute units)
     assert batch_serves_linear(N, K, bits, M) is batch
+
+
+STACKS = {"7b": (4096, 11008, 4096), "13b": (5120, 13824, 5120), "70b": (8192, 28672, 1024)}
+
+
+@pytest.mark.parametrize("widths", [(4,), (8,), (4, 8), (4, 8, 16)])
+@pytest.mark.parametrize("M", [2, 16])
+@pytest.mark.parametrize("stack", list(STACKS))
+def test_stages_of_a_decoder_run_on_the_small_batch_kernel(stack, M, widths):
+    h, ffn, kv = STACKS[stack]
+    for stage in ([(h, h), (kv, h), (kv, h)], [(h, h)], [(ffn, h)] * 2, [(h, ffn)]):
+        assert batch_serves([(N, K, widths) for N, K in stage], M), stage
+
+
+@pytest.mark.parametrize("entries,M,batch", [
+    ([(16384, 512, (4, 8))] * 4, 2, False), ([(24576, 1024, (4,))] * 3, 16, False),   # short rows
+    ([(1024, 512, (4, 8))] * 8, 2, True),                                             # two tiles per compute unit
+    ([(16384, 5120, (4,))] * 4, 16, False), ([(16384, 4096, (4,))] * 4, 16, True),    # full rounds of the other kernel
+    ([(16384, 4096, (4,))] * 4, 17, False), ([(16384, 4096, (4, 8))] * 4, 17, True),
+    ([(8192, 4096, (4, 8))] * 13, 16, False), ([(16, 4096, (4, 8))] * 65, 16, False)])  # rows and entries of a plan
+def test_plans_take_the_faster_small_batch_kernel(entries, M, batch):
+    assert batch_serves(entries, M) is batch
