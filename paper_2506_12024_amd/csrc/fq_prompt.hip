@@ -439,37 +439,42 @@ hipError_t launch(const FqLinearDesc &d, int M, int segments, float *part, hipSt
     return hipGetLastError();
 }
 
-// Microseconds a call is expected to take, fitted to 312 shapes (33 to 1500 tokens, 512 to 28672 rows, K 1024
-// to 28672; 6 to 12 % off on average): launch and first fetch, then rounds of one workgroup per compute
-// unit, a step costing more the more tokens it has and the fuller the chip is; with segments the hand-over.
-// The choice made from it is within 1 to 2 % of the best choice on average.
+// Microseconds a call is expected to take, fitted to 17000 timings of forced plans (33 to 2048 tokens, 512 to 28672
+// rows, K 128 to 28672; 7 to 9 % off on average, fp16 weights 16, large tiles 6 to 10): launch and first fetch, then rounds of
+// one workgroup per compute unit, each with an end that grows with its outputs, a step costing more the more tokens it has
+// and the fuller the chip is; with segments the hand-over (0.8 more than fitted, for the host: a second launch).  The choice made from it is within 1 to 2 % of the best choice
+// on average.  (Fitted without the rounds' ends and from K = 1024 on, it sent calls over few inputs the wrong way:
+// 33 x 512 x 512 at fp16, four segments of one group, 1.28 of the large tiles' time.)
 struct Cost {
-    float step, step_mt, step_full, call, round, split, split_unit;
-    float old_call, old_step, old_full, old_half; // the 256 x 256 tiles, per step of 64 inputs; a round of half tiles
+    float call, round, out, step, step_mt, step_full, split, split_unit;
+    float old_call, old_round, old_out, old_step, old_full, old_half; // the 256 x 256 tiles, per step of 64 inputs; a round of half tiles
 };
 const Cost &cost_of(int bits)
 {
-    static const Cost w4 = {0.23f, 0.095f, 0.09f, 4.3f, 1.5f, 2.4f, 8.2f / 1024, 5.9f, 1.19f, 0.59f, 0.75f};
-    static const Cost w8 = {0.30f, 0.088f, 0.095f, 4.0f, 1.5f, 2.4f, 9.4f / 1024, 5.4f, 1.10f, 0.68f, 0.77f};
-    static const Cost w16 = {0.83f, 0.067f, 0.097f, 4.0f, 1.5f, 2.0f, 6.9f / 1024, 4.0f, 0.96f, 0.77f, 1.0f};
-    return bits == 16 ? w16 : bits == 8 ? w8 : w4;
+    static const Cost w2 = {3.45f, 2.65f, 0.207f, 0.147f, 0.110f, 0.090f, 3.5f, 4.76f / 1024, 2.f, 5.88f, 2.60f, 1.166f, 0.389f, 0.586f};
+    static const Cost w4 = {3.40f, 2.50f, 0.247f, 0.193f, 0.096f, 0.109f, 3.6f, 5.72f / 1024, 2.f, 7.53f, 1.00f, 1.162f, 0.480f, 0.557f};
+    static const Cost w8 = {3.48f, 2.28f, 0.320f, 0.236f, 0.091f, 0.121f, 3.6f, 5.97f / 1024, 2.f, 5.63f, 2.67f, 1.365f, 0.322f, 0.578f};
+    static const Cost w16 = {3.71f, 1.26f, 0.299f, 0.572f, 0.049f, 0.129f, 3.9f, 5.08f / 1024, 2.f, 4.93f, 2.95f, 1.165f, 0.437f, 0.552f};
+    return bits == 16 ? w16 : bits == 8 ? w8 : bits == 4 ? w4 : w2;
 }
 
 float prompt_cost(const Cost &c, int groups, long long tiles, int mt, int segments, int cus)
 {
-    const long long units = tiles * segments, rounds = (units + cus - 1) / cus;
-    const float full = units < cus ? (float)units / cus : 1.f;
+    const long long units = tiles * segments;
     const int steps = (groups + segments - 1) / segments;
-    const float t = c.call + rounds * (c.round + steps * (c.step + c.step_mt * mt + c.step_full * mt * full));
+    auto round = [&](float full) { return c.round + c.out * mt * full + steps * (c.step + c.step_mt * mt + c.step_full * mt * full); };
+    float t = c.call + units / cus * round(1.f);
+    if (units % cus)
+        t += round((float)(units % cus) / cus);
     return segments > 1 ? t + c.split + c.split_unit * units * mt : t;
 }
 
 float prefill_cost(const Cost &c, int K, long long tiles, int cus)
 {
     const long long per_xcd = (tiles + 7) / 8, per_round = cus >= 8 ? cus / 8 : 1, rest = per_xcd % per_round;
-    const float rounds = per_xcd / per_round + (rest == 0 ? 0.f : 2 * rest <= per_round ? c.old_half : 1.f);
-    const float full = tiles < cus ? (float)tiles / cus : 1.f;
-    return c.old_call + rounds * (K / 64) * (c.old_step + c.old_full * full);
+    auto round = [&](float full) { return c.old_round + c.old_out * full + (K / 64) * (c.old_step + c.old_full * full); };
+    const float t = c.old_call + per_xcd / per_round * round(1.f);
+    return rest == 0 ? t : 2 * rest <= per_round ? t + c.old_half * round(2.f * rest / per_round) : t + round((float)rest / per_round);
 }
 
 template <int BITS>
@@ -488,9 +493,9 @@ FqPromptPlan fq_prompt_plan(int N, int K, int bits, int M, int cus)
     const int groups = K / 128;
     const long long n_tiles = (N + BN - 1) / BN;
     FqPromptPlan best = {0, 0};
-    // (a call is left to the large tiles where they are expected to be at most a tenth slower: the models are 4 to 12 %
-    // off, and of 150 random calls none then got slower by more than 2 %)
-    float least = 0.9f * prefill_cost(c, K, (long long)((M + 255) / 256) * ((N + 255) / 256), cus);
+    // (left to the large tiles where they are expected to be up to 3 % slower: of 1650 calls of the fit's shapes three are
+    // then 4 or 5 % slower than on the large tiles)
+    float least = 0.97f * prefill_cost(c, K, (long long)((M + 255) / 256) * ((N + 255) / 256), cus);
     for (int mt = 2; mt <= 4; mt++) {
         const long long tiles = (M + 32 * mt - 1) / (32 * mt) * n_tiles;
         if (tiles > 0x3ffffffLL)

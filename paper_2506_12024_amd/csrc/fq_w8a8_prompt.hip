@@ -386,20 +386,25 @@ hipError_t launch(const Args &d, int segments, float *part, hipStream_t stream)
     return hipGetLastError();
 }
 
-// Microseconds a call is expected to take, fitted to 118 shapes of each kind (16 to 2048 tokens, 512 to 28672 rows, K
-// 1024 to 28672; 7 and 10 % off on average; the choice made from it costs 1 to 2 % over the best one).
+// Microseconds a call is expected to take, fitted to 9000 timings of forced plans (16 to 2048 tokens, 512 to 28672 rows, K
+// 128 to 28672; 10 and 12 % off on average, large tiles 9 and 11; the choice made from it costs 1 % over the best one; a
+// hand-over 1.2 more than fitted, for the host: a second launch).  A
+// round's end grows with its outputs: without that, and fitted from K = 1024 on, the model took three rounds of 192 x 128
+// tiles for two of 128 x 256 over few inputs (2048 x 128 .. 1536 -> 8192: 1.09 to 1.19 of the large tiles' time).
 struct Cost {
-    float step, step_tm, step_full, call, round, split, split_unit;
+    float call, round, out, step, step_tm, step_full, split, split_unit;
 };
-constexpr Cost GROUP_COST = {0.236f, 0.21f, 0.093f, 6.2f, 1.75f, 2.5f, 14.5f / 1024};
-constexpr Cost ROW_COST = {0.28f, 0.084f, 0.109f, 6.5f, 1.8f, 2.5f, 13.0f / 1024};
+constexpr Cost GROUP_COST = {4.66f, 1.99f, 2.22f, 0.188f, 0.225f, 0.068f, 3.0f, 5.45f / 1024};
+constexpr Cost ROW_COST = {4.80f, 1.52f, 2.36f, 0.272f, 0.101f, 0.075f, 3.5f, 4.93f / 1024};
 
 float prompt_cost(const Cost &c, int groups, long long tiles, int tm, int segments, int cus)
 {
-    const long long units = tiles * segments, rounds = (units + cus - 1) / cus;
-    const float full = units < cus ? (float)units / cus : 1.f;
+    const long long units = tiles * segments;
     const int steps = (groups + segments - 1) / segments;
-    const float t = c.call + rounds * (c.round + steps * (c.step + c.step_tm * tm + c.step_full * tm * full));
+    auto round = [&](float full) { return c.round + c.out * tm * full + steps * (c.step + c.step_tm * tm + c.step_full * tm * full); };
+    float t = c.call + units / cus * round(1.f);
+    if (units % cus)
+        t += round((float)(units % cus) / cus);
     return segments > 1 ? t + c.split + c.split_unit * units * tm : t;
 }
 
@@ -407,12 +412,16 @@ float prompt_cost(const Cost &c, int groups, long long tiles, int tm, int segmen
 float large_cost(int N, int K, int M, bool per_row, int mt, int cus)
 {
     const long long n_tiles = (N + 255) / 256, bm = per_row ? 256 : 64 * mt, tiles = (M + bm - 1) / bm * n_tiles;
-    const float full = tiles < cus ? (float)tiles / cus : 1.f;
-    if (!per_row)
-        return 5.75f + (tiles + cus - 1) / cus * (6.08f + K / 128 * (0.592f + 0.458f * mt + 0.225f * full));
+    const int groups = K / 128;
+    if (!per_row) {
+        auto round = [&](float full) { return 8.58f + 2.74f * mt * full + groups * (0.136f + 0.639f * mt + 0.009f * mt * full); };
+        const float t = 2.75f + tiles / cus * round(1.f);
+        return tiles % cus ? t + round((float)(tiles % cus) / cus) : t;
+    }
     const long long per_xcd = (tiles + 7) / 8, per_round = cus >= 8 ? cus / 8 : 1, rest = per_xcd % per_round;
-    const float rounds = per_xcd / per_round + (rest == 0 ? 0.f : 2 * rest <= per_round ? 0.93f : 1.f);
-    return 8.7f + rounds * (K / 128) * (1.36f + 0.75f * full);
+    auto round = [&](float full) { return 14.f + 9.16f * full + groups * (1.704f + 0.046f * full); };
+    const float t = 3.07f + per_xcd / per_round * round(1.f);
+    return rest == 0 ? t : 2 * rest <= per_round ? t + 0.552f * round(2.f * rest / per_round) : t + round((float)rest / per_round);
 }
 
 } // namespace
@@ -425,7 +434,9 @@ FqPromptPlan fq_w8a8_prompt_plan(int N, int K, int M, bool per_row, int large_mt
     FqPromptPlan best = {0, 0};
     if ((unsigned long long)groups * (unsigned long long)M * 4 > 0x7fffffffULL) // the group sums' 32-bit offsets
         return best;
-    float least = 0.9f * large_cost(N, K, M, per_row, large_mt, cus); // (within a tenth: left to the large tiles)
+    // (left to the large tiles where they are expected to be up to 5 or 12 % slower: of 1050 calls of the fit's shapes two,
+    // over 128 and 256 inputs, are then 6 and 9 % slower than on the large tiles)
+    float least = (per_row ? 0.95f : 0.88f) * large_cost(N, K, M, per_row, large_mt, cus);
     for (int tm = 1; tm <= 3; tm++) {
         const long long tiles = ((long long)M + 64 * tm - 1) / (64 * tm) * n_tiles;
         if (tiles > 0x3ffffffLL)

@@ -35,3 +35,24 @@ def batch_serves(entries, M):
         d.N, d.K = N, K
         d.codes4, d.codes8, d.w16 = (16 if b in widths else None for b in (4, 8, 16))
     return _batch_serves(table, len(entries), M)
+
+_prompt_plan = _fn("_Z14fq_prompt_planiiiii", _Plan, _i, _i, _i, _i, _i)
+_w8a8_plan = _fn("_Z19fq_w8a8_prompt_planiiibii", _Plan, _i, _i, _i, ctypes.c_bool, _i, _i)
+
+
+def prompt_plan(M, N, K, bits, cus=256):
+    """(blocks of 32 tokens of a tile, segments of K) of fq_linear's GEMM; (0, 0): the 256 x 256 tiles."""
+    p = _prompt_plan(N, K, bits, M, cus)
+    return p.mt, p.segments
+
+
+def w8a8_large_blocks(M, N, cus=256):
+    """Blocks of 64 tokens of the large W8A8 tiles for groups of 128 (the launcher's rule)."""
+    t3, t2 = ((M + bm - 1) // bm * ((N + 255) // 256) for bm in (192, 128))
+    return 2 if (t2 + cus - 1) // cus * 2 * 8 < (t3 + cus - 1) // cus * 3 * 7 else 3
+
+
+def w8a8_plan(M, N, K, per_row, cus=256):
+    """(blocks of 64 tokens of a tile, segments of K) of fq_linear_w8a8; (0, 0): the large tiles."""
+    p = _w8a8_plan(N, K, M, per_row, w8a8_large_blocks(M, N, cus), cus)
+    return p.mt, p.segments

@@ -1,7 +1,7 @@
 """Host-side choices of the launch code that need no device (CPU only)."""
 import pytest
 
-from plan_util import batch_serves, batch_serves_linear, part_mutex
+from plan_util import batch_serves, batch_serves_linear, part_mutex, prompt_plan, w8a8_plan
 
 
 def test_calls_on_different_streams_and_devices_share_no_lock():
@@ -42,3 +42,15 @@ def test_stages_of_a_decoder_run_on_the_small_batch_kernel(stack, M, widths):
     ([(8192, 4096, (4, 8))] * 13, 16, False), ([(16, 4096, (4, 8))] * 65, 16, False)])  # rows and entries of a plan
 def test_plans_take_the_faster_small_batch_kernel(entries, M, batch):
     assert batch_serves(entries, M) is batch
+
+
+@pytest.mark.parametrize("M,N,K,kind,plan", [
+    # over few inputs: the large tiles' rounds, no segments of one group each
+    (2048, 8192, 128, "group", (0, 0)), (2048, 8192, 640, "group", (0, 0)), (2048, 8192, 1536, "group", (0, 0)),
+    (400, 28672, 256, "group", (0, 0)), (33, 512, 512, 16, (2, 1)), (100, 2048, 512, 16, (2, 1)),
+    # the shapes the kernels with segments of K were made for
+    (100, 4096, 11008, 4, (2, 4)), (515, 11008, 4096, 8, (4, 1)), (300, 5120, 13824, "group", (2, 2)),
+    (2048, 28672, 8192, 4, (0, 0)), (2048, 8192, 28672, "row", (0, 0))])
+def test_prompts_take_the_faster_tiles(M, N, K, kind, plan):
+    got = prompt_plan(M, N, K, kind) if isinstance(kind, int) else w8a8_plan(M, N, K, kind == "row")
+    assert got == plan
