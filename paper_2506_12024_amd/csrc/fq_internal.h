@@ -180,6 +180,8 @@ hipError_t fq_launch_w8a8(const FqLinearDesc &d, const void *xq, const float *sx
 // The same on smaller tiles and segments of K (mt: 64-token blocks of a tile; 0: the large tiles, of 64 * large_mt
 // tokens for groups of 128, serve the shape better).
 FqPromptPlan fq_w8a8_prompt_plan(int N, int K, int M, bool per_row, int large_mt, int cus);
+// The large tiles address 256 rows of x and weights by 32-bit offsets.
+inline bool fq_w8a8_too_long(int K) { return (unsigned long long)K * 256 > 0xffffffffULL; }
 hipError_t fq_launch_w8a8_prompt(const FqLinearDesc &d, const void *xq, const float *sx, const int32_t *xsum, int M,
                                  bool per_row, FqPromptPlan plan, hipStream_t stream);
 

@@ -495,7 +495,9 @@ FqPromptPlan fq_prompt_plan(int N, int K, int bits, int M, int cus)
     FqPromptPlan best = {0, 0};
     // (left to the large tiles where they are expected to be up to 3 % slower: of 1650 calls of the fit's shapes three are
     // then 4 or 5 % slower than on the large tiles)
-    float least = 0.97f * prefill_cost(c, K, (long long)((M + 255) / 256) * ((N + 255) / 256), cus);
+    // The large tiles address 256 rows of x (and of fp16 weights) by 32-bit offsets: longer rows are not for them.
+    const bool too_long = (unsigned long long)K * 2 * 256 > 0xffffffffULL;
+    float least = too_long ? 3.4e38f : 0.97f * prefill_cost(c, K, (long long)((M + 255) / 256) * ((N + 255) / 256), cus);
     for (int mt = 2; mt <= 4; mt++) {
         const long long tiles = (M + 32 * mt - 1) / (32 * mt) * n_tiles;
         if (tiles > 0x3ffffffLL)

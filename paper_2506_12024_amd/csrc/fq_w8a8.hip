@@ -624,6 +624,8 @@ hipError_t fq_launch_w8a8(const FqLinearDesc &l, const void *xq, const float *sx
     const FqPromptPlan plan = fq_w8a8_prompt_plan(l.N, l.K, M, per_row, mt, cus > 0 ? cus : 1);
     if (plan.mt > 0)
         return fq_launch_w8a8_prompt(l, xq, sx, xsum, M, per_row, plan, stream);
+    if (fq_w8a8_too_long(l.K)) // (and the group sums of 4096 tokens and more too many for the small tiles)
+        return hipErrorInvalidValue;
     const int bm = per_row ? RBM_FULL : 2 * mt * 32;
     const int m_tiles = (M + bm - 1) / bm;
     const long long total = (long long)m_tiles * n_tiles;

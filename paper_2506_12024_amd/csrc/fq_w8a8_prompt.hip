@@ -432,11 +432,12 @@ FqPromptPlan fq_w8a8_prompt_plan(int N, int K, int M, bool per_row, int large_mt
     const int groups = K / 128;
     const long long n_tiles = (N + BN - 1) / BN;
     FqPromptPlan best = {0, 0};
+    const bool too_long = fq_w8a8_too_long(K);
     if ((unsigned long long)groups * (unsigned long long)M * 4 > 0x7fffffffULL) // the group sums' 32-bit offsets
         return best;
     // (left to the large tiles where they are expected to be up to 5 or 12 % slower: of 1050 calls of the fit's shapes two,
     // over 128 and 256 inputs, are then 6 and 9 % slower than on the large tiles)
-    float least = (per_row ? 0.95f : 0.88f) * large_cost(N, K, M, per_row, large_mt, cus);
+    float least = too_long ? 3.4e38f : (per_row ? 0.95f : 0.88f) * large_cost(N, K, M, per_row, large_mt, cus);
     for (int tm = 1; tm <= 3; tm++) {
         const long long tiles = ((long long)M + 64 * tm - 1) / (64 * tm) * n_tiles;
         if (tiles > 0x3ffffffLL)

@@ -54,3 +54,13 @@ def test_plans_take_the_faster_small_batch_kernel(entries, M, batch):
 def test_prompts_take_the_faster_tiles(M, N, K, kind, plan):
     got = prompt_plan(M, N, K, kind) if isinstance(kind, int) else w8a8_plan(M, N, K, kind == "row")
     assert got == plan
+
+
+@pytest.mark.parametrize("M,N,K,kind,large", [
+    # a large tile's 256 rows of x or weights are addressed by 32-bit offsets: longer rows go to the smaller tiles
+    (2048, 8192, 1 << 23, 4, False), (4096, 65536, 1 << 23, 16, False), (2048, 65536, (1 << 23) - 128, 4, True),
+    (2048, 65536, (1 << 23) - 128, 16, True), (4000, 65536, 1 << 24, "group", False),
+    (4000, 65536, (1 << 24) - 128, "group", True)])
+def test_rows_too_long_for_the_large_tiles(M, N, K, kind, large):
+    got = prompt_plan(M, N, K, kind) if isinstance(kind, int) else w8a8_plan(M, N, K, False)
+    assert (got == (0, 0)) is large
