@@ -10,8 +10,9 @@
 // System/6000 processor", 1990).  The result is RN(w / s), the IEEE quotient, unless w / s lies that close to the
 // middle between two floats.  What the quantizers take from it is round(RN(w / s) + z) for a half w and an integer
 // z: that can differ only next to the numbers n / 2 and n / 2 +- 2^-i at which the sum's rounding turns over, and for the
-// 11-bit w and 24-bit s all the pairs within 64 units of such a middle (1943 of them) were enumerated on the host:
-// every one rounds like the division; so do 5 10^9 random pairs.  For finite halves and scales of groups of halves
+// 11-bit w and 24-bit s all the pairs within 2^-18 ulp of such a middle (1956 of them) round like the division, as do all
+// symmetric codes (92 10^6 up to powers of two) and random groups: tests/test_division_pins.py compiles this
+// header for the host and goes through them.  For finite halves and scales of groups of halves
 // (2^-32 .. 2^17) nothing under- or overflows on the way.  An infinite scale (a group that holds an infinity)
 // has y = 0 and would make the residual 0 * infinity: it is left out of the residual, so that finite numerators
 // divide to 0 and infinite ones to NaN.
