@@ -56,3 +56,10 @@ def w8a8_plan(M, N, K, per_row, cus=256):
     """(blocks of 64 tokens of a tile, segments of K) of fq_linear_w8a8; (0, 0): the large tiles."""
     p = _w8a8_plan(N, K, M, per_row, w8a8_large_blocks(M, N, cus), cus)
     return p.mt, p.segments
+
+_part_bank = _fn("_Z12fq_part_bankP12ihipStream_tPi", _i, ctypes.c_void_p, ctypes.c_void_p)
+
+
+def part_bank(stream):
+    """The index of a stream's array for partial sums on the current device, -1 if it has none."""
+    return _part_bank(stream, ctypes.byref(_i()))

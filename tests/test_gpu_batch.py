@@ -1,4 +1,5 @@
-"""The small-batch kernel of single calls and stage-sized plans (csrc/fq_batch.hip) at its edges: rows around its
+"""The small-batch kernel of single calls and stage-sized plans (csrc/fq_batch.hip) at its edges, and what its rules
+leave to the register-fed kernel (csrc/fq_skinny.hip) at 4, 8 and 16 bits: rows around its
 tiles of 16, batch rows around 16, inputs of one group, an odd number of groups, and more than one
 panel of x in LDS (4096 inputs up to 16 batch rows, 2048 above), runs longer than the six tiles a workgroup
 holds at a time, entries that share x and entries that do not, against the oracle."""
@@ -65,10 +66,11 @@ def test_single_call_left_to_the_register_fed_kernel(M, N, K, bits):
 
 @pytest.mark.parametrize("M", [3, 16, 32])
 def test_plan_of_mixed_entries(M):
-    # 30000 rows are seven tiles of 16 per workgroup on 256 compute units; the rest are slivers beside them
+    # short rows over many tiles, slivers beside them: the register-fed kernel
     shapes = [(30000, 256), (48, 256), (17, 384), (300, 2304), (5, 256)]
     bits = [4, 16, 8, 4, 8]
     shared = {1: 0, 4: 0}  # entries that read entry 0's x
+    assert not batch_serves([(N, K, (4, 8, 16)) for N, K in shapes], M)
     layers, xs, ys, ws, packs = [], [], [], [], []
     for i, (N, K) in enumerate(shapes):
         w = synth.weight(13, "batch/plan/w%d" % i, N, K, 0.02)
@@ -92,7 +94,8 @@ def test_plan_of_mixed_entries(M):
 
 
 def test_plan_of_long_runs():
-    # as above over rows that are not short: seven tiles of 16 per workgroup and more, x in one panel and in several
+    # the same over rows that are not short, on the small-batch kernel: seven tiles of 16 per workgroup and more (30000
+    # rows on 256 compute units), x in one panel and in several
     shapes = [(30000, 4096), (48, 4096), (17, 384), (300, 8320), (5, 256)]
     bits = [4, 16, 8, 4, 8]
     layers, ws, packs = [], [], []
@@ -121,3 +124,25 @@ def test_plan_of_long_runs():
                     else:
                         ref = oracle.linear(x, *(t.cpu().numpy() for t in packs[i][pattern[i]]), pattern[i], row0=row0, rows=n)
                     assert rel_err(y[:, row0:row0 + n], ref) <= TOL, (M, i, row0)
+
+
+@pytest.mark.parametrize("M", [3, 20])
+def test_plan_of_more_entries_than_the_small_batch_kernel_takes(M):
+    # 70 entries of a few rows: the register-fed kernel with K split between the wavefronts
+    shapes = [(17 + i % 5 * 16, (128, 384, 1152)[i % 3]) for i in range(70)]
+    assert not batch_serves([(N, K, (4, 8, 16)) for N, K in shapes], M)
+    bits = [(4, 8, 16)[i % 7 % 3] for i in range(70)]
+    layers, xs, ys, refs = [], [], [], []
+    for i, (N, K) in enumerate(shapes):
+        w = synth.weight(13, "batch/many/w%d" % i, N, K, 0.02)
+        x = synth.activations(13, "batch/many/x%d/%d" % (i, M), M, K)
+        layer, packed = make_layer(w, (4, 8, 16))
+        layers.append(layer), xs.append(to_dev(x)), refs.append(_ref(w, packed, bits[i], x))
+        ys.append(torch.full((M, N), float("nan"), dtype=torch.float16, device=DEV))
+    wsp = torch.empty(fq.Plan.workspace_bytes(70), dtype=torch.uint8, device=DEV)
+    plan = fq.Plan(layers, xs, ys, M, wsp)
+    plan.run(torch.tensor(bits, dtype=torch.int32, device=DEV))
+    torch.cuda.synchronize()
+    assert plan.status() == (0, 0)
+    for i in range(70):
+        assert rel_err(ys[i].cpu().numpy(), refs[i]) <= TOL, i

@@ -390,8 +390,8 @@ def test_entropy_r0_is_a_no_op():
 @pytest.mark.parametrize("M,shapes", [(1, [(256, 1024), (100, 1408)]), (4, [(256, 1024), (100, 1408)]),
                                       (2, [(40, 256), (24, 128)]), (16, [(11008, 512)] * 24)])
 def test_plan_status_reports_entries_that_could_not_be_served(M, shapes):
-    # M = 1: the batch-1 kernel; 4: the register-fed batch kernel; 2 with few rows: its K-split
-    # form; 16 with many rows: the streaming kernel behind plan_order_kernel
+    # M = 1: the batch-1 kernel; 4 and 2, few rows: the small-batch kernel; 16 with many rows: the streaming
+    # kernel behind plan_order_kernel
     layers, xs, ys = [], [], []
     for i, (N, K) in enumerate(shapes):
         w = synth.weight(0, "par/status/w%d" % (i % 3), N, K, 0.02)

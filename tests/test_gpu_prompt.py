@@ -2,7 +2,8 @@
 its blocks of 32 and of its tiles, rows at the edges of 128, one to many groups of K (its scales come
 eight groups at a time, its steps three to a turn), one and several segments of K, against the oracle; and
 that the result is the same bits wherever the partial sums of the segments are kept.  The same for the W8A8
-product (csrc/fq_w8a8_prompt.hip) with groups of 128 and with one scale per row."""
+product (csrc/fq_w8a8_prompt.hip) with groups of 128 and with one scale per row.  Few rows: most shapes here take
+the smallest tiles, 64 tokens; the others are in test_gpu_gemm_tiles.py."""
 import ctypes
 import threading
 

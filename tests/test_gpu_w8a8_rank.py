@@ -89,12 +89,12 @@ def test_linear_w8a8_matches_oracle(M, N, K):
 
 
 def test_linear_w8a8_both_token_tilings_on_a_full_grid():
-    # The kernel for groups of 128 exists with 192 and with 128 tokens per workgroup and the launcher
-    # takes the one whose rounds (one workgroup per compute unit at a time) cost less.  One round or
-    # less always goes to 128 tokens, which is what the shapes above exercise; 1536 x 8192 is 8 x 32 =
-    # 256 tiles of 192 tokens (one round on 256 compute units) against 384 tiles of 128 (two), so
-    # this launch runs the 192-token kernel.  Weight rows sampled from every part of a tile, all
-    # tokens; both launches repeatable bit for bit.
+    # The kernel of large tiles for groups of 128 exists with 192 and with 128 tokens per workgroup and the
+    # launcher takes the one whose rounds (one workgroup per compute unit at a time) cost less: 1536 x
+    # 8192 is 8 x 32 = 256 tiles of 192 tokens (one round on 256 compute units) against 384 tiles of 128
+    # (two), so this launch runs the 192-token kernel, if on 256 compute units.  (The shapes above run on the small tiles of
+    # csrc/fq_w8a8_prompt.hip; ragged ones on both large tiles are in test_gpu_gemm_tiles.py.)  Weight rows sampled
+    # from every part of a tile, all tokens; both launches repeatable bit for bit.
     M, N, K = 1536, 8192, 256
     w = synth.weight(0, "par/w8a8/grid/w", N, K, 0.015, outlier_p=0.001)
     x = synth.activations(0, "par/w8a8/grid/x", M, K)
@@ -354,9 +354,10 @@ def test_rank_feeds_the_scheduler():
 
 
 def test_prefill_paths_repeatable_on_a_large_tile_grid():
-    # Several workgroup tiles per CU and many steps: repeated launches must agree bit for bit
-    # (a wavefront reading a buffer another one is already refilling shows up here), and a
-    # sample of columns from every part of a workgroup tile must match the oracle.
+    # Many steps: repeated launches must agree bit for bit (a wavefront reading a buffer another one is already
+    # refilling shows up here), and a sample of columns from every part of a workgroup tile must match
+    # the oracle.  On 256 compute units these are small tiles and segments of K; the same on the
+    # large tiles is in test_gpu_gemm_tiles.py.
     M, N, K = 600, 1024, 4096
     w = synth.weight(0, "par/rep/w", N, K, 0.015)
     x = synth.activations(0, "par/rep/x", M, K)
