@@ -127,20 +127,21 @@ __device__ __forceinline__ int x_chunk(int i, int c)
     return BITS == 4 || BITS == 2 ? 4 * c + i : 2 * i + c;
 }
 
-// NT: MFMA tiles of a wavefront along the weight rows.  One, the wavefront taking all of the tile's tokens: every
+// NT (below): MFMA tiles of a wavefront along the weight rows.  One, the wavefront taking all of the tile's tokens: every
 // weight is unpacked by one wavefront (with two tiles, by two, but x is read from LDS half as often), worth it where
 // the unpacking is 16 instructions per operand: 2048 x 8192 x 28672 at 4 bits 872 -> 838 us, 2 bits 900 -> 881; at 8 bits
-// 864 -> 860 but 803 -> 822 with the sizes exchanged; fp16 weights, nothing to unpack, 833 -> 868.  Calls over fewer than
-// 2048 inputs are mostly the writing of y, whose lines one wavefront writes whole only with two: 633 x 512 -> 18304 at 2
-// bits 22.8 us against 25.0.
-// HALF: the workgroup takes half a tile, 128 tokens x 256 weight rows (a wavefront half the tokens): the tiles left over after the last full round of workgroups are cut in two, so that they
-// keep twice as many CUs busy for half as long.  `skip`: first tile of this launch inside an XCD's
+// 864 -> 860 but 803 -> 822 with the sizes exchanged; fp16 weights, nothing to unpack, 833 -> 868.  Over 153 calls of 256 to
+// 4096 inputs, 9000 to 28672 rows and 200 to 4096 tokens one takes 0.97 of the time with two at 4 bits (0.87 to 1.03) and
+// 0.99 at 2 bits (0.89 to 1.05), alike below and above 2048 inputs.
+// HALF: the workgroup takes half a tile, 128 tokens x 256 weight rows (a wavefront half the tokens): the tiles left over
+// after the last full round of workgroups are cut in two, so that they keep twice as many CUs busy for half as long.  `skip`: first tile of this launch inside an XCD's
 // run of `per_xcd` tiles.
-template <int BITS, bool HALF, int NT>
+template <int BITS, bool HALF>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void prefill_kernel(
     const FqLinearDesc d, int M, int m_tiles, int n_tiles, int per_xcd, int skip)
 {
     constexpr int BM = HALF ? BM_FULL / 2 : BM_FULL; // tokens per workgroup
+    constexpr int NT = BITS <= 4 ? 1 : 2;            // MFMA tiles of a wavefront along the weight rows
     constexpr int WN = 32 * NT;                      // weight rows per wavefront
     constexpr int WM = BM / NT;                      // tokens per wavefront
     constexpr int MTL = WM / 32;                     // MFMA tiles of a wavefront along the tokens (4 or 2)
@@ -199,14 +200,13 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
         aofs[i] = slab_offset<XRB>(l32, x_chunk<BITS>(i, c));
     // Weights: 8-bit and fp16 rows are 64 / 128 bytes, the second n-tile (32 rows on) sits a
     // whole number of 16-line blocks further and keeps the permutation: one offset per
-    // k16-step.  4-bit rows are 32 bytes (one read per n-tile and step): 32 rows are 8 lines,
-    // which changes the permutation, so each n-tile has its own offset.
+    // k16-step.  2- and 4-bit rows are 16 and 32 bytes: one read per step, of the wavefront's only n-tile.
     constexpr int WRB_ = BK * BITS / 8;
     int bofs[4];
 #pragma unroll
     for (int i = 0; i < 4; i++)
-        bofs[i] = BITS == 2 ? slab_offset<WRB_>(wn + (NT == 2 ? (i & 1) * 32 : 0) + l32, 0) + 8 * c
-                : BITS == 4 ? slab_offset<WRB_>(wn + (NT == 2 ? (i & 1) * 32 : 0) + l32, c)
+        bofs[i] = BITS == 2 ? slab_offset<WRB_>(wn + l32, 0) + 8 * c
+                : BITS == 4 ? slab_offset<WRB_>(wn + l32, c)
                 : BITS == 8 ? slab_offset<WRB_>(wn + l32, i) + 8 * c
                             : slab_offset<WRB_>(wn + l32, 2 * i + c);
 
@@ -347,15 +347,12 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
         for (int i = 0; i < 4; i++)
             asm volatile("" : "+v"(aofs[i]), "+v"(bofs[i]));
 
-        u32x4 w4[NT]; // 4-bit: the lane's 32 codes of the step, per n-tile; 2-bit: the same in 8 bytes
-#pragma unroll
-        for (int j = 0; j < NT; j++) {
-            if (BITS == 4)
-                w4[j] = *reinterpret_cast<const u32x4 *>(wc + bofs[j]);
-            if (BITS == 2) {
-                const u32x2 q = *reinterpret_cast<const u32x2 *>(wc + bofs[j]);
-                w4[j].x = q.x, w4[j].y = q.y;
-            }
+        u32x4 w4; // 4-bit: the lane's 32 codes of the step; 2-bit: the same in 8 bytes
+        if (BITS == 4)
+            w4 = *reinterpret_cast<const u32x4 *>(wc + bofs[0]);
+        if (BITS == 2) {
+            const u32x2 q = *reinterpret_cast<const u32x2 *>(wc + bofs[0]);
+            w4.x = q.x, w4.y = q.y;
         }
 #pragma unroll
         for (int i = 0; i < 4; i++) {
@@ -367,9 +364,9 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
             for (int j = 0; j < NT; j++) {
                 uint32_t b[4];
                 if constexpr (BITS == 2) {
-                    deq8<2>(i < 2 ? w4[j].x : w4[j].y, 0u, i, dc[j], mg, b);
+                    deq8<2>(i < 2 ? w4.x : w4.y, 0u, i, dc[j], mg, b);
                 } else if constexpr (BITS == 4) {
-                    deq8<4>(w4[j][i], 0u, 0, dc[j], mg, b);
+                    deq8<4>(w4[i], 0u, 0, dc[j], mg, b);
                 } else if constexpr (BITS == 8) {
                     const u32x2 q = *reinterpret_cast<const u32x2 *>(wc + j * BJ + bofs[i]); // k = 16 i + 8 c ..
                     deq8<8>(q.x, q.y, 0, dc[j], mg, b);
@@ -459,19 +456,14 @@ static hipError_t launch_prefill(const FqLinearDesc &d, int bits, int M, int m_t
     if (per_launch <= 0)
         return hipSuccess;
     const unsigned grid = (unsigned)per_launch * (HALF ? 16u : 8u);
-    const bool once = d.K >= 2048;
-    if (bits == 2 && once)
-        prefill_kernel<2, HALF, 1><<<grid, THREADS, 0, stream>>>(d, M, m_tiles, n_tiles, per_xcd, skip);
-    else if (bits == 2)
-        prefill_kernel<2, HALF, 2><<<grid, THREADS, 0, stream>>>(d, M, m_tiles, n_tiles, per_xcd, skip);
-    else if (bits == 4 && once)
-        prefill_kernel<4, HALF, 1><<<grid, THREADS, 0, stream>>>(d, M, m_tiles, n_tiles, per_xcd, skip);
+    if (bits == 2)
+        prefill_kernel<2, HALF><<<grid, THREADS, 0, stream>>>(d, M, m_tiles, n_tiles, per_xcd, skip);
     else if (bits == 4)
-        prefill_kernel<4, HALF, 2><<<grid, THREADS, 0, stream>>>(d, M, m_tiles, n_tiles, per_xcd, skip);
+        prefill_kernel<4, HALF><<<grid, THREADS, 0, stream>>>(d, M, m_tiles, n_tiles, per_xcd, skip);
     else if (bits == 8)
-        prefill_kernel<8, HALF, 2><<<grid, THREADS, 0, stream>>>(d, M, m_tiles, n_tiles, per_xcd, skip);
+        prefill_kernel<8, HALF><<<grid, THREADS, 0, stream>>>(d, M, m_tiles, n_tiles, per_xcd, skip);
     else
-        prefill_kernel<16, HALF, 2><<<grid, THREADS, 0, stream>>>(d, M, m_tiles, n_tiles, per_xcd, skip);
+        prefill_kernel<16, HALF><<<grid, THREADS, 0, stream>>>(d, M, m_tiles, n_tiles, per_xcd, skip);
     return hipGetLastError();
 }
 

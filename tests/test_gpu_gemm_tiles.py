@@ -1,6 +1,6 @@
 """Every instance of the matrix-core products at shapes that reach it: the tiles of fq_linear above 32 rows (csrc/fq_prompt.hip:
-64, 96 and 128 tokens, one segment of K and several; csrc/fq_prefill.hip: whole and half tiles, one and two row tiles per
-wavefront, scales one and four groups at a time) and of fq_linear_w8a8 (csrc/fq_w8a8_prompt.hip: 64, 128 and 192
+64, 96 and 128 tokens, one segment of K and several; csrc/fq_prefill.hip: whole and half tiles, scales one and
+four groups at a time) and of fq_linear_w8a8 (csrc/fq_w8a8_prompt.hip: 64, 128 and 192
 tokens; csrc/fq_w8a8.hip: 128 and 192 tokens, whole and half tiles with one scale per row).  Each case asks the
 library's own rule that it does reach the instance; tokens and rows are ragged, numbers of groups odd and even.
 Sampled rows over all tokens and sampled tokens over all rows, against the oracle."""
@@ -91,8 +91,7 @@ def test_prompt_tiles(bits, mt, segments, M, N, K):
     _check(y, M, N, ref)
 
 
-# rounds of whole tiles with half tiles behind them, half tiles alone, whole tiles alone; K / 128 a multiple of 4 or not, on both
-# sides of the 2048 inputs from which a wavefront takes one row tile at 2 and 4 bits
+# rounds of whole tiles with half tiles behind them, half tiles alone, whole tiles alone; K / 128 a multiple of 4 or not
 LARGE = [(515, 25001, 384), (193, 18001, 2048), (385, 18001, 512), (515, 28641, 2176)]
 
 
