@@ -387,8 +387,8 @@ bool fq_batch_serves(const FqLinearDesc *table, int count, int M)
 // bits 1.5 to 1.7; from 3072 inputs at 4 bits, 1792 at 8 and 1024 at 16 on 0.7 to 1.0 -- unless there are at most three tiles
 // per compute unit, where the launch is what counts (0.85 to 1.03 at any K).  The register-fed kernel's 64-row tiles
 // come in rounds of one per compute unit; where they fill the last round (32768 rows: two full rounds) it wins
-// back 10 to 20 %: at 4 bits it then keeps the calls over more than 16 batch rows (1.02 to 1.16) or over a K that leaves
-// part of a panel of x (5120: 1.08; 4096: 0.93, 8192: 0.95), up to six rounds (beyond: 0.75 to 1.0).  With 512 rows per
+// back 10 to 20 %: at 4 bits it then keeps the calls over more than 16 batch rows (1.02 to 1.16; with that round three
+// quarters full, 28672 x 8192: 0.92 to 0.99) or over a K that leaves part of a panel of x (5120: 1.08; 4096: 0.93, 8192: 0.95), up to six rounds (beyond: 0.75 to 1.0).  With 512 rows per
 // compute unit it goes over to larger tiles and is as good or better (131072 rows at 4 bits: 1.1 to 2.9).  Under this rule
 // 0.86 of the register-fed kernel's time on average over 5900 calls; one shape stays behind it (29696 x 5120 at 16 bits, 1.14).
 // 2 and 3 bits: this kernel does not unpack them.
@@ -401,10 +401,11 @@ bool fq_batch_serves_linear(int N, int K, int bits, int M)
         return true;
     const int weight = (K >> 7) * (3 * bits + 5); // what a tile's bytes and arithmetic grow with
     const int rest = N % (64 * cus);              // rows of the last round of 64-row tiles (0: a full one)
-    const bool filled = N > 96 * cus && (rest == 0 || rest > (M > 16 ? 35 : 48) * cus);
-    if (!filled)
+    const bool half = N > 96 * cus && (rest == 0 || rest > (M > 16 ? 35 : 48) * cus); // it is half or more full
+    const bool filled = half && (rest == 0 || rest > 48 * cus);
+    if (!half)
         return weight >= 400;
-    return weight >= 470 && (bits != 4 || N > 384 * cus || (M <= 16 && K % 4096 == 0));
+    return weight >= 470 && (!filled || bits != 4 || N > 384 * cus || (M <= 16 && K % 4096 == 0));
 }
 
 hipError_t fq_launch_batch(const FqLinearDesc *single, int bits_host, const FqLinearDesc *descs_dev, const int32_t *bits_dev,
