@@ -172,6 +172,9 @@ int fq_layer_destroy(fq_layer *layer);
  * order, through a static device array of the library (16 MiB for each of the first FQ_PART_STREAMS streams of a
  * device that make such a call).  Calls on further streams, on hipStreamPerThread and under stream capture use no such
  * array: they take longer and give the same bits, so any of these calls may overlap.
+ * The order in which a row's products are added depends on the call's sizes, M among them, and on the device, on
+ * nothing else: equal calls give equal bits, but a row of x need not give the same bits in calls of different M (a
+ * prompt in chunks against the whole prompt, a batch of 16 against one of 17).
  */
 int fq_linear(const fq_layer *layer, int bits, const void *x_fp16, int M,
               void *y_fp16, void *stream);
@@ -289,7 +292,8 @@ int fq_stream_read(const void *src, size_t bytes, uint32_t *sink, void *stream);
  * the sum over g is one term: the whole row is summed exactly in int32 and scaled once,
  * y[m][n] = fp16( s_x[m] * (s[n] * float( sum_k xq[m][k] (q[n][k] - z[n]) )) ).
  *   y_fp16  device, fp16 [M][N], 2-byte aligned             (written)
- * M >= 1.  Calls with few output tiles split K, as fq_linear's GEMM calls do.
+ * M >= 1.  Calls with few output tiles split K, as fq_linear's GEMM calls do; with groups of 128 the order of the
+ * groups' sums then depends on M as theirs does (with one scale per row the sums are exact and it does not show).
  */
 int fq_quantize_act(const void *x_fp16, int M, int K, void *xq, float *sx, int32_t *xsum,
                     void *stream);

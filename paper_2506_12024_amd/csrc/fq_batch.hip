@@ -17,9 +17,9 @@
 // shares, RD lines ahead.
 //
 // Measured (us at 16 batch rows, 4 / 8 / 16 bits, cold weights; before: the register-fed kernel with K split between four
-// wavefronts below 8192 rows and 64-row tiles above): 4096 x 4096 9.1 / 11.3 / 14.0 -> 8.2 / 9.8 / 11.9; 11008 rows x 4096
-// 17.2 / 26.0 / 36.1 -> 11.3 / 15.1 / 21.3; 4096 rows x 11008 17.7 / 23.9 / 30.7 -> 14.6 / 19.2 / 26.2; 22016 rows x 4096
-// 23.8 / 34.8 / 46.9 -> 17.0 / 24.6 / 40.6.  What was found on the way: requests past a run's end must cost nothing (as
+// wavefronts below 8192 rows and 64-row tiles above): 4096 x 4096 9.1 / 11.3 / 14.0 -> 8.5 / 9.8 / 11.9; 11008 rows x 4096
+// 17.2 / 26.0 / 36.1 -> 11.8 / 15.3 / 21.5; 4096 rows x 11008 17.7 / 23.9 / 30.7 -> 14.9 / 19.4 / 26.3; 22016 rows x 4096
+// 23.8 / 34.8 / 46.9 -> 17.1 / 24.6 / 40.4; where the register-fed kernel is the faster one: fq_batch_serves below.  What was found on the way: requests past a run's end must cost nothing (as
 // re-reads of the last line, 8 ahead, they made 4096 x 4096 cost 12 us: the loads' line accesses, not HBM, were the
 // limit) -- they ask beyond the buffer's end; two lines ahead are as fast as eight (19.6 against 23.8 us at 22016 rows);
 // sixteen wavefronts the same as eight; without the arithmetic 16.6 instead of 19.3 us, without x 1.1 us less.  What

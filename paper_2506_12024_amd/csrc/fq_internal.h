@@ -18,10 +18,10 @@ struct FqLinearDesc {
     const float *scales8;
     const uint8_t *zeros8;
     const uint16_t *w16;    // fp16 [N][K] or null
-    const uint8_t *codes2;  // [N][K/4] or null (not served by the streaming batch kernel and the GEMM)
+    const uint8_t *codes2;  // [N][K/4] or null (not served by the small-batch kernel of fq_batch.hip)
     const float *scales2;
     const uint8_t *zeros2;
-    const uint8_t *codes3;  // [N][K/32] blocks of 12 bytes, or null (not served by the streaming batch kernel and the GEMM)
+    const uint8_t *codes3;  // [N][K/32] blocks of 12 bytes, or null (not served by fq_batch.hip, fq_stream.hip and the GEMM)
     const float *scales3;
     const uint8_t *zeros3;
     const uint16_t *x;      // fp16 [M][K]

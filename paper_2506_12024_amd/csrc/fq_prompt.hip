@@ -6,7 +6,7 @@
 //
 // Split.  A workgroup (8 wavefronts) takes 64, 96 or 128 tokens x 128 weight rows and one of up to 16
 // segments of K; the segments' sums meet, in binary32, in a static device array and a second launch
-// adds them in order (26 us for the call above).  In a workgroup four wavefronts stand along the rows, 32
+// adds them in order (23 us for the call above, four segments).  In a workgroup four wavefronts stand along the rows, 32
 // each, and two along K: one takes the first 64 inputs of every group, one the last 64, so that a weight
 // is unpacked by one wavefront only and eight wavefronts share one slab of x; the two halves meet in
 // LDS at the end.  Tokens and segments are chosen by a cost model (prompt_cost below).

@@ -13,9 +13,10 @@
 // is folded under the first chain of the next one, so that with one block of tokens per wavefront the two pipes
 // still overlap.  The zero points' part runs on v_mfma_f32_32x32x2_f32, two groups at a time.
 //
-// What bounds it: the fold, 32 vector instructions per 32 x 32 tile and group (a step of 128 tokens about 0.75 us,
-// 0.21 of it MFMAs); with one scale per row the LDS reads and the fetch (0.45 us); with few steps the launch,
-// the first fetch and the hand-over of the partial sums.
+// What bounds it: a step of 128 tokens takes about 0.75 us, and no pipe is busy for most of it (MFMAs 0.21, the
+// fold's 128 vector instructions a SIMD 0.24, side by side): the operand reads, scales, zero points and group sums all
+// stand between the step's barrier and its first MFMA.  With one scale per row the LDS reads and the fetch (0.45 us);
+// with few steps the launch, the first fetch and the hand-over of the partial sums.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <type_traits>
@@ -286,7 +287,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
         __builtin_amdgcn_s_waitcnt(0);
         if (!ROW) {
             // the last step's last tile, and the zero points of an unpaired last group
-            const int last = (ng & 1) && (TM & 1) ? 0 : (TM & 1) ? 1 : 1;
+            const bool last = !((ng & 1) && (TM & 1)); // which accumulator holds it
 #pragma unroll
             for (int v = 0; v < 16; v++)
                 out[TM - 1][v] += prev_s * (float)(last ? acc[1][v] : acc[0][v]);
