@@ -11,7 +11,7 @@ import torch
 import oracle
 import synth
 import paper_2506_12024_amd as fq
-from gpu_util import DEV, make_layer, rel_err, to_dev
+from gpu_util import DEV, gpu_quantize, make_layer, rel_err, to_dev
 from plan_util import part_bank, prompt_plan, w8a8_large_blocks, w8a8_plan
 
 pytestmark = pytest.mark.gpu
@@ -222,3 +222,39 @@ def test_same_bits_with_and_without_partial_sums(kind, M, N, K):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(y, want)
+
+
+@pytest.mark.parametrize("M,N,K", [(300, 5120, 13824), (200, 11008, 4096), (700, 5120, 5120), (33, 1000, 4096), (150, 18001, 1280)])
+def test_w8a8_sums_of_groups_with_outliers(M, N, K):
+    # Groups with an outlier have their zero point off the middle: what the codes (less 128) and what the zero points bring
+    # are both large there and cancel, group by group.  Each is added to the result's sum with one rounding, the zero
+    # points' factor s (128 - z) is rounded once: errors of rms 2^-23 / sqrt(12) of what is rounded, independent of each
+    # other.  Their rms is worked out for every result from the sums in binary64, and of some million results none
+    # may be off by more than six times that beyond its rounding to fp16.
+    g = torch.Generator(device=DEV).manual_seed(5)
+    w = torch.randn(N, K, generator=g, dtype=torch.float16, device=DEV) * K ** -0.5
+    w.view(-1)[torch.randint(0, N * K, (N * K // 1000,), generator=g, device=DEV)] *= 20.0
+    x = torch.randn(M, K, generator=g, dtype=torch.float16, device=DEV)
+    codes, scales, zeros = gpu_quantize(w, 8)
+    layer = fq.Layer(N, K)
+    layer.attach(8, codes, scales, zeros)
+    xq, sx, xsum = (torch.empty(s, dtype=t, device=DEV) for s, t in
+                    (((M, K), torch.int8), ((M,), torch.float32), ((K // 128, M), torch.int32)))
+    y = torch.empty((M, N), dtype=torch.float16, device=DEV)
+    fq.fq_quantize_act(x, M, K, xq, sx, xsum)
+    fq.fq_linear_w8a8(layer, xq, sx, xsum, M, y)
+    total = torch.zeros(M, N, dtype=torch.float64, device=DEV)
+    var = torch.zeros_like(total)
+    q, xd = codes.view(N, K).double() - 128, xq.double()
+    for i in range(K // 128):
+        k = slice(128 * i, 128 * i + 128)
+        scale = scales[:, i].double()
+        total += (xd[:, k] @ q[:, k].t()) * scale
+        var += total ** 2
+        part = xsum[i].double().unsqueeze(1) * (scale * (128 - zeros[:, i].double()))
+        total += part
+        var += total ** 2 + part ** 2
+    exact = total * sx.double().unsqueeze(1)
+    rms = var.sqrt() * (2.0 ** -23 / 12 ** 0.5) * sx.double().unsqueeze(1)
+    ulp = 2.0 ** (torch.floor(torch.log2(exact.abs().clamp_min(2.0 ** -14))) - 10)
+    assert (((y.double() - exact).abs() - ulp / 2) / rms).max().item() <= 6.0
