@@ -170,8 +170,9 @@ int fq_layer_destroy(fq_layer *layer);
  * FQ_MAX_DECODE_M rows of x, one launch per slab, reading the weights once per slab.
  * GEMM calls with too few output tiles for the chip split K and add the parts, in binary32 and in a fixed
  * order, through a static device array of the library (16 MiB for each of the first FQ_PART_STREAMS streams of a
- * device that make such a call).  Calls on further streams, on hipStreamPerThread and under stream capture use no such
- * array: they take longer and give the same bits, so any of these calls may overlap.
+ * device that make such a call).  Calls on further streams, on hipStreamPerThread, under stream capture, and on the null
+ * stream while a stream that synchronizes with it is captured, use no such array: they take longer and give the same
+ * bits, so any of these calls may overlap.
  * The order in which a row's products are added depends on the call's sizes, M among them, and on the device, on
  * nothing else: equal calls give equal bits, but a row of x need not give the same bits in calls of different M (a
  * prompt in chunks against the whole prompt, a batch of 16 against one of 17).
