@@ -366,7 +366,7 @@ bool fq_batch_serves(const FqLinearDesc *table, int count, int M)
         const int per_group = (d.codes4 ? 17 : 0) + (d.codes8 ? 29 : 0) + (d.w16 ? 53 : 0); // 3 * bits + 5
         four_alone = four_alone && !d.codes8 && !d.w16;
         rows += d.N;
-        tiles += (d.N + 15) / 16;
+        tiles += ((long long)d.N + 15) / 16;
         weight += (double)d.N * (d.K >> 7) * per_group / (copies > 0 ? copies : 1);
         inputs += (double)d.N * d.K;
         padded += (double)d.N * ((d.K + panel - 1) / panel) * panel;
@@ -388,8 +388,8 @@ bool fq_batch_serves(const FqLinearDesc *table, int count, int M)
 // per compute unit, where the launch is what counts (0.85 to 1.03 at any K).  The register-fed kernel's 64-row tiles
 // come in rounds of one per compute unit; where they fill the last round (32768 rows: two full rounds) it wins
 // back 10 to 20 %: at 4 bits it then keeps the calls over more than 16 batch rows (1.02 to 1.16; with that round three
-// quarters full, 28672 x 8192: 0.92 to 0.99) or over a K that leaves part of a panel of x (5120: 1.08; 4096: 0.93, 8192: 0.95), up to six rounds (beyond: 0.75 to 1.0).  With 512 rows per
-// compute unit it goes over to larger tiles and is as good or better (131072 rows at 4 bits: 1.1 to 2.9).  Under this rule
+// quarters full, 28672 x 8192: 0.92 to 0.99) or over a K that leaves part of a panel of x (5120: 1.08; 4096: 0.93,
+// 8192: 0.95), up to six rounds (beyond: 0.75 to 1.0).  With 512 rows per compute unit it goes over to larger tiles and is as good or better (131072 rows at 4 bits: 1.1 to 2.9).  Under this rule
 // 0.86 of the register-fed kernel's time on average over 5900 calls; one shape stays behind it (29696 x 5120 at 16 bits, 1.14).
 // 2 and 3 bits: this kernel does not unpack them.
 bool fq_batch_serves_linear(int N, int K, int bits, int M)
