@@ -16,6 +16,7 @@ LIB = os.path.join(HERE, "libflexq.so")
 OBJDIR = os.path.join(HERE, "_build")
 SOURCES = ["fq_api.hip", "fq_device.hip", "fq_noalloc.hip", "fq_probe.hip", "fq_quantize.hip", "fq_entropy.hip", "fq_decode.hip", "fq_staged.hip", "fq_skinny.hip", "fq_batch.hip", "fq_stream.hip", "fq_prefill.hip", "fq_prompt.hip", "fq_w8a8.hip", "fq_w8a8_prompt.hip", "fq_sched.hip", "fq_lmhead.hip"]
 HEADERS = [os.path.join(CSRC, "fq_internal.h"), os.path.join(CSRC, "fq_gemv.h"), os.path.join(CSRC, "fq_mfma.h"), os.path.join(CSRC, "fq_div.h"), os.path.join(CSRC, "fq_batch_at.h"),
+           os.path.join(CSRC, "fq_staged_src.h"),
            os.path.join(os.path.dirname(HERE), "include", "flexq.h")]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          # packed fp32 ops are kept off for device code (the host pass warns it does not know the feature)

@@ -12,6 +12,7 @@
 
 #include "../../include/flexq.h"
 #include "fq_internal.h"
+#include "fq_staged_src.h"
 
 namespace {
 
@@ -565,6 +566,18 @@ int fq_plan_create_staged(fq_plan **out, int count, const fq_layer *const *layer
             if (stage[a] <= stage[b] && xs[a] == ys[b])
                 return fail(FQ_ERR_SHAPE, "fq_plan_create_staged: x of entry %d (stage %d) is y of entry %d (stage %d)",
                             a, stage[a], b, stage[b]);
+    std::vector<uintptr_t> xa, ya;
+    std::vector<int> Ks, Ns;
+    std::vector<int32_t> src((size_t)count);
+    for (const FqLinearDesc &d : table) {
+        xa.push_back(reinterpret_cast<uintptr_t>(d.x));
+        ya.push_back(reinterpret_cast<uintptr_t>(d.y));
+        Ks.push_back(d.K);
+        Ns.push_back(d.N);
+    }
+    staged_sources(count, xa.data(), ya.data(), Ks.data(), Ns.data(), stage, begin.data(), n_stages, src.data());
+    for (int i = 0; i < count; i++)
+        table[i].src = src[i];
     const size_t lds = fq_staged_lds_bytes(n_stages, geom.max_K, STAGED_RES_CHUNKS);
     if (lds > 160 * 1024)
         return fail(FQ_ERR_SHAPE, "fq_plan_create_staged: %d stages with rows of up to %d inputs need %zu bytes of "

@@ -280,14 +280,6 @@ __device__ __forceinline__ uint4 load16_stream(const void *p)
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
-// The same from an address that is only 4-byte aligned (one instruction all the same).
-__device__ __forceinline__ uint4 load16_stream_a4(const void *p)
-{
-    typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
-    const u32x4 v = __builtin_nontemporal_load((const FQ_GLOBAL u32x4_a4 *)p);
-    return make_uint4(v.x, v.y, v.z, v.w);
-}
-
 // 96-bit streaming load (a 3-bit block: 4-byte aligned); .w is left 0.
 __device__ __forceinline__ uint4 load12_stream(const void *p)
 {

@@ -29,7 +29,7 @@ struct FqLinearDesc {
     int N;
     int K;
     int tile_begin;         // first row tile of this entry in the plan's global tile numbering
-    int pad;
+    int src;                // stage-ordered plans: 1 + the entry whose y is polled for this x, 0 if none is
 };
 
 // Geometry of a plan: how its entries are cut into row tiles for the kernel that serves its M.

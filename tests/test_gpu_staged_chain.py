@@ -1,0 +1,84 @@
+"""Stage-ordered plans whose stages wait for the rows they read (no grid barrier), and plans that look like them but go
+through the barrier: chains through a part of a y, two stages back, through buffers used again, past an entry that has no
+copy at its bit-width, and rows that are NaNs.  Against the same stages as plans of their own, in turn: bit for bit."""
+import pytest
+import torch
+
+import synth
+import paper_2506_12024_amd as fq
+from gpu_util import DEV, make_layer, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _plan(layers, xs, ys, stage):
+    ws = torch.empty(fq.StagedPlan.workspace_bytes(len(layers), max(stage) + 1), dtype=torch.uint8, device=DEV)
+    return fq.StagedPlan(layers, xs, ys, stage, 1, ws)
+
+
+def _layer(tag, N, K, widths=(2, 3, 4, 8, 16), nan_row=None):
+    w = synth.weight(21, "stgc/" + tag, N, K, K ** -0.5)
+    if nan_row is not None:
+        w = w.copy()
+        w.view("uint16")[nan_row] = 0xFFFF
+    return make_layer(w, widths)[0]
+
+
+# how each linear finds its x: ("y", entry, first) or ("new", tag); its y: None for a buffer of its own, else entry whose y it reuses
+CHAIN = [(0, 515, 512, ("new", "a"), None), (1, 1100, 512, ("y", 0, 0), None), (1, 384, 512, ("y", 0, 0), None),
+         (2, 640, 1024, ("y", 1, 8), None), (3, 37, 640, ("y", 3, 0), None), (3, 12400, 640, ("y", 3, 0), None),
+         (4, 515, 12288, ("y", 5, 16), None), (5, 130, 512, ("y", 6, 0), None)]
+
+
+def _variant(name):
+    c = list(CHAIN)
+    if name == "two_back":        # stage 4 reads what stage 2 wrote: through the barrier there, polled elsewhere
+        c[6] = (4, 515, 640, ("y", 3, 0), None)
+    if name == "reused":          # stage 5 writes where stage 1 did: barriers everywhere
+        c[7] = (5, 130, 512, ("y", 6, 0), 2)
+    if name == "outside":         # an entry whose x is none of the plan's
+        c[4] = (3, 37, 640, ("new", "b"), None)
+    return c
+
+
+@pytest.mark.parametrize("name", ["chain", "two_back", "reused", "outside", "unattached", "nan"])
+def test_chains_match_their_stages_one_by_one(name):
+    ents = _variant(name)
+    widths = [(4, 8) if name == "unattached" and i == 3 else (2, 3, 4, 8, 16) for i in range(len(ents))]
+    layers = [_layer("%d" % i, N, K, widths[i], 5 if name == "nan" and i == 1 else None)
+              for i, (_, N, K, _, _) in enumerate(ents)]
+    new = {t: torch.zeros(1, 640, dtype=torch.float16, device=DEV) for t in ("a", "b")}
+
+    def buffers():
+        ys, xs = [], []
+        for st, N, K, (kind, src, *first), again in ents:
+            xs.append(new[src][:, :K].contiguous() if kind == "new" else ys[src][:, first[0]:first[0] + K])
+            ys.append(ys[again][:, :N] if again is not None else torch.zeros(1, N, dtype=torch.float16, device=DEV))
+        return xs, ys
+
+    new["a"].copy_(to_dev(synth.activations(21, "stgc/a", 1, 640)))
+    new["b"].copy_(to_dev(synth.activations(21, "stgc/b", 1, 640)))
+    xs, ys = buffers()
+    xr, yr = buffers()
+    stage = [e[0] for e in ents]
+    plan = _plan(layers, xs, ys, stage)
+    sets = [[i for i, v in enumerate(stage) if v == st] for st in range(max(stage) + 1)]
+    ones = [_plan([layers[i] for i in set_], [xr[i] for i in set_], [yr[i] for i in set_], [0] * len(set_)) for set_ in sets]
+    for rep, pattern in enumerate([(4, 8), (8, 4, 16), (2, 3, 4), (16,), (4,)]):
+        bits = [16 if name == "nan" and i == 1 else pattern[i % len(pattern)] for i in range(len(ents))]
+        if name == "unattached":
+            bits[3] = 16 if rep % 2 else 8      # every other time nobody writes stage 2's y: its old content is read
+        for b in range(rep % 2 + 1):
+            plan.run(torch.tensor(bits, dtype=torch.int32, device=DEV))
+        for set_, one in zip(sets, ones):
+            one.run(torch.tensor([bits[i] for i in set_], dtype=torch.int32, device=DEV))
+        torch.cuda.synchronize()
+        for i in range(len(ents)):
+            a, b = ys[i].view(torch.int16), yr[i].view(torch.int16)
+            if name == "nan":
+                a, b = torch.where(ys[i].isnan(), 0, a), torch.where(yr[i].isnan(), 0, b)
+                assert torch.equal(ys[i].isnan(), yr[i].isnan()), (rep, i)
+            assert torch.equal(a, b), (rep, i)
+        assert plan.status()[0] == 0
+    if name == "nan":
+        assert ys[1].isnan().any()
