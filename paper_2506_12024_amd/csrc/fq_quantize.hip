@@ -199,25 +199,37 @@ __global__ __launch_bounds__(256) void fake_quantize_kernel(const half8 *w, long
 
 // One scale and zero point per weight row (group = K) at 8 bits: the granularity at which the INT8 copy
 // meets 8-bit activations on the integer matrix cores without a fold per group (Sec. 4.1, 4.3).  Eq. (2)
-// as above with Xmin / Xmax taken over the whole row.  One workgroup per row, two passes over it (the
-// second finds it in cache).
-template <bool SYM>
-__global__ __launch_bounds__(256) void quantize_row8_kernel(const half8 *__restrict__ w, int K,
-                                                            uint8_t *__restrict__ codes, float *__restrict__ scales,
-                                                            uint8_t *__restrict__ zeros)
+// as above with Xmin / Xmax taken over the whole row.  One workgroup of T threads per row, which a thread's NV vectors of
+// 8 weights hold in registers, requested together and read once (two walks over it in a loop waited for memory a dozen times in
+// turn: 8192 x 28672 182 -> 123 us = 5.7 TB/s, 5120 x 13824 58 -> 40, 11008 x 4096 30 -> 25); NV = 0: rows beyond 32768 weights, in
+// that loop.
+template <bool SYM, int T, int NV>
+__global__ __launch_bounds__(T) void quantize_row8_kernel(const half8 *__restrict__ w, int K, uint8_t *__restrict__ codes,
+                                                          float *__restrict__ scales, uint8_t *__restrict__ zeros)
 {
 #pragma clang fp contract(off)
-    __shared__ float s_lo[4], s_hi[4];
+    __shared__ float s_lo[T / 64], s_hi[T / 64];
     const int t = threadIdx.x, nvec = K >> 3;
     const half8 *row = w + (size_t)blockIdx.x * nvec;
+    half8 v[NV > 0 ? NV : 1];
     float lo = 0.0f, hi = 0.0f; // the range always contains 0
-    for (int i = t; i < nvec; i += 256) {
-        const half8 v = row[i];
+    auto range = [&](const half8 h) {
 #pragma unroll
         for (int j = 0; j < 8; j++) {
-            lo = fminf(lo, (float)v[j]);
-            hi = fmaxf(hi, (float)v[j]);
+            lo = fminf(lo, (float)h[j]);
+            hi = fmaxf(hi, (float)h[j]);
         }
+    };
+    if constexpr (NV > 0) {
+#pragma unroll
+        for (int u = 0; u < NV; u++)
+            v[u] = row[min(u * T + t, nvec - 1)]; // (past the end: the last vector once more)
+#pragma unroll
+        for (int u = 0; u < NV; u++)
+            range(v[u]);
+    } else {
+        for (int i = t; i < nvec; i += T)
+            range(row[i]);
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
@@ -229,16 +241,18 @@ __global__ __launch_bounds__(256) void quantize_row8_kernel(const half8 *__restr
         s_hi[t >> 6] = hi;
     }
     __syncthreads();
-    lo = fminf(fminf(s_lo[0], s_lo[1]), fminf(s_lo[2], s_lo[3]));
-    hi = fmaxf(fmaxf(s_hi[0], s_hi[1]), fmaxf(s_hi[2], s_hi[3]));
+#pragma unroll
+    for (int i = 0; i < T / 64; i++) {
+        lo = fminf(lo, s_lo[i]);
+        hi = fmaxf(hi, s_hi[i]);
+    }
     const GroupParams p = group_params<SYM>(lo, hi, 8);
     const float z = SYM ? 128.0f : p.z; // what is stored
-    for (int i = t; i < nvec; i += 256) {
-        const half8 v = row[i];
+    auto put = [&](const half8 h, int i) {
         uint32_t q[8];
 #pragma unroll
         for (int j = 0; j < 8; j++) {
-            float c = rintf(__fadd_rn(p.by.of((float)v[j]), p.z));
+            float c = rintf(__fadd_rn(p.by.of((float)h[j]), p.z));
             c = fminf(fmaxf(c, p.qlo), p.qhi);
             q[j] = (uint32_t)(int)(SYM ? c + z : c);
         }
@@ -246,11 +260,35 @@ __global__ __launch_bounds__(256) void quantize_row8_kernel(const half8 *__restr
         word.x = q[0] | (q[1] << 8) | (q[2] << 16) | (q[3] << 24);
         word.y = q[4] | (q[5] << 8) | (q[6] << 16) | (q[7] << 24);
         reinterpret_cast<uint2 *>(codes + (size_t)blockIdx.x * K)[i] = word;
+    };
+    if constexpr (NV > 0) {
+#pragma unroll
+        for (int u = 0; u < NV; u++)
+            if (u * T + t < nvec)
+                put(v[u], u * T + t);
+    } else {
+        for (int i = t; i < nvec; i += T)
+            put(row[i], i);
     }
     if (t == 0) {
         scales[blockIdx.x] = p.s;
         zeros[blockIdx.x] = (uint8_t)(int)z;
     }
+}
+
+template <bool SYM>
+void launch_row8(const half8 *w, int N, int K, uint8_t *codes, float *scales, uint8_t *zeros, hipStream_t stream)
+{
+    if (K <= 4096) // 256 threads x 2 vectors x 8 weights
+        quantize_row8_kernel<SYM, 256, 2><<<N, 256, 0, stream>>>(w, K, codes, scales, zeros);
+    else if (K <= 8192)
+        quantize_row8_kernel<SYM, 256, 4><<<N, 256, 0, stream>>>(w, K, codes, scales, zeros);
+    else if (K <= 16384)
+        quantize_row8_kernel<SYM, 256, 8><<<N, 256, 0, stream>>>(w, K, codes, scales, zeros);
+    else if (K <= 32768)
+        quantize_row8_kernel<SYM, 512, 8><<<N, 512, 0, stream>>>(w, K, codes, scales, zeros);
+    else
+        quantize_row8_kernel<SYM, 256, 0><<<N, 256, 0, stream>>>(w, K, codes, scales, zeros);
 }
 
 } // namespace
@@ -303,8 +341,8 @@ hipError_t fq_launch_quantize_row8(const void *w, int N, int K, bool symmetric, 
     if (N <= 0)
         return hipSuccess;
     if (symmetric)
-        quantize_row8_kernel<true><<<N, 256, 0, stream>>>((const half8 *)w, K, (uint8_t *)codes, (float *)scales, (uint8_t *)zeros);
+        launch_row8<true>((const half8 *)w, N, K, (uint8_t *)codes, (float *)scales, (uint8_t *)zeros, stream);
     else
-        quantize_row8_kernel<false><<<N, 256, 0, stream>>>((const half8 *)w, K, (uint8_t *)codes, (float *)scales, (uint8_t *)zeros);
+        launch_row8<false>((const half8 *)w, N, K, (uint8_t *)codes, (float *)scales, (uint8_t *)zeros, stream);
     return hipGetLastError();
 }
