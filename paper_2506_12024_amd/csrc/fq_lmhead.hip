@@ -7,9 +7,13 @@
 //
 // A wavefront takes four vocabulary rows at a time; lane l reads 16 bytes (8 halves) of each at
 // k = 512 j + 8 l, j = 0 .. K / 512 - 1 -- one non-temporal 128-bit load per row and j, a
-// wavefront load is 1 KiB contiguous -- with the loads of step j + 1 in flight while step j is
+// wavefront load is 1 KiB contiguous -- with the loads of the next DEPTH steps in flight while step j is
 // multiplied (v_dot2_f32_f16) against the matching x blocks, which sit in LDS for the whole
-// kernel ([j][m][lane], conflict free).  The four sums are reduced across the wavefront and
+// kernel ([j][m][lane], conflict free).  The steps run on from one four rows to the next: begun anew for every four
+// rows, with one step in flight and the sums through LDS, short rows and several rows of x waited for memory most (us;
+// before, then with 2 / 3 / 4 steps: 4 x 8192 -> 32000 123, 112 / 111 / 110; 1 x 1024 -> 32000 19.5, 17.2 / 17.3 / 17.2; 2 x
+// 2048 -> 9001 18.8, 16.5 / 16.8 / 16.7; 1 x 4096 -> 32000 46.4, 48.1 / 47.1 / 46.5 and -> 128256 159.5, 162 / 160 / 159.7, where
+// it is HBM: 6.4 TB/s and the second launch; one, three, four workgroups per compute unit instead of two: 46.3, 47.8, 48.6).  The four sums are reduced across the wavefront and
 // handed to lanes 0 .. 3, each of which keeps an online softmax state per row of x: running
 // maximum and its index, S = sum exp(a - max), U = sum (a - max) exp(a - max).  States meet per
 // wavefront, per workgroup (LDS) and per call: every workgroup leaves its partial in a static
@@ -32,6 +36,7 @@ constexpr int THREADS = 256;
 constexpr int WAVES = THREADS / 64;
 constexpr int RPW = 4;                 // vocabulary rows per wavefront and iteration
 constexpr int ROWS_PER_WG = WAVES * RPW;
+constexpr int DEPTH = 4;               // steps in flight per wavefront
 constexpr int MAX_M = 4;
 constexpr int MAX_WGS = 1024; // also the size of the combining workgroup: one partial per thread
 
@@ -52,12 +57,23 @@ __device__ __forceinline__ float dot8(const u32x4 w, const u32x4 x, float acc)
     return acc;
 }
 
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ float dpp(float v) // (0 in the rows that are masked out)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, ROW_MASK, 0xF, false));
+}
+
+// Sum over the wavefront in vector instructions alone, in every lane: neighbours, quads, halves and rows of 16, then
+// (rows 0 + 1) + (rows 2 + 3).
 __device__ __forceinline__ float wave_sum(float v)
 {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1)
-        v += __shfl_xor(v, off, 64);
-    return v;
+    v += dpp<0xB1, 0xF>(v);  // quad_perm [1,0,3,2]
+    v += dpp<0x4E, 0xF>(v);  // quad_perm [2,3,0,1]
+    v += dpp<0x141, 0xF>(v); // row_half_mirror
+    v += dpp<0x140, 0xF>(v); // row_mirror
+    v += dpp<0x142, 0xA>(v); // row_bcast15 into rows 1 and 3
+    v += dpp<0x143, 0xC>(v); // row_bcast31 into rows 2 and 3
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
 }
 
 // Online softmax state of one row of x.
@@ -143,54 +159,75 @@ __global__ __launch_bounds__(THREADS) void lm_head_entropy_kernel(const uint16_t
     for (int m = 0; m < M; m++)
         st[m].init();
 
+    // Items (row block, step), DEPTH of them in flight in registers, run through the row blocks: while a block's sums are
+    // reduced, the next block's first steps are on their way.
     const int nblocks = (V + ROWS_PER_WG - 1) / ROWS_PER_WG;
-    for (int rb = blockIdx.x; rb < nblocks; rb += gridDim.x) {
-        const int row0 = rb * ROWS_PER_WG + wave * RPW;
-        const FQ_GLOBAL u32x4 *wp[RPW];
+    u32x4 in[DEPTH][RPW];
+    const FQ_GLOBAL u32x4 *wp[RPW];
+    int ib = blockIdx.x, ij = 0; // the next item to request
+    auto rows_of = [&](int rb) {
 #pragma unroll
         for (int r = 0; r < RPW; r++) // rows past V repeat row V - 1 and are dropped below
-            wp[r] = (const FQ_GLOBAL u32x4 *)(w + (size_t)min(row0 + r, V - 1) * K) + lane;
-        float acc[RPW][M];
+            wp[r] = (const FQ_GLOBAL u32x4 *)(w + (size_t)min((long long)rb * ROWS_PER_WG + wave * RPW + r, (long long)V - 1) * K) + lane;
+    };
+    auto request = [&](u32x4 (&to)[RPW]) {
 #pragma unroll
         for (int r = 0; r < RPW; r++)
+            to[r] = __builtin_nontemporal_load(wp[r] + ij * 64);
+        asm volatile("" ::: "memory"); // (where it is issued, not where it is used)
+        if (++ij == J && ib + (int)gridDim.x < nblocks) { // (past the last block: its steps once more)
+            ij = 0;
+            ib += gridDim.x;
+            rows_of(ib);
+        } else if (ij == J) {
+            ij = J - 1;
+        }
+    };
+    rows_of(ib);
 #pragma unroll
-            for (int m = 0; m < M; m++)
-                acc[r][m] = 0.f;
-        u32x4 cur[RPW], nxt[RPW];
+    for (int d = 0; d < DEPTH; d++)
+        request(in[d]);
+    float acc[RPW][M];
 #pragma unroll
-        for (int r = 0; r < RPW; r++)
-            cur[r] = __builtin_nontemporal_load(wp[r]);
-        for (int j = 0; j < J; j++) {
-            const int jn = min(j + 1, J - 1); // the last step re-reads itself: the wait stays counted
+    for (int r = 0; r < RPW; r++)
 #pragma unroll
-            for (int r = 0; r < RPW; r++)
-                nxt[r] = __builtin_nontemporal_load(wp[r] + jn * 64);
+        for (int m = 0; m < M; m++)
+            acc[r][m] = 0.f;
+    int rb = blockIdx.x, j = 0; // the item being multiplied
+    while (rb < nblocks) {
+#pragma unroll
+        for (int d = 0; d < DEPTH; d++) {
+            if (rb < nblocks) {
+#pragma unroll
+                for (int m = 0; m < M; m++) {
+                    const u32x4 xv = xs[(j * M + m) * 64 + lane];
+#pragma unroll
+                    for (int r = 0; r < RPW; r++)
+                        acc[r][m] = dot8(in[d][r], xv, acc[r][m]);
+                }
+            }
+            request(in[d]);
+            if (++j < J || rb >= nblocks)
+                continue;
 #pragma unroll
             for (int m = 0; m < M; m++) {
-                const u32x4 xv = xs[(j * M + m) * 64 + lane];
+                float mine = 0.f;
 #pragma unroll
-                for (int r = 0; r < RPW; r++)
-                    acc[r][m] = dot8(cur[r], xv, acc[r][m]);
+                for (int r = 0; r < RPW; r++) {
+                    const float s = wave_sum(acc[r][m]);
+                    if (lane == r)
+                        mine = s;
+                    acc[r][m] = 0.f;
+                }
+                const int v = rb * ROWS_PER_WG + wave * RPW + lane;
+                if (lane < RPW && v < V) {
+                    st[m].add(mine, v);
+                    if (logits)
+                        logits[(size_t)m * V + v] = mine;
+                }
             }
-#pragma unroll
-            for (int r = 0; r < RPW; r++)
-                cur[r] = nxt[r];
-        }
-#pragma unroll
-        for (int m = 0; m < M; m++) {
-            float mine = 0.f;
-#pragma unroll
-            for (int r = 0; r < RPW; r++) {
-                const float s = wave_sum(acc[r][m]);
-                if (lane == r)
-                    mine = s;
-            }
-            const int v = row0 + lane;
-            if (lane < RPW && v < V) {
-                st[m].add(mine, v);
-                if (logits)
-                    logits[(size_t)m * V + v] = mine;
-            }
+            j = 0;
+            rb += gridDim.x;
         }
     }
 
