@@ -11,9 +11,10 @@
 // multiplied (v_dot2_f32_f16) against the matching x blocks, which sit in LDS for the whole
 // kernel ([j][m][lane], conflict free).  The steps run on from one four rows to the next: begun anew for every four
 // rows, with one step in flight and the sums through LDS, short rows and several rows of x waited for memory most (us;
-// before, then with 2 / 3 / 4 steps: 4 x 8192 -> 32000 123, 112 / 111 / 110; 1 x 1024 -> 32000 19.5, 17.2 / 17.3 / 17.2; 2 x
-// 2048 -> 9001 18.8, 16.5 / 16.8 / 16.7; 1 x 4096 -> 32000 46.4, 48.1 / 47.1 / 46.5 and -> 128256 159.5, 162 / 160 / 159.7, where
-// it is HBM: 6.4 TB/s and the second launch; one, three, four workgroups per compute unit instead of two: 46.3, 47.8, 48.6).  The four sums are reduced across the wavefront and
+// before and now: 4 x 8192 -> 32000 123 and 109, 1 x 1024 -> 32000 19.5 and 16.7, 2 x 2048 -> 9001 18.7 and 16.4; 1 x 4096 ->
+// 32000 46.7 and 46.1, -> 128256 158.7 and 158.4, where it is HBM: 6.4 TB/s and the second launch).  With 2 and 3 steps the
+// last but one takes 1.6 and 0.6 more; with one, three, four workgroups per compute unit instead of two 0, 1.4 and 2.2 more;
+// with the requests past a wavefront's last block repeating its last steps instead of one line of x 0.6 more.  The four sums are reduced across the wavefront and
 // handed to lanes 0 .. 3, each of which keeps an online softmax state per row of x: running
 // maximum and its index, S = sum exp(a - max), U = sum (a - max) exp(a - max).  States meet per
 // wavefront, per workgroup (LDS) and per call: every workgroup leaves its partial in a static
@@ -175,12 +176,16 @@ __global__ __launch_bounds__(THREADS) void lm_head_entropy_kernel(const uint16_t
         for (int r = 0; r < RPW; r++)
             to[r] = __builtin_nontemporal_load(wp[r] + ij * 64);
         asm volatile("" ::: "memory"); // (where it is issued, not where it is used)
-        if (++ij == J && ib + (int)gridDim.x < nblocks) { // (past the last block: its steps once more)
+        if (++ij == J) {
             ij = 0;
             ib += gridDim.x;
-            rows_of(ib);
-        } else if (ij == J) {
-            ij = J - 1;
+            if (ib < nblocks) {
+                rows_of(ib);
+            } else { // past the last block: one line of x, so that every path has the same requests in flight
+#pragma unroll
+                for (int r = 0; r < RPW; r++)
+                    wp[r] = (const FQ_GLOBAL u32x4 *)x;
+            }
         }
     };
     rows_of(ib);
