@@ -302,7 +302,7 @@ int fq_linear(const fq_layer *layer, int bits, const void *x_fp16, int M, void *
         }
     } else if (M <= FQ_MAX_DECODE_M && layer->K <= MAX_DECODE_K) {
         if (M > 1 && fq_batch_serves_linear(layer->N, layer->K, bits, M)) {
-            e = fq_launch_batch(&d, bits, nullptr, nullptr, 1, (layer->N + 15) / 16, M, nullptr, (hipStream_t)stream);
+            e = fq_launch_batch(&d, bits, nullptr, nullptr, 1, (layer->N + 15) / 16, M, nullptr, d.x, d.K, (hipStream_t)stream);
             if (e != hipSuccess)
                 return hip_fail(e, "fq_linear launch");
             return FQ_OK;
@@ -437,6 +437,11 @@ int fq_plan_layout(const char *who, int count, const fq_layer *const *layers, co
         if (tiles > 0x7fffffffLL)
             return fail(FQ_ERR_SHAPE, "%s: too many row tiles", who);
     }
+    geom->x_all = table[0].x;
+    geom->K_all = table[0].K;
+    for (int i = 1; i < count; i++)
+        if (table[i].x != table[0].x || table[i].K != table[0].K)
+            geom->x_all = nullptr;
     geom->count = count;
     geom->M = M;
     geom->total_tiles = (int)tiles;
@@ -454,7 +459,7 @@ hipError_t fq_plan_launch(const FqPlanGeom &g, const FqLinearDesc *table_dev, in
 {
     if (g.batch)
         return fq_launch_batch(nullptr, 0, table_dev, bits_dev, g.count, g.total_tiles, g.M, queue_dev ? queue_dev + FQ_Q_FLAGS : nullptr,
-                               stream);
+                               g.x_all, g.K_all, stream);
     hipError_t e = g.M == 1
         ? fq_launch_decode(nullptr, 0, table_dev, bits_dev, g.count, g.total_tiles, g.tile_rows, g.max_K, g.M,
                            queue_dev ? queue_dev + FQ_Q_FLAGS : nullptr, stream)

@@ -11,9 +11,9 @@
 //
 // x sits in LDS, 128 KiB of it at a time (4096 inputs of 16 batch rows, 2048 of 32), brought by direct-to-LDS loads
 // in slabs of 64 inputs whose 16-byte pieces are permuted (w_offset) so that operand reads are conflict free; projections of
-// 4096 inputs are one panel, and entries that share x (q, k, v) do not fetch it again.  Scales and
-// zero points of the run's tiles are laid beside it.  Weights go straight to registers: lane (n, c) takes 16 bytes of
-// each half line of row n, the operand layout of v_mfma_f32_16x16x32_f16 up to a permutation of the inputs that x
+// 4096 inputs are one panel, and entries that share x (q, k, v) do not fetch it again: then the sums of a run
+// stay out of x's place.  Scales and zero points of the run's tiles are laid beside it.  Weights go straight to
+// registers: lane (n, c) takes 16 bytes of each half line of row n, the operand layout of v_mfma_f32_16x16x32_f16 up to a permutation of the inputs that x
 // shares, RD lines ahead.
 //
 // Measured (us at 16 batch rows, 4 / 8 / 16 bits, cold weights; before: the register-fed kernel with K split between four
@@ -22,9 +22,14 @@
 // 23.8 / 34.8 / 46.9 -> 17.1 / 24.6 / 40.4; where the register-fed kernel is the faster one: fq_batch_serves below.  What was found on the way: requests past a run's end must cost nothing (as
 // re-reads of the last line, 8 ahead, they made 4096 x 4096 cost 12 us: the loads' line accesses, not HBM, were the
 // limit) -- they ask beyond the buffer's end; two lines ahead are as fast as eight (19.6 against 23.8 us at 22016 rows);
-// sixteen wavefronts the same as eight; without the arithmetic 16.6 instead of 19.3 us, without x 1.1 us less.  What
-// bounds it now: 4.3 us of launch, division and end, the ramp of the first request, and tiles that do not
-// divide evenly (22016 rows are 5.4 per workgroup).
+// sixteen wavefronts the same as eight; without the arithmetic 16.6 instead of 19.3 us, without x 1.1 us less.  Then, by time stamps
+// (one 4096 x 4096 entry, 4 bits, 9.1 us of which 1.3 between launches): 0.9 for the table, 0.9 for the division, up to six trips
+// to memory for the scales, one barrier pair per two tiles of sums.  With the scales requested together, the sums in one
+// round, x requested ahead of the table's arrival where the host knows it and integer divisions out of the way, plans at 16
+// batch rows: 2 x 11008 x 4096 at 4 / 8 / 16 bits 19.5 / 25.0 / 39.2 -> 16.6 / 22.8 / 38.8, 3 x 4096 x 4096 12.9 / 16.7 / 23.6 -> 12.4 /
+// 16.1 / 23.2, 4096 x 4096 8.2 / 9.7 / 11.8 -> 7.8 / 9.2 / 10.4, 4096 x 11008 15.0 / 19.6 / 26.9 -> 14.9 / 19.6 / 26.1; the 7B-shaped layers
+// at 4 and 8 bits 544 -> 512 us for 32 launches.  What bounds it now: launch, table and first request 4 us, instructions
+// (137 vector ones per 4-bit line of 16 rows, 11 lines a wavefront at 22016 rows), three panels one after the other at K = 11008.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <type_traits>
@@ -60,10 +65,47 @@ struct Lds {
     float4_t red[2 * WAVES * 64];
 };
 
+// Inputs of a panel; its quantization groups; their stride in LDS.
+template <int MB>
+struct Panel {
+    static constexpr int KP = XBYTES / (32 * MB), GP = KP / 128, GS = GP + 1;
+};
+
+// Up to NB consecutive tiles of an entry at its selected width.
+struct Run {
+    const uint8_t *codes, *zeros;
+    const float *scales;
+    const uint16_t *x;
+    uint16_t *y;
+    int bits, N, K, t0, nt;
+};
+
+// Panel 0 of x, before the launch's widths are known; x may be null (nothing is read).  (Every workgroup reads this x: each
+// starts somewhere else in it, or they would all ask the same L2 channel at the same time.)  Slabs past K repeat the
+// row's last, so that the number of requests does not depend on it.
+template <int MB>
+__device__ __forceinline__ void fetch_first_x(Lds &L, const uint16_t *x, int K, int M)
+{
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const __amdgpu_buffer_rsrc_t xbuf = buffer_of(x, x ? (uint32_t)M * (uint32_t)K * 2 : 0u);
+    // (request j fills KiB j of the panel; a wavefront's have j % 8 in common, and with it the rows and pieces they take)
+    const int first = (int)((blockIdx.x >> 3) * 37u % 32u) / 2 * 8, last = max(K - 64, 0);
+    int r, byte;
+    w_piece<128>(wave & 1, lane, r, byte);
+    const int mb = MB == 2 ? (wave >> 1) & 1 : 0;
+    const uint32_t at = (uint32_t)min(mb * 16 + r, M - 1) * (uint32_t)K * 2 + byte;
+#pragma unroll
+    for (int i = 0; i < XBYTES / 1024 / WAVES; i++) {
+        const int j = (i * WAVES + first) % (XBYTES / 1024) + wave, k = j / (2 * MB) * 64;
+        load_to_lds<16>(xbuf, L.x + j * 1024, at, (uint32_t)min(k, last) * 2);
+    }
+}
+
 // The tiles [t0, t0 + nt) of one entry.
 template <int BITS, int MB>
 __device__ __forceinline__ void run_batch(Lds &L, const uint8_t *codes, const float *scales, const uint8_t *zeros,
-                                          const uint16_t *x, uint16_t *y, int N, int K, int M, int t0, int nt, bool x_there)
+                                          const uint16_t *x, uint16_t *y, int N, int K, int M, int t0, int nt, bool x_there,
+                                          bool keep_x)
 {
     constexpr int KP = XBYTES / (32 * MB); // inputs of a panel: 4096 or 2048
     constexpr int GP = KP / 128, GS = GP + 1; // groups of a panel; their stride in LDS
@@ -134,13 +176,26 @@ __device__ __forceinline__ void run_batch(Lds &L, const uint8_t *codes, const fl
                 issue(w[j]);
         }
         if (BITS != 16) {
-            // scales and zero points of the batch's tiles for the panel's groups: [tile][row][group]
-            const int rows = nt * 16;
-            for (int i = threadIdx.x; i < rows * GP; i += THREADS) {
-                const int r = i / GP, g = i % GP;
-                const size_t at = (size_t)min(n0 + r, N - 1) * G + min(g0 + g, G - 1);
-                L.s[r * GS + g] = ((const FQ_GLOBAL float *)scales)[at];
-                L.z[r * GS + g] = ((const FQ_GLOBAL uint8_t *)zeros)[at];
+            // Scales and zero points of the batch's tiles for the panel's groups, [tile][row][group]: all requested together (a
+            // loop that stored each before it asked for the next made up to six trips to memory).  A thread's rows are THREADS /
+            // GP apart; rows past the run are beyond both buffers, groups past K are put there.
+            constexpr int ML = NB * 16 * GP / THREADS;
+            const int rows = min(nt * 16, N - n0), r0 = threadIdx.x / GP, g = threadIdx.x % GP;
+            const __amdgpu_buffer_rsrc_t sbuf = buffer_of(scales + (size_t)n0 * G, (uint32_t)rows * G * 4);
+            const __amdgpu_buffer_rsrc_t zbuf = buffer_of(zeros + (size_t)n0 * G, (uint32_t)rows * G);
+            uint32_t at = g0 + g < G ? (uint32_t)(r0 * G + g0 + g) : 0x1f000000u;
+            float s[ML];
+            uint8_t z[ML];
+#pragma unroll
+            for (int i = 0; i < ML; i++) {
+                s[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(sbuf, (int)(at * 4), 0, 0));
+                z[i] = __builtin_amdgcn_raw_buffer_load_b8(zbuf, (int)at, 0, 0);
+                at += (uint32_t)(THREADS / GP) * (uint32_t)G;
+            }
+#pragma unroll
+            for (int i = 0; i < ML; i++) {
+                L.s[(r0 + i * (THREADS / GP)) * GS + g] = s[i];
+                L.z[(r0 + i * (THREADS / GP)) * GS + g] = z[i];
             }
         }
         __builtin_amdgcn_s_waitcnt(0);
@@ -240,106 +295,155 @@ __device__ __forceinline__ void run_batch(Lds &L, const uint8_t *codes, const fl
             }
         }
     }
-    // the wavefronts' sums, added in their order: two blocks of 16 x 16 outputs at a time (MB = 1: two tiles)
-#pragma unroll
-    for (int t = 0; t < NB * MB; t += 2) {
-        if (t >= nt * MB)
-            break;
+    // The wavefronts' sums, added in their order: all blocks of 16 x 16 outputs at once through the panel's place, or, if the
+    // next run reads the panel, two at a time (six tiles 1.9 us instead of 1.0).
+    static_assert(NB * MB * WAVES * 1024 <= XBYTES, "the sums of a run fit a panel");
+    float4_t *red = keep_x ? L.red : reinterpret_cast<float4_t *>(L.x);
+    const int blocks = nt * MB, round = keep_x ? 2 : NB * MB;
+    for (int b0 = 0; b0 < blocks; b0 += round) {
+        const int b1 = min(b0 + round, blocks);
         __syncthreads();
 #pragma unroll
-        for (int u = 0; u < 2; u++)
-            L.red[(u * WAVES + wave) * 64 + lane] = sum[(t + u) / MB][(t + u) % MB];
+        for (int u = 0; u < NB * MB; u++)
+            if (u >= b0 && u < b1)
+                red[((u - b0) * WAVES + wave) * 64 + lane] = sum[u / MB][u % MB];
         __syncthreads();
-        // D layout of the 16x16 MFMA: lane holds column n (weight row), rows (batch) 4 * c + r
-        const int u = threadIdx.x >> 8, m16 = (threadIdx.x >> 4) & 15, nn = threadIdx.x & 15;
-        const float *p = reinterpret_cast<const float *>(L.red + u * WAVES * 64) + ((m16 >> 2) * 16 + nn) * 4 + (m16 & 3);
-        float v = p[0];
+        for (int u = b0 + (threadIdx.x >> 8); u < b1; u += 2) {
+            // D layout of the 16x16 MFMA: lane holds column n (weight row), rows (batch) 4 * c + r
+            const int m16 = (threadIdx.x >> 4) & 15, nn = threadIdx.x & 15;
+            const float *p = reinterpret_cast<const float *>(red + (u - b0) * WAVES * 64) + ((m16 >> 2) * 16 + nn) * 4 + (m16 & 3);
+            float v = p[0];
 #pragma unroll
-        for (int q = 1; q < WAVES; q++)
-            v += p[q * 256];
-        const int tile = (t + u) / MB, row = n0 + tile * 16 + nn, m = (t + u) % MB * 16 + m16;
-        if (tile < nt && m < M && row < N)
-            ((FQ_GLOBAL uint16_t *)y)[(size_t)m * N + row] = __builtin_bit_cast(uint16_t, (_Float16)v);
+            for (int q = 1; q < WAVES; q++)
+                v += p[q * 256];
+            const int tile = u / MB, row = n0 + tile * 16 + nn, m = u % MB * 16 + m16;
+            if (m < M && row < N)
+                ((FQ_GLOBAL uint16_t *)y)[(size_t)m * N + row] = __builtin_bit_cast(uint16_t, (_Float16)v);
+        }
     }
 }
 
+// A wavefront's view of the launch: lane e holds entry e, all of it, so that one trip to memory serves the whole table;
+// every wavefront works out the same division of the launch's cost.
+template <bool SINGLE, int MB>
+struct Division {
+    int bits, N, K, lo, hi; // lo, hi: the entry's tiles that fall to this workgroup
+    const void *codes, *scales, *zeros, *x;
+    void *y;
+    const void *c4, *c8, *c16, *s4, *s8, *z4, *z8;
+    unsigned long long todo;
+    int t, te;
+
+    // Request lane e's entry (lanes past the last repeat it).
+    __device__ __forceinline__ void request_table(const FqLinearDesc &single, int bits_host, const FqLinearDesc *table,
+                                                  const int32_t *bits_dev, int count)
+    {
+        const int e = min((int)(threadIdx.x & 63), count - 1);
+        const FqLinearDesc *d = SINGLE ? &single : &table[e];
+        bits = SINGLE ? bits_host : bits_dev[e];
+        c4 = d->codes4, c8 = d->codes8, c16 = d->w16, s4 = d->scales4, s8 = d->scales8, z4 = d->zeros4, z8 = d->zeros8;
+        x = d->x, y = d->y, N = d->N, K = d->K;
+        __builtin_amdgcn_sched_barrier(0); // ahead of what is requested next
+    }
+    __device__ __forceinline__ void settle(int count, uint32_t step, int *flags)
+    {
+        const int lane = threadIdx.x & 63;
+        if (!SINGLE) // (all of it has been asked for, whatever the width: chosen pointers alone would be a second trip)
+            asm volatile("" : "+v"(c4), "+v"(c8), "+v"(c16), "+v"(s4), "+v"(s8), "+v"(z4), "+v"(z8), "+v"(bits), "+v"(N), "+v"(K),
+                              "+v"(x), "+v"(y));
+        codes = bits == 4 ? c4 : bits == 8 ? c8 : bits == 16 ? c16 : nullptr;
+        scales = bits == 4 ? s4 : s8;
+        zeros = bits == 4 ? z4 : z8;
+        int tiles = 0, cost = 0;
+        if (lane < count) {
+            if (codes) {
+                tiles = (N + 15) >> 4;
+                cost = batch_tile_cost(2 * Panel<MB>::KP, K, bits);
+            } else if (flags && blockIdx.x == 0 && threadIdx.x < 64) {
+                *flags = 1; // no such width here, or no copy of it: nobody runs this entry
+            }
+        }
+        const uint32_t mine = tiles > 0 ? (uint32_t)tiles * cost + BATCH_START_COST : 0u;
+        uint32_t upto = mine; // inclusive prefix
+        if (!SINGLE)
+            for (int off = 1; off < count; off <<= 1) {
+                const uint32_t o = __shfl_up(upto, off, 64);
+                if (lane >= off)
+                    upto += o;
+            }
+        const uint32_t all = __builtin_amdgcn_readlane(upto, count - 1);
+        // this workgroup's share of the cost; a tile belongs to the share its first unit lies in
+        lo = hi = 0;
+        if (tiles > 0) {
+            lo = batch_first_tile(batch_share_at(all, blockIdx.x, gridDim.x, step), upto - mine, cost, tiles);
+            hi = batch_first_tile(batch_share_at(all, blockIdx.x + 1, gridDim.x, step), upto - mine, cost, tiles);
+        }
+        todo = __ballot(hi > lo);
+        t = te = 0;
+    }
+    __device__ __forceinline__ static const void *of(const void *p, int e) // lane e's pointer
+    {
+        const uint64_t v = reinterpret_cast<uint64_t>(p);
+        const uint32_t lo32 = __builtin_amdgcn_readlane((uint32_t)v, e), hi32 = __builtin_amdgcn_readlane((uint32_t)(v >> 32), e);
+        return reinterpret_cast<const void *>((uint64_t)hi32 << 32 | lo32);
+    }
+    // The run after `r`; nt = 0: there is none.
+    __device__ __forceinline__ Run next_run(Run r)
+    {
+        if (t >= te) {
+            if (!todo) {
+                r.nt = 0;
+                return r;
+            }
+            const int e = __builtin_ctzll(todo);
+            todo &= todo - 1;
+            r.bits = __builtin_amdgcn_readlane(bits, e);
+            t = __builtin_amdgcn_readlane(lo, e), te = __builtin_amdgcn_readlane(hi, e);
+            r.N = __builtin_amdgcn_readlane(N, e), r.K = __builtin_amdgcn_readlane(K, e);
+            r.codes = (const uint8_t *)of(codes, e), r.zeros = (const uint8_t *)of(zeros, e);
+            r.scales = (const float *)of(scales, e);
+            r.x = (const uint16_t *)of(x, e);
+            r.y = (uint16_t *)const_cast<void *>(of(y, e));
+        }
+        r.t0 = t;
+        r.nt = min(NB, te - t);
+        t += r.nt;
+        return r;
+    }
+};
+
+// x0, K0: what every entry reads, if they all read one x (else null): requested before anything else is known.  `step`:
+// batch_step of the grid.
 template <bool SINGLE, int MB>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_batch_kernel(
     const FqLinearDesc single, int bits_host, const FqLinearDesc *__restrict__ table, const int32_t *__restrict__ bits_dev,
-    int count, int M, int *flags)
+    int count, int M, int *flags, const uint16_t *x0, int K0, uint32_t step)
 {
     __shared__ Lds L;
-    const int lane = threadIdx.x & 63;
-    // Every wavefront works out the same division of the launch's cost: lane e holds entry e, all of it, so that
-    // one trip to memory serves the whole table.
-    int e_bits = 0, e_tiles = 0, e_cost = 0, e_N = 0, e_K = 0;
-    const void *e_codes = nullptr, *e_scales = nullptr, *e_zeros = nullptr, *e_x = nullptr;
-    void *e_y = nullptr;
-    if (SINGLE ? lane == 0 : lane < count) {
-        const FqLinearDesc *d = SINGLE ? &single : &table[lane];
-        e_bits = SINGLE ? bits_host : bits_dev[lane];
-        const void *c4 = d->codes4, *c8 = d->codes8, *c16 = d->w16, *s4 = d->scales4, *s8 = d->scales8, *z4 = d->zeros4,
-                   *z8 = d->zeros8;
-        e_x = d->x, e_y = d->y, e_N = d->N, e_K = d->K;
-        e_codes = e_bits == 4 ? c4 : e_bits == 8 ? c8 : e_bits == 16 ? c16 : nullptr;
-        e_scales = e_bits == 4 ? s4 : s8;
-        e_zeros = e_bits == 4 ? z4 : z8;
-        if (e_codes) {
-            e_tiles = (e_N + 15) >> 4;
-            e_cost = batch_tile_cost(XBYTES / (32 * MB), e_K, e_bits);
-        } else if (flags && blockIdx.x == 0 && threadIdx.x < 64) {
-            *flags = 1; // no such width here, or no copy of it: nobody runs this entry
-        }
+    Division<SINGLE, MB> dv;
+    dv.request_table(single, bits_host, table, bits_dev, count);
+    fetch_first_x<MB>(L, x0, K0, M);
+    dv.settle(count, step, flags);
+    Run r = {};
+    r = dv.next_run(r);
+    bool there = x0 && r.nt > 0; // the run's first panel is in LDS, or on its way
+    if (!there) {
+        __builtin_amdgcn_s_waitcnt(0); // (nothing of the request ahead may arrive after what is asked for later)
+        __syncthreads();
     }
-    auto of = [](const void *p, int e) -> const void * { // lane e's pointer
-        const uint64_t v = reinterpret_cast<uint64_t>(p);
-        const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)v, e), hi = __builtin_amdgcn_readlane((uint32_t)(v >> 32), e);
-        return reinterpret_cast<const void *>((uint64_t)hi << 32 | lo);
-    };
-    const uint32_t e_all = e_tiles > 0 ? (uint32_t)e_tiles * e_cost + BATCH_START_COST : 0u;
-    uint32_t upto = e_all; // inclusive prefix
-    if (!SINGLE) {
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t o = __shfl_up(upto, off, 64);
-            if (lane >= off)
-                upto += o;
-        }
-    }
-    const uint32_t all = SINGLE ? __builtin_amdgcn_readfirstlane(upto) : __builtin_amdgcn_readlane(upto, 63);
-    // this workgroup's share of the cost; a tile belongs to the share its first unit lies in
-    int t_lo = 0, t_hi = 0;
-    if (e_tiles > 0) {
-        t_lo = batch_first_tile(batch_share(all, blockIdx.x, gridDim.x), upto - e_all, e_cost, e_tiles);
-        t_hi = batch_first_tile(batch_share(all, blockIdx.x + 1, gridDim.x), upto - e_all, e_cost, e_tiles);
-    }
-    unsigned long long todo = __ballot(t_hi > t_lo);
-    const uint16_t *x_in = nullptr; // whose first panel is in LDS (all of it: one panel)
-    int x_K = 0;
-    while (todo) {
-        const int e = __builtin_ctzll(todo);
-        todo &= todo - 1;
-        const int bits = __builtin_amdgcn_readlane(e_bits, e);
-        const int tb = __builtin_amdgcn_readlane(t_lo, e), te = __builtin_amdgcn_readlane(t_hi, e);
-        const int N = __builtin_amdgcn_readlane(e_N, e), K = __builtin_amdgcn_readlane(e_K, e);
-        const uint8_t *codes = (const uint8_t *)of(e_codes, e), *zeros = (const uint8_t *)of(e_zeros, e);
-        const float *scales = (const float *)of(e_scales, e);
-        const uint16_t *x = (const uint16_t *)of(e_x, e);
-        uint16_t *y = (uint16_t *)const_cast<void *>(of(e_y, e));
-        for (int t = tb; t < te; t += NB) {
-            const bool there = x == x_in && K == x_K && K <= XBYTES / (32 * MB);
-            if (t > tb || x_in)
-                __syncthreads(); // LDS is free again
-            const int nt = min(NB, te - t);
-            if (bits == 4)
-                run_batch<4, MB>(L, codes, scales, zeros, x, y, N, K, M, t, nt, there);
-            else if (bits == 8)
-                run_batch<8, MB>(L, codes, scales, zeros, x, y, N, K, M, t, nt, there);
-            else
-                run_batch<16, MB>(L, codes, nullptr, nullptr, x, y, N, K, M, t, nt, there);
-            x_in = x;
-            x_K = K;
-        }
+    while (r.nt > 0) {
+        const Run next = dv.next_run(r);
+        const bool keep = next.nt > 0 && next.x == r.x && next.K == r.K && r.K <= Panel<MB>::KP;
+        if (r.bits == 4)
+            run_batch<4, MB>(L, r.codes, r.scales, r.zeros, r.x, r.y, r.N, r.K, M, r.t0, r.nt, there, keep);
+        else if (r.bits == 8)
+            run_batch<8, MB>(L, r.codes, r.scales, r.zeros, r.x, r.y, r.N, r.K, M, r.t0, r.nt, there, keep);
+        else
+            run_batch<16, MB>(L, r.codes, nullptr, nullptr, r.x, r.y, r.N, r.K, M, r.t0, r.nt, there, keep);
+        there = keep;
+        r = next;
+        if (r.nt > 0)
+            __syncthreads(); // LDS is free again
     }
 }
 
@@ -409,20 +513,23 @@ bool fq_batch_serves_linear(int N, int K, int bits, int M)
 }
 
 hipError_t fq_launch_batch(const FqLinearDesc *single, int bits_host, const FqLinearDesc *descs_dev, const int32_t *bits_dev,
-                           int count, long long tiles, int M, int *flags, hipStream_t stream)
+                           int count, long long tiles, int M, int *flags, const uint16_t *x0, int K0, hipStream_t stream)
 {
     const int cus = fq_device_cus();
     const unsigned grid = (unsigned)(tiles < cus ? tiles : cus);
+    const uint32_t step = batch_step(grid);
+    if (K0 < 2048) // (the request ahead is of a whole panel)
+        x0 = nullptr;
     FqLinearDesc none = {};
     if (single) {
         if (M <= 16)
-            decode_batch_kernel<true, 1><<<grid, THREADS, 0, stream>>>(*single, bits_host, nullptr, nullptr, 1, M, nullptr);
+            decode_batch_kernel<true, 1><<<grid, THREADS, 0, stream>>>(*single, bits_host, nullptr, nullptr, 1, M, nullptr, x0, K0, step);
         else
-            decode_batch_kernel<true, 2><<<grid, THREADS, 0, stream>>>(*single, bits_host, nullptr, nullptr, 1, M, nullptr);
+            decode_batch_kernel<true, 2><<<grid, THREADS, 0, stream>>>(*single, bits_host, nullptr, nullptr, 1, M, nullptr, x0, K0, step);
     } else if (M <= 16) {
-        decode_batch_kernel<false, 1><<<grid, THREADS, 0, stream>>>(none, 0, descs_dev, bits_dev, count, M, flags);
+        decode_batch_kernel<false, 1><<<grid, THREADS, 0, stream>>>(none, 0, descs_dev, bits_dev, count, M, flags, x0, K0, step);
     } else {
-        decode_batch_kernel<false, 2><<<grid, THREADS, 0, stream>>>(none, 0, descs_dev, bits_dev, count, M, flags);
+        decode_batch_kernel<false, 2><<<grid, THREADS, 0, stream>>>(none, 0, descs_dev, bits_dev, count, M, flags, x0, K0, step);
     }
     return hipGetLastError();
 }

@@ -37,6 +37,8 @@ struct FqPlanGeom {
     int count, M, total_tiles, tile_rows, max_K;
     int has3; // some layer of the plan holds a 3-bit copy
     int batch; // served by fq_launch_batch
+    const uint16_t *x_all; // the x that every entry reads, all of them K_all long, or null
+    int K_all;
 };
 struct fq_layer;
 // Records a message for fq_last_error() on the calling thread and returns `code`.
@@ -118,11 +120,11 @@ hipError_t fq_launch_skinny(const FqLinearDesc *single, int bits_host,
                             hipStream_t stream);
 int fq_skinny_tile_rows(long long total_rows, int M);
 // Single calls and small plans (up to 64 entries) at 2 <= M <= 32 and 4, 8 or 16 bits (fq_batch.hip); `tiles`: tiles of
-// 16 rows in all.
+// 16 rows in all; x0, K0: the x every entry reads and its row length, or null.
 bool fq_batch_serves(const FqLinearDesc *table, int count, int M); // a plan (host table)
 bool fq_batch_serves_linear(int N, int K, int bits, int M);
 hipError_t fq_launch_batch(const FqLinearDesc *single, int bits_host, const FqLinearDesc *descs_dev, const int32_t *bits_dev,
-                           int count, long long tiles, int M, int *flags, hipStream_t stream);
+                           int count, long long tiles, int M, int *flags, const uint16_t *x0, int K0, hipStream_t stream);
 // Streaming variant for plan launches with 2 <= M <= 32 and tiles of 256 rows (fq_launch_skinny
 // hands those to it).
 hipError_t fq_launch_skinny_stream(const FqLinearDesc *descs_dev, const int32_t *bits_dev, int count,

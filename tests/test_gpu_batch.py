@@ -146,3 +146,27 @@ def test_plan_of_more_entries_than_the_small_batch_kernel_takes(M):
     assert plan.status() == (0, 0)
     for i in range(70):
         assert rel_err(ys[i].cpu().numpy(), refs[i]) <= TOL, i
+
+
+@pytest.mark.parametrize("M", [16, 32])
+@pytest.mark.parametrize("K,share", [(1920, True), (2048, True), (4096, True), (4224, True), (4096, False)])
+def test_plan_whose_workgroups_cross_entries(K, share, M):
+    # x requested ahead of the table from 2048 inputs on where all entries read it, kept for the next entry up to one
+    # panel (4096 or 2048 inputs), and neither; the widths changing in between
+    rows, bits = [2100, 1000, 4500, 8192], [4, 16, 8, 4]
+    name = "batch/cross/%d" % K
+    layers, xs, ys, ws, packs = [], [], [], [], []
+    shared = to_dev(synth.activations(13, name + "/x", M, K))
+    for i, N in enumerate(rows):
+        w = synth.weight(13, name + "/w%d" % i, N, K, 0.02)
+        layer, packed = make_layer(w, (bits[i],))
+        layers.append(layer), ws.append(w), packs.append(packed)
+        xs.append(shared if share or i == 1 else to_dev(synth.activations(13, name + "/x%d" % i, M, K)))
+        ys.append(torch.full((M, N), float("nan"), dtype=torch.float16, device=DEV))
+    space = torch.empty(fq.Plan.workspace_bytes(len(rows)), dtype=torch.uint8, device=DEV)
+    plan = fq.Plan(layers, xs, ys, M, space)
+    plan.run(torch.tensor(bits, dtype=torch.int32, device=DEV))
+    torch.cuda.synchronize()
+    for i in range(len(rows)):
+        ref = _ref(ws[i], packs[i], bits[i], xs[i].cpu().numpy())
+        assert rel_err(ys[i].cpu().numpy(), ref) <= TOL, i
