@@ -42,7 +42,7 @@ namespace {
 
 constexpr int THREADS = 512;
 constexpr int WAVES = 8;
-constexpr int XBYTES = 128 * 1024; // x of a panel
+constexpr int XBYTES = BATCH_X_BYTES; // x of a panel
 constexpr int NB = 6;              // tiles of 16 rows a workgroup takes at a time
 constexpr int RD = 2;              // 128-byte lines of each row a wavefront has in flight
 constexpr int MAX_ENTRIES = 64;
@@ -68,7 +68,7 @@ struct Lds {
 // Inputs of a panel; its quantization groups; their stride in LDS.
 template <int MB>
 struct Panel {
-    static constexpr int KP = XBYTES / (32 * MB), GP = KP / 128, GS = GP + 1;
+    static constexpr int KP = batch_panel(MB), GP = KP / 128, GS = GP + 1;
 };
 
 // Up to NB consecutive tiles of an entry at its selected width.
@@ -107,7 +107,7 @@ __device__ __forceinline__ void run_batch(Lds &L, const uint8_t *codes, const fl
                                           const uint16_t *x, uint16_t *y, int N, int K, int M, int t0, int nt, bool x_there,
                                           bool keep_x)
 {
-    constexpr int KP = XBYTES / (32 * MB); // inputs of a panel: 4096 or 2048
+    constexpr int KP = batch_panel(MB);   // inputs of a panel: 4096 or 2048
     constexpr int GP = KP / 128, GS = GP + 1; // groups of a panel; their stride in LDS
     constexpr int KL = 1024 / BITS;        // inputs of a line: 256 / 128 / 64
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -358,7 +358,7 @@ struct Division {
         if (lane < count) {
             if (codes) {
                 tiles = (N + 15) >> 4;
-                cost = batch_tile_cost(2 * Panel<MB>::KP, K, bits);
+                cost = batch_tile_cost(MB, K, bits);
             } else if (flags && blockIdx.x == 0 && threadIdx.x < 64) {
                 *flags = 1; // no such width here, or no copy of it: nobody runs this entry
             }
@@ -460,7 +460,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 // one more than full runs or a round of the other kernel is just full.
 bool fq_batch_serves(const FqLinearDesc *table, int count, int M)
 {
-    const int cus = fq_device_cus(), panel = M <= 16 ? 4096 : 2048;
+    const int cus = fq_device_cus(), panel = batch_panel(M <= 16 ? 1 : 2);
     long long rows = 0, tiles = 0;
     double weight = 0, inputs = 0, padded = 0; // summed over the rows
     bool four_alone = true;

@@ -33,20 +33,26 @@ FQ_BATCH_FN uint32_t batch_request(uint32_t row_bytes, uint32_t lane_offset, int
     return lane_offset + ((uint32_t)tile * 16 * row_bytes + line0 + (uint32_t)line * 128);
 }
 
+// x sits in LDS, so many bytes of it at a time: a panel.  `blocks`: blocks of 16 batch rows a launch takes, 1 or 2.
+constexpr int BATCH_X_BYTES = 128 * 1024;
+FQ_BATCH_FN constexpr int batch_panel(int blocks) { return BATCH_X_BYTES / (32 * blocks); } // inputs: 4096 or 2048
+
 // What a tile of 16 rows costs, in units of 10 ns, fitted to single calls of 128 to 11008 inputs and 1024 to 98304
 // rows: a part that does not depend on K (sums, stores, its share of a run's start), its bytes, its lines in turns of
-// the eight wavefronts -- a panel (4096 inputs up to 16 batch rows, 2048 above) that does not fill its last turn pays for all of
+// the eight wavefronts -- a panel that does not fill its last turn pays for all of
 // it -- and, for each panel after the first, its share of the wait for x and scales.  Without the first part
 // short rows look free beside long ones, and one workgroup gets hundreds of their tiles: rows 14848 x 5120, 12741 x
 // 512, 1408 x 5120, 21248 x 5120 at 16, 4, 8 and 4 bits, 4 batch rows, took 205 us against 71 on the register-fed kernel; now
 // 60.  An entry's first tile also pays for the start on it (100 to 200 units do the same; 50 are 1 % slower over 1200 plans).
+// The panel follows from `blocks` here and nowhere else, so that nobody costs a launch by a panel that it does not have.
 constexpr uint32_t BATCH_START_COST = 160;
-FQ_BATCH_FN int batch_tile_cost(int panel, int K, int bits)
+FQ_BATCH_FN int batch_tile_cost(int blocks, int K, int bits)
 {
+    const int panel = batch_panel(blocks);
     const int turns = K / panel * (panel / 1024 * bits / 8) + (((K % panel * bits + 1023) >> 10) + 7) / 8;
     const int per_group = bits == 4 ? 54 : bits == 8 ? 75 : 142;
-    return (bits == 16 ? 40 : 66) + (K >> 7) * per_group / 10 + turns * (panel == 4096 ? 11 : 25) +
-           ((K + panel - 1) / panel - 1) * (panel == 4096 ? 55 : 30);
+    return (bits == 16 ? 40 : 66) + (K >> 7) * per_group / 10 + turns * (blocks == 1 ? 11 : 25) +
+           ((K + panel - 1) / panel - 1) * (blocks == 1 ? 55 : 30);
 }
 
 // Share i of n of a launch's cost begins here; `step`: batch_step(n).  (A share is a few instructions, worked out by every

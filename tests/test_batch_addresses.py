@@ -60,16 +60,18 @@ extern "C" long walk(int N, int K, int bits, int n0, int nt, int kp_max, unsigne
         *missing += !seen[p];
     return bad;
 }
+extern "C" int tile_cost(int blocks, int K, int bits) { return batch_tile_cost(blocks, K, bits); }
+extern "C" int panel_of(int blocks) { return batch_panel(blocks); }
 // The tiles of each entry that share i of `shares` takes: out[2 * (i * count + e)] .. out[2 * (i * count + e) + 1].
-extern "C" void divide(int count, const int *N, const int *K, const int *bits, int panel, int shares, int *out)
+extern "C" void divide(int count, const int *N, const int *K, const int *bits, int blocks, int shares, int *out)
 {
     uint32_t all = 0;
     for (int e = 0; e < count; e++)
-        all += (uint32_t)((N[e] + 15) / 16) * batch_tile_cost(panel, K[e], bits[e]) + BATCH_START_COST;
+        all += (uint32_t)((N[e] + 15) / 16) * batch_tile_cost(blocks, K[e], bits[e]) + BATCH_START_COST;
     for (int i = 0; i < shares; i++) {
         uint32_t begin = 0;
         for (int e = 0; e < count; e++) {
-            const int tiles = (N[e] + 15) / 16, cost = batch_tile_cost(panel, K[e], bits[e]);
+            const int tiles = (N[e] + 15) / 16, cost = batch_tile_cost(blocks, K[e], bits[e]);
             for (int h = 0; h < 2; h++)
                 out[2 * (i * count + e) + h] = batch_first_tile(batch_share(all, i + h, shares), begin, cost, tiles);
             begin += (uint32_t)tiles * cost + BATCH_START_COST;
@@ -127,15 +129,15 @@ MIXES = [[(14848, 5120, 16), (12741, 512, 4), (1408, 5120, 8), (21248, 5120, 4)]
          [(98304, 32768, 16)]]
 
 
-@pytest.mark.parametrize("panel", [4096, 2048])
+@pytest.mark.parametrize("blocks", [1, 2])
 @pytest.mark.parametrize("mix", MIXES)
-def test_division_of_a_launch(lib, mix, panel):
+def test_division_of_a_launch(lib, mix, blocks):
     count = len(mix)
     tiles = [(n + 15) // 16 for n, _, _ in mix]
     shares = min(256, sum(tiles))
     arr = [(ctypes.c_int * count)(*[m[j] for m in mix]) for j in range(3)]
     out = (ctypes.c_int * (2 * shares * count))()
-    lib.divide(count, *arr, panel, shares, out)
+    lib.divide(count, *arr, blocks, shares, out)
     most = 0
     for e in range(count):
         ranges = [(out[2 * (i * count + e)], out[2 * (i * count + e) + 1]) for i in range(shares)]
@@ -146,3 +148,15 @@ def test_division_of_a_launch(lib, mix, panel):
     # 6.5 TB/s: no workgroup may get so many short tiles that the launch waits for it.
     stream_us = sum(n * k * b / 8 for n, k, b in mix) / 6.5e6
     assert 0.5 * most <= 2 * stream_us + 2
+
+
+@pytest.mark.parametrize("blocks,panel,turn,wait", [(1, 4096, 11, 55), (2, 2048, 25, 30)])
+def test_a_tile_costs_what_was_fitted_for_its_batch_rows(lib, blocks, panel, turn, wait):
+    # The kernel hands the cost its number of 16-row blocks and nothing else.  Up to 16 batch rows a panel of x is 4096 inputs
+    # and its figures are the first ones, above 2048 and the second: the fit written out.
+    assert lib.panel_of(blocks) == panel
+    for bits, fixed, per_group in ((4, 66, 5.4), (8, 66, 7.5), (16, 40, 14.2)):
+        for K in list(range(128, 4352, 128)) + [5120, 8192, 11008, 28672, 32768]:
+            turns = sum(-(-min(panel, K - k) * bits // 8192) for k in range(0, K, panel))   # 8 lines of 128 bytes each
+            want = fixed + int(K // 128 * per_group + 1e-6) + turns * turn + (-(-K // panel) - 1) * wait
+            assert lib.tile_cost(blocks, K, bits) == want, (bits, K)
