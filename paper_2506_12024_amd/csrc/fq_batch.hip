@@ -80,16 +80,16 @@ struct Run {
     int bits, N, K, t0, nt;
 };
 
-// Panel 0 of x, before the launch's widths are known; x may be null (nothing is read).  (Every workgroup reads this x: each
+// Panel 0 of x, before the launch's widths are known.  (Every workgroup reads this x: each
 // starts somewhere else in it, or they would all ask the same L2 channel at the same time.)  Slabs past K repeat the
 // row's last, so that the number of requests does not depend on it.
 template <int MB>
 __device__ __forceinline__ void fetch_first_x(Lds &L, const uint16_t *x, int K, int M)
 {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const __amdgpu_buffer_rsrc_t xbuf = buffer_of(x, x ? (uint32_t)M * (uint32_t)K * 2 : 0u);
+    const __amdgpu_buffer_rsrc_t xbuf = buffer_of(x, (uint32_t)M * (uint32_t)K * 2);
     // (request j fills KiB j of the panel; a wavefront's have j % 8 in common, and with it the rows and pieces they take)
-    const int first = (int)((blockIdx.x >> 3) * 37u % 32u) / 2 * 8, last = max(K - 64, 0);
+    const int first = (int)((blockIdx.x >> 3) * 37u % 32u) / 2 * 8, last = K - 64;
     int r, byte;
     w_piece<128>(wave & 1, lane, r, byte);
     const int mb = MB == 2 ? (wave >> 1) & 1 : 0;
@@ -422,15 +422,14 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
     __shared__ Lds L;
     Division<SINGLE, MB> dv;
     dv.request_table(single, bits_host, table, bits_dev, count);
-    fetch_first_x<MB>(L, x0, K0, M);
+    if (x0)
+        fetch_first_x<MB>(L, x0, K0, M);
     dv.settle(count, step, flags);
     Run r = {};
     r = dv.next_run(r);
     bool there = x0 && r.nt > 0; // the run's first panel is in LDS, or on its way
-    if (!there) {
-        __builtin_amdgcn_s_waitcnt(0); // (nothing of the request ahead may arrive after what is asked for later)
-        __syncthreads();
-    }
+    if (x0 && !there) // (no run: what was asked for arrives while the workgroup still has its LDS)
+        __builtin_amdgcn_s_waitcnt(0);
     while (r.nt > 0) {
         const Run next = dv.next_run(r);
         const bool keep = next.nt > 0 && next.x == r.x && next.K == r.K && r.K <= Panel<MB>::KP;
