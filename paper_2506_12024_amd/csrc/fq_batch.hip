@@ -183,20 +183,26 @@ __device__ __forceinline__ void run_batch(Lds &L, const uint8_t *codes, const fl
             const int rows = min(nt * 16, N - n0), r0 = threadIdx.x / GP, g = threadIdx.x % GP;
             const __amdgpu_buffer_rsrc_t sbuf = buffer_of(scales + (size_t)n0 * G, (uint32_t)rows * G * 4);
             const __amdgpu_buffer_rsrc_t zbuf = buffer_of(zeros + (size_t)n0 * G, (uint32_t)rows * G);
-            uint32_t at = g0 + g < G ? (uint32_t)(r0 * G + g0 + g) : 0x1f000000u;
-            float s[ML];
-            uint8_t z[ML];
+            auto fetch = [&](auto n) __attribute__((always_inline)) {
+                uint32_t at = g0 + g < G ? (uint32_t)(r0 * G + g0 + g) : 0x1f000000u;
+                float s[n];
+                uint8_t z[n];
 #pragma unroll
-            for (int i = 0; i < ML; i++) {
-                s[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(sbuf, (int)(at * 4), 0, 0));
-                z[i] = __builtin_amdgcn_raw_buffer_load_b8(zbuf, (int)at, 0, 0);
-                at += (uint32_t)(THREADS / GP) * (uint32_t)G;
-            }
+                for (int i = 0; i < n; i++) {
+                    s[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(sbuf, (int)(at * 4), 0, 0));
+                    z[i] = __builtin_amdgcn_raw_buffer_load_b8(zbuf, (int)at, 0, 0);
+                    at += (uint32_t)(THREADS / GP) * (uint32_t)G;
+                }
 #pragma unroll
-            for (int i = 0; i < ML; i++) {
-                L.s[(r0 + i * (THREADS / GP)) * GS + g] = s[i];
-                L.z[(r0 + i * (THREADS / GP)) * GS + g] = z[i];
-            }
+                for (int i = 0; i < n; i++) {
+                    L.s[(r0 + i * (THREADS / GP)) * GS + g] = s[i];
+                    L.z[(r0 + i * (THREADS / GP)) * GS + g] = z[i];
+                }
+            };
+            if (nt * 16 <= THREADS / GP)
+                fetch(std::integral_constant<int, 1>{});
+            else
+                fetch(std::integral_constant<int, ML>{});
         }
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
