@@ -304,17 +304,11 @@ __device__ __forceinline__ void run_batch(Lds &L, const uint8_t *codes, const fl
     // The wavefronts' sums, added in their order: all blocks of 16 x 16 outputs at once through the panel's place, or, if the
     // next run reads the panel, two at a time (six tiles 1.9 us instead of 1.0).
     static_assert(NB * MB * WAVES * 1024 <= XBYTES, "the sums of a run fit a panel");
-    float4_t *red = keep_x ? L.red : reinterpret_cast<float4_t *>(L.x);
-    const int blocks = nt * MB, round = keep_x ? 2 : NB * MB;
-    for (int b0 = 0; b0 < blocks; b0 += round) {
-        const int b1 = min(b0 + round, blocks);
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < NB * MB; u++)
-            if (u >= b0 && u < b1)
-                red[((u - b0) * WAVES + wave) * 64 + lane] = sum[u / MB][u % MB];
-        __syncthreads();
-        for (int u = b0 + (threadIdx.x >> 8); u < b1; u += 2) {
+    auto leave = [&](float4_t *red, int u, int at) __attribute__((always_inline)) {
+        red[(at * WAVES + wave) * 64 + lane] = sum[u / MB][u % MB];
+    };
+    auto add_up = [&](const float4_t *red, int b0, int b1) __attribute__((always_inline)) {
+        for (int u = b0 + (int)(threadIdx.x >> 8); u < b1; u += 2) {
             // D layout of the 16x16 MFMA: lane holds column n (weight row), rows (batch) 4 * c + r
             const int m16 = (threadIdx.x >> 4) & 15, nn = threadIdx.x & 15;
             const float *p = reinterpret_cast<const float *>(red + (u - b0) * WAVES * 64) + ((m16 >> 2) * 16 + nn) * 4 + (m16 & 3);
@@ -326,6 +320,28 @@ __device__ __forceinline__ void run_batch(Lds &L, const uint8_t *codes, const fl
             if (m < M && row < N)
                 ((FQ_GLOBAL uint16_t *)y)[(size_t)m * N + row] = __builtin_bit_cast(uint16_t, (_Float16)v);
         }
+    };
+    const int blocks = nt * MB;
+    if (keep_x) {
+#pragma unroll
+        for (int t = 0; t < NB * MB; t += 2) {
+            if (t >= blocks)
+                break;
+            __syncthreads();
+            leave(L.red, t, 0);
+            leave(L.red, t + 1, 1);
+            __syncthreads();
+            add_up(L.red, t, min(t + 2, blocks));
+        }
+    } else {
+        float4_t *red = reinterpret_cast<float4_t *>(L.x);
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < NB * MB; u++)
+            if (u < blocks)
+                leave(red, u, u);
+        __syncthreads();
+        add_up(red, 0, blocks);
     }
 }
 
