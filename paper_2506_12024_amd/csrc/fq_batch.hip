@@ -201,6 +201,8 @@ __device__ __forceinline__ void run_batch(Lds &L, const uint8_t *codes, const fl
             };
             if (nt * 16 <= THREADS / GP)
                 fetch(std::integral_constant<int, 1>{});
+            else if (ML > 3 && nt * 16 <= 3 * (THREADS / GP))
+                fetch(std::integral_constant<int, 3>{});
             else
                 fetch(std::integral_constant<int, ML>{});
         }
