@@ -617,7 +617,9 @@ hipError_t fq_launch_quantize_act(const void *x, int M, int K, void *xq, float *
     const half8 *xp = (const half8 *)x;
     int8_t *q = (int8_t *)xq;
     const unsigned grid = ((unsigned)M + 7) / 8 * 8;
-    if (K <= 4096) // 256 threads x 2 vectors x 8 inputs
+    if (K <= 2048) // 256 threads x 1 vector x 8 inputs
+        quantize_act_kernel<256, 1><<<grid, 256, 0, stream>>>(xp, M, K, q, sx, xsum);
+    else if (K <= 4096)
         quantize_act_kernel<256, 2><<<grid, 256, 0, stream>>>(xp, M, K, q, sx, xsum);
     else if (K <= 8192)
         quantize_act_kernel<256, 4><<<grid, 256, 0, stream>>>(xp, M, K, q, sx, xsum);

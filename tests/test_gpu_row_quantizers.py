@@ -11,7 +11,7 @@ from gpu_util import DEV, to_dev
 
 pytestmark = pytest.mark.gpu
 
-LENGTHS = [128, 384, 4096, 4224, 8192, 8320, 16384, 16512, 32768, 32896]
+LENGTHS = [128, 384, 2048, 2176, 4096, 4224, 8192, 8320, 16384, 16512, 32768, 32896]
 
 
 @pytest.mark.parametrize("K", LENGTHS)
