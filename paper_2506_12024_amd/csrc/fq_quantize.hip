@@ -279,7 +279,9 @@ __global__ __launch_bounds__(T) void quantize_row8_kernel(const half8 *__restric
 template <bool SYM>
 void launch_row8(const half8 *w, int N, int K, uint8_t *codes, float *scales, uint8_t *zeros, hipStream_t stream)
 {
-    if (K <= 4096) // 256 threads x 2 vectors x 8 weights
+    if (K <= 2048) // 256 threads x 1 vector x 8 weights
+        quantize_row8_kernel<SYM, 256, 1><<<N, 256, 0, stream>>>(w, K, codes, scales, zeros);
+    else if (K <= 4096)
         quantize_row8_kernel<SYM, 256, 2><<<N, 256, 0, stream>>>(w, K, codes, scales, zeros);
     else if (K <= 8192)
         quantize_row8_kernel<SYM, 256, 4><<<N, 256, 0, stream>>>(w, K, codes, scales, zeros);
