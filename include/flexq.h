@@ -216,10 +216,12 @@ int fq_plan_destroy(fq_plan *plan);
  * independent of each other, and an entry may read (as x) what an entry of an EARLIER stage writes
  * (as y).  fq_plan_run runs all stages in order with ONE launch of a persistent kernel.  Between two
  * stages stands a grid-wide barrier -- or, where every x of a stage lies in the y of one entry of the
- * stage before it, no two ys of the plan overlap and every x lies in one y of an earlier stage or meets
- * none, each workgroup waits for the rows it reads (such a y is filled with NaNs when the launch begins).
- * The first weights of the next stage are already being fetched while it is crossed.  Results are bit-identical to the same stages run as separate stage-ordered
- * plans (against fq_plan_create's kernel a row may be summed in a different order).
+ * stage before it (one that no bit-widths of its stage give a workgroup more than 4096 rows of), no two
+ * ys of the plan overlap and every x lies in one y of an earlier stage or meets none, each workgroup
+ * waits for the rows it reads (such a y is filled with NaNs when the launch begins).  The first weights
+ * of the next stage are already being fetched while it is crossed.  Results are bit-identical to the
+ * same stages run as separate stage-ordered plans (against fq_plan_create's kernel a row may be summed
+ * in a different order).
  *   stage      HOST, int32 [count]: stage[0] = 0, never decreasing, rising by at most 1;
  *              at most FQ_MAX_STAGE_ENTRIES entries per stage
  *   workspace  device, fq_plan_staged_workspace_bytes(count, number of stages) bytes, 256-byte

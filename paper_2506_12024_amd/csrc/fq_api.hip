@@ -571,24 +571,28 @@ int fq_plan_create_staged(fq_plan **out, int count, const fq_layer *const *layer
             if (stage[a] <= stage[b] && xs[a] == ys[b])
                 return fail(FQ_ERR_SHAPE, "fq_plan_create_staged: x of entry %d (stage %d) is y of entry %d (stage %d)",
                             a, stage[a], b, stage[b]);
+    const size_t lds = fq_staged_lds_bytes(n_stages, geom.max_K, STAGED_RES_CHUNKS);
+    if (lds > 160 * 1024)
+        return fail(FQ_ERR_SHAPE, "fq_plan_create_staged: %d stages with rows of up to %d inputs need %zu bytes of "
+                                  "LDS (160 KiB at most)", n_stages, geom.max_K, lds);
+    const int grid = fq_staged_grid(lds);
+    if (grid < 1)
+        return fail(FQ_ERR_HIP, "fq_plan_create_staged: the stage-ordered kernel does not fit this device");
     std::vector<uintptr_t> xa, ya;
-    std::vector<int> Ks, Ns;
+    std::vector<int> Ks, Ns, widths;
     std::vector<int32_t> src((size_t)count);
     for (const FqLinearDesc &d : table) {
         xa.push_back(reinterpret_cast<uintptr_t>(d.x));
         ya.push_back(reinterpret_cast<uintptr_t>(d.y));
         Ks.push_back(d.K);
         Ns.push_back(d.N);
+        widths.push_back((d.codes2 != nullptr) | (d.codes3 != nullptr) << 1 | (d.codes4 != nullptr) << 2 |
+                         (d.codes8 != nullptr) << 3 | (d.w16 != nullptr) << 4);
     }
-    staged_sources(count, xa.data(), ya.data(), Ks.data(), Ns.data(), stage, begin.data(), n_stages, src.data());
+    staged_sources(count, xa.data(), ya.data(), Ks.data(), Ns.data(), widths.data(), stage, begin.data(), n_stages, grid,
+                   STAGED_RES_CHUNKS, src.data());
     for (int i = 0; i < count; i++)
         table[i].src = src[i];
-    const size_t lds = fq_staged_lds_bytes(n_stages, geom.max_K, STAGED_RES_CHUNKS);
-    if (lds > 160 * 1024)
-        return fail(FQ_ERR_SHAPE, "fq_plan_create_staged: %d stages with rows of up to %d inputs need %zu bytes of "
-                                  "LDS (160 KiB at most)", n_stages, geom.max_K, lds);
-    if (fq_staged_grid(lds) < 1)
-        return fail(FQ_ERR_HIP, "fq_plan_create_staged: the stage-ordered kernel does not fit this device");
     fq_plan *p = new (std::nothrow) fq_plan();
     if (!p)
         return fail(FQ_ERR_HIP, "fq_plan_create_staged: out of host memory");

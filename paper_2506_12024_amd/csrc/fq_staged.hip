@@ -61,6 +61,7 @@
 #include "fq_internal.h"
 #include "fq_gemv.h"
 #include "fq_mfma.h"
+#include "fq_staged_src.h"
 
 namespace {
 
@@ -92,20 +93,16 @@ constexpr int POLL_STAGE = 1024; // no grid barrier ahead of this stage (set for
 static_assert(sizeof(Share) == 64, "Share is read from LDS as four 16-byte pieces");
 static_assert(CW <= 15, "a wavefront's number fits four bits");
 
-// Relative cost of one row of one quantization group at each width (the one-launch kernel's table).
+// Relative cost of one row of one quantization group of an entry; 0: no such width, or no copy of it.
 __device__ __forceinline__ long long group_cost(const FqLinearDesc &d, int bits)
 {
-    if (bits == 2)
-        return d.codes2 ? 64 * 230 * 730 / 1000 : 0;
-    if (bits == 3)
-        return d.codes3 ? 64 * 230 * 950 / 1000 : 0;
-    if (bits == 4)
-        return d.codes4 ? 64 * 230 : 0;
-    if (bits == 8)
-        return d.codes8 ? 128 * 200 : 0;
-    if (bits == 16)
-        return d.w16 ? 256 * 200 : 0;
-    return 0;
+    const void *copy = bits == 2    ? (const void *)d.codes2
+                       : bits == 3  ? (const void *)d.codes3
+                       : bits == 4  ? (const void *)d.codes4
+                       : bits == 8  ? (const void *)d.codes8
+                       : bits == 16 ? (const void *)d.w16
+                                    : nullptr;
+    return copy ? staged_group_cost(bits) : 0;
 }
 
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }

@@ -1,12 +1,12 @@
 """Stage-ordered plans whose stages wait for the rows they read (no grid barrier), and plans that look like them but go
 through the barrier: chains through a part of a y, two stages back, through buffers used again, past an entry that has no
-copy at its bit-width, and rows that are NaNs.  Against the same stages as plans of their own, in turn: bit for bit."""
+copy at its bit-width, past rows that a launch refuses, and rows that are NaNs.  Against the same stages as plans of their own, in turn: bit for bit."""
 import pytest
 import torch
 
 import synth
 import paper_2506_12024_amd as fq
-from gpu_util import DEV, make_layer, to_dev
+from gpu_util import DEV, gpu_quantize, make_layer, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -82,3 +82,31 @@ def test_chains_match_their_stages_one_by_one(name):
         assert plan.status()[0] == 0
     if name == "nan":
         assert ys[1].isnan().any()
+
+
+def test_rows_of_a_share_that_is_refused_are_not_waited_for():
+    # 40000 short rows beside 1500 long ones: a workgroup would be dealt more of the short ones than it holds results
+    # for, so they keep what they held, a 0xFFFF half in every one of them among the rest; their reader goes on all the same
+    def layer(N, K, bits):
+        w = torch.randn(N, K, dtype=torch.float16, device=DEV) * K ** -0.5
+        return fq.Layer(N, K).attach(bits, *((w,) if bits == 16 else gpu_quantize(w, bits)))
+
+    torch.manual_seed(3)
+    shapes, bits, stage = [(128, 128), (40000, 128), (1500, 32768), (256, 1024)], [4, 4, 16, 8], [0, 1, 1, 2]
+    layers = [layer(N, K, b) for (N, K), b in zip(shapes, bits)]
+    ys = [torch.zeros(1, N, dtype=torch.float16, device=DEV) for N, _ in shapes]
+    xs = [torch.randn(1, K, dtype=torch.float16, device=DEV) for _, K in shapes[:3]] + [ys[1][:, :1024]]
+    plan = _plan(layers, xs, ys, stage)
+    plan.set_wait_limit(1 << 16)
+    bits_dev = torch.tensor(bits, dtype=torch.int32, device=DEV)
+    ys[1].view(torch.int16).fill_(-1)
+    plan.run(bits_dev)
+    torch.cuda.synchronize()
+    assert plan.status() == (0, 2)
+    assert (ys[1].view(torch.int16) == -1).all() and ys[3].isnan().all()
+    ys[1].copy_(torch.randn(1, 40000, dtype=torch.float16, device=DEV))
+    held, ref = ys[1].clone(), torch.zeros_like(ys[3])
+    plan.run(bits_dev)
+    _plan([layers[3]], [xs[3]], [ref], [0]).run(bits_dev[3:])
+    torch.cuda.synchronize()
+    assert plan.status() == (0, 2) and torch.equal(ys[1], held) and torch.equal(ys[3], ref)
