@@ -233,7 +233,7 @@ int fq_plan_destroy(fq_plan *plan);
  * The kernel's workgroups wait for each other, so the launch needs the device to itself: while
  * another kernel holds compute units the waits may run out.  A wait is bounded (about a second
  * by default, fq_plan_set_wait_limit sets the number of polls): a launch that gives up leaves y
- * incomplete, every workgroup still exits, the barrier's counters are put back, and the next
+ * incomplete (rows that others were to wait for as NaNs), every workgroup still exits, the barrier's counters are put back, and the next
  * launch starts clean.  fq_plan_status (for either kind of plan) waits for `stream` and reports
  *   gave_up  launches of this plan that gave up so far (never reset)
  *   flags    bit 0: an entry's bit-width was not 2, 3, 4, 8 or 16 or had no copy attached (its y was

@@ -39,7 +39,9 @@
 //
 // Either wait is bounded: a wavefront that has polled `wait_limit` times raises the abort flag and, if it is the first,
 // adds one to a sticky count; every waiter looks at the flag and every workgroup leaves the
-// kernel.  The last workgroup out (one more counter) puts the counters and the flag back to zero,
+// kernel, all of it ahead of one stage: what a wavefront that gives up leaves in LDS is the stage it was to enter (as a plain
+// flag it could be read by the service wavefront still in the stage before, which then counted its workgroup out
+// while the others were waiting yet, to raise the abort flag behind its being put back).  The last workgroup out (one more counter) puts the counters and the flag back to zero,
 // so that the next launch, and a replayed HIP graph, find them clean.  All workgroups must be
 // resident together (the host launches at most as many as fit).
 //
@@ -255,8 +257,10 @@ static_assert((SY_COUNTERS + NC * CSTRIDE) * 4 <= FQ_STAGED_SYNC_BYTES, "the syn
 struct Wait {
     int *sync;
     long long limit;
-    int *aborted; // LDS: the workgroup leaves at its next barrier
+    int *leave; // LDS: the stage ahead of which the workgroup leaves the kernel
+    int stage;  // the one whose x is waited for
 };
+constexpr int NEVER = 0x7fffffff;
 
 // A half that no finished row holds: what a polled y is filled with when a launch begins.  (A NaN whose bits are
 // all ones is stored as another NaN.)
@@ -316,7 +320,7 @@ __device__ __forceinline__ bool give_up(const Wait &w, long long round)
                      : "=&v"(up) : "v"(zero), "s"(w.sync), "n"(SY_ABORT * 4) : "memory");
     }
     if (uni(up)) {
-        *w.aborted = 1;
+        *w.leave = w.stage;
         return true;
     }
     return false;
@@ -561,7 +565,7 @@ __device__ __forceinline__ bool cross(const ShareReg &sh, int s, int *flags, uin
     if (s > 0) {
         if (!sh.has(POLL_STAGE)) {
             wg_barrier(); // every workgroup has arrived (or the abort flag is up)
-            if (uni(flags[0]))
+            if (uni(flags[0]) <= s)
                 return false;
         }
         wait_rows(&flags[1], s - 1); // nobody reads the present x any more
@@ -569,7 +573,7 @@ __device__ __forceinline__ bool cross(const ShareReg &sh, int s, int *flags, uin
     if constexpr (BITS != 0)
         stage_x_all<BITS>(sh.x(), sh.K(), xbuf, sh.has(POLL_X), w);
     wg_barrier(); // x of stage s is in LDS
-    return uni(flags[0]) == 0;
+    return uni(flags[0]) > s;
 }
 
 // One stage of a compute wavefront (BITS = 0: no share of it).
@@ -665,7 +669,7 @@ __global__ __launch_bounds__(THREADS) void decode_staged_kernel(const FqLinearDe
     const int PK = res_chunks / CW + 2; // chunks one wavefront can have a hand in per stage
     Share *shares = reinterpret_cast<Share *>(lds);                  // [n_stages]
     float *part = reinterpret_cast<float *>(lds + 4 * n_stages);     // [CW][PK][4] partial rows
-    int *flags = reinterpret_cast<int *>(lds + 4 * n_stages + CW * PK); // [0]: abort; [1]: rows left in LDS, by compute wavefronts and stages
+    int *flags = reinterpret_cast<int *>(lds + 4 * n_stages + CW * PK); // [0]: the stage ahead of which to leave; [1]: rows left in LDS, by compute wavefronts and stages
     uint4 *xbuf = lds + 4 * n_stages + CW * PK + 4;
     const int wave = uni(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int G = gridDim.x, b = blockIdx.x;
@@ -734,15 +738,17 @@ __global__ __launch_bounds__(THREADS) void decode_staged_kernel(const FqLinearDe
             sh.mode |= POLL_STAGE;
         shares[s] = sh;
     }
-    if (threadIdx.x == 0)
-        flags[0] = flags[1] = 0;
+    if (threadIdx.x == 0) {
+        flags[0] = NEVER;
+        flags[1] = 0;
+    }
     if (unattached && b == 0)
         __hip_atomic_fetch_or(&sync[SY_FLAGS], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (too_large)
         __hip_atomic_fetch_or(&sync[SY_FLAGS], 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
 
-    const Wait w = {sync, wait_limit, flags};
+    Wait w = {sync, wait_limit, flags, 0};
 
     if (wave == CW) {
         // ---- service wavefront ------------------------------------------------------------
@@ -768,15 +774,16 @@ __global__ __launch_bounds__(THREADS) void decode_staged_kernel(const FqLinearDe
                 const bool aborted = !wait_stage(sync, met, G, wait_limit);
                 met++;
                 if (aborted && lane == 0)
-                    flags[0] = 1;
+                    flags[0] = s + 1;
                 wg_barrier(); // every workgroup has arrived (or the abort flag is up)
                 if (aborted)
                     break;
             }
+            w.stage = s + 1;
             stage_share_x(sh, xbuf, w); // with the compute wavefronts
             __builtin_amdgcn_s_waitcnt(0xc07f);
             wg_barrier(); // x of stage s + 1 is in LDS
-            if (uni(flags[0]))
+            if (uni(flags[0]) <= s + 1)
                 break;
         }
         // last workgroup out puts the counters back
@@ -798,6 +805,7 @@ __global__ __launch_bounds__(THREADS) void decode_staged_kernel(const FqLinearDe
         const ShareReg sh = next;
         next = ShareReg(&shares[min(s + 1, n_stages - 1)]);
         const int bits = sh.bits();
+        w.stage = s;
         const bool go = bits == 2    ? run_stage<2>(sh, s, wave, part, PK, flags, xbuf, w)
                         : bits == 3  ? run_stage<3>(sh, s, wave, part, PK, flags, xbuf, w)
                         : bits == 4  ? run_stage<4>(sh, s, wave, part, PK, flags, xbuf, w)

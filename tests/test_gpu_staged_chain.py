@@ -1,6 +1,7 @@
 """Stage-ordered plans whose stages wait for the rows they read (no grid barrier), and plans that look like them but go
 through the barrier: chains through a part of a y, two stages back, through buffers used again, past an entry that has no
-copy at its bit-width, past rows that a launch refuses, and rows that are NaNs.  Against the same stages as plans of their own, in turn: bit for bit."""
+copy at its bit-width, past rows that a launch refuses, rows that are NaNs, and rows that never
+come.  Against the same stages as plans of their own, in turn: bit for bit."""
 import pytest
 import torch
 
@@ -110,3 +111,40 @@ def test_rows_of_a_share_that_is_refused_are_not_waited_for():
     _plan([layers[3]], [xs[3]], [ref], [0]).run(bits_dev[3:])
     torch.cuda.synchronize()
     assert plan.status() == (0, 2) and torch.equal(ys[1], held) and torch.equal(ys[3], ref)
+
+
+def test_a_wait_for_rows_that_runs_out_returns_and_the_next_launch_is_whole():
+    # Forced from the host: in the plan's table the third linear's x, which the kernel waits for, is put to a buffer that nobody
+    # writes.  Every launch gives up there, and not at a barrier; with the x put back the plan is whole.
+    shapes, stage = [(1024, 1024), (1152, 1024), (1024, 1024), (512, 1024)], [0, 1, 2, 3]
+    layers = [_layer("gu%d" % i, N, K, (8,)) for i, (N, K) in enumerate(shapes)]
+    ys = [torch.zeros(1, N, dtype=torch.float16, device=DEV) for N, _ in shapes]
+    xs = [to_dev(synth.activations(21, "stgc/gu", 1, 1024)), ys[0], ys[1][:, 16:1040], ys[2]]
+    ws = torch.zeros(fq.StagedPlan.workspace_bytes(4, 4), dtype=torch.uint8, device=DEV)
+    plan = fq.StagedPlan(layers, xs, ys, stage, 1, ws)
+    words = ws.view(torch.int64)
+    at = (words == xs[2].data_ptr()).nonzero().flatten().tolist()
+    assert len(at) == 1
+    never = torch.full((1, 1024), -1, dtype=torch.int16, device=DEV)
+    words[at[0]] = never.data_ptr()
+    bits = torch.full((4,), 8, dtype=torch.int32, device=DEV)
+    plan.set_wait_limit(1 << 12)
+    for n in range(3):
+        ys[3].fill_(7)
+        plan.run(bits)
+        torch.cuda.synchronize()
+        assert plan.status() == (n + 1, 0)
+        assert ys[0].isfinite().all() and ys[1].isfinite().all()
+        assert (ys[2].view(torch.int16) == -1).all() and (ys[3] == 7).all()
+    words[at[0]] = xs[2].data_ptr()
+    plan.set_wait_limit(1 << 21)
+    refs = [torch.zeros_like(y) for y in ys]
+    for i in range(4):
+        x = xs[0] if i == 0 else refs[i - 1][:, 16:1040] if i == 2 else refs[i - 1]
+        _plan([layers[i]], [x], [refs[i]], [0]).run(bits[:1])
+    for _ in range(2):
+        plan.run(bits)
+        torch.cuda.synchronize()
+        assert plan.status() == (3, 0)
+        for y, r in zip(ys, refs):
+            assert torch.equal(y.view(torch.int16), r.view(torch.int16))

@@ -1,6 +1,7 @@
 """A thread-per-workgroup model of the stage-ordered kernel's barrier protocol (CPU only).
 
-The kernel (csrc/fq_staged.hip) separates two stages by a grid-wide barrier built from plain
+Where a stage does not wait for the rows it reads (that boundary, and the two together wavefront by wavefront:
+test_staged_polled_model.py), the kernel (csrc/fq_staged.hip) puts a grid-wide barrier ahead of it, built from plain
 device-scope atomics: 128 arrival counters that count up through the launch (workgroup b adds to
 counter b % 128; after stage s counter l must hold (s + 1) * |{b : b % 128 = l}|), an abort flag, a
 sticky count of launches that gave up, and a count of finished workgroups whose last arrival puts
