@@ -16,20 +16,22 @@
 // registers: lane (n, c) takes 16 bytes of each half line of row n, the operand layout of v_mfma_f32_16x16x32_f16 up to a permutation of the inputs that x
 // shares, RD lines ahead.
 //
-// Measured (us at 16 batch rows, 4 / 8 / 16 bits, cold weights; before: the register-fed kernel with K split between four
-// wavefronts below 8192 rows and 64-row tiles above): 4096 x 4096 9.1 / 11.3 / 14.0 -> 8.5 / 9.8 / 11.9; 11008 rows x 4096
-// 17.2 / 26.0 / 36.1 -> 11.8 / 15.3 / 21.5; 4096 rows x 11008 17.7 / 23.9 / 30.7 -> 14.9 / 19.4 / 26.3; 22016 rows x 4096
-// 23.8 / 34.8 / 46.9 -> 17.1 / 24.6 / 40.4; where the register-fed kernel is the faster one: fq_batch_serves below.  What was found on the way: requests past a run's end must cost nothing (as
-// re-reads of the last line, 8 ahead, they made 4096 x 4096 cost 12 us: the loads' line accesses, not HBM, were the
-// limit) -- they ask beyond the buffer's end; two lines ahead are as fast as eight (19.6 against 23.8 us at 22016 rows);
-// sixteen wavefronts the same as eight; without the arithmetic 16.6 instead of 19.3 us, without x 1.1 us less.  Then, by time stamps
-// (one 4096 x 4096 entry, 4 bits, 9.1 us of which 1.3 between launches): 0.9 for the table, 0.9 for the division, up to six trips
-// to memory for the scales, one barrier pair per two tiles of sums.  With the scales requested together, the sums in one
-// round, x requested ahead of the table's arrival where the host knows it and integer divisions out of the way, plans at 16
-// batch rows: 2 x 11008 x 4096 at 4 / 8 / 16 bits 19.5 / 25.0 / 39.2 -> 16.6 / 22.8 / 38.8, 3 x 4096 x 4096 12.9 / 16.7 / 23.6 -> 12.4 /
-// 16.1 / 23.2, 4096 x 4096 8.2 / 9.7 / 11.8 -> 7.8 / 9.2 / 10.4, 4096 x 11008 15.0 / 19.6 / 26.9 -> 14.9 / 19.6 / 26.1; the 7B-shaped layers
-// at 4 and 8 bits 544 -> 512 us for 32 launches.  What bounds it now: launch, table and first request 4 us, instructions
-// (137 vector ones per 4-bit line of 16 rows, 11 lines a wavefront at 22016 rows), three panels one after the other at K = 11008.
+// Measured (us a plan launch at 4 / 8 / 16 bits, cold weights; in brackets the register-fed kernel): 16 batch rows, 4096 x 4096
+// 7.3 / 9.3 / 10.7 (9.1 / 11.3 / 14.0), 3 x 4096 x 4096 12.2 / 16.0 / 23.3, 4096 rows x 11008 14.3 / 19.5 / 26.3 (17.7 / 23.9 / 30.7),
+// 2 x 11008 x 4096 16.8 / 23.3 / 39.0 (23.8 / 34.8 / 46.9); 32 batch rows 9.7 / 12.2 / 13.4, 19.5 / 24.5 / 31.7, 21.1 / 27.3 / 33.0,
+// 22.4 / 29.0 / 42.2; the 7B-shaped layers at 16 rows, 4 and 8 bits, 512 for 32 launches.  Where the register-fed kernel is the faster
+// one: fq_batch_serves below.  Why it is as it is:
+//   - requests past a run's end ask beyond the buffer's end: as re-reads of the last line, 8 ahead, they made 4096 x 4096 cost
+//     12 us (the loads' line accesses, not HBM, were the limit);
+//   - two lines ahead are as fast as eight (19.6 against 23.8 us at 22016 rows), sixteen wavefronts the same as eight;
+//   - scales and zero points of a run are requested together (a loop that stored each before it asked for the next made up to
+//     six trips to memory), but no more of them than the run has tiles: six tiles' for every run cost runs of one 0.3 us a panel;
+//   - the sums meet in one round (six tiles 1.0 us, two blocks at a time 1.9), the two at a time of a run that keeps x in rounds
+//     fixed at compile time (as a run-time choice, plans of many short runs took up to 1.14 times as long);
+//   - an x that all entries read is requested ahead of the table, and nothing where there is none (out of range it cost 1 us);
+//   - the division has no integer divisions: they were half of the 0.9 us between table and first request.
+// What bounds it: launch, table and first request 4 us of a launch, instructions (137 vector ones per 4-bit line of 16 rows, 11 lines a
+// wavefront at 22016 rows), three panels one after the other at K = 11008.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <type_traits>
@@ -541,7 +543,9 @@ hipError_t fq_launch_batch(const FqLinearDesc *single, int bits_host, const FqLi
     const int cus = fq_device_cus();
     const unsigned grid = (unsigned)(tiles < cus ? tiles : cus);
     const uint32_t step = batch_step(grid);
-    if (K0 < 2048) // (the request ahead is of a whole panel)
+    // The request ahead is of a whole panel.  Times with it over those without: 128 inputs 1.11 to 1.15, 512 1.03 to 1.12, 1024 0.96 (above
+    // 16 rows) to 1.10 (plans), 1920 0.90 to 0.98 for single calls, 0.94 to 1.04 for plans.
+    if (K0 < 2048)
         x0 = nullptr;
     FqLinearDesc none = {};
     if (single) {

@@ -11,8 +11,9 @@
 // multiplied (v_dot2_f32_f16) against the matching x blocks, which sit in LDS for the whole
 // kernel ([j][m][lane], conflict free).  The steps run on from one four rows to the next: begun anew for every four
 // rows, with one step in flight and the sums through LDS, short rows and several rows of x waited for memory most (us;
-// before and now: 4 x 8192 -> 32000 123 and 109, 1 x 1024 -> 32000 19.5 and 16.7, 2 x 2048 -> 9001 18.7 and 16.4; 1 x 4096 ->
-// 32000 46.7 and 46.1, -> 128256 158.7 and 158.4, where it is HBM: 6.4 TB/s and the second launch).  With 2 and 3 steps the
+// before and now: 4 x 8192 -> 32000 123 and 109, 1 x 1024 -> 32000 19.9 and 16.8, 2 x 2048 -> 9001 19.2 and 18.1; 1 x 4096 ->
+// 32000 47.5 and 46.8, -> 128256 163 and 162, where it is HBM: 6.4 TB/s and the second launch; against it 1 x 512 -> 9001 10.0 and 11.0,
+// where most that is in flight lies past the last block: leaving the loop there instead makes 1 x 4096 -> 1000 1.09 times as long).  With 2 and 3 steps the
 // last but one takes 1.6 and 0.6 more; with one, three, four workgroups per compute unit instead of two 0, 1.4 and 2.2 more;
 // with the requests past a wavefront's last block repeating its last steps instead of one line of x 0.6 more.  The four sums are reduced across the wavefront and
 // handed to lanes 0 .. 3, each of which keeps an online softmax state per row of x: running

@@ -201,8 +201,8 @@ __global__ __launch_bounds__(256) void fake_quantize_kernel(const half8 *w, long
 // meets 8-bit activations on the integer matrix cores without a fold per group (Sec. 4.1, 4.3).  Eq. (2)
 // as above with Xmin / Xmax taken over the whole row.  One workgroup of T threads per row, which a thread's NV vectors of
 // 8 weights hold in registers, requested together and read once (two walks over it in a loop waited for memory a dozen times in
-// turn: 8192 x 28672 182 -> 123 us = 5.7 TB/s, 5120 x 13824 58 -> 40, 11008 x 4096 30 -> 25); NV = 0: rows beyond 32768 weights, in
-// that loop.
+// turn: 8192 x 28672 182 -> 123 us = 5.7 TB/s, 5120 x 13824 58 -> 40, 11008 x 4096 30 -> 25, and where one vector a thread is the
+// whole row 11008 x 512 12.4 -> 11.9: as two it was 13.5); NV = 0: rows beyond 32768 weights, in that loop.
 template <bool SYM, int T, int NV>
 __global__ __launch_bounds__(T) void quantize_row8_kernel(const half8 *__restrict__ w, int K, uint8_t *__restrict__ codes,
                                                           float *__restrict__ scales, uint8_t *__restrict__ zeros)

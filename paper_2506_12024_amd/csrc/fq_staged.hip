@@ -45,12 +45,12 @@
 // so that the next launch, and a replayed HIP graph, find them clean.  All workgroups must be
 // resident together (the host launches at most as many as fit).
 //
-// Measured (7B-shaped stack in a chain, us per step, bits from {4, 8} / all 4 / all 8): 1488 / 1273 / 1685 with the grid
-// barrier at every stage and the weights requested three items ahead through all stages -> 1344 / - / - with x polled, rows
-// announced ahead of the next request and the places of their sums worked out in advance -> 1161 / 975 / 1348 with the
-// requests of a stage held back until the one before is done: requested as items were consumed, all of a stage's bytes had
-// to be asked for in its compute part (6.1 us at memory speed) and none while the boundary was crossed (4).  Without the
-// arithmetic (results invalid) 1076 / 848 / 1292; the bytes alone take 762 at the best read rate.  A stage of 9.1 us: 4.9
+// Measured (7B-shaped stack in a chain, us per step, bits from {4, 8} / all 4 / all 8): 1170 / 975 / 1348; with the grid barrier at
+// every stage 1310 / 1117 / 1501.  The bytes alone take 762 at the best read rate.  x polled, rows announced
+// ahead of the next request and the places of their sums worked out in advance are worth a tenth (1488 -> 1344 at {4, 8} when
+// requests ran on through the stages), the requests of a stage held back until the one before is done another (1344 -> 1161 in that
+// run): requested as items were consumed, all of a stage's bytes had to be asked for in its compute part (6.1 us at memory speed) and
+// none while the boundary was crossed (4).  Without the arithmetic (results invalid) 1076 / 848 / 1292.  A stage of 9.1 us: 4.9
 // until the last wavefront is done (mean 4.1), 3.3 from the last workgroup's last row to the next x in LDS, the rest spread.
 //
 // Arithmetic: the item code of the one-launch kernel (fq_gemv.h).  A row whose slices are shared
@@ -165,8 +165,12 @@ struct Item {
 // shared by neighbouring wavefronts (a stage often gives a workgroup fewer chunks than it has wavefronts).  The share is
 // read through buffer descriptors that end with it: a request past the run, or past the matrix's last row, asks beyond
 // the descriptor's end and costs no access, so that every step issues the same loads and the compiler's count of the loads
-// in flight holds.  A share is at most 4096 rows of 114688 bytes, far below BEYOND.  Uniform over the wavefront.
-constexpr uint32_t BEYOND = 0xF0000000u; // an offset (with what is added to it) past every descriptor's end
+// in flight holds.  Uniform over the wavefront.
+constexpr uint32_t BEYOND = 0xF0000000u; // an offset past every descriptor's end, and not past 2^32 with what is added to it
+static_assert(FQ_STAGED_CHUNKS * 4ull * FQ_MAX_DECODE_K * 2 < BEYOND && BEYOND + 5ull * FQ_MAX_DECODE_K * 2 < 1ull << 32,
+              "a share at 16 bits is below BEYOND, a row's offset beside it in range");
+constexpr int MAX_SLICES = FQ_MAX_DECODE_K / (64 * 8); // of K in a row: 64 at 16 bits, fewer at the others
+static_assert((long long)FQ_STAGED_CHUNKS * MAX_SLICES * (CW + 1) < 1 << 30, "a share's items times wavefronts are an int");
 template <int BITS>
 struct Run {
     __amdgpu_buffer_rsrc_t codes, scales, zeros;
@@ -452,7 +456,7 @@ __device__ __forceinline__ void plan_rows(const ShareReg &sh, int PK, Rows &R)
     R.y = sh.y() + c0 * ROWS_PER_WAVE;
     R.rows = min(c1 * ROWS_PER_WAVE, sh.N()) - c0 * ROWS_PER_WAVE;
     R.nslice = (sh.K() + slice_span(bits) - 1) / slice_span(bits);
-    R.n = (c1 - c0) * R.nslice; // (at most 1024 chunks x 112 slices)
+    R.n = (c1 - c0) * R.nslice; // (at most FQ_STAGED_CHUNKS x MAX_SLICES)
 #pragma unroll
     for (int u = 0; u < 2; u++)
         R.first[u] = row_first(min(64 * u + (int)(threadIdx.x & 63), R.rows - 1), R.n, R.nslice, PK, R.more[u]);
@@ -596,7 +600,7 @@ __device__ __forceinline__ bool run_stage(const ShareReg &sh, int s, int wave, f
     } else {
         const int K = sh.K(), c0 = sh.c0(), c1 = sh.c1();
         const int nslice = (K + slice_span(BITS) - 1) / slice_span(BITS);
-        const int n = (c1 - c0) * nslice; // (at most 1024 chunks x 64 slices x CW: no overflow)
+        const int n = (c1 - c0) * nslice; // (at most FQ_STAGED_CHUNKS x MAX_SLICES)
         const int i0 = n * wave / CW, i1 = n * (wave + 1) / CW, first = sh.over_slices(i0);
         const Run<BITS> run(sh, min(c1 * ROWS_PER_WAVE, sh.N()) - c0 * ROWS_PER_WAVE, nslice, i1);
         // the next item to request and the next to compute: number, chunk and slice
