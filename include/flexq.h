@@ -313,11 +313,13 @@ int fq_linear_w8a8(const fq_layer *layer, const void *xq, const float *sx, const
  * inputs.  -inf entries carry no mass; +inf and NaN are unspecified.
  *   logits_p, logits_q  device, f32 [R][V]     (read)
  *   entropy_out, kl_out device, f32 [R]        (written)
- * R >= 0 (R = 0 launches nothing), V >= 1.  Calls with R <= 64 combine per-row
+ * R >= 0 (R = 0 launches nothing), V >= 1.  Calls with R <= 64 and V > 4096 combine per-row
  * partials in a small device-resident scratch of the library, of which every stream
  * gets a copy of its own (FQ_SCRATCH_BANKS per device; further streams take a slower path that
  * needs none): such calls may overlap on different streams.  A launch captured into a
- * graph keeps the copy of the stream it was captured on.
+ * graph keeps the copy of the stream it was captured on.  Calls with 65 to 512 rows and V > 10240 do the
+ * same in copies of the first 8 streams that make them; on other streams, on hipStreamPerThread and
+ * under capture they need none.
  */
 int fq_entropy_kl(const float *logits_p, const float *logits_q, int R, int V,
                   float *entropy_out, float *kl_out, void *stream);

@@ -30,6 +30,8 @@ struct DeviceFacts {
     size_t raised_to[MAX_KERNEL_FACTS];
     int n_banks;
     hipStream_t bank_stream[FQ_BANKS]; // the stream that bank i of the static scratch arrays belongs to
+    int n_rows_banks;
+    hipStream_t rows_stream[FQ_ROWS_BANKS]; // the same for the entropies of 65 to 512 rows
     int n_part_banks;
     hipStream_t part_stream[FQ_PART_BANKS]; // the same for the partial sums of products split along K
 };
@@ -101,6 +103,22 @@ int fq_stream_bank(hipStream_t stream)
     std::lock_guard<std::mutex> hold(g_lock);
     DeviceFacts *d = current();
     return d ? bank_of(d->bank_stream, d->n_banks, FQ_BANKS, stream) : -1;
+}
+
+int fq_rows_bank(hipStream_t stream)
+{
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (stream == hipStreamPerThread)
+        return -1;
+    if (hipStreamIsCapturing(stream, &capture) != hipSuccess) {
+        (void)hipGetLastError(); // (the null stream while a blocking stream is captured: only the question fails)
+        return -1;
+    }
+    if (capture != hipStreamCaptureStatusNone)
+        return -1;
+    std::lock_guard<std::mutex> hold(g_lock);
+    DeviceFacts *d = current();
+    return d ? bank_of(d->rows_stream, d->n_rows_banks, FQ_ROWS_BANKS, stream) : -1;
 }
 
 int fq_part_bank(hipStream_t stream, int *device)

@@ -64,6 +64,11 @@ hipError_t fq_raise_dynamic_lds(const void *func, size_t bytes);
 // current device (the first FQ_BANKS distinct streams get one each), or -1 if none is left.
 constexpr int FQ_BANKS = 16; // FQ_SCRATCH_BANKS of the public header
 int fq_stream_bank(hipStream_t stream);
+// The same for the entropies of 65 to 512 rows, which any number of streams may also ask for without a bank: the first
+// FQ_ROWS_BANKS streams; -1 also while the stream is captured (a graph may be replayed beside anything) and for
+// hipStreamPerThread, one handle for as many streams as there are threads.
+constexpr int FQ_ROWS_BANKS = 8;
+int fq_rows_bank(hipStream_t stream);
 // The same for the partial sums of products split along K, whose copies are larger and fewer; -1 also for
 // hipStreamPerThread, one handle for as many streams as there are threads.
 constexpr int FQ_PART_BANKS = 4;

@@ -1,0 +1,85 @@
+"""Entropy and KL at the sizes where rows change from whole workgroups to pieces that meet in scratch (64 | 65, 160 | 161,
+256 | 257, 350 | 351, 512 | 513 rows; 4096 | 4097, 10240 | 10241 and 65535 | 65536 entries) and where a lane's last round is partly
+empty, against the oracle; and calls of more rows than 64 that overlap on more streams than have scratch, and under capture."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+import paper_2506_12024_amd as fq
+from gpu_util import DEV, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _inputs(tag, R, V, half):
+    # a few distinct rows, repeated: what is tested does not depend on a row's neighbours
+    a, b = synth.logits_pair(5, "rows/%s" % tag, min(R, 7), V)
+    if half:
+        a, b = a.astype(np.float16), b.astype(np.float16)
+    H, KL = oracle.entropy_kl(a.astype(np.float32), b.astype(np.float32))
+    i = np.arange(R) % a.shape[0]
+    ti = torch.from_numpy(i).to(DEV)
+    return to_dev(a).index_select(0, ti), to_dev(b).index_select(0, ti), H[i], KL[i]
+
+
+def _close(got, ref):
+    # the bound the entry points are held to everywhere: 1e-4 of the value
+    return np.all(np.abs(got.cpu().numpy() - ref) <= 1e-4 * np.abs(ref) + 1e-7)
+
+
+@pytest.mark.parametrize("half", [False, True])
+@pytest.mark.parametrize("R,V", [(1, 4096), (65, 4097), (1, 10240), (65, 10240), (1, 10241), (3, 10244), (9, 32000), (21, 32001), (64, 32000), (65, 32000), (64, 65536),
+                                 (65, 65536), (160, 12291), (161, 12292), (256, 65535), (257, 65536), (350, 11264), (351, 11265),
+                                 (512, 10248), (513, 10248), (1, 3), (2, 1023), (5, 4097), (2, 33792)])
+def test_rows_and_pieces(R, V, half):
+    a, b, H_ref, KL_ref = _inputs("%d/%d" % (R, V), R, V, half)
+    H = torch.full((R,), float("nan"), device=DEV)
+    KL = torch.full((R,), float("nan"), device=DEV)
+    call = fq.fq_entropy_kl_f16 if half else fq.fq_entropy_kl
+    for _ in range(2):  # the second call finds the tickets as the first left them
+        call(a, b, R, V, H, KL)
+        assert _close(H, H_ref) and _close(KL, KL_ref)
+        H.fill_(float("nan"))
+        KL.fill_(float("nan"))
+    call(a, None, R, V, H, None)
+    assert _close(H, H_ref)
+
+
+def test_minus_infinity_carries_no_mass():
+    V = 32001
+    a, b = synth.logits_pair(5, "rows/inf", 2, V)
+    a[:, 7::3] = -np.inf
+    H_ref, KL_ref = oracle.entropy_kl(a, b)
+    H = torch.zeros(2, device=DEV)
+    KL = torch.zeros(2, device=DEV)
+    fq.fq_entropy_kl(to_dev(a), to_dev(b), 2, V, H, KL)
+    assert _close(H, H_ref) and _close(KL, KL_ref)
+
+
+def test_overlapping_streams_and_capture():
+    R, V, n = 100, 20000, 11  # more streams than have scratch for so many rows
+    sets = [_inputs("streams/%d" % s, R, V, False) for s in range(n)]
+    H = [torch.full((4, R), float("nan"), device=DEV) for _ in range(n)]
+    KL = [torch.full((4, R), float("nan"), device=DEV) for _ in range(n)]
+    streams = [torch.cuda.Stream() for _ in range(n)]
+    torch.cuda.synchronize()
+    for i in range(4):
+        for s in range(n):
+            fq.fq_entropy_kl(sets[s][0], sets[s][1], R, V, H[s][i], KL[s][i], stream=streams[s])
+    torch.cuda.synchronize()
+    for s in range(n):
+        for i in range(4):
+            assert _close(H[s][i], sets[s][2]) and _close(KL[s][i], sets[s][3]), (s, i)
+    Hg = torch.full((R,), float("nan"), device=DEV)
+    KLg = torch.full((R,), float("nan"), device=DEV)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        fq.fq_entropy_kl(sets[0][0], sets[0][1], R, V, Hg, KLg)
+    for _ in range(3):
+        Hg.fill_(float("nan"))
+        KLg.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert _close(Hg, sets[0][2]) and _close(KLg, sets[0][3])
