@@ -81,9 +81,11 @@ __device__ __forceinline__ void raise_max_a(Partial<FINE> &p, float cm)
         if (p.S > 0) {
             const float d = p.m - cm;
             const float c = EXPF(d);
-            p.U = c * (p.U + d * (float)p.S);
+            // (c = 0: nothing is left of what was summed.  Logits masked with the type's lowest value get here with d * S
+            // and D beyond binary32.)
+            p.U = c > 0.0f ? c * (p.U + d * (float)p.S) : 0.0f;
             p.S *= c;
-            p.D *= c;
+            p.D = c > 0.0f ? c * p.D : 0.0f;
         }
         p.m = cm;
     }
@@ -241,7 +243,7 @@ __global__ __launch_bounds__(THREADS) void entropy_kl_kernel(const T *__restrict
         const double c = (double)expf(d);
         S = c * (double)p.S;
         U = c * ((double)p.U + (double)d * (double)p.S);
-        D = c * (double)p.D;
+        D = c > 0.0 ? c * (double)p.D : 0.0;
     }
     if (HAS_B && p.Sb > 0)
         Sb = (double)expf(p.mb - gmb) * (double)p.Sb;
@@ -307,7 +309,7 @@ __global__ __launch_bounds__(THREADS) void entropy_kl_kernel(const T *__restrict
             const double c = (double)expf(d);
             U = c * (U + (double)d * S);
             S *= c;
-            D *= c;
+            D = c > 0.0 ? c * D : 0.0;
         }
         if (Sb > 0.0)
             Sb *= (double)expf((float)pmb - gmb);

@@ -47,15 +47,20 @@ def test_rows_and_pieces(R, V, half):
     assert _close(H, H_ref)
 
 
-def test_minus_infinity_carries_no_mass():
-    V = 32001
-    a, b = synth.logits_pair(5, "rows/inf", 2, V)
-    a[:, 7::3] = -np.inf
-    H_ref, KL_ref = oracle.entropy_kl(a, b)
-    H = torch.zeros(2, device=DEV)
-    KL = torch.zeros(2, device=DEV)
-    fq.fq_entropy_kl(to_dev(a), to_dev(b), 2, V, H, KL)
-    assert _close(H, H_ref) and _close(KL, KL_ref)
+@pytest.mark.parametrize("value", [-np.inf, np.finfo(np.float32).min])
+@pytest.mark.parametrize("R,V", [(2, 32001), (30, 32000), (3, 4096), (100, 32000), (520, 12000)])
+def test_masked_entries_carry_no_mass(R, V, value):
+    # every third entry, and the first half of the row: lanes that have seen nothing else when they meet their first logit
+    a, b, _, _ = _inputs("mask", R, V, False)
+    for t in (a, b):
+        t[:, 7::3] = float(value)
+        t[:, :V // 2] = float(value)
+    H_ref, KL_ref = oracle.entropy_kl(a[:7].cpu().numpy(), b[:7].cpu().numpy())
+    i = np.arange(R) % min(R, 7)
+    H = torch.zeros(R, device=DEV)
+    KL = torch.zeros(R, device=DEV)
+    fq.fq_entropy_kl(a, b, R, V, H, KL)
+    assert _close(H, H_ref[i]) and _close(KL, KL_ref[i])
 
 
 def test_overlapping_streams_and_capture():
