@@ -289,8 +289,8 @@ int fq_linear(const fq_layer *layer, int bits, const void *x_fp16, int M, void *
     fill_desc(d, layer, x_fp16, y_fp16);
     hipError_t e = hipSuccess;
     if (bits == 3 && (M > FQ_MAX_DECODE_M || layer->K > MAX_DECODE_K)) {
-        // The GEMM has no 3-bit unpacking: the small-batch kernel runs the call in slabs of
-        // FQ_MAX_DECODE_M batch rows (it walks K in chunks, whatever its length), reading the
+        // The GEMM has no 3-bit unpacking: the small-batch kernels run the call in slabs of
+        // FQ_MAX_DECODE_M batch rows (the register-fed one walks K in chunks, whatever its length), reading the
         // weights once per slab.
         const int rows = 128;
         const int tiles = (layer->N + rows - 1) / rows;
@@ -298,11 +298,15 @@ int fq_linear(const fq_layer *layer, int bits, const void *x_fp16, int M, void *
             const int m = M - m0 < FQ_MAX_DECODE_M ? M - m0 : FQ_MAX_DECODE_M;
             d.x = (const uint16_t *)x_fp16 + (size_t)m0 * layer->K;
             d.y = (uint16_t *)y_fp16 + (size_t)m0 * layer->N;
-            e = fq_launch_skinny(&d, bits, nullptr, nullptr, 1, tiles, rows, m, true, nullptr, nullptr, (hipStream_t)stream);
+            if (m > 1 && fq_batch_serves_slab(layer->N, layer->K, m) && layer->K <= MAX_DECODE_K)
+                e = fq_launch_batch(&d, bits, nullptr, nullptr, 1, (layer->N + 15) / 16, m, true, nullptr, d.x, d.K, (hipStream_t)stream);
+            else
+                e = fq_launch_skinny(&d, bits, nullptr, nullptr, 1, tiles, rows, m, true, nullptr, nullptr, (hipStream_t)stream);
         }
     } else if (M <= FQ_MAX_DECODE_M && layer->K <= MAX_DECODE_K) {
-        if (M > 1 && fq_batch_serves_linear(layer->N, layer->K, bits, M)) {
-            e = fq_launch_batch(&d, bits, nullptr, nullptr, 1, (layer->N + 15) / 16, M, nullptr, d.x, d.K, (hipStream_t)stream);
+        const bool narrow = bits == 2 || bits == 3;
+        if (M > 1 && (narrow ? fq_batch_serves_narrow(layer->N, layer->K, bits, M) : fq_batch_serves_linear(layer->N, layer->K, bits, M))) {
+            e = fq_launch_batch(&d, bits, nullptr, nullptr, 1, (layer->N + 15) / 16, M, narrow, nullptr, d.x, d.K, (hipStream_t)stream);
             if (e != hipSuccess)
                 return hip_fail(e, "fq_linear launch");
             return FQ_OK;
@@ -427,7 +431,7 @@ int fq_plan_layout(const char *who, int count, const fq_layer *const *layers, co
     // token, runs on the register-fed kernel
     if (M > 1 && has3 && rows == 256)
         rows = 128;
-    geom->batch = M > 1 && rows != 256 && !has2 && !has3 && fq_batch_serves(table, count, M) ? 1 : 0;
+    geom->batch = M > 1 && rows != 256 && fq_batch_serves(table, count, M) ? 1 : 0;
     if (geom->batch)
         rows = 16;
     long long tiles = 0;
@@ -448,6 +452,7 @@ int fq_plan_layout(const char *who, int count, const fq_layer *const *layers, co
     geom->max_K = max_K;
     geom->tile_rows = rows;
     geom->has3 = has3 ? 1 : 0;
+    geom->narrow = has2 || has3 ? 1 : 0;
     return FQ_OK;
 }
 
@@ -458,7 +463,7 @@ hipError_t fq_plan_launch(const FqPlanGeom &g, const FqLinearDesc *table_dev, in
                           const int32_t *bits_dev, hipStream_t stream)
 {
     if (g.batch)
-        return fq_launch_batch(nullptr, 0, table_dev, bits_dev, g.count, g.total_tiles, g.M, queue_dev ? queue_dev + FQ_Q_FLAGS : nullptr,
+        return fq_launch_batch(nullptr, 0, table_dev, bits_dev, g.count, g.total_tiles, g.M, g.narrow != 0, queue_dev ? queue_dev + FQ_Q_FLAGS : nullptr,
                                g.x_all, g.K_all, stream);
     hipError_t e = g.M == 1
         ? fq_launch_decode(nullptr, 0, table_dev, bits_dev, g.count, g.total_tiles, g.tile_rows, g.max_K, g.M,

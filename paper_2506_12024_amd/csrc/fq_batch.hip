@@ -1,5 +1,5 @@
 // Decode-phase weight-only quantized linear for small batches (2 <= M <= 32): single calls and plans of the
-// size a decoder's stages have (q/k/v, o, gate/up, down of one layer; up to 64 entries), 4, 8 and 16 bits; y[M][N] =
+// size a decoder's stages have (q/k/v, o, gate/up, down of one layer; up to 64 entries), 2, 3, 4, 8 and 16 bits; y[M][N] =
 // x[M][K] . dequant(W[N][K])^T, dequant = Sec. 2.2 Eq. (3).  Bound by the weight stream (Sec. 4.1) on paper; a launch of
 // 10 to 90 MB lasts 8 to 25 us, so that its start, its end and an even division count as much.
 //
@@ -29,6 +29,9 @@
 //   - the sums meet in one round (six tiles 1.0 us, two blocks at a time 1.9), the two at a time of a run that keeps x in rounds
 //     fixed at compile time (as a run-time choice, plans of many short runs took up to 1.14 times as long);
 //   - an x that all entries read is requested ahead of the table, and nothing where there is none (out of range it cost 1 us);
+//   - 2 and 3 bits, register-fed kernel before and this one now (us a plan launch, 16 batch rows, {2, 4, 8} resident, all at 2 bits):
+//     4096 x 4096 13.6 and 7.1, 3 x 4096 x 4096 14.3 and 11.8, 2 x 11008 x 4096 21.2 and 14.2, 4096 rows x 11008 33.9 and 13.2; {3, 4, 8}, all at 3: 9.2
+//     and 7.7, 18.7 and 13.1, 26.7 and 17.1, 19.2 and 15.2;
 //   - the division has no integer divisions: they were half of the 0.9 us between table and first request.
 // What bounds it: launch, table and first request 4 us of a launch, instructions (137 vector ones per 4-bit line of 16 rows, 11 lines a
 // wavefront at 22016 rows), three panels one after the other at K = 11008.
@@ -59,6 +62,91 @@ __device__ __forceinline__ uint32_t pk_add(uint32_t a, uint32_t b)
 {
     return __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, a) + __builtin_bit_cast(half2_t, b));
 }
+
+// What a request brings of a row: a lane's 32 codes of a group at 2, 3 and 4 bits, 16 bytes at 8 and 16.
+template <int BITS>
+__device__ __forceinline__ u32x4 load_piece(__amdgpu_buffer_rsrc_t buf, uint32_t at)
+{
+    if constexpr (BITS == 2) {
+        const u32x2 q = __builtin_amdgcn_raw_buffer_load_b64(buf, (int)at, 0, 0);
+        return u32x4{q.x, q.y, 0, 0};
+    } else if constexpr (BITS == 3) {
+        const auto q = __builtin_amdgcn_raw_buffer_load_b96(buf, (int)at, 0, 0);
+        return u32x4{(uint32_t)q[0], (uint32_t)q[1], (uint32_t)q[2], 0};
+    } else {
+        return __builtin_amdgcn_raw_buffer_load_b128(buf, (int)at, 0, 0);
+    }
+}
+
+// A lane's 32 codes of a group -> q - z as four operands of eight halves, in the order of the inputs.
+template <int BITS>
+struct Unpack : DeqMagic<BITS> {
+    __device__ __forceinline__ void group(const u32x4 &v, uint32_t z, uint32_t (&b)[4][4]) const
+    {
+        if constexpr (BITS == 4) {
+            const uint32_t nz = (z | 0xE400u) | (((z << 4) | 0xD400u) << 16); // -(1024 + z), -(64 + z)
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const uint32_t q = v[i];
+                b[i][0] = pk_add((__builtin_amdgcn_perm(0u, q, 0x0c000c00u) & this->m0) | this->e0, nz);
+                b[i][1] = pk_add((__builtin_amdgcn_perm(0u, q, 0x0c010c01u) & this->m0) | this->e0, nz);
+                b[i][2] = pk_add((__builtin_amdgcn_perm(0u, q, 0x0c020c02u) & this->m0) | this->e0, nz);
+                b[i][3] = pk_add((__builtin_amdgcn_perm(0u, q, 0x0c030c03u) & this->m0) | this->e0, nz);
+            }
+        } else if constexpr (BITS == 2) {
+            // A byte holds four consecutive codes: copied under both halves, fields 0 and 1, then 2 and 3, stay where they are,
+            // each under the exponent that makes it offset + q.
+            const uint32_t nz = (z | 0xE400u) | (((z << 2) | 0xDC00u) << 16);         // -(1024 + z), -(256 + z)
+            const uint32_t nz2 = ((z << 4) | 0xD400u) | (((z << 6) | 0xCC00u) << 16); // -(64 + z), -(16 + z)
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const uint32_t q = v[i >> 1];
+                const uint32_t lo = __builtin_amdgcn_perm(0u, q, (i & 1) ? 0x0c020c02u : 0x0c000c00u);
+                const uint32_t hi = __builtin_amdgcn_perm(0u, q, (i & 1) ? 0x0c030c03u : 0x0c010c01u);
+                b[i][0] = pk_add((lo & this->m0) | this->e0, nz);
+                b[i][1] = pk_add((lo & this->m1) | this->e1, nz2);
+                b[i][2] = pk_add((hi & this->m0) | this->e0, nz);
+                b[i][3] = pk_add((hi & this->m1) | this->e1, nz2);
+            }
+        }
+    }
+};
+
+// 3 bits: a word holds ten codes, five to a half from bit 0 on (code 5 h + p of them at bit 16 h + 3 p), and in bits 15 and 31
+// one bit of the codes 30 and 31.  Pairs of consecutive codes are put together from either half copied under
+// both, as it is and shifted by nine: a field at bits 0 / 3 / 6 of a half reads 1024 / 128 / 16 + q.
+template <>
+struct Unpack<3> {
+    uint32_t ea, eb, ec, ed, ef, m1, m2, m3, m5;
+    __device__ __forceinline__ void pin()
+    {
+        ea = 0x58006400u, eb = 0x64004C00u, ec = 0x64005800u, ed = 0x4C005800u, ef = 0x64006400u;
+        m1 = 0x00380007u, m2 = 0x000001C0u, m3 = 0x00070000u, m5 = 0x01C00038u;
+        asm volatile("" : "+v"(ea), "+v"(eb), "+v"(ec), "+v"(ed), "+v"(ef), "+s"(m1), "+s"(m2), "+s"(m3), "+s"(m5));
+    }
+    __device__ __forceinline__ void group(const u32x4 &v, uint32_t z, uint32_t (&b)[4][4]) const
+    {
+        const uint32_t z0 = z | 0xE400u, z3 = (z << 3) | 0xD800u, z6 = (z << 6) | 0xCC00u; // -(1024 + z), -(128 + z), -(16 + z)
+        const uint32_t na = z0 | z3 << 16, nb = z6 | z0 << 16, nc = z3 | z0 << 16, nd = z3 | z6 << 16, nf = z0 | z0 << 16;
+        uint32_t t[16];
+#pragma unroll
+        for (int j = 0; j < 3; j++) {
+            const uint32_t w = v[j];
+            const uint32_t lo = __builtin_amdgcn_perm(0u, w, 0x01000100u), hi = __builtin_amdgcn_perm(0u, w, 0x03020302u);
+            const uint32_t lo9 = lo >> 9, hi9 = hi >> 9;
+            t[5 * j] = pk_add((lo & m1) | ea, na);                      // codes 0, 1 of the word
+            t[5 * j + 1] = pk_add((lo9 & m3) | ((lo & m2) | eb), nb);   // 2, 3
+            t[5 * j + 2] = pk_add((w & m3) | ((lo9 & 0x38u) | ec), nc); // 4, 5
+            t[5 * j + 3] = pk_add((hi & m5) | ed, nd);                  // 6, 7
+            t[5 * j + 4] = pk_add((hi9 & m1) | ea, na);                 // 8, 9
+        }
+        const uint32_t last = ((v[0] >> 15) & 0x00010001u) | ((v[1] >> 14) & 0x00020002u) | ((v[2] >> 13) & 0x00040004u);
+        t[15] = pk_add(last | ef, nf);
+#pragma unroll
+        for (int i = 0; i < 16; i++)
+            b[i >> 2][i & 3] = t[i];
+    }
+};
 
 struct Lds {
     __attribute__((aligned(1024))) uint8_t x[XBYTES];
@@ -111,10 +199,10 @@ __device__ __forceinline__ void run_batch(Lds &L, const uint8_t *codes, const fl
 {
     constexpr int KP = batch_panel(MB);   // inputs of a panel: 4096 or 2048
     constexpr int GP = KP / 128, GS = GP + 1; // groups of a panel; their stride in LDS
-    constexpr int KL = 1024 / BITS;        // inputs of a line: 256 / 128 / 64
+    constexpr int KL = batch_line_inputs(BITS), LB = batch_line_bytes(BITS); // inputs and bytes of a line
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int n = lane & 15, c = lane >> 4;
-    const uint32_t row_bytes = (uint32_t)K * BITS / 8;
+    const uint32_t row_bytes = (uint32_t)K / 8 * BITS;
     const int G = K >> 7;
     const int n0 = t0 * 16;
     float4_t sum[NB][MB];
@@ -125,15 +213,15 @@ __device__ __forceinline__ void run_batch(Lds &L, const uint8_t *codes, const fl
             sum[t][mb] = float4_t{0.f, 0.f, 0.f, 0.f};
     const __amdgpu_buffer_rsrc_t xbuf = buffer_of(x, (uint32_t)M * (uint32_t)K * 2);
     const __amdgpu_buffer_rsrc_t wbuf = buffer_of(codes + (size_t)n0 * row_bytes, batch_run_bytes(row_bytes, nt, N - n0));
-    const uint32_t lane_off = batch_lane_offset(row_bytes, n, c);
+    const uint32_t lane_off = batch_lane_offset(row_bytes, n, c, LB);
     // x operand reads: piece p of batch row n in a slab of 64 inputs
     uint32_t xat[8];
 #pragma unroll
     for (int i = 0; i < 8; i++)
-        xat[i] = BITS == 4   ? (uint32_t)((c >> 1) * 2048 * MB + w_offset<128>(n, 4 * (c & 1) + (i & 3)))
+        xat[i] = BITS <= 4   ? (uint32_t)((c >> 1) * 2048 * MB + w_offset<128>(n, 4 * (c & 1) + (i & 3)))
                  : BITS == 8 ? (uint32_t)w_offset<128>(n, 2 * c + (i & 1))
                              : (uint32_t)w_offset<128>(n, 4 * (i & 1) + c);
-    DeqMagic<BITS> mg;
+    Unpack<BITS> mg;
     mg.pin();
 
     for (int k0 = 0; k0 < K; k0 += KP) {
@@ -159,13 +247,13 @@ __device__ __forceinline__ void run_batch(Lds &L, const uint8_t *codes, const fl
         const int items = max(mine, 0) * nt;
         u32x4 w[RD][2];
         int it = 0, il = wave; // the next request: tile and line
-        const uint32_t line0 = (uint32_t)k0 * BITS / 8;
+        const uint32_t line0 = (uint32_t)k0 / 8 * BITS;
         auto issue = [&](u32x4 (&to)[2]) {
             // Past the last line the lanes ask beyond the buffer's end, which costs no access (fq_batch_at.h).  An odd
             // number of groups at 4 bits: the second half of a row's last line is the next row's, and not used.
-            const uint32_t at = batch_request(row_bytes, lane_off, it, line0, il);
-            to[0] = __builtin_amdgcn_raw_buffer_load_b128(wbuf, (int)at, 0, 0);
-            to[1] = __builtin_amdgcn_raw_buffer_load_b128(wbuf, (int)(at + 64), 0, 0);
+            const uint32_t at = batch_request(row_bytes, lane_off, it, line0, il, LB);
+            to[0] = load_piece<BITS>(wbuf, at);
+            to[1] = load_piece<BITS>(wbuf, at + LB / 2);
             il += WAVES;
             if (il >= lines) {
                 il = wave;
@@ -217,7 +305,7 @@ __device__ __forceinline__ void run_batch(Lds &L, const uint8_t *codes, const fl
             out[mb] = float4_t{0.f, 0.f, 0.f, 0.f};
         int ct = 0, cl = wave;
         auto compute = [&](const u32x4 (&v)[2]) {
-            if (BITS == 4) {
+            if constexpr (BITS <= 4) {
                 const int g = cl * 2;
                 const uint8_t *xs = L.x + (size_t)g * 4096 * MB;
 #pragma unroll
@@ -226,28 +314,22 @@ __device__ __forceinline__ void run_batch(Lds &L, const uint8_t *codes, const fl
                         break;
                     const float s = L.s[(ct * 16 + n) * GS + g + h];
                     const uint32_t z = L.z[(ct * 16 + n) * GS + g + h];
-                    const uint32_t nz = (z | 0xE400u) | (((z << 4) | 0xD400u) << 16);
                     float4_t acc[MB];
 #pragma unroll
                     for (int mb = 0; mb < MB; mb++)
                         acc[mb] = float4_t{0.f, 0.f, 0.f, 0.f};
+                    uint32_t b[4][4];
+                    mg.group(v[h], z, b);
 #pragma unroll
-                    for (int i = 0; i < 4; i++) {
-                        uint32_t b[4];
-                        const uint32_t q = v[h][i];
-                        b[0] = pk_add((__builtin_amdgcn_perm(0u, q, 0x0c000c00u) & mg.m0) | mg.e0, nz);
-                        b[1] = pk_add((__builtin_amdgcn_perm(0u, q, 0x0c010c01u) & mg.m0) | mg.e0, nz);
-                        b[2] = pk_add((__builtin_amdgcn_perm(0u, q, 0x0c020c02u) & mg.m0) | mg.e0, nz);
-                        b[3] = pk_add((__builtin_amdgcn_perm(0u, q, 0x0c030c03u) & mg.m0) | mg.e0, nz);
+                    for (int i = 0; i < 4; i++)
 #pragma unroll
                         for (int mb = 0; mb < MB; mb++)
-                            acc[mb] = mfma16(*reinterpret_cast<const u32x4 *>(xs + h * 4096 * MB + mb * 2048 + xat[i]), b, acc[mb]);
-                    }
+                            acc[mb] = mfma16(*reinterpret_cast<const u32x4 *>(xs + h * 4096 * MB + mb * 2048 + xat[i]), b[i], acc[mb]);
 #pragma unroll
                     for (int mb = 0; mb < MB; mb++)
                         out[mb] += s * acc[mb];
                 }
-            } else if (BITS == 8) {
+            } else if constexpr (BITS == 8) {
                 const uint8_t *xs = L.x + (size_t)cl * 4096 * MB;
                 const float s = L.s[(ct * 16 + n) * GS + cl];
                 const uint32_t z = L.z[(ct * 16 + n) * GS + cl], nz = (z | (z << 16)) | 0xE400E400u;
@@ -351,12 +433,13 @@ __device__ __forceinline__ void run_batch(Lds &L, const uint8_t *codes, const fl
 
 // A wavefront's view of the launch: lane e holds entry e, all of it, so that one trip to memory serves the whole table;
 // every wavefront works out the same division of the launch's cost.
-template <bool SINGLE, int MB>
+template <bool SINGLE, int MB, bool NARROW>
 struct Division {
     int bits, N, K, lo, hi; // lo, hi: the entry's tiles that fall to this workgroup
     const void *codes, *scales, *zeros, *x;
     void *y;
     const void *c4, *c8, *c16, *s4, *s8, *z4, *z8;
+    const void *c2, *c3, *s2, *s3, *z2, *z3; // NARROW
     unsigned long long todo;
     int t, te;
 
@@ -369,6 +452,8 @@ struct Division {
         bits = SINGLE ? bits_host : bits_dev[e];
         c4 = d->codes4, c8 = d->codes8, c16 = d->w16, s4 = d->scales4, s8 = d->scales8, z4 = d->zeros4, z8 = d->zeros8;
         x = d->x, y = d->y, N = d->N, K = d->K;
+        if (NARROW)
+            c2 = d->codes2, c3 = d->codes3, s2 = d->scales2, s3 = d->scales3, z2 = d->zeros2, z3 = d->zeros3;
         __builtin_amdgcn_sched_barrier(0); // ahead of what is requested next
     }
     __device__ __forceinline__ void settle(int count, uint32_t step, int *flags)
@@ -377,9 +462,13 @@ struct Division {
         if (!SINGLE) // (all of it has been asked for, whatever the width: chosen pointers alone would be a second trip)
             asm volatile("" : "+v"(c4), "+v"(c8), "+v"(c16), "+v"(s4), "+v"(s8), "+v"(z4), "+v"(z8), "+v"(bits), "+v"(N), "+v"(K),
                               "+v"(x), "+v"(y));
+        if (!SINGLE && NARROW)
+            asm volatile("" : "+v"(c2), "+v"(c3), "+v"(s2), "+v"(s3), "+v"(z2), "+v"(z3));
         codes = bits == 4 ? c4 : bits == 8 ? c8 : bits == 16 ? c16 : nullptr;
         scales = bits == 4 ? s4 : s8;
         zeros = bits == 4 ? z4 : z8;
+        if (NARROW && (bits == 2 || bits == 3))
+            codes = bits == 2 ? c2 : c3, scales = bits == 2 ? s2 : s3, zeros = bits == 2 ? z2 : z3;
         int tiles = 0, cost = 0;
         if (lane < count) {
             if (codes) {
@@ -440,13 +529,14 @@ struct Division {
 
 // x0, K0: what every entry reads, if they all read one x (else null): requested before anything else is known.  `step`:
 // batch_step of the grid.
-template <bool SINGLE, int MB>
+// NARROW: entries may hold 2- and 3-bit copies (the other instances are without their code and pointers).
+template <bool SINGLE, int MB, bool NARROW>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_batch_kernel(
     const FqLinearDesc single, int bits_host, const FqLinearDesc *__restrict__ table, const int32_t *__restrict__ bits_dev,
     int count, int M, int *flags, const uint16_t *x0, int K0, uint32_t step)
 {
     __shared__ Lds L;
-    Division<SINGLE, MB> dv;
+    Division<SINGLE, MB, NARROW> dv;
     dv.request_table(single, bits_host, table, bits_dev, count);
     if (x0)
         fetch_first_x<MB>(L, x0, K0, M);
@@ -463,6 +553,10 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
             run_batch<4, MB>(L, r.codes, r.scales, r.zeros, r.x, r.y, r.N, r.K, M, r.t0, r.nt, there, keep);
         else if (r.bits == 8)
             run_batch<8, MB>(L, r.codes, r.scales, r.zeros, r.x, r.y, r.N, r.K, M, r.t0, r.nt, there, keep);
+        else if (NARROW && r.bits == 2)
+            run_batch<2, MB>(L, r.codes, r.scales, r.zeros, r.x, r.y, r.N, r.K, M, r.t0, r.nt, there, keep);
+        else if (NARROW && r.bits == 3)
+            run_batch<3, MB>(L, r.codes, r.scales, r.zeros, r.x, r.y, r.N, r.K, M, r.t0, r.nt, there, keep);
         else
             run_batch<16, MB>(L, r.codes, nullptr, nullptr, r.x, r.y, r.N, r.K, M, r.t0, r.nt, there, keep);
         there = keep;
@@ -483,17 +577,22 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 // their rounds it keeps plans of 4-bit copies alone over more than 16 batch rows or over part panels (65536 x 5120: 1.15).
 // Under this rule 0.85 of its time on average; one plan in a hundred is 1.06 to 1.19, where a workgroup's tiles are
 // one more than full runs or a round of the other kernel is just full.
+// 2- and 3-bit copies: the register-fed kernel loses more on them (over 800 timings of the 7B, 13B and 70B shapes' stages and of short rows, with
+// {2}, {3}, {2, 4, 8} and {3, 4, 8} resident, 0.70 of its time; 7B stages of {2, 4, 8} 0.54, of {3, 4, 8} 0.72), so that shorter rows come here;
+// 2-bit rows of two part panels stay (5120 inputs, one 2-bit copy: 1.1).  Behind it: the 13B q/k/v stage of {2, 4, 8} when all three run at 2 bits,
+// 18.9 us against 17.0 (all at 4 bits 20.9 against 22.5, at 8 26.7 against 33.3).
 bool fq_batch_serves(const FqLinearDesc *table, int count, int M)
 {
     const int cus = fq_device_cus(), panel = batch_panel(M <= 16 ? 1 : 2);
     long long rows = 0, tiles = 0;
     double weight = 0, inputs = 0, padded = 0; // summed over the rows
-    bool four_alone = true;
+    bool four_alone = true, narrow = false;
     for (int i = 0; i < count; i++) {
         const FqLinearDesc &d = table[i];
-        const int copies = (d.codes4 != nullptr) + (d.codes8 != nullptr) + (d.w16 != nullptr);
-        const int per_group = (d.codes4 ? 17 : 0) + (d.codes8 ? 29 : 0) + (d.w16 ? 53 : 0); // 3 * bits + 5
-        four_alone = four_alone && !d.codes8 && !d.w16;
+        const int copies = (d.codes2 != nullptr) + (d.codes3 != nullptr) + (d.codes4 != nullptr) + (d.codes8 != nullptr) + (d.w16 != nullptr);
+        const int per_group = (d.codes2 ? 11 : 0) + (d.codes3 ? 14 : 0) + (d.codes4 ? 17 : 0) + (d.codes8 ? 29 : 0) + (d.w16 ? 53 : 0); // 3 * bits + 5
+        narrow = narrow || d.codes2 || d.codes3;
+        four_alone = four_alone && !d.codes2 && !d.codes3 && !d.codes8 && !d.w16;
         rows += d.N;
         tiles += ((long long)d.N + 15) / 16;
         weight += (double)d.N * (d.K >> 7) * per_group / (copies > 0 ? copies : 1);
@@ -504,7 +603,7 @@ bool fq_batch_serves(const FqLinearDesc *table, int count, int M)
         return false;
     if (tiles <= 2 * cus)
         return true;
-    if (weight / rows * inputs / padded < 400)
+    if (weight / rows * inputs / padded < (narrow ? 340 : 400))
         return false;
     const int rest = (int)(rows % (64 * cus));
     const bool filled = rows > 96 * cus && (rest == 0 || rest > 48 * cus);
@@ -537,8 +636,25 @@ bool fq_batch_serves_linear(int N, int K, int bits, int M)
     return weight >= 470 && (!filled || bits != 4 || N > 384 * cus || (M <= 16 && K % 4096 == 0));
 }
 
+// Single calls at 2 and 3 bits: as a plan of that entry alone, which has the copy's width alone.  Over 512 to 28672 rows and as many
+// inputs, 2 to 32 batch rows, 0.42 (28672 inputs, 2 bits) to 0.86 (1024, 3 bits) of the register-fed kernel's time on average, none more than 1.02.
+bool fq_batch_serves_narrow(int N, int K, int bits, int M)
+{
+    FqLinearDesc d = {};
+    d.N = N, d.K = K;
+    (bits == 2 ? d.codes2 : d.codes3) = reinterpret_cast<const uint8_t *>(16); // (that there is one)
+    return fq_batch_serves(&d, 1, M);
+}
+
+// (A slab finds the weights in the caches, where the register-fed kernel's 64-row tiles gain more: 28672 x 5120 over 100 batch rows
+// took 1.07 of its time here, 8192 x 512 1.04; 4096 x 4096 over 100: 113 us there, 35 here.)
+bool fq_batch_serves_slab(int N, int K, int M)
+{
+    return K >= 1024 && (K % batch_panel(2) == 0 || N <= 64 * fq_device_cus()) && fq_batch_serves_narrow(N, K, 3, M);
+}
+
 hipError_t fq_launch_batch(const FqLinearDesc *single, int bits_host, const FqLinearDesc *descs_dev, const int32_t *bits_dev,
-                           int count, long long tiles, int M, int *flags, const uint16_t *x0, int K0, hipStream_t stream)
+                           int count, long long tiles, int M, bool narrow, int *flags, const uint16_t *x0, int K0, hipStream_t stream)
 {
     const int cus = fq_device_cus();
     const unsigned grid = (unsigned)(tiles < cus ? tiles : cus);
@@ -548,15 +664,19 @@ hipError_t fq_launch_batch(const FqLinearDesc *single, int bits_host, const FqLi
     if (K0 < 2048)
         x0 = nullptr;
     FqLinearDesc none = {};
-    if (single) {
-        if (M <= 16)
-            decode_batch_kernel<true, 1><<<grid, THREADS, 0, stream>>>(*single, bits_host, nullptr, nullptr, 1, M, nullptr, x0, K0, step);
+    auto go = [&](auto mb, auto narrow) {
+        constexpr int MB = decltype(mb)::value;
+        constexpr bool NARROW = decltype(narrow)::value;
+        if (single)
+            decode_batch_kernel<true, MB, NARROW><<<grid, THREADS, 0, stream>>>(*single, bits_host, nullptr, nullptr, 1, M, nullptr, x0, K0, step);
         else
-            decode_batch_kernel<true, 2><<<grid, THREADS, 0, stream>>>(*single, bits_host, nullptr, nullptr, 1, M, nullptr, x0, K0, step);
-    } else if (M <= 16) {
-        decode_batch_kernel<false, 1><<<grid, THREADS, 0, stream>>>(none, 0, descs_dev, bits_dev, count, M, flags, x0, K0, step);
-    } else {
-        decode_batch_kernel<false, 2><<<grid, THREADS, 0, stream>>>(none, 0, descs_dev, bits_dev, count, M, flags, x0, K0, step);
-    }
+            decode_batch_kernel<false, MB, NARROW><<<grid, THREADS, 0, stream>>>(none, 0, descs_dev, bits_dev, count, M, flags, x0, K0, step);
+    };
+    typedef std::integral_constant<int, 1> One;
+    typedef std::integral_constant<int, 2> Two;
+    if (narrow)
+        M <= 16 ? go(One(), std::true_type()) : go(Two(), std::true_type());
+    else
+        M <= 16 ? go(One(), std::false_type()) : go(Two(), std::false_type());
     return hipGetLastError();
 }

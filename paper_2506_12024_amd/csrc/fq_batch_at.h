@@ -24,13 +24,22 @@ FQ_BATCH_FN uint32_t batch_run_bytes(uint32_t row_bytes, int tiles, int rows_lef
     return (uint32_t)(tiles * 16 < rows_left ? tiles * 16 : rows_left) * row_bytes;
 }
 
-// A lane's part of the offset: row `n` of 16, piece `c` of four in a half line.
-FQ_BATCH_FN uint32_t batch_lane_offset(uint32_t row_bytes, int n, int c) { return (uint32_t)n * row_bytes + (uint32_t)c * 16; }
+// A line is what a request reads of a row: 128 bytes, at 2 and 3 bits the 64 or 96 of two quantization groups (256
+// inputs as at 4 bits, so that eight wavefronts share a panel's lines evenly), in two halves of four pieces.
+FQ_BATCH_FN constexpr int batch_line_bytes(int bits) { return bits < 4 ? 32 * bits : 128; }
+FQ_BATCH_FN constexpr int batch_line_inputs(int bits) { return bits < 4 ? 256 : 1024 / bits; }
 
-// Lane offset of a request's first half line; the second is 64 bytes on.  `line0`: the panel's first byte in a row.
-FQ_BATCH_FN uint32_t batch_request(uint32_t row_bytes, uint32_t lane_offset, int tile, uint32_t line0, int line)
+// A lane's part of the offset: row `n` of 16, piece `c` of four in a half line.
+FQ_BATCH_FN uint32_t batch_lane_offset(uint32_t row_bytes, int n, int c, int line_bytes = 128)
 {
-    return lane_offset + ((uint32_t)tile * 16 * row_bytes + line0 + (uint32_t)line * 128);
+    return (uint32_t)n * row_bytes + (uint32_t)(c * (line_bytes / 8));
+}
+
+// Lane offset of a request's first half line; the second is half a line on.  `line0`: the panel's first byte in a row.
+FQ_BATCH_FN uint32_t batch_request(uint32_t row_bytes, uint32_t lane_offset, int tile, uint32_t line0, int line,
+                                   int line_bytes = 128)
+{
+    return lane_offset + ((uint32_t)tile * 16 * row_bytes + line0 + (uint32_t)(line * line_bytes));
 }
 
 // x sits in LDS, so many bytes of it at a time: a panel.  `blocks`: blocks of 16 batch rows a launch takes, 1 or 2.
@@ -49,8 +58,9 @@ constexpr uint32_t BATCH_START_COST = 160;
 FQ_BATCH_FN int batch_tile_cost(int blocks, int K, int bits)
 {
     const int panel = batch_panel(blocks);
-    const int turns = K / panel * (panel / 1024 * bits / 8) + (((K % panel * bits + 1023) >> 10) + 7) / 8;
-    const int per_group = bits == 4 ? 54 : bits == 8 ? 75 : 142;
+    const int line_bits = bits < 4 ? 4 : bits; // (their lines hold as many inputs as those of 4 bits)
+    const int turns = K / panel * (panel / 1024 * line_bits / 8) + (((K % panel * line_bits + 1023) >> 10) + 7) / 8;
+    const int per_group = bits == 2 ? 46 : bits == 3 ? 54 : bits == 4 ? 54 : bits == 8 ? 75 : 142;
     return (bits == 16 ? 40 : 66) + (K >> 7) * per_group / 10 + turns * (blocks == 1 ? 11 : 25) +
            ((K + panel - 1) / panel - 1) * (blocks == 1 ? 55 : 30);
 }

@@ -18,10 +18,10 @@ struct FqLinearDesc {
     const float *scales8;
     const uint8_t *zeros8;
     const uint16_t *w16;    // fp16 [N][K] or null
-    const uint8_t *codes2;  // [N][K/4] or null (not served by the small-batch kernel of fq_batch.hip)
+    const uint8_t *codes2;  // [N][K/4] or null
     const float *scales2;
     const uint8_t *zeros2;
-    const uint8_t *codes3;  // [N][K/32] blocks of 12 bytes, or null (not served by fq_batch.hip, fq_stream.hip and the GEMM)
+    const uint8_t *codes3;  // [N][K/32] blocks of 12 bytes, or null (not served by fq_stream.hip and the GEMM)
     const float *scales3;
     const uint8_t *zeros3;
     const uint16_t *x;      // fp16 [M][K]
@@ -36,6 +36,7 @@ struct FqLinearDesc {
 struct FqPlanGeom {
     int count, M, total_tiles, tile_rows, max_K;
     int has3; // some layer of the plan holds a 3-bit copy
+    int narrow; // ... a 2- or a 3-bit copy
     int batch; // served by fq_launch_batch
     const uint16_t *x_all; // the x that every entry reads, all of them K_all long, or null
     int K_all;
@@ -125,12 +126,14 @@ hipError_t fq_launch_skinny(const FqLinearDesc *single, int bits_host,
                             int total_tiles, int tile_rows, int M, bool with3, int *queue, void *order,
                             hipStream_t stream);
 int fq_skinny_tile_rows(long long total_rows, int M);
-// Single calls and small plans (up to 64 entries) at 2 <= M <= 32 and 4, 8 or 16 bits (fq_batch.hip); `tiles`: tiles of
-// 16 rows in all; x0, K0: the x every entry reads and its row length, or null.
+// Single calls and small plans (up to 64 entries) at 2 <= M <= 32 (fq_batch.hip); `tiles`: tiles of
+// 16 rows in all; narrow: the launch may meet 2- and 3-bit entries; x0, K0: the x every entry reads and its row length, or null.
 bool fq_batch_serves(const FqLinearDesc *table, int count, int M); // a plan (host table)
-bool fq_batch_serves_linear(int N, int K, int bits, int M);
+bool fq_batch_serves_linear(int N, int K, int bits, int M); // 4, 8 and 16 bits
+bool fq_batch_serves_narrow(int N, int K, int bits, int M); // 2 and 3 bits
+bool fq_batch_serves_slab(int N, int K, int M); // the slabs of a 3-bit prompt
 hipError_t fq_launch_batch(const FqLinearDesc *single, int bits_host, const FqLinearDesc *descs_dev, const int32_t *bits_dev,
-                           int count, long long tiles, int M, int *flags, const uint16_t *x0, int K0, hipStream_t stream);
+                           int count, long long tiles, int M, bool narrow, int *flags, const uint16_t *x0, int K0, hipStream_t stream);
 // Streaming variant for plan launches with 2 <= M <= 32 and tiles of 256 rows (fq_launch_skinny
 // hands those to it).
 hipError_t fq_launch_skinny_stream(const FqLinearDesc *descs_dev, const int32_t *bits_dev, int count,

@@ -31,9 +31,9 @@
 // computed.
 //
 // Launches with few rows use a second kernel further down, in which the four wavefronts of a workgroup
-// share one row tile and split K.  What fq_batch.hip serves better goes there (single calls at 4, 8 and 16 bits
-// over rows that are not short, plans of a decoder's stages at these widths); what is left here are 2- and 3-bit copies, plans that
-// hold any, short rows, plans of more than 64 small entries, and plans between two layers' size and the streaming kernel's.
+// share one row tile and split K.  What fq_batch.hip serves better goes there (single calls over rows that are not short,
+// plans of a decoder's stages); what is left here are short rows, plans of more than 64 small entries, plans between two
+// layers' size and the streaming kernel's, larger ones that hold a 3-bit copy, and most slabs of 3-bit prompts over short or many rows.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
