@@ -579,7 +579,9 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 // one more than full runs or a round of the other kernel is just full.
 // 2- and 3-bit copies: the register-fed kernel loses more on them (over 800 timings of the 7B, 13B and 70B shapes' stages and of short rows, with
 // {2}, {3}, {2, 4, 8} and {3, 4, 8} resident, 0.70 of its time; 7B stages of {2, 4, 8} 0.54, of {3, 4, 8} 0.72), so that shorter rows come here;
-// 2-bit rows of two part panels stay (5120 inputs, one 2-bit copy: 1.1).  Behind it: the 13B q/k/v stage of {2, 4, 8} when all three run at 2 bits,
+// rows of two part panels with a 2- or 3-bit copy alone stay (5120 inputs: 1.1, 1.05).  No more rows than above: at 27 x 8192 x 8192 3 bits
+// took 1.1 of its time here, 35 x 6000 x 5120 1.2.  Behind it: 8 x 6000 x 5120 of {3, 4, 8}, each with an x of its own (1.1),
+// and the 13B q/k/v stage of {2, 4, 8} when all three run at 2 bits,
 // 18.9 us against 17.0 (all at 4 bits 20.9 against 22.5, at 8 26.7 against 33.3).
 bool fq_batch_serves(const FqLinearDesc *table, int count, int M)
 {
@@ -590,7 +592,7 @@ bool fq_batch_serves(const FqLinearDesc *table, int count, int M)
     for (int i = 0; i < count; i++) {
         const FqLinearDesc &d = table[i];
         const int copies = (d.codes2 != nullptr) + (d.codes3 != nullptr) + (d.codes4 != nullptr) + (d.codes8 != nullptr) + (d.w16 != nullptr);
-        const int per_group = (d.codes2 ? 11 : 0) + (d.codes3 ? 14 : 0) + (d.codes4 ? 17 : 0) + (d.codes8 ? 29 : 0) + (d.w16 ? 53 : 0); // 3 * bits + 5
+        const int per_group = (d.codes2 ? 11 : 0) + (d.codes3 ? 13 : 0) + (d.codes4 ? 17 : 0) + (d.codes8 ? 29 : 0) + (d.w16 ? 53 : 0); // about 3 * bits + 5
         narrow = narrow || d.codes2 || d.codes3;
         four_alone = four_alone && !d.codes2 && !d.codes3 && !d.codes8 && !d.w16;
         rows += d.N;
