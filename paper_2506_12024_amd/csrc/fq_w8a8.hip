@@ -251,7 +251,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
     // operand reads of a step do not touch the slabs its direct-to-LDS loads are filling, and
     // does not wait for those loads before the first read.
     __shared__ __attribute__((aligned(1024))) uint8_t xs0[XSLAB], xs1[XSLAB], ws0[WSLAB], ws1[WSLAB];
-    __shared__ float xsm[2][BM];
+    __shared__ __attribute__((aligned(16))) float xsm[2][BM];
     __shared__ __attribute__((aligned(1024))) float sm[2][MB * BN];   // scales of two blocks of groups: [group][row]
     __shared__ __attribute__((aligned(1024))) uint32_t zm[2][MB * BN]; // zero points, same order
 
@@ -440,25 +440,33 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
     if (s < nsteps)
         step(s, IntC<2>());
 
+    // The tokens' scales come through LDS: a load from memory among the stores waits for the stores ahead of it, and the next
+    // stores for the load (1455 x 512 -> 22912 80 -> 49 us).
+    if (threadIdx.x < BM)
+        xsm[0][threadIdx.x] = d.sx[min(m0 + (int)threadIdx.x, d.M - 1)];
+    __syncthreads();
     // D layout of the 32x32 MFMA: lane holds column l32 (weight row), rows (tokens)
     // 8 * (v / 4) + 4 * (lane / 32) + v % 4.
 #pragma unroll
-    for (int mt = 0; mt < MT; mt++) {
+    for (int mt = 0; mt < MT; mt++)
 #pragma unroll
-        for (int v = 0; v < 16; v++) {
-            const int m = m0 + wm + mt * 32 + 8 * (v >> 2) + 4 * c + (v & 3);
-            if (m < d.M) {
-                const float sxm = d.sx[m];
+        for (int q = 0; q < 4; q++) {
+            const int tl = wm + mt * 32 + 8 * q + 4 * c;
+            const float4_t sx = *reinterpret_cast<const float4_t *>(xsm[0] + tl); // (ahead of the rows' branches)
 #pragma unroll
-                for (int j = 0; j < 2; j++) {
-                    const int n = n_wave0 + j * 32 + l32;
-                    if (n < d.N)
-                        ((FQ_GLOBAL uint16_t *)d.y)[(size_t)m * d.N + n] =
-                            __builtin_bit_cast(uint16_t, (_Float16)(sxm * out[mt][j][v]));
+            for (int r = 0; r < 4; r++) {
+                const int m = m0 + tl + r;
+                if (m < d.M) {
+#pragma unroll
+                    for (int j = 0; j < 2; j++) {
+                        const int n = n_wave0 + j * 32 + l32;
+                        if (n < d.N)
+                            ((FQ_GLOBAL uint16_t *)d.y)[(size_t)m * d.N + n] =
+                                __builtin_bit_cast(uint16_t, (_Float16)(sx[r] * out[mt][j][4 * q + r]));
+                    }
                 }
             }
         }
-    }
 }
 
 // ---- one scale per weight row ------------------------------------------------------------------
@@ -483,7 +491,8 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
     constexpr int RXSLAB = RBM * BKB;
     static_assert(RBM == (HALF ? RBM_FULL / 2 : RBM_FULL), "two half tiles to a tile");
     __shared__ __attribute__((aligned(1024))) uint8_t xs0[RXSLAB], xs1[RXSLAB], ws0[WSLAB], ws1[WSLAB];
-    __shared__ int xtot[RBM];
+    __shared__ __attribute__((aligned(16))) int xtot[RBM];
+    __shared__ __attribute__((aligned(16))) float sxs[RBM];
 
     const int in_run = skip + (HALF ? (int)(blockIdx.x >> 4) : (int)(blockIdx.x >> 3));
     const int logical = (blockIdx.x & 7) * per_xcd + in_run;
@@ -574,8 +583,11 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
     if (s < nsteps)
         step(s, std::false_type());
 
-    if (threadIdx.x < RBM)
+    // (the tokens' scales through LDS, as above: 1455 x 512 -> 22994 85 -> 62 us)
+    if (threadIdx.x < RBM) {
         xtot[threadIdx.x] = xt;
+        sxs[threadIdx.x] = d.sx[min(m0 + (int)threadIdx.x, d.M - 1)];
+    }
     __syncthreads();
     // D layout of the 32x32 MFMA: lane holds column l32 (weight row), rows (tokens)
     // 8 * (v / 4) + 4 * (lane / 32) + v % 4.
@@ -588,24 +600,26 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
         zn[j] = (int)d.zeros[n] - 128;
     }
 #pragma unroll
-    for (int mt = 0; mt < RMT; mt++) {
+    for (int mt = 0; mt < RMT; mt++)
 #pragma unroll
-        for (int v = 0; v < 16; v++) {
-            const int tl = wm + mt * 32 + 8 * (v >> 2) + 4 * c + (v & 3);
-            const int m = m0 + tl;
-            if (m < d.M) {
-                const float sxm = d.sx[m];
-                const int xt = xtot[tl];
+        for (int q = 0; q < 4; q++) {
+            const int tl = wm + mt * 32 + 8 * q + 4 * c;
+            const float4_t sx = *reinterpret_cast<const float4_t *>(sxs + tl);
+            const v4i xt = *reinterpret_cast<const v4i *>(xtot + tl);
 #pragma unroll
-                for (int j = 0; j < 2; j++) {
-                    const int n = n_wave0 + j * 32 + l32;
-                    if (n < d.N)
-                        ((FQ_GLOBAL uint16_t *)d.y)[(size_t)m * d.N + n] = __builtin_bit_cast(
-                            uint16_t, (_Float16)(sxm * (sn_[j] * (float)(acc[mt][j][v] - zn[j] * xt))));
+            for (int r = 0; r < 4; r++) {
+                const int m = m0 + tl + r;
+                if (m < d.M) {
+#pragma unroll
+                    for (int j = 0; j < 2; j++) {
+                        const int n = n_wave0 + j * 32 + l32;
+                        if (n < d.N)
+                            ((FQ_GLOBAL uint16_t *)d.y)[(size_t)m * d.N + n] = __builtin_bit_cast(
+                                uint16_t, (_Float16)(sx[r] * (sn_[j] * (float)(acc[mt][j][4 * q + r] - zn[j] * xt[r]))));
+                    }
                 }
             }
         }
-    }
 }
 
 } // namespace
