@@ -276,8 +276,9 @@ __global__ __launch_bounds__(THREADS) void lm_head_entropy_kernel(const uint16_t
 // alternative, a ticket that lets the last workgroup do it, needs every workgroup to make its
 // partial visible to the other XCDs first, and that fence writes back an L2 per workgroup
 // (measured: 50 us for 1024 workgroups, more than the whole weight stream).
-// One wavefront to a row of x, PER partials to a lane, all requested together; the maximum first, then the sums, in double (4 x 1024 -> 8000: 3.4 us of a call of 12.8, 10.7 of 20.4 with
-// one partial to each of 1024 threads, states merged pair by pair through the wavefront, LDS and once more).
+// One wavefront to a row of x, PER partials to a lane, all requested together; the maximum first, then the sums, in double
+// (4 x 1024 -> 8000: 3.4 us of a call of 12.8; 10.7 of 20.4 with one partial to each of 1024 threads, states merged pair by
+// pair through the wavefront, LDS and once more).
 template <int PER>
 __global__ __launch_bounds__(64 * MAX_M) void lm_head_combine_kernel(int parts, int bank, float *__restrict__ H,
                                                                      int32_t *__restrict__ argmax)

@@ -441,7 +441,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
         step(s, IntC<2>());
 
     // The tokens' scales come through LDS: a load from memory among the stores waits for the stores ahead of it, and the next
-    // stores for the load (1455 x 512 -> 22912 80 -> 49 us).
+    // stores for the load (1455 x 512 -> 22912 80 -> 47 us).
     if (threadIdx.x < BM)
         xsm[0][threadIdx.x] = d.sx[min(m0 + (int)threadIdx.x, d.M - 1)];
     __syncthreads();
@@ -454,16 +454,13 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
             const int tl = wm + mt * 32 + 8 * q + 4 * c;
             const float4_t sx = *reinterpret_cast<const float4_t *>(xsm[0] + tl); // (ahead of the rows' branches)
 #pragma unroll
-            for (int r = 0; r < 4; r++) {
-                const int m = m0 + tl + r;
-                if (m < d.M) {
+            for (int j = 0; j < 2; j++) {
+                const int n = n_wave0 + j * 32 + l32;
 #pragma unroll
-                    for (int j = 0; j < 2; j++) {
-                        const int n = n_wave0 + j * 32 + l32;
-                        if (n < d.N)
-                            ((FQ_GLOBAL uint16_t *)d.y)[(size_t)m * d.N + n] =
-                                __builtin_bit_cast(uint16_t, (_Float16)(sx[r] * out[mt][j][4 * q + r]));
-                    }
+                for (int r = 0; r < 4; r++) {
+                    const _Float16 v = (_Float16)(sx[r] * out[mt][j][4 * q + r]);
+                    if (m0 + tl + r < d.M && n < d.N)
+                        ((FQ_GLOBAL uint16_t *)d.y)[(size_t)(m0 + tl + r) * d.N + n] = __builtin_bit_cast(uint16_t, v);
                 }
             }
         }
@@ -583,7 +580,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
     if (s < nsteps)
         step(s, std::false_type());
 
-    // (the tokens' scales through LDS, as above: 1455 x 512 -> 22994 85 -> 62 us)
+    // (the tokens' scales through LDS, as above: 1455 x 512 -> 22994 85 -> 49 us, with one branch a store)
     if (threadIdx.x < RBM) {
         xtot[threadIdx.x] = xt;
         sxs[threadIdx.x] = d.sx[min(m0 + (int)threadIdx.x, d.M - 1)];
@@ -599,6 +596,8 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
         sn_[j] = d.scales[n];
         zn[j] = (int)d.zeros[n] - 128;
     }
+    // (One branch a store, the product outside it: with a row's branch around the columns' 1455 x 512 -> 22994 65 us instead of 49.
+    // Eight bytes a lane, four neighbouring columns exchanged between four lanes: 50, with odd N 1.07 times as long.)
 #pragma unroll
     for (int mt = 0; mt < RMT; mt++)
 #pragma unroll
@@ -607,16 +606,13 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
             const float4_t sx = *reinterpret_cast<const float4_t *>(sxs + tl);
             const v4i xt = *reinterpret_cast<const v4i *>(xtot + tl);
 #pragma unroll
-            for (int r = 0; r < 4; r++) {
-                const int m = m0 + tl + r;
-                if (m < d.M) {
+            for (int j = 0; j < 2; j++) {
+                const int n = n_wave0 + j * 32 + l32;
 #pragma unroll
-                    for (int j = 0; j < 2; j++) {
-                        const int n = n_wave0 + j * 32 + l32;
-                        if (n < d.N)
-                            ((FQ_GLOBAL uint16_t *)d.y)[(size_t)m * d.N + n] = __builtin_bit_cast(
-                                uint16_t, (_Float16)(sx[r] * (sn_[j] * (float)(acc[mt][j][4 * q + r] - zn[j] * xt[r]))));
-                    }
+                for (int r = 0; r < 4; r++) {
+                    const _Float16 v = (_Float16)(sx[r] * (sn_[j] * (float)(acc[mt][j][4 * q + r] - zn[j] * xt[r])));
+                    if (m0 + tl + r < d.M && n < d.N)
+                        ((FQ_GLOBAL uint16_t *)d.y)[(size_t)(m0 + tl + r) * d.N + n] = __builtin_bit_cast(uint16_t, v);
                 }
             }
         }
