@@ -81,7 +81,8 @@ typedef struct fq_plan fq_plan;   /* opaque: a list of linears run by one launch
 #define FQ_MAX_LM_HEAD_M 4 /* rows of x served by fq_lm_head_entropy */
 #define FQ_PART_STREAMS 4 /* streams per device with an array for the partial sums of products split along K */
 #define FQ_SCRATCH_BANKS 16 /* streams per device with a copy of their own of the library's static
-                               scratch (fq_entropy_kl over a few rows, fq_lm_head_entropy) */
+                               scratch (fq_entropy_kl over a few rows, fq_lm_head_entropy); as many threads
+                               that name hipStreamPerThread have one besides */
 
 /* Message describing the calling thread's most recent error ("" if none).  (Interface only: the
  * paper defines no error model.) */
@@ -316,7 +317,8 @@ int fq_linear_w8a8(const fq_layer *layer, const void *xq, const float *sx, const
  * R >= 0 (R = 0 launches nothing), V >= 1.  Calls with R <= 64 and V > 4096 combine per-row
  * partials in a small device-resident scratch of the library, of which every stream
  * gets a copy of its own (FQ_SCRATCH_BANKS per device; further streams take a slower path that
- * needs none): such calls may overlap on different streams.  A launch captured into a
+ * needs none): such calls may overlap on different streams.  On hipStreamPerThread every thread gets one, the first
+ * FQ_SCRATCH_BANKS of them; further threads take the path without.  A launch captured into a
  * graph keeps the copy of the stream it was captured on.  Calls with 65 to 512 rows and V > 10240 do the
  * same in copies of the first 8 streams that make them; on other streams, on hipStreamPerThread and
  * under capture they need none.
@@ -364,7 +366,8 @@ int fq_rank_ascending(const float *values, int n, int m, int32_t *order, void *s
  * differ by less than the rounding of a binary32 sum of K products may swap places in argmax.
  * Uses a static device array for the partial results of its workgroups, of which every stream
  * gets a copy of its own, so calls may overlap on different streams; a stream beyond the first
- * FQ_SCRATCH_BANKS distinct ones on a device is refused (FQ_ERR_HIP).  A call captured into a graph keeps the copy of the
+ * FQ_SCRATCH_BANKS distinct ones on a device is refused (FQ_ERR_HIP).  On hipStreamPerThread every thread gets one, the
+ * first FQ_SCRATCH_BANKS of them; for further threads a single workgroup takes the call (two orders of magnitude slower).  A call captured into a graph keeps the copy of the
  * stream it was captured on.
  */
 int fq_lm_head_entropy(const void *x_fp16, const void *w_fp16, int M, int V, int K,

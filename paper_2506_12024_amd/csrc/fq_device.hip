@@ -5,6 +5,7 @@
 // bank of the library's static scratch arrays a stream uses.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <mutex>
 
 #include "fq_internal.h"
@@ -29,7 +30,9 @@ struct DeviceFacts {
     const void *raised[MAX_KERNEL_FACTS]; // kernels whose dynamic LDS limit was raised
     size_t raised_to[MAX_KERNEL_FACTS];
     int n_banks;
-    hipStream_t bank_stream[FQ_BANKS]; // the stream that bank i of the static scratch arrays belongs to
+    hipStream_t bank_stream[FQ_STREAM_BANKS]; // the stream that bank i of the static scratch arrays belongs to
+    int n_thread_banks;
+    unsigned int bank_thread[FQ_THREAD_BANKS]; // the thread whose hipStreamPerThread bank FQ_STREAM_BANKS + i belongs to
     int n_rows_banks;
     hipStream_t rows_stream[FQ_ROWS_BANKS]; // the same for the entropies of 65 to 512 rows
     int n_part_banks;
@@ -86,8 +89,9 @@ int fq_workgroups_per_cu(const void *func, int threads, size_t lds, int fallback
     return per_cu;
 }
 
-// The index of `stream` in a table of at most `most` streams, entered if there is room; -1 if not.
-static int bank_of(hipStream_t *table, int &n, int most, hipStream_t stream)
+// The index of `stream` (or of a thread) in a table of at most `most`, entered if there is room; -1 if not.
+template <typename Key>
+static int bank_of(Key *table, int &n, int most, Key stream)
 {
     for (int i = 0; i < n; i++)
         if (table[i] == stream)
@@ -98,11 +102,25 @@ static int bank_of(hipStream_t *table, int &n, int most, hipStream_t stream)
     return n++;
 }
 
+// hipStreamPerThread is one handle for as many streams as there are threads, so there the thread counts: by a number that
+// no later thread gets, for what an ended thread left behind may still run.
+static unsigned int thread_number()
+{
+    static std::atomic<unsigned int> last{0};
+    static thread_local const unsigned int mine = ++last;
+    return mine;
+}
+
 int fq_stream_bank(hipStream_t stream)
 {
     std::lock_guard<std::mutex> hold(g_lock);
     DeviceFacts *d = current();
-    return d ? bank_of(d->bank_stream, d->n_banks, FQ_BANKS, stream) : -1;
+    if (!d)
+        return -1;
+    if (stream != hipStreamPerThread)
+        return bank_of(d->bank_stream, d->n_banks, FQ_STREAM_BANKS, stream);
+    const int i = bank_of(d->bank_thread, d->n_thread_banks, FQ_THREAD_BANKS, thread_number());
+    return i < 0 ? -1 : FQ_STREAM_BANKS + i;
 }
 
 int fq_rows_bank(hipStream_t stream)

@@ -62,8 +62,11 @@ hipError_t fq_raise_dynamic_lds(const void *func, size_t bytes);
 // The kernels that combine the partial results of their workgroups through a static device array
 // (entropy / KL over a few long rows, the fused output layer) keep FQ_BANKS copies of it,
 // one per stream: calls on different streams then never share one.  The bank of `stream` on the
-// current device (the first FQ_BANKS distinct streams get one each), or -1 if none is left.
-constexpr int FQ_BANKS = 16; // FQ_SCRATCH_BANKS of the public header
+// current device, or -1 if none is left: the first FQ_STREAM_BANKS distinct streams get one each, and so do the first
+// FQ_THREAD_BANKS threads that name hipStreamPerThread.
+constexpr int FQ_STREAM_BANKS = 16; // FQ_SCRATCH_BANKS of the public header
+constexpr int FQ_THREAD_BANKS = 16;
+constexpr int FQ_BANKS = FQ_STREAM_BANKS + FQ_THREAD_BANKS;
 int fq_stream_bank(hipStream_t stream);
 // The same for the entropies of 65 to 512 rows, which any number of streams may also ask for without a bank: the first
 // FQ_ROWS_BANKS streams; -1 also while the stream is captured (a graph may be replayed beside anything) and for

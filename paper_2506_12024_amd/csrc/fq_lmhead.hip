@@ -141,7 +141,8 @@ struct State {
 template <int M>
 __global__ __launch_bounds__(THREADS) void lm_head_entropy_kernel(const uint16_t *__restrict__ x,
                                                                   const uint16_t *__restrict__ w, int V, int K,
-                                                                  int bank, float *__restrict__ logits)
+                                                                  int bank, float *__restrict__ logits,
+                                                                  float *__restrict__ H, int32_t *__restrict__ argmax)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[]; // x: [K / 512][M][64] blocks of 16 bytes
     __shared__ float s_part[WAVES][M][3];
@@ -265,7 +266,11 @@ __global__ __launch_bounds__(THREADS) void lm_head_entropy_kernel(const uint16_t
             wg[m].idx = s_idx[lane][m];
         }
         wg[m].merge_lanes(WAVES - 1);
-        if (lane == 0) {
+        if (lane == 0 && bank < 0) { // the call's only workgroup
+            H[m] = (float)(log((double)wg[m].S) - (double)wg[m].U / (double)wg[m].S);
+            if (argmax)
+                argmax[m] = wg[m].idx;
+        } else if (lane == 0) {
             g_part[bank][m][blockIdx.x] = u32x4{__builtin_bit_cast(uint32_t, wg[m].mx), __builtin_bit_cast(uint32_t, wg[m].S),
                                                 __builtin_bit_cast(uint32_t, wg[m].U), (uint32_t)wg[m].idx};
         }
@@ -342,9 +347,13 @@ hipError_t launch(const uint16_t *x, const uint16_t *w, int V, int K, float *log
     if (grid > nblocks)
         grid = nblocks;
     const int bank = fq_stream_bank(stream);
+    if (bank < 0 && stream == hipStreamPerThread) { // more threads than banks: one workgroup, which needs none
+        lm_head_entropy_kernel<M><<<1, THREADS, lds, stream>>>(x, w, V, K, bank, logits, H, argmax);
+        return hipGetLastError();
+    }
     if (bank < 0) // more streams than banks of partial results have used this call on this device
         return hipErrorOutOfMemory;
-    lm_head_entropy_kernel<M><<<grid, THREADS, lds, stream>>>(x, w, V, K, bank, logits);
+    lm_head_entropy_kernel<M><<<grid, THREADS, lds, stream>>>(x, w, V, K, bank, logits, nullptr, nullptr);
     static_assert(MAX_WGS == 16 * 64, "partials of a lane");
     if (grid <= 512)
         lm_head_combine_kernel<8><<<1, 64 * M, 0, stream>>>(grid, bank, H, argmax);

@@ -63,3 +63,6 @@ _part_bank = _fn("_Z12fq_part_bankP12ihipStream_tPi", _i, ctypes.c_void_p, ctype
 def part_bank(stream):
     """The index of a stream's array for partial sums on the current device, -1 if it has none."""
     return _part_bank(stream, ctypes.byref(_i()))
+
+
+stream_bank = _fn("_Z14fq_stream_bankP12ihipStream_t", _i, ctypes.c_void_p)  # -1: no copy of the static scratch for this stream
