@@ -45,11 +45,11 @@ __device__ __forceinline__ float4 ld4_nt(const float4 *p)
 }
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
 // Vector i of a row: four consecutive logits widened to binary32 (binary16 widens exactly).
-__device__ __forceinline__ float4 load4(const float *row, int i)
+__device__ __forceinline__ float4 load4(const float *row, unsigned i)
 {
     return ld4_nt(reinterpret_cast<const float4 *>(row) + i);
 }
-__device__ __forceinline__ float4 load4(const _Float16 *row, int i)
+__device__ __forceinline__ float4 load4(const _Float16 *row, unsigned i)
 {
     const half4_t v = __builtin_nontemporal_load((const __attribute__((address_space(1))) half4_t *)row + i);
     return make_float4((float)v.x, (float)v.y, (float)v.z, (float)v.w);
@@ -171,8 +171,9 @@ __global__ __launch_bounds__(THREADS) void entropy_kl_kernel(const T *__restrict
     __shared__ float s_max[2][WAVES];
     __shared__ double s_sum[4][WAVES];
 
-    const int r = blockIdx.x / splits, sidx = blockIdx.x % splits;
-    const int t = threadIdx.x;
+    const int r = blockIdx.x / splits;
+    const unsigned sidx = blockIdx.x % splits; // (unsigned, and what follows: a row of nearly 2^31 entries ends within a round of them)
+    const unsigned t = threadIdx.x;
     const T *ar = a + (size_t)r * V;
     const T *br = HAS_B ? b + (size_t)r * V : ar;
 
@@ -180,17 +181,17 @@ __global__ __launch_bounds__(THREADS) void entropy_kl_kernel(const T *__restrict
     part_init(p);
     const float4 none4 = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY); // entries that carry no mass
     if (VEC) { // V % 4 == 0 and rows aligned to four entries
-        const int nvec = V >> 2;
-        const int per = (nvec + splits - 1) / splits;
-        const int end = min(nvec, (sidx + 1) * per);
+        const unsigned nvec = (unsigned)V >> 2;
+        const unsigned per = (nvec + splits - 1) / splits;
+        const unsigned end = min(nvec, (sidx + 1) * per);
         // Four vectors of a row in flight, the last round too: its requests past the end repeat the last vector and
         // are not added (one after the other, the up to three vectors of a last round cost a trip to memory each,
         // as much as everything else where a row is split).
-        for (int i = sidx * per + t; i < end; i += 4 * THREADS) {
+        for (unsigned i = sidx * per + t; i < end; i += 4 * THREADS) {
             float4 av[4], bv[4];
 #pragma unroll
             for (int j = 0; j < 4; j++) {
-                const int at = min(i + j * THREADS, end - 1);
+                const unsigned at = min(i + j * THREADS, end - 1);
                 av[j] = load4(ar, at);
                 bv[j] = HAS_B ? load4(br, at) : none4;
             }
@@ -204,13 +205,13 @@ __global__ __launch_bounds__(THREADS) void entropy_kl_kernel(const T *__restrict
         }
     } else {
         // Rows that 128-bit loads do not fit: eight entries in flight.
-        const int per = (V + splits - 1) / splits;
-        const int end = min(V, (sidx + 1) * per);
-        for (int i = sidx * per + t; i < end; i += 8 * THREADS) {
+        const unsigned per = ((unsigned)V + splits - 1) / splits;
+        const unsigned end = min((unsigned)V, (sidx + 1) * per);
+        for (unsigned i = sidx * per + t; i < end; i += 8 * THREADS) {
             float av[8], bv[8];
 #pragma unroll
             for (int j = 0; j < 8; j++) {
-                const int at = min(i + j * THREADS, end - 1);
+                const unsigned at = min(i + j * THREADS, end - 1);
                 av[j] = (float)ar[at];
                 bv[j] = HAS_B ? (float)br[at] : -INFINITY;
             }

@@ -88,3 +88,12 @@ def test_overlapping_streams_and_capture():
         graph.replay()
         torch.cuda.synchronize()
         assert _close(Hg, sets[0][2]) and _close(KLg, sets[0][3])
+
+
+@pytest.mark.parametrize("V", [2 ** 31 - 1001, 2 ** 31 - 1, 2 ** 31 - 4])
+def test_a_row_of_nearly_two_to_the_31_entries(V):
+    # uniform, so that the sums are whole numbers: the entropy is ln V in binary32 (a lost piece of 32 would show at 1.5e-3)
+    a = torch.zeros(V, dtype=torch.float16, device=DEV)
+    H = torch.full((1,), float("nan"), device=DEV)
+    fq.fq_entropy_kl_f16(a, None, 1, V, H, None)
+    assert abs(H.item() - np.log(V)) <= 2e-7 * np.log(V)
