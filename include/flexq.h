@@ -319,9 +319,10 @@ int fq_linear_w8a8(const fq_layer *layer, const void *xq, const float *sx, const
  * gets a copy of its own (FQ_SCRATCH_BANKS per device; further streams take a slower path that
  * needs none): such calls may overlap on different streams.  On hipStreamPerThread every thread gets one, the first
  * FQ_SCRATCH_BANKS of them; further threads take the path without.  A launch captured into a
- * graph keeps the copy of the stream it was captured on.  Calls with 65 to 512 rows and V > 10240 do the
- * same in copies of the first 8 streams that make them; on other streams, on hipStreamPerThread and
- * under capture they need none.
+ * graph keeps the copy of the stream it was captured on.  The path without sums in another order: its results may differ in
+ * their last bits.  Calls with 65 to 512 rows and V > 10240 are split too where that is faster, in copies of the first 8
+ * streams that make them; on other streams, on hipStreamPerThread and under capture they need none, take longer (from 65536
+ * entries on up to 1.5 times as long at 256 rows, twice at 65) and give the same bits.
  */
 int fq_entropy_kl(const float *logits_p, const float *logits_q, int R, int V,
                   float *entropy_out, float *kl_out, void *stream);

@@ -4,7 +4,7 @@
 // Sec. 3.1 / 4.3, taken between two next-token distributions.
 //
 // One workgroup per row -- or, for up to 512 long rows (the decode step has one), up to 32
-// workgroups per row whose partials meet in a small static device array and are combined
+// workgroups per row, one to a piece of it, whose partials meet in a small static device array and are combined
 // by whichever workgroup arrives last (one launch either way; a single workgroup needs
 // 11 us for one 32000-entry pair, 32 of them 5.9).  Bound by HBM for many rows, by launch and
 // latency for few: 5 x 32000 6.1 us, 52 x 32000 8.2 (36 with a fence per partial and a ticket line shared by the rows).
@@ -45,11 +45,11 @@ __device__ __forceinline__ float4 ld4_nt(const float4 *p)
 }
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
 // Vector i of a row: four consecutive logits widened to binary32 (binary16 widens exactly).
-__device__ __forceinline__ float4 load4(const float *row, unsigned i)
+__device__ __forceinline__ float4 load4(const float *row, size_t i)
 {
     return ld4_nt(reinterpret_cast<const float4 *>(row) + i);
 }
-__device__ __forceinline__ float4 load4(const _Float16 *row, unsigned i)
+__device__ __forceinline__ float4 load4(const _Float16 *row, size_t i)
 {
     const half4_t v = __builtin_nontemporal_load((const __attribute__((address_space(1))) half4_t *)row + i);
     return make_float4((float)v.x, (float)v.y, (float)v.z, (float)v.w);
@@ -135,6 +135,51 @@ __device__ __forceinline__ void add_pair(Partial<FINE> &p, const float4 a0, cons
     }
 }
 
+// Entries of a row's piece [from, end) (in vectors of four if VEC) that fall to thread t of THREADS: four vectors or, where
+// 128-bit loads do not fit the rows, eight entries of a row in flight, in the last round too: its requests past the end repeat the
+// piece's last vector and are not added (one after the other, the up to three vectors of a last
+// round cost a trip to memory each, as much as everything else where a row is split).
+template <int THREADS, bool HAS_B, bool VEC, bool FINE, typename T>
+__device__ __forceinline__ void add_entries(Partial<FINE> &p, const T *ar, const T *br, unsigned from, unsigned end, unsigned t)
+{
+    const float4 none4 = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY); // entries that carry no mass
+    unsigned i = from + t;
+    if (VEC) {
+        for (; i < end; i += 4 * THREADS) {
+            float4 av[4], bv[4];
+#pragma unroll
+            for (unsigned j = 0; j < 4; j++) {
+                const unsigned at = min(i + j * THREADS, end - 1);
+                av[j] = load4(ar, at);
+                bv[j] = HAS_B ? load4(br, at) : none4;
+            }
+#pragma unroll
+            for (unsigned j = 0; j < 4; j += 2) {
+                if (i + (j + 1) * THREADS >= end)
+                    av[j + 1] = bv[j + 1] = none4;
+                if (i + j * THREADS < end)
+                    add_pair<HAS_B, FINE>(p, av[j], av[j + 1], bv[j], bv[j + 1]);
+            }
+        }
+    } else {
+        for (; i < end; i += 8 * THREADS) {
+            float av[8], bv[8];
+#pragma unroll
+            for (int j = 0; j < 8; j++) {
+                const unsigned at = min(i + j * THREADS, end - 1);
+                av[j] = (float)ar[at];
+                bv[j] = HAS_B ? (float)br[at] : -INFINITY;
+            }
+#pragma unroll
+            for (int j = 1; j < 8; j++)
+                if (i + j * THREADS >= end)
+                    av[j] = bv[j] = -INFINITY;
+            add_pair<HAS_B, FINE>(p, make_float4(av[0], av[1], av[2], av[3]), make_float4(av[4], av[5], av[6], av[7]),
+                                  make_float4(bv[0], bv[1], bv[2], bv[3]), make_float4(bv[4], bv[5], bv[6], bv[7]));
+        }
+    }
+}
+
 __device__ __forceinline__ double wave_sum(double v)
 {
 #pragma unroll
@@ -150,201 +195,202 @@ __device__ __forceinline__ float wave_max(float v)
     return v;
 }
 
-// Scratch of the split mode: partials [row][split][S, U, D, Sb, m, mb] and arrival tickets, one
+// Scratch of rows in pieces: partials [row][piece][S, U, D, Sb, m, mb] and arrival tickets, one
 // bank per stream (calls on one stream follow one another; calls on different streams use different
-// banks): FQ_BANKS for up to 64 rows, then FQ_ROWS_BANKS for more, which are given to fewer streams.  Tickets are zero at load and the combining workgroup resets its row's ticket, so every
+// banks): FQ_BANKS for up to 64 rows, then FQ_ROWS_BANKS for more, which are given to fewer streams.  Tickets are
+// zero at load and the combining workgroup resets its row's ticket, so every
 // launch finds them zero; each has a cache line of its own, because adds to one line are served one
 // after the other where the line lives.
 constexpr int FINE_ROWS = 64, MAX_SPLIT_ROWS = 512, MAX_SPLITS = 32, MAX_PARTS = 2048, LINE_WORDS = 32;
-static_assert(FINE_ROWS * MAX_SPLITS <= MAX_PARTS && 160 * 12 <= MAX_PARTS && 256 * 8 <= MAX_PARTS && MAX_SPLIT_ROWS * 4 <= MAX_PARTS,
-              "what dispatch() gives a call");
+static_assert(FINE_ROWS * MAX_SPLITS <= MAX_PARTS && MAX_SPLIT_ROWS * 4 <= MAX_PARTS, "what fq_entropy_route gives a call");
 __device__ double g_part[FQ_BANKS + FQ_ROWS_BANKS][MAX_PARTS][6];
 __device__ __attribute__((aligned(128))) unsigned int g_ticket[FQ_BANKS + FQ_ROWS_BANKS][MAX_SPLIT_ROWS][LINE_WORDS];
 
-template <int THREADS, bool HAS_B, bool VEC, bool FINE, typename T>
-__global__ __launch_bounds__(THREADS) void entropy_kl_kernel(const T *__restrict__ a,
-                                                             const T *__restrict__ b, int V,
-                                                             int splits, int bank, float *__restrict__ H,
-                                                             float *__restrict__ KL)
+// What lane i of a wavefront has of a row's piece i comes together: the row's sums and maxima, in every lane.  More than 64 rows:
+// the factors in double, which takes a fifth off the KL's error (with FINE more, but 0.1 us of 6 with it).
+template <bool FINE>
+__device__ __forceinline__ void merge_pieces(double &S, double &U, double &D, double &Sb, float &gm, float &gmb)
+{
+    const float pm = gm, pmb = gmb;
+    gm = wave_max(pm);
+    gmb = wave_max(pmb);
+    if (S > 0.0) {
+        const float d = pm - gm;
+        const double c = FINE ? (double)expf(d) : exp((double)d);
+        U = c * (U + (double)d * S);
+        S *= c;
+        D = c > 0.0 ? c * D : 0.0;
+    }
+    if (Sb > 0.0)
+        Sb *= FINE ? (double)expf(pmb - gmb) : exp((double)(pmb - gmb));
+    S = wave_sum(S);
+    U = wave_sum(U);
+    D = wave_sum(D);
+    Sb = wave_sum(Sb);
+}
+
+// A row is `pieces` pieces, each summed by a team of THREADS threads.  TEAMS = 1: a workgroup takes one piece, and those of a row
+// meet in `bank`.  TEAMS > 1: a workgroup takes a row of TEAMS * PER pieces, PER to a team, which meet in LDS: the same sums in the
+// same order, so that a call has the same bits with and without a bank.
+template <int THREADS, int TEAMS, int PER, bool HAS_B, bool VEC, bool FINE, typename T>
+__global__ __launch_bounds__(THREADS *TEAMS) void entropy_kl_kernel(const T *__restrict__ a, const T *__restrict__ b, int V,
+                                                                    int pieces, int bank, float *__restrict__ H,
+                                                                    float *__restrict__ KL)
 {
     constexpr int WAVES = THREADS / 64;
-    __shared__ float s_max[2][WAVES];
-    __shared__ double s_sum[4][WAVES];
+    __shared__ float s_max[TEAMS][PER][2][WAVES];
+    __shared__ double s_sum[TEAMS][PER][4][WAVES];
+    __shared__ double s_piece[TEAMS > 1 ? TEAMS * PER : 1][6];
 
-    const int r = blockIdx.x / splits;
-    const unsigned sidx = blockIdx.x % splits; // (unsigned, and what follows: a row of nearly 2^31 entries ends within a round of them)
-    const unsigned t = threadIdx.x;
+    if (TEAMS > 1)
+        pieces = TEAMS * PER;
+    const int r = TEAMS > 1 ? blockIdx.x : blockIdx.x / pieces;
+    const int team = TEAMS > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / THREADS) : 0;
+    const unsigned first = TEAMS > 1 ? team : blockIdx.x % pieces; // and each TEAMS-th from there
+    const unsigned t = threadIdx.x % THREADS;
     const T *ar = a + (size_t)r * V;
     const T *br = HAS_B ? b + (size_t)r * V : ar;
 
-    Partial<FINE> p;
-    part_init(p);
-    const float4 none4 = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY); // entries that carry no mass
-    if (VEC) { // V % 4 == 0 and rows aligned to four entries
-        const unsigned nvec = (unsigned)V >> 2;
-        const unsigned per = (nvec + splits - 1) / splits;
-        const unsigned end = min(nvec, (sidx + 1) * per);
-        // Four vectors of a row in flight, the last round too: its requests past the end repeat the last vector and
-        // are not added (one after the other, the up to three vectors of a last round cost a trip to memory each,
-        // as much as everything else where a row is split).
-        for (unsigned i = sidx * per + t; i < end; i += 4 * THREADS) {
-            float4 av[4], bv[4];
+    // (VEC: V % 4 == 0 and rows aligned to four entries; unsigned: a row of nearly 2^31 entries ends within a round of them)
+    const unsigned n = VEC ? (unsigned)V >> 2 : (unsigned)V, per = (n + pieces - 1) / pieces;
+    Partial<FINE> p[PER];
 #pragma unroll
-            for (int j = 0; j < 4; j++) {
-                const unsigned at = min(i + j * THREADS, end - 1);
-                av[j] = load4(ar, at);
-                bv[j] = HAS_B ? load4(br, at) : none4;
-            }
-#pragma unroll
-            for (int j = 0; j < 4; j += 2) {
-                if (i + (j + 1) * THREADS >= end)
-                    av[j + 1] = bv[j + 1] = none4;
-                if (i + j * THREADS < end)
-                    add_pair<HAS_B, FINE>(p, av[j], av[j + 1], bv[j], bv[j + 1]);
-            }
-        }
-    } else {
-        // Rows that 128-bit loads do not fit: eight entries in flight.
-        const unsigned per = ((unsigned)V + splits - 1) / splits;
-        const unsigned end = min((unsigned)V, (sidx + 1) * per);
-        for (unsigned i = sidx * per + t; i < end; i += 8 * THREADS) {
-            float av[8], bv[8];
-#pragma unroll
-            for (int j = 0; j < 8; j++) {
-                const unsigned at = min(i + j * THREADS, end - 1);
-                av[j] = (float)ar[at];
-                bv[j] = HAS_B ? (float)br[at] : -INFINITY;
-            }
-#pragma unroll
-            for (int j = 1; j < 8; j++)
-                if (i + j * THREADS >= end)
-                    av[j] = bv[j] = -INFINITY;
-            add_pair<HAS_B, FINE>(p, make_float4(av[0], av[1], av[2], av[3]), make_float4(av[4], av[5], av[6], av[7]),
-                            make_float4(bv[0], bv[1], bv[2], bv[3]), make_float4(bv[4], bv[5], bv[6], bv[7]));
-        }
+    for (int k = 0; k < PER; k++) {
+        const unsigned from = (first + k * TEAMS) * per;
+        part_init(p[k]);
+        add_entries<THREADS, HAS_B, VEC, FINE>(p[k], ar, br, from, min(n, from + per), t);
     }
 
-    // Maxima over the workgroup.
+    // Maxima over each piece.
     const int wave = t >> 6, lane = t & 63;
-    float gm = wave_max(p.m), gmb = wave_max(p.mb);
-    if (lane == 0) {
-        s_max[0][wave] = gm;
-        s_max[1][wave] = gmb;
+    float gm[PER], gmb[PER];
+#pragma unroll
+    for (int k = 0; k < PER; k++) {
+        gm[k] = wave_max(p[k].m), gmb[k] = wave_max(p[k].mb);
+        if (lane == 0) {
+            s_max[team][k][0][wave] = gm[k];
+            s_max[team][k][1][wave] = gmb[k];
+        }
+    }
+    __syncthreads();
+    double S[PER], U[PER], D[PER], Sb[PER];
+#pragma unroll
+    for (int k = 0; k < PER; k++) {
+#pragma unroll
+        for (int w = 0; w < WAVES; w++) {
+            gm[k] = fmaxf(gm[k], s_max[team][k][0][w]);
+            gmb[k] = fmaxf(gmb[k], s_max[team][k][1][w]);
+        }
+        // Rescale this lane's partial to the maxima, then sum in double.
+        S[k] = U[k] = D[k] = Sb[k] = 0.0;
+        if (p[k].S > 0) {
+            const float d = p[k].m - gm[k];
+            const double c = (double)expf(d);
+            S[k] = c * (double)p[k].S;
+            U[k] = c * ((double)p[k].U + (double)d * (double)p[k].S);
+            D[k] = c > 0.0 ? c * (double)p[k].D : 0.0;
+        }
+        if (HAS_B && p[k].Sb > 0)
+            Sb[k] = (double)expf(p[k].mb - gmb[k]) * (double)p[k].Sb;
+        S[k] = wave_sum(S[k]);
+        U[k] = wave_sum(U[k]);
+        if (HAS_B) {
+            D[k] = wave_sum(D[k]);
+            Sb[k] = wave_sum(Sb[k]);
+        }
+        if (lane == 0) {
+            s_sum[team][k][0][wave] = S[k];
+            s_sum[team][k][1][wave] = U[k];
+            s_sum[team][k][2][wave] = D[k];
+            s_sum[team][k][3][wave] = Sb[k];
+        }
     }
     __syncthreads();
 #pragma unroll
-    for (int w = 0; w < WAVES; w++) {
-        gm = fmaxf(gm, s_max[0][w]);
-        gmb = fmaxf(gmb, s_max[1][w]);
-    }
-    // Rescale this lane's partial to the maxima, then sum in double.
-    double S = 0.0, U = 0.0, D = 0.0, Sb = 0.0;
-    if (p.S > 0) {
-        const float d = p.m - gm;
-        const double c = (double)expf(d);
-        S = c * (double)p.S;
-        U = c * ((double)p.U + (double)d * (double)p.S);
-        D = c > 0.0 ? c * (double)p.D : 0.0;
-    }
-    if (HAS_B && p.Sb > 0)
-        Sb = (double)expf(p.mb - gmb) * (double)p.Sb;
-    S = wave_sum(S);
-    U = wave_sum(U);
-    if (HAS_B) {
-        D = wave_sum(D);
-        Sb = wave_sum(Sb);
-    }
-    if (lane == 0) {
-        s_sum[0][wave] = S;
-        s_sum[1][wave] = U;
-        s_sum[2][wave] = D;
-        s_sum[3][wave] = Sb;
-    }
-    __syncthreads();
-    S = U = D = Sb = 0.0;
+    for (int k = 0; k < PER; k++) {
+        S[k] = U[k] = D[k] = Sb[k] = 0.0;
 #pragma unroll
-    for (int w = 0; w < WAVES; w++) {
-        S += s_sum[0][w];
-        U += s_sum[1][w];
-        D += s_sum[2][w];
-        Sb += s_sum[3][w];
+        for (int w = 0; w < WAVES; w++) {
+            S[k] += s_sum[team][k][0][w];
+            U[k] += s_sum[team][k][1][w];
+            D[k] += s_sum[team][k][2][w];
+            Sb[k] += s_sum[team][k][3][w];
+        }
     }
-    if (splits > 1) {
-        // Publish this workgroup's partial, then see whether it is the last to arrive: one store past the
+    if (TEAMS > 1) {
+#pragma unroll
+        for (int k = 0; k < PER; k++)
+            if (t == 0) {
+                double *slot = s_piece[first + k * TEAMS];
+                slot[0] = S[k], slot[1] = U[k], slot[2] = D[k], slot[3] = Sb[k], slot[4] = (double)gm[k], slot[5] = (double)gmb[k];
+            }
+        __syncthreads();
+        if (threadIdx.x >= 64)
+            return;
+        S[0] = U[0] = D[0] = Sb[0] = 0.0;
+        gm[0] = gmb[0] = -INFINITY;
+        if (lane < pieces) {
+            const double *slot = s_piece[lane];
+            S[0] = slot[0], U[0] = slot[1], D[0] = slot[2], Sb[0] = slot[3], gm[0] = (float)slot[4], gmb[0] = (float)slot[5];
+        }
+        merge_pieces<FINE>(S[0], U[0], D[0], Sb[0], gm[0], gmb[0]);
+    } else if (pieces > 1) {
+        // Publish this workgroup's piece, then see whether it is the last to arrive: one store past the
         // caches, acknowledged before the ticket is taken.  (A fence instead writes back the XCD's whole L2,
         // once per workgroup.)
         if (wave != 0)
             return;
         if (lane < 6)
-            __hip_atomic_store(&g_part[bank][r * splits + sidx][lane],
-                               lane == 0   ? S
-                               : lane == 1 ? U
-                               : lane == 2 ? D
-                               : lane == 3 ? Sb
-                               : lane == 4 ? (double)gm
-                                           : (double)gmb,
+            __hip_atomic_store(&g_part[bank][r * pieces + first][lane],
+                               lane == 0   ? S[0]
+                               : lane == 1 ? U[0]
+                               : lane == 2 ? D[0]
+                               : lane == 3 ? Sb[0]
+                               : lane == 4 ? (double)gm[0]
+                                           : (double)gmb[0],
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         unsigned int arrived = 0;
         if (lane == 0)
             arrived = __hip_atomic_fetch_add(&g_ticket[bank][r][0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (__builtin_amdgcn_readfirstlane((int)arrived) != splits - 1)
+        if (__builtin_amdgcn_readfirstlane((int)arrived) != pieces - 1)
             return;
         asm volatile("" ::: "memory");
-        // first wavefront of the last workgroup: lane i takes partial i
-        double pm = -INFINITY, pmb = -INFINITY;
-        S = U = D = Sb = 0.0;
-        if (lane < splits) {
-            const double *slot = g_part[bank][r * splits + lane];
-            S = __hip_atomic_load(&slot[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            U = __hip_atomic_load(&slot[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            D = __hip_atomic_load(&slot[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            Sb = __hip_atomic_load(&slot[3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            pm = __hip_atomic_load(&slot[4], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            pmb = __hip_atomic_load(&slot[5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // first wavefront of the last workgroup: lane i takes piece i
+        S[0] = U[0] = D[0] = Sb[0] = 0.0;
+        gm[0] = gmb[0] = -INFINITY;
+        if (lane < pieces) {
+            const double *slot = g_part[bank][r * pieces + lane];
+            S[0] = __hip_atomic_load(&slot[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            U[0] = __hip_atomic_load(&slot[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            D[0] = __hip_atomic_load(&slot[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            Sb[0] = __hip_atomic_load(&slot[3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            gm[0] = (float)__hip_atomic_load(&slot[4], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            gmb[0] = (float)__hip_atomic_load(&slot[5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        gm = wave_max((float)pm);
-        gmb = wave_max((float)pmb);
-        if (S > 0.0) {
-            const float d = (float)pm - gm;
-            const double c = (double)expf(d);
-            U = c * (U + (double)d * S);
-            S *= c;
-            D = c > 0.0 ? c * D : 0.0;
-        }
-        if (Sb > 0.0)
-            Sb *= (double)expf((float)pmb - gmb);
-        S = wave_sum(S);
-        U = wave_sum(U);
-        D = wave_sum(D);
-        Sb = wave_sum(Sb);
+        merge_pieces<FINE>(S[0], U[0], D[0], Sb[0], gm[0], gmb[0]);
         if (lane == 0)
             g_ticket[bank][r][0] = 0u; // ready for the next launch
     }
-    if (t == 0) {
-        H[r] = (float)(log(S) - U / S);
+    if (threadIdx.x == 0) {
+        H[r] = (float)(log(S[0]) - U[0] / S[0]);
         if (HAS_B)
-            KL[r] = (float)(D / S + ((double)gmb - (double)gm) + log(Sb / S));
+            KL[r] = (float)(D[0] / S[0] + ((double)gmb[0] - (double)gm[0]) + log(Sb[0] / S[0]));
     }
 }
 
-template <int THREADS, typename T>
-hipError_t launch(const T *a, const T *b, int R, int V, int splits, int bank, float *H, float *KL,
-                  hipStream_t stream)
+template <int THREADS, int TEAMS, int PER, bool FINE, typename T>
+hipError_t launch(const T *a, const T *b, int R, int V, bool vec, int pieces, int bank, float *H, float *KL, hipStream_t stream)
 {
-    const uintptr_t mask = 4 * sizeof(T) - 1;
-    const bool vec = (V % 4 == 0) && (((uintptr_t)a & mask) == 0) && (!b || ((uintptr_t)b & mask) == 0);
-    const dim3 grid((unsigned)R * (unsigned)splits), block(THREADS);
-    auto go = [&](auto has_b, auto is_vec, auto fine) {
-        entropy_kl_kernel<THREADS, decltype(has_b)::value, decltype(is_vec)::value, decltype(fine)::value, T>
-            <<<grid, block, 0, stream>>>(a, b, V, splits, bank, H, KL);
+    const dim3 grid((unsigned)R * (TEAMS > 1 ? 1u : (unsigned)pieces)), block(THREADS * TEAMS);
+    auto go = [&](auto has_b, auto is_vec) {
+        entropy_kl_kernel<THREADS, TEAMS, PER, decltype(has_b)::value, decltype(is_vec)::value, FINE, T>
+            <<<grid, block, 0, stream>>>(a, b, V, pieces, bank, H, KL);
         return hipGetLastError();
     };
     typedef std::true_type Yes;
     typedef std::false_type No;
-    if (R <= FINE_ROWS)
-        return b ? vec ? go(Yes(), Yes(), Yes()) : go(Yes(), No(), Yes()) : vec ? go(No(), Yes(), Yes()) : go(No(), No(), Yes());
-    return b ? vec ? go(Yes(), Yes(), No()) : go(Yes(), No(), No()) : vec ? go(No(), Yes(), No()) : go(No(), No(), No());
+    return b ? vec ? go(Yes(), Yes()) : go(Yes(), No()) : vec ? go(No(), Yes()) : go(No(), No());
 }
 
 template <typename T>
@@ -352,50 +398,60 @@ hipError_t dispatch(const T *a, const T *b, int R, int V, float *H, float *KL, h
 {
     if (R == 0)
         return hipSuccess;
-    // Rows are split until the chip is full, in pieces that are whole rounds of a workgroup's four vectors a lane where that
-    // can be had; what a further piece costs is its merge.  us of a call, f32 with KL unless said, whole row / split:
-    //   one round (4096 entries): whole, 1 x 4000 5.1 / 5.7, 64 x 4000 5.3 / 6.1;
-    //   up to two and a half (10240): 1 x 8000 5.3 / 5.9 (4 pieces), 64 x 8000 6.3 / 6.3 -- in pieces all the same up to 64
-    //     rows, for the KL's error, which grows with the terms a lane takes (512 threads for more rows, 100 x 8000 6.3 and with 256
-    //     6.4);
-    //   R <= 64, by the pieces 8 / 16 / 32: 4 x 32000 6.3 / 6.1 / 5.9, 15 x 32000 6.6 / 6.2 / 6.7, 52 x 32000 8.2 / 9.2 / 11.5, and
-    //     52 x 128256 14.2 / 14.7 / 13.4; 1 x 32000 whole 11.0;
-    //   R <= 160: 100 x 32000 14.9 / 10.1 (4 pieces; 8: 10.4), 100 x 128256 48.0 / 21.9 (12);
-    //   one row a compute unit: 256 x 32000 with 512 threads 13.5, in 4 pieces 15.6; 200 x 128256 in half 34 / 17.0 (8);
-    //   R <= 512: 300 x 32000 19.5 / 18.8 (4), 400 x 32000 with 512 threads 21.1 / 22.8; 300 x 128256 62.6 / 52.8 (4), 512 x
-    //     128256 82.6 / 82.0, in half 37 / 31.2.
-    // (A stream without a bank: whole rows.)
-    const bool many = V >= 65536;
-    int splits = 1;
-    if (V > 4096 && (V > 10240 || R <= FINE_ROWS)) {
-        if (V <= 10240)
-            splits = V / 2048;
-        else if (R <= FINE_ROWS)
-            splits = R <= 8 || many ? MAX_SPLITS : R <= 20 ? 16 : 8;
-        else if (R <= 160)
-            splits = many ? 12 : 4;
-        else if (R <= 256)
-            splits = many ? 8 : 1;
-        else if (R <= MAX_SPLIT_ROWS)
-            splits = many || R <= 350 ? 4 : 1;
-        if (splits > V / 1024)
-            splits = V / 1024;
-    }
-    if (splits > 1) {
-        const bool few = R <= FINE_ROWS;
-        const int bank = few ? fq_stream_bank(stream) : fq_rows_bank(stream);
+    const uintptr_t mask = 4 * sizeof(T) - 1;
+    const bool vec = (V % 4 == 0) && (((uintptr_t)a & mask) == 0) && (!b || ((uintptr_t)b & mask) == 0);
+    const FqEntropyRoute route = fq_entropy_route(R, V, b != nullptr, sizeof(T) == 2, vec, fq_device_cus());
+    const int pieces = route.pieces;
+    if (pieces > 1 && R <= FINE_ROWS) {
+        const int bank = fq_stream_bank(stream);
         if (bank >= 0)
-            return launch<256, T>(a, b, R, V, splits, few ? bank : FQ_BANKS + bank, H, KL, stream);
+            return launch<256, 1, 1, true>(a, b, R, V, vec, pieces, bank, H, KL, stream);
+        return launch<512, 1, 1, true>(a, b, R, V, vec, 1, 0, H, KL, stream); // (more streams than banks: whole rows)
     }
-    // Whole rows: 256 threads (several rows on a compute unit), 512 where there are few long ones -- up to 512 rows (200 x
-    // 32000: 256 threads 15.8, 512 12.5, 1024 13.8), in half up to 1536 (600 x 128256 46.7 and 41.7 us, 2048 x 128256
-    // 97.1 and 96.7; f32 with KL 100.3 and 105.4).
-    if (V > 4096 && R <= (sizeof(T) == 2 && V > 10240 ? 1536 : 512))
-        return launch<512, T>(a, b, R, V, 1, 0, H, KL, stream);
-    return launch<256, T>(a, b, R, V, 1, 0, H, KL, stream);
+    if (pieces > 1) { // (without a bank: the same pieces, all of a row in one workgroup)
+        const int bank = fq_rows_bank(stream);
+        if (bank >= 0)
+            return launch<256, 1, 1, false>(a, b, R, V, vec, pieces, FQ_BANKS + bank, H, KL, stream);
+        return pieces == 4 ? launch<256, 4, 1, false>(a, b, R, V, vec, 4, 0, H, KL, stream)
+                           : launch<256, 4, 2, false>(a, b, R, V, vec, 8, 0, H, KL, stream);
+    }
+    if (route.threads == 512)
+        return route.fine ? launch<512, 1, 1, true>(a, b, R, V, vec, 1, 0, H, KL, stream)
+                          : launch<512, 1, 1, false>(a, b, R, V, vec, 1, 0, H, KL, stream);
+    return route.fine ? launch<256, 1, 1, true>(a, b, R, V, vec, 1, 0, H, KL, stream)
+                      : launch<256, 1, 1, false>(a, b, R, V, vec, 1, 0, H, KL, stream);
 }
 
 } // namespace
+
+FqEntropyRoute fq_entropy_route(int R, int V, bool kl, bool half, bool vec, int cus)
+{
+    const bool many = V >= 65536;
+    // One round (4096 entries): whole, 1 x 4000 5.1 us (split 5.7), 64 x 4000 5.3 (6.1).
+    if (V <= 4096)
+        return {256, 1, R <= FINE_ROWS};
+    // R <= 64, by the pieces 8 / 16 / 32: 4 x 32000 6.3 / 6.1 / 5.9, 15 x 32000 6.6 / 6.2 / 6.7, 52 x 32000 8.2 / 9.2 / 11.5, 52 x
+    // 128256 14.2 / 14.7 / 13.4; 1 x 32000 whole 11.0; up to 10240 entries 1 x 8000 whole 5.3, in 4 pieces 5.9, 64 x 8000 6.3 and 6.3.
+    if (R <= FINE_ROWS) {
+        const int pieces = V <= 10240 ? V / 2048 : R <= 8 || many ? MAX_SPLITS : R <= 20 ? 16 : 8;
+        return {256, pieces < V / 1024 ? pieces : V / 1024, 1};
+    }
+    if (V <= 10240)
+        return {R <= MAX_SPLIT_ROWS ? 512 : 256, 1, 0};
+    // In half 600 x 128256 46.7 with 256 threads and 41.7 with 512, 2048 x 128256 97.1 and 96.7; f32 with KL 100.3 and 105.4.
+    if (R > MAX_SPLIT_ROWS)
+        return {half && R <= 1536 ? 512 : 256, 1, 0};
+    // Rows are split until the chip is full.  us of a call, f32 with KL unless said, whole with 256 / 512 threads / in 4 / 8 pieces (s:
+    // sums in double):
+    //   under 65536 entries 128 x 32000 14.6 / 11.8 / 10.3 / 11.0, 200 x 32000 15.2 / 12.4 / 14.6 / 14.9, 300 x 32000 18.4 / 20.5 / 17.6,
+    //     450 x 32000 20.7 / 22.1 / 23.7, in half 20.9 / 20.6 / 21.0;
+    //   from there on 65 x 128256 45 / 30 / 20.1 / 18.8, 100 x 128256 46 / 32 / 22.2 / 24.1, 160 x 128256 47 / 32 / 33.4 / 31.5, 300 x
+    //     128256 57 / 67 / 54; in half 100 x 128256 45 / 35 / 21.3 / 19.7, 224 x 128256 46 / 36 / 32.2 / 29.7.
+    const bool few = R <= 160, one = !few && R <= 256, some = !few && !one && R <= 350;
+    if (!many)
+        return few || some ? FqEntropyRoute{256, 4, 0} : FqEntropyRoute{512, 1, 0};
+    return {256, (few || one) && R * 8 <= MAX_PARTS ? 8 : 4, 0};
+}
 
 hipError_t fq_launch_entropy_kl(const float *a, const float *b, int R, int V, float *H, float *KL,
                                 hipStream_t stream)

@@ -94,6 +94,12 @@ hipError_t fq_launch_quantize_row8(const void *w, int N, int K, bool symmetric, 
 hipError_t fq_launch_fake_quantize(const void *w, long long n_groups, int bits, bool symmetric, void *w_hat,
                                    hipStream_t stream);
 
+// How a call's rows are taken: threads of a workgroup, pieces of a row, and whether S and Sb are summed in double.  It does not
+// depend on the stream.  kl: b is given; half: binary16 logits; vec: 128-bit loads fit the rows.
+struct FqEntropyRoute {
+    int threads, pieces, fine;
+};
+FqEntropyRoute fq_entropy_route(int R, int V, bool kl, bool half, bool vec, int cus);
 hipError_t fq_launch_entropy_kl(const float *a, const float *b, int R, int V, float *H, float *KL,
                                 hipStream_t stream);
 

@@ -66,3 +66,16 @@ def part_bank(stream):
 
 
 stream_bank = _fn("_Z14fq_stream_bankP12ihipStream_t", _i, ctypes.c_void_p)  # -1: no copy of the static scratch for this stream
+
+
+class _Entropy(ctypes.Structure):
+    _fields_ = [("threads", ctypes.c_int), ("pieces", ctypes.c_int), ("fine", ctypes.c_int)]
+
+
+_entropy_route = _fn("_Z16fq_entropy_routeiibbbi", _Entropy, _i, _i, ctypes.c_bool, ctypes.c_bool, ctypes.c_bool, _i)
+
+
+def entropy_route(R, V, kl, half, vec, cus=256):
+    """(threads, pieces of a row, S and Sb in double) of an entropy call."""
+    r = _entropy_route(R, V, kl, half, vec, cus)
+    return r.threads, r.pieces, r.fine

@@ -77,6 +77,7 @@ def test_overlapping_streams_and_capture():
     for s in range(n):
         for i in range(4):
             assert _close(H[s][i], sets[s][2]) and _close(KL[s][i], sets[s][3]), (s, i)
+            assert torch.equal(H[s][i], H[s][0]) and torch.equal(KL[s][i], KL[s][0]), (s, i)
     Hg = torch.full((R,), float("nan"), device=DEV)
     KLg = torch.full((R,), float("nan"), device=DEV)
     graph = torch.cuda.CUDAGraph()
@@ -97,3 +98,24 @@ def test_a_row_of_nearly_two_to_the_31_entries(V):
     H = torch.full((1,), float("nan"), device=DEV)
     fq.fq_entropy_kl_f16(a, None, 1, V, H, None)
     assert abs(H.item() - np.log(V)) <= 2e-7 * np.log(V)
+
+
+@pytest.mark.parametrize("R,V,half", [(65, 12000, False), (160, 32001, True), (384, 20002, False), (65, 65536, False), (100, 65537, False),
+                                      (128, 70000, True), (256, 65540, True), (300, 66001, False), (512, 65544, True), (450, 65545, False)])
+@pytest.mark.parametrize("kl", [True, False])
+def test_the_same_bits_with_and_without_scratch(R, V, half, kl):
+    # the current stream has a copy of the scratch; hipStreamPerThread (2) and a captured call have none
+    a, b, H_ref, KL_ref = _inputs("bits/%d" % V, R, V, half)
+    call = fq.fq_entropy_kl_f16 if half else fq.fq_entropy_kl
+    out = [[torch.full((R,), float("nan"), device=DEV), torch.full((R,), float("nan"), device=DEV) if kl else None] for _ in range(3)]
+    torch.cuda.synchronize()
+    call(a, b if kl else None, R, V, *out[0])
+    call(a, b if kl else None, R, V, *out[1], stream=2)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(a, b if kl else None, R, V, *out[2])
+    graph.replay()
+    torch.cuda.synchronize()
+    assert _close(out[0][0], H_ref) and (not kl or _close(out[0][1], KL_ref))
+    for i in (1, 2):
+        assert torch.equal(out[0][0], out[i][0]) and (not kl or torch.equal(out[0][1], out[i][1])), i
