@@ -56,8 +56,8 @@ __device__ __forceinline__ float4 load4(const _Float16 *row, size_t i)
 }
 
 // FINE: S and Sb in double.  In binary32 the small terms beside a lane's maximum, whose term is 1, are rounded at 2^-24, most of the
-// KL's error once a lane takes more than a vector.  For up to 64 rows, where a call waits for memory and not for
-// arithmetic (800 x 128256 in half would).
+// KL's error once a lane takes more than a vector (relative, 100 x 4096 with 256 threads 6.1e-6, with 1024 4.4e-6, FINE 1.1e-6).  For up to
+// 64 rows and for short ones, where a call waits for memory and not for arithmetic (800 x 128256 in half would).
 template <bool FINE>
 struct Partial {
     typedef std::conditional_t<FINE, double, float> Sum;
@@ -429,15 +429,16 @@ FqEntropyRoute fq_entropy_route(int R, int V, bool kl, bool half, bool vec, int 
     const bool many = V >= 65536;
     // One round (4096 entries): whole, 1 x 4000 5.1 us (split 5.7), 64 x 4000 5.3 (6.1).
     if (V <= 4096)
-        return {256, 1, R <= FINE_ROWS};
+        return {256, 1, R <= MAX_SPLIT_ROWS};
     // R <= 64, by the pieces 8 / 16 / 32: 4 x 32000 6.3 / 6.1 / 5.9, 15 x 32000 6.6 / 6.2 / 6.7, 52 x 32000 8.2 / 9.2 / 11.5, 52 x
     // 128256 14.2 / 14.7 / 13.4; 1 x 32000 whole 11.0; up to 10240 entries 1 x 8000 whole 5.3, in 4 pieces 5.9, 64 x 8000 6.3 and 6.3.
     if (R <= FINE_ROWS) {
         const int pieces = V <= 10240 ? V / 2048 : R <= 8 || many ? MAX_SPLITS : R <= 20 ? 16 : 8;
         return {256, pieces < V / 1024 ? pieces : V / 1024, 1};
     }
+    // (With 256 and 512 threads: 300 x 5000 7.2 and 8.0, 512 x 10240 9.9 and 11.2, 128 x 10240 without KL 5.8 and 5.3.)
     if (V <= 10240)
-        return {R <= MAX_SPLIT_ROWS ? 512 : 256, 1, 0};
+        return {!kl && R <= cus ? 512 : 256, 1, R <= MAX_SPLIT_ROWS};
     // In half 600 x 128256 46.7 with 256 threads and 41.7 with 512, 2048 x 128256 97.1 and 96.7; f32 with KL 100.3 and 105.4.
     if (R > MAX_SPLIT_ROWS)
         return {half && R <= 1536 ? 512 : 256, 1, 0};

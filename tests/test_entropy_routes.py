@@ -23,5 +23,5 @@ def test_pieces_fit_the_scratch_and_one_workgroup():
                             assert threads == 256 and R <= MAX_SPLIT_ROWS and R * pieces <= MAX_PARTS and V >= 1024 * pieces, where
                         if pieces > 1 and R > FINE_ROWS:  # what a workgroup of a whole row can take where the stream has no scratch
                             assert pieces in (4, 8) and not fine, where
-                        if R <= FINE_ROWS:
+                        if R <= FINE_ROWS or (R <= MAX_SPLIT_ROWS and V <= 10240):
                             assert fine, where
