@@ -145,22 +145,32 @@ __device__ __forceinline__ void add_entries(Partial<FINE> &p, const T *ar, const
     const float4 none4 = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY); // entries that carry no mass
     unsigned i = from + t;
     if (VEC) {
-        for (; i < end; i += 4 * THREADS) {
+        auto round = [&](auto full) {
+            constexpr bool FULL = decltype(full)::value;
             float4 av[4], bv[4];
 #pragma unroll
             for (unsigned j = 0; j < 4; j++) {
-                const unsigned at = min(i + j * THREADS, end - 1);
+                const unsigned at = FULL ? i + j * THREADS : min(i + j * THREADS, end - 1);
                 av[j] = load4(ar, at);
                 bv[j] = HAS_B ? load4(br, at) : none4;
             }
+            if (FULL)
+                __builtin_amdgcn_sched_barrier(0); // (else the first sums' waits come ahead of the last requests)
 #pragma unroll
             for (unsigned j = 0; j < 4; j += 2) {
-                if (i + (j + 1) * THREADS >= end)
+                if (!FULL && i + (j + 1) * THREADS >= end)
                     av[j + 1] = bv[j + 1] = none4;
-                if (i + j * THREADS < end)
+                if (FULL || i + j * THREADS < end)
                     add_pair<HAS_B, FINE>(p, av[j], av[j + 1], bv[j], bv[j + 1]);
             }
-        }
+        };
+        // Whole rounds without a look at the end where arithmetic counts, in half with b (450 x 128256 55.6 -> 51.8 us in four pieces, 256 x
+        // 100000 28.9 -> 27.1 in eight; in f32 no gain, without b 200 x 50000 in half 10.4 -> 11.6).
+        if (HAS_B && sizeof(T) == 2)
+            for (; from + 4 * THREADS <= end; from += 4 * THREADS, i += 4 * THREADS)
+                round(std::true_type());
+        for (; i < end; i += 4 * THREADS)
+            round(std::false_type());
     } else {
         for (; i < end; i += 8 * THREADS) {
             float av[8], bv[8];
@@ -242,8 +252,6 @@ __global__ __launch_bounds__(THREADS *TEAMS) void entropy_kl_kernel(const T *__r
     __shared__ double s_sum[TEAMS][PER][4][WAVES];
     __shared__ double s_piece[TEAMS > 1 ? TEAMS * PER : 1][6];
 
-    if (TEAMS > 1)
-        pieces = TEAMS * PER;
     const int r = TEAMS > 1 ? blockIdx.x : blockIdx.x / pieces;
     const int team = TEAMS > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / THREADS) : 0;
     const unsigned first = TEAMS > 1 ? team : blockIdx.x % pieces; // and each TEAMS-th from there
@@ -442,16 +450,23 @@ FqEntropyRoute fq_entropy_route(int R, int V, bool kl, bool half, bool vec, int 
     // In half 600 x 128256 46.7 with 256 threads and 41.7 with 512, 2048 x 128256 97.1 and 96.7; f32 with KL 100.3 and 105.4.
     if (R > MAX_SPLIT_ROWS)
         return {half && R <= 1536 ? 512 : 256, 1, 0};
-    // Rows are split until the chip is full.  us of a call, f32 with KL unless said, whole with 256 / 512 threads / in 4 / 8 pieces (s:
-    // sums in double):
-    //   under 65536 entries 128 x 32000 14.6 / 11.8 / 10.3 / 11.0, 200 x 32000 15.2 / 12.4 / 14.6 / 14.9, 300 x 32000 18.4 / 20.5 / 17.6,
-    //     450 x 32000 20.7 / 22.1 / 23.7, in half 20.9 / 20.6 / 21.0;
-    //   from there on 65 x 128256 45 / 30 / 20.1 / 18.8, 100 x 128256 46 / 32 / 22.2 / 24.1, 160 x 128256 47 / 32 / 33.4 / 31.5, 300 x
-    //     128256 57 / 67 / 54; in half 100 x 128256 45 / 35 / 21.3 / 19.7, 224 x 128256 46 / 36 / 32.2 / 29.7.
-    const bool few = R <= 160, one = !few && R <= 256, some = !few && !one && R <= 350;
+    // Rows are split until the chip is full.  us of a call in f32 with KL unless said, whole with 256 / with 512 threads / in 4 / in 8
+    // pieces; under 65536 entries:
+    //   128 x 32000 14.6 / 11.8 / 10.3 / 11.0, 200 x 32000 15.2 / 12.4 / 14.6 / 14.9, 300 x 32000 18.4 / 20.5 / 17.6, 350 x 12000 9.7 / 10.7 /
+    //   12.8, 350 x 50000 27.6 / 30.2 / 29.1, 450 x 32000 20.7 / 22.1 / 23.7 and in half 20.9 / 20.6 / 21.0;
+    // from there on:
+    //   65 x 128256 45 / 30 / 20.1 / 18.8, 100 x 128256 46 / 32 / 22.2 / 24.1, 160 x 128256 47 / 32 / 33.4 / 31.5, 300 x 128256 57 / 67 / 54, in
+    //   half 100 x 128256 45 / 35 / 21.3 / 19.7, 224 x 128256 46 / 36 / 32.2 / 29.7, 480 x 100000 47.5 / 46.0 / 43.8;
+    // the same with the whole rows' sums in double, which costs nothing where the chip waits for memory:
+    //   200 x 100000 39.5 / 29.5 / 34.6 / 32.7, 256 x 100000 41.0 / 35.1 / 37.9 / 38.4, 400 x 100000 52.6 / 58.3 / 59.6, 512 x 128256 81.4 / 83.5 /
+    //   83.9, and where 128-bit loads do not fit the rows 400 x 90001 62.6 / 54.7 / 52.0.
     if (!many)
-        return few || some ? FqEntropyRoute{256, 4, 0} : FqEntropyRoute{512, 1, 0};
-    return {256, (few || one) && R * 8 <= MAX_PARTS ? 8 : 4, 0};
+        return R <= cus * 5 / 8 || (R > cus && R * 256 <= (V >= 24576 ? 350 : 320) * cus) ? FqEntropyRoute{256, 4, 0} : FqEntropyRoute{512, 1, 0};
+    if (kl && !half && R > cus * 3 / 4 && R <= cus)
+        return {512, 1, 1};
+    if (kl && !half && vec && R > cus * 3 / 2)
+        return {256, 1, 1};
+    return {256, R <= cus && R * 8 <= MAX_PARTS ? 8 : 4, 0};
 }
 
 hipError_t fq_launch_entropy_kl(const float *a, const float *b, int R, int V, float *H, float *KL,

@@ -1,5 +1,8 @@
-"""How the entropies' rows are taken (fq_entropy_route, a host function): what the kernels and their scratch assume of it (CPU only)."""
+"""How the entropies' rows are taken (fq_entropy_route, a host function): what the kernels and their scratch assume of it, and its
+two sides at every line (CPU only)."""
 import random
+
+import pytest
 
 from plan_util import entropy_route
 
@@ -25,3 +28,19 @@ def test_pieces_fit_the_scratch_and_one_workgroup():
                             assert pieces in (4, 8) and not fine, where
                         if R <= FINE_ROWS or (R <= MAX_SPLIT_ROWS and V <= 10240):
                             assert fine, where
+
+
+@pytest.mark.parametrize("R,V,kl,half,vec,route", [
+    (64, 4096, True, False, True, (256, 1, 1)), (512, 4096, True, True, True, (256, 1, 1)), (513, 4096, True, False, True, (256, 1, 0)),
+    (64, 4097, True, False, False, (256, 2, 1)), (8, 32000, True, False, True, (256, 31, 1)), (9, 32000, True, False, True, (256, 16, 1)),
+    (21, 32000, True, False, True, (256, 8, 1)), (64, 65536, False, True, True, (256, 32, 1)),
+    (300, 10240, True, False, True, (256, 1, 1)), (256, 10240, False, False, True, (512, 1, 1)), (257, 10240, False, False, True, (256, 1, 1)),
+    (160, 32000, True, False, True, (256, 4, 0)), (161, 32000, True, False, True, (512, 1, 0)), (320, 24575, True, True, True, (256, 4, 0)),
+    (321, 24575, True, True, True, (512, 1, 0)), (350, 24576, True, True, True, (256, 4, 0)), (351, 24576, True, True, True, (512, 1, 0)), (160, 65535, True, False, False, (256, 4, 0)), (160, 65536, True, False, True, (256, 8, 0)), (384, 65536, True, False, True, (256, 4, 0)),
+    (192, 65536, True, False, True, (256, 8, 0)), (193, 65536, True, False, True, (512, 1, 1)),
+    (256, 65536, False, False, True, (256, 8, 0)), (256, 65536, True, True, True, (256, 8, 0)),
+    (257, 65536, True, False, True, (256, 4, 0)), (385, 65536, True, False, True, (256, 1, 1)), (385, 90001, True, False, False, (256, 4, 0)),
+    (385, 65536, False, False, True, (256, 4, 0)), (512, 65536, True, True, True, (256, 4, 0)), (513, 65536, True, True, True, (512, 1, 0)),
+    (1537, 65536, True, True, True, (256, 1, 0)), (513, 65536, True, False, True, (256, 1, 0))])
+def test_both_sides_of_the_lines(R, V, kl, half, vec, route):
+    assert entropy_route(R, V, kl, half, vec) == route
