@@ -578,22 +578,30 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 // Under this rule 0.85 of its time on average; one plan in a hundred is 1.06 to 1.19, where a workgroup's tiles are
 // one more than full runs or a round of the other kernel is just full.
 // 2- and 3-bit copies: the register-fed kernel loses more on them (over 800 timings of the 7B, 13B and 70B shapes' stages and of short rows, with
-// {2}, {3}, {2, 4, 8} and {3, 4, 8} resident, 0.70 of its time; 7B stages of {2, 4, 8} 0.54, of {3, 4, 8} 0.72), so that shorter rows come here;
-// rows of two part panels with a 2- or 3-bit copy alone stay (5120 inputs: 1.1, 1.05).  No more rows than above: at 27 x 8192 x 8192 3 bits
-// took 1.1 of its time here, 35 x 6000 x 5120 1.2.  Behind it: 8 x 6000 x 5120 of {3, 4, 8}, each with an x of its own (1.1),
-// and the 13B q/k/v stage of {2, 4, 8} when all three run at 2 bits,
-// 18.9 us against 17.0 (all at 4 bits 20.9 against 22.5, at 8 26.7 against 33.3).
+// {2}, {3}, {2, 4, 8} and {3, 4, 8} resident, 0.70 of its time; 7B stages of {2, 4, 8} 0.54, of {3, 4, 8} 0.72), so that shorter rows come here.
+// No more rows than above: at 27 x 8192 x 8192 3 bits took 1.1 of its time here, 35 x 6000 x 5120 1.2.  What stays (times here over
+// times there, each width for all entries and mixed):
+//   - rows of two part panels with a 2- or 3-bit copy alone (5120 inputs: 1.1, 1.05; it is why 3 bits count 13 and not 14 below);
+//   - several entries of part panels over up to 16 batch rows whose 64-row tiles fill their rounds: 5 x 6000 x 5120 {2, 4, 8} 1.08 / 1.04 /
+//     0.92 / 0.83, 8 x 6000 x 5120 {3, 4, 8} 1.02 / 1.03 / 0.96 / 1.12, 24 x 2048 x 6144 (full rounds) {2, 4, 8} 1.09 / 1.05 / 0.95 / 1.07; not
+//     60 x 512 x 6144, 0.98 / 0.93 / 0.82 / 0.82;
+//   - short entries of more than three panels over more than 16, each with an x of its own, which every workgroup reads again
+//     for each of its runs: 30 x 1000 x 8192 {3, 4, 8} 1.13 / 1.14 / 1.01 / 1.01, {2} 1.11 (one x for all 0.78 to 0.89; 60 x 512 x 6144, 24 x 1200 x
+//     11008 and 50 x 1000 x 8192, whose 64-row tiles leave a round unfilled, 0.95, 0.96 and 0.78 on average).
+// Behind the other kernel here: the 13B q/k/v stage of {2, 4, 8} when all three run at 2 bits, 18.9 us against 17.0 (all at 4 bits 20.9 against
+// 22.5, at 8 26.7 against 33.3, mixed 19.7 against 30.9), and up to 1.04 60 x 512 x 6144 and 24 x 1200 x 11008 at one narrow width over 32 rows.
 bool fq_batch_serves(const FqLinearDesc *table, int count, int M)
 {
     const int cus = fq_device_cus(), panel = batch_panel(M <= 16 ? 1 : 2);
     long long rows = 0, tiles = 0;
     double weight = 0, inputs = 0, padded = 0; // summed over the rows
-    bool four_alone = true, narrow = false;
+    bool four_alone = true, narrow = false, own_x = false;
     for (int i = 0; i < count; i++) {
         const FqLinearDesc &d = table[i];
         const int copies = (d.codes2 != nullptr) + (d.codes3 != nullptr) + (d.codes4 != nullptr) + (d.codes8 != nullptr) + (d.w16 != nullptr);
         const int per_group = (d.codes2 ? 11 : 0) + (d.codes3 ? 13 : 0) + (d.codes4 ? 17 : 0) + (d.codes8 ? 29 : 0) + (d.w16 ? 53 : 0); // about 3 * bits + 5
         narrow = narrow || d.codes2 || d.codes3;
+        own_x = own_x || d.x != table[0].x;
         four_alone = four_alone && !d.codes2 && !d.codes3 && !d.codes8 && !d.w16;
         rows += d.N;
         tiles += ((long long)d.N + 15) / 16;
@@ -609,6 +617,9 @@ bool fq_batch_serves(const FqLinearDesc *table, int count, int M)
         return false;
     const int rest = (int)(rows % (64 * cus));
     const bool filled = rows > 96 * cus && (rest == 0 || rest > 48 * cus);
+    const bool parts = inputs < (rest == 0 || rest > 60 * cus ? 0.8 : 0.7) * padded; // rows are mostly part panels
+    if (filled && narrow && (M <= 16 ? count > 1 && parts : own_x && rows <= 1024LL * count && inputs > 3.0 * panel * rows))
+        return false;
     return !(filled && four_alone && (M > 16 || padded > inputs));
 }
 

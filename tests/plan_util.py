@@ -28,13 +28,18 @@ class _Desc(ctypes.Structure):  # FqLinearDesc
 _batch_serves = _fn("_Z15fq_batch_servesPK12FqLinearDescii", ctypes.c_bool, ctypes.c_void_p, _i, _i)
 
 
-def batch_serves(entries, M):
-    """Whether a plan of (N, K, attached widths out of 4, 8, 16) runs on the small-batch kernel (sizes permitting)."""
+def batch_serves(entries, M, own_x=False):
+    """Whether a plan of (N, K, attached widths) runs on the small-batch kernel (sizes permitting); own_x: each entry has an x of its own."""
     table = (_Desc * len(entries))()
-    for d, (N, K, widths) in zip(table, entries):
-        d.N, d.K = N, K
-        d.codes4, d.codes8, d.w16 = (16 if b in widths else None for b in (4, 8, 16))
+    for i, (d, (N, K, widths)) in enumerate(zip(table, entries)):
+        d.N, d.K, d.x = N, K, 16 + 16 * (i if own_x else 0)
+        d.codes2, d.codes3, d.codes4, d.codes8, d.w16 = (16 if b in widths else None for b in (2, 3, 4, 8, 16))
     return _batch_serves(table, len(entries), M)
+
+
+batch_serves_narrow = _fn("_Z22fq_batch_serves_narrowiiii", ctypes.c_bool, _i, _i, _i, _i)  # a single call at 2 or 3 bits
+batch_serves_slab = _fn("_Z20fq_batch_serves_slabiii", ctypes.c_bool, _i, _i, _i)  # a slab of a 3-bit prompt
+
 
 _prompt_plan = _fn("_Z14fq_prompt_planiiiii", _Plan, _i, _i, _i, _i, _i)
 _w8a8_plan = _fn("_Z19fq_w8a8_prompt_planiiibii", _Plan, _i, _i, _i, ctypes.c_bool, _i, _i)

@@ -1,7 +1,7 @@
 """Host-side choices of the launch code that need no device (CPU only)."""
 import pytest
 
-from plan_util import batch_serves, batch_serves_linear, part_mutex, prompt_plan, w8a8_plan
+from plan_util import batch_serves, batch_serves_linear, batch_serves_narrow, batch_serves_slab, part_mutex, prompt_plan, w8a8_plan
 
 
 def test_calls_on_different_streams_and_devices_share_no_lock():
@@ -42,6 +42,47 @@ def test_stages_of_a_decoder_run_on_the_small_batch_kernel(stack, M, widths):
     ([(8192, 4096, (4, 8))] * 13, 16, False), ([(16, 4096, (4, 8))] * 65, 16, False)])  # rows and entries of a plan
 def test_plans_take_the_faster_small_batch_kernel(entries, M, batch):
     assert batch_serves(entries, M) is batch
+
+
+@pytest.mark.parametrize("widths", [(2,), (3,), (2, 4, 8), (3, 4, 8)])
+@pytest.mark.parametrize("M", [2, 16, 17, 32])
+@pytest.mark.parametrize("stack", list(STACKS))
+def test_stages_with_narrow_copies_run_on_the_small_batch_kernel(stack, M, widths):
+    h, ffn, kv = STACKS[stack]
+    for stage in ([(h, h), (kv, h), (kv, h)], [(h, h)], [(ffn, h)] * 2, [(h, ffn)]):
+        # (two part panels of x: a narrow copy alone over more than two tiles per compute unit stays)
+        stays = h == 5120 and len(stage) > 1 and len(widths) == 1 and M <= 16
+        assert batch_serves([(N, K, widths) for N, K in stage], M) is not stays, stage
+
+
+W2, W3 = (2, 4, 8), (3, 4, 8)
+
+
+@pytest.mark.parametrize("entries,M,own_x,batch", [
+    ([(16384, 512, (2,))] * 4, 2, False, False), ([(12289, 2048, (3,))], 17, False, False), ([(12289, 4096, (3,))], 17, False, True),
+    ([(30000, 3072, W2)] * 3, 2, False, True), ([(30000, 3072, (2,))] * 3, 2, False, False),            # short rows
+    ([(8192, 8192, (3,))] * 12, 16, True, True), ([(8192, 8192, (3,))] * 13, 16, True, False),          # rows of a plan
+    ([(6000, 5120, W2)] * 3, 16, True, True), ([(6000, 5120, W2)] * 5, 16, True, False),                # part panels, full rounds
+    ([(6000, 5120, W2)] * 5, 17, True, True), ([(6000, 5120, W3)] * 8, 2, False, False), ([(6000, 5120, (4, 8))] * 5, 16, True, True),
+    ([(30000, 5120, W2)], 16, False, True), ([(2048, 6144, W2)] * 24, 16, True, False), ([(512, 6144, W2)] * 60, 16, True, True),
+    ([(1000, 8192, W3)] * 30, 17, True, False), ([(1000, 8192, W3)] * 30, 17, False, True),             # short entries, an x each
+    ([(1000, 8192, W3)] * 30, 16, True, True), ([(1000, 8192, W3)] * 50, 32, True, True), ([(1200, 11008, W3)] * 24, 32, True, True),
+    ([(512, 6144, W3)] * 60, 32, True, True), ([(1000, 8192, (4, 8))] * 30, 32, True, True)])
+def test_plans_with_narrow_copies_take_the_faster_small_batch_kernel(entries, M, own_x, batch):
+    assert batch_serves(entries, M, own_x) is batch
+
+
+@pytest.mark.parametrize("bits", [2, 3])
+@pytest.mark.parametrize("N,K,M,batch", [(4096, 4096, 16, True), (8192, 128, 2, True), (8193, 1152, 20, False), (8193, 4096, 32, True), (8193, 5120, 16, False),
+                                         (8193, 5120, 17, True), (98304, 8192, 2, True), (98305, 8192, 2, False)])
+def test_single_narrow_calls_take_the_faster_small_batch_kernel(N, K, M, bits, batch):
+    assert batch_serves_narrow(N, K, bits, M) is batch
+
+
+@pytest.mark.parametrize("N,K,M,batch", [(4096, 4096, 32, True), (1000, 896, 2, False), (1000, 1024, 2, True), (16384, 5120, 32, True),
+                                         (16385, 5120, 32, False), (16385, 8192, 32, True)])
+def test_slabs_of_a_three_bit_prompt(N, K, M, batch):
+    assert batch_serves_slab(N, K, M) is batch
 
 
 @pytest.mark.parametrize("M,N,K,kind,plan", [
