@@ -311,9 +311,7 @@ int fq_linear(const fq_layer *layer, int bits, const void *x_fp16, int M, void *
                 return hip_fail(e, "fq_linear launch");
             return FQ_OK;
         }
-        int rows = M == 1 ? fq_decode_tile_rows(layer->N, layer->K, M) : fq_skinny_tile_rows(layer->N, M);
-        if (M > 1 && bits == 2 && rows == 16) // the K-split kernel takes 3, 4, 8 and 16 bits
-            rows = 64;
+        const int rows = M == 1 ? fq_decode_tile_rows(layer->N, layer->K, M) : fq_skinny_tile_rows(layer->N, M);
         const int tiles = (layer->N + rows - 1) / rows;
         e = M == 1 ? fq_launch_decode(&d, bits, nullptr, nullptr, 1, tiles, rows, layer->K, M, nullptr, (hipStream_t)stream)
                    : fq_launch_skinny(&d, bits, nullptr, nullptr, 1, tiles, rows, M, bits == 3, nullptr, nullptr, (hipStream_t)stream);

@@ -250,7 +250,7 @@ __device__ __forceinline__ void run_batch(Lds &L, const uint8_t *codes, const fl
         const uint32_t line0 = (uint32_t)k0 / 8 * BITS;
         auto issue = [&](u32x4 (&to)[2]) {
             // Past the last line the lanes ask beyond the buffer's end, which costs no access (fq_batch_at.h).  An odd
-            // number of groups at 4 bits: the second half of a row's last line is the next row's, and not used.
+            // number of groups at 2, 3 and 4 bits: the second half of a row's last line is the next row's, and not used.
             const uint32_t at = batch_request(row_bytes, lane_off, it, line0, il, LB);
             to[0] = load_piece<BITS>(wbuf, at);
             to[1] = load_piece<BITS>(wbuf, at + LB / 2);
@@ -529,12 +529,14 @@ struct Division {
 
 // x0, K0: what every entry reads, if they all read one x (else null): requested before anything else is known.  `step`:
 // batch_step of the grid.
-// NARROW: entries may hold 2- and 3-bit copies (the other instances are without their code and pointers).
+// NARROW: entries may hold 2- and 3-bit copies (the other instances are without their code and pointers); a single call's
+// instance with them meets nothing else.
 template <bool SINGLE, int MB, bool NARROW>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_batch_kernel(
     const FqLinearDesc single, int bits_host, const FqLinearDesc *__restrict__ table, const int32_t *__restrict__ bits_dev,
     int count, int M, int *flags, const uint16_t *x0, int K0, uint32_t step)
 {
+    constexpr bool WIDE = !SINGLE || !NARROW;
     __shared__ Lds L;
     Division<SINGLE, MB, NARROW> dv;
     dv.request_table(single, bits_host, table, bits_dev, count);
@@ -549,15 +551,15 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
     while (r.nt > 0) {
         const Run next = dv.next_run(r);
         const bool keep = next.nt > 0 && next.x == r.x && next.K == r.K && r.K <= Panel<MB>::KP;
-        if (r.bits == 4)
-            run_batch<4, MB>(L, r.codes, r.scales, r.zeros, r.x, r.y, r.N, r.K, M, r.t0, r.nt, there, keep);
-        else if (r.bits == 8)
-            run_batch<8, MB>(L, r.codes, r.scales, r.zeros, r.x, r.y, r.N, r.K, M, r.t0, r.nt, there, keep);
-        else if (NARROW && r.bits == 2)
+        if (NARROW && r.bits == 2)
             run_batch<2, MB>(L, r.codes, r.scales, r.zeros, r.x, r.y, r.N, r.K, M, r.t0, r.nt, there, keep);
         else if (NARROW && r.bits == 3)
             run_batch<3, MB>(L, r.codes, r.scales, r.zeros, r.x, r.y, r.N, r.K, M, r.t0, r.nt, there, keep);
-        else
+        else if (WIDE && r.bits == 4)
+            run_batch<4, MB>(L, r.codes, r.scales, r.zeros, r.x, r.y, r.N, r.K, M, r.t0, r.nt, there, keep);
+        else if (WIDE && r.bits == 8)
+            run_batch<8, MB>(L, r.codes, r.scales, r.zeros, r.x, r.y, r.N, r.K, M, r.t0, r.nt, there, keep);
+        else if (WIDE)
             run_batch<16, MB>(L, r.codes, nullptr, nullptr, r.x, r.y, r.N, r.K, M, r.t0, r.nt, there, keep);
         there = keep;
         r = next;
@@ -632,11 +634,10 @@ bool fq_batch_serves(const FqLinearDesc *table, int count, int M)
 // quarters full, 28672 x 8192: 0.92 to 0.99) or over a K that leaves part of a panel of x (5120: 1.08; 4096: 0.93,
 // 8192: 0.95), up to six rounds (beyond: 0.75 to 1.0).  With 512 rows per compute unit it goes over to larger tiles and is as good or better (131072 rows at 4 bits: 1.1 to 2.9).  Under this rule
 // 0.86 of the register-fed kernel's time on average over 5900 calls; one shape stays behind it (29696 x 5120 at 16 bits, 1.14).
-// 2 and 3 bits: this kernel does not unpack them.
 bool fq_batch_serves_linear(int N, int K, int bits, int M)
 {
     const int cus = fq_device_cus();
-    if (bits == 2 || bits == 3 || fq_skinny_tile_rows(N, M) > 64)
+    if (fq_skinny_tile_rows(N, M) > 64)
         return false;
     if ((N + 15) / 16 <= 3 * cus)
         return true;

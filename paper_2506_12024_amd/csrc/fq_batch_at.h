@@ -5,7 +5,7 @@
 // in range must not depend on the scalar offset of the instruction (compilers are free to leave it out of the
 // check, and a scalar offset beyond the descriptor's size has no defined meaning), so tile, line and half
 // line are all in the lane's offset and the scalar offset is zero.  Requests that leave the run -- rows past the
-// last one of a partial tile, the second half line of an odd last group at 4 bits, requests ahead past the
+// last one of a partial tile, the second half line of an odd last group at 2, 3 and 4 bits, requests ahead past the
 // last tile -- are then beyond the descriptor's end: no access, zeros.
 #ifndef FQ_BATCH_AT_H
 #define FQ_BATCH_AT_H

@@ -30,9 +30,10 @@
 // Both x and the metadata of chunk c + 1 are prefetched into registers while chunk c is
 // computed.
 //
-// Launches with few rows use a second kernel further down, in which the four wavefronts of a workgroup
-// share one row tile and split K.  What fq_batch.hip serves better goes there (single calls over rows that are not short,
-// plans of a decoder's stages); what is left here are short rows, plans of more than 64 small entries, plans between two
+// Plans with few rows use a second kernel further down, in which the four wavefronts of a workgroup
+// share one row tile and split K.  What fq_batch.hip serves better goes there (single calls over rows that are not short or over few
+// rows, plans of a decoder's stages); what is left here are short rows, plans of more than 64 small entries (the second kernel's,
+// unless one holds a 2-bit copy), plans between two
 // layers' size and the streaming kernel's, larger ones that hold a 3-bit copy, and most slabs of 3-bit prompts over short or many rows.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -631,9 +632,8 @@ __device__ __forceinline__ void run_tile_sk(const Sel &d, const uint16_t *x, uin
 
 // W3: with the 3-bit path (its unpacking and the regrouping of x cost registers: a launch that cannot
 // meet a 3-bit entry runs the instance without)
-template <bool SINGLE, int MT, bool W3>
-__global__ __launch_bounds__(WG_THREADS) void decode_skinny_sk_kernel(const FqLinearDesc single, int bits_host,
-                                                                      const FqLinearDesc *__restrict__ table,
+template <int MT, bool W3>
+__global__ __launch_bounds__(WG_THREADS) void decode_skinny_sk_kernel(const FqLinearDesc *__restrict__ table,
                                                                       const int32_t *__restrict__ bits_dev,
                                                                       int count, int total_tiles, int M, int *flags)
 {
@@ -645,17 +645,10 @@ __global__ __launch_bounds__(WG_THREADS) void decode_skinny_sk_kernel(const FqLi
     const int wave = threadIdx.x >> 6;
     int e = 0;
     for (int tile = blockIdx.x; tile < total_tiles; tile += gridDim.x) {
-        const FqLinearDesc *dp;
-        int bits;
-        if (SINGLE) {
-            dp = &single;
-            bits = bits_host;
-        } else {
-            while (e + 1 < count && tile >= table[e + 1].tile_begin)
-                e++;
-            dp = &table[e];
-            bits = bits_dev[e];
-        }
+        while (e + 1 < count && tile >= table[e + 1].tile_begin)
+            e++;
+        const FqLinearDesc *dp = &table[e];
+        const int bits = bits_dev[e];
         Sel d;
         d.N = dp->N;
         d.K = dp->K;
@@ -761,20 +754,12 @@ hipError_t launch(const FqLinearDesc *single, int bits_host, const FqLinearDesc 
 }
 
 template <int MT, bool W3>
-hipError_t launch_sk(const FqLinearDesc *single, int bits_host, const FqLinearDesc *descs_dev,
-                     const int32_t *bits_dev, int count, int total_tiles, int M, int cus, hipStream_t stream,
-                     int *flags = nullptr)
+hipError_t launch_sk(const FqLinearDesc *descs_dev, const int32_t *bits_dev, int count, int total_tiles, int M, int cus,
+                     hipStream_t stream, int *flags)
 {
-    const int cap = cus * fq_workgroups_per_cu((const void *)decode_skinny_sk_kernel<false, MT, W3>, WG_THREADS, 0, 2);
+    const int cap = cus * fq_workgroups_per_cu((const void *)decode_skinny_sk_kernel<MT, W3>, WG_THREADS, 0, 2);
     const int grid = total_tiles < cap ? total_tiles : cap;
-    if (single) {
-        decode_skinny_sk_kernel<true, MT, W3><<<grid, WG_THREADS, 0, stream>>>(*single, bits_host, nullptr, nullptr, 1,
-                                                                            total_tiles, M, nullptr);
-    } else {
-        FqLinearDesc none = {};
-        decode_skinny_sk_kernel<false, MT, W3><<<grid, WG_THREADS, 0, stream>>>(none, 0, descs_dev, bits_dev, count,
-                                                                             total_tiles, M, flags);
-    }
+    decode_skinny_sk_kernel<MT, W3><<<grid, WG_THREADS, 0, stream>>>(descs_dev, bits_dev, count, total_tiles, M, flags);
     return hipGetLastError();
 }
 
@@ -784,9 +769,12 @@ hipError_t launch_any(const FqLinearDesc *single, int bits_host, const FqLinearD
                       hipStream_t stream, int *fl)
 {
     const int rt = tile_rows / 64;
-    if (tile_rows == 16)
-        return M <= 16 ? launch_sk<1, W3>(single, bits_host, descs_dev, bits_dev, count, total_tiles, M, cus, stream, fl)
-                       : launch_sk<2, W3>(single, bits_host, descs_dev, bits_dev, count, total_tiles, M, cus, stream, fl);
+    if (tile_rows == 16) { // (single calls over so few rows run on the small-batch kernel)
+        if (single)
+            return hipErrorInvalidValue;
+        return M <= 16 ? launch_sk<1, W3>(descs_dev, bits_dev, count, total_tiles, M, cus, stream, fl)
+                       : launch_sk<2, W3>(descs_dev, bits_dev, count, total_tiles, M, cus, stream, fl);
+    }
     if (M <= 16) {
         if (rt == 4)
             return launch<1, 4, W3>(single, bits_host, descs_dev, bits_dev, count, total_tiles, M, cus, stream, fl);

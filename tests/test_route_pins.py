@@ -13,10 +13,10 @@ def test_calls_on_different_streams_and_devices_share_no_lock():
 
 @pytest.mark.parametrize("N,K,bits,M,batch", [
     (4096, 4096, 4, 16, True), (11008, 4096, 8, 32, True), (28672, 8192, 4, 16, True), (12288, 128, 4, 2, True),
-    # short rows over many tiles; many rows; tiles of the register-fed kernel that fill their rounds; 2 and 3 bits
+    # short rows over many tiles; many rows; tiles of the register-fed kernel that fill their rounds
     (32768, 512, 4, 16, False), (55552, 512, 4, 24, False), (65536, 1024, 8, 2, False), (40960, 512, 16, 17, False),
     (128256, 4096, 4, 16, True), (131071, 8192, 8, 32, True), (131072, 8192, 8, 32, False), (32768, 5120, 4, 16, False), (30720, 3072, 4, 32, False),
-    (32768, 4096, 4, 16, True), (32768, 4096, 4, 17, False), (28672, 8192, 4, 32, True), (28672, 3072, 4, 32, False), (4096, 4096, 2, 16, False), (4096, 4096, 3, 16, False)])
+    (32768, 4096, 4, 16, True), (32768, 4096, 4, 17, False), (28672, 8192, 4, 32, True), (28672, 3072, 4, 32, False)])
 def test_single_calls_take_the_faster_small_batch_kernel(N, K, bits, M, batch):
     # (a host without a device counts 256 compute units)
     assert batch_serves_linear(N, K, bits, M) is batch
