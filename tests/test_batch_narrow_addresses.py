@@ -1,6 +1,7 @@
 """The small-batch kernel's requests at 2 and 3 bits (csrc/fq_batch_at.h): two quantization groups of a row to a request,
 a lane's 8 or 12 bytes of each at a time.  Walked as the kernel walks them, every one stays inside the weight it reads and the
-run's rows are read whole; and a 3-bit block of 32 codes unpacks into the inputs' order (CPU only)."""
+run's rows are read whole (CPU only).  And the arithmetic by which a 3-bit block of 32 codes unpacks into the inputs' order, in
+a copy here: that masks, shifts and exponents give exact differences; the kernel's own are checked in test_gpu_batch_narrow.py."""
 import ctypes
 import itertools
 import os

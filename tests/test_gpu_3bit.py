@@ -11,6 +11,7 @@ import oracle
 import synth
 import paper_2506_12024_amd as fq
 from gpu_util import DEV, gpu_linear, gpu_quantize, make_layer, rel_err, to_dev
+from plan_util import batch_serves
 
 pytestmark = pytest.mark.gpu
 
@@ -181,15 +182,28 @@ def test_plans_with_3bit_entries_match_individual_calls_and_oracle():
 
 @pytest.mark.parametrize("M,widths", [(4, (3, 4, 8, 16)), (4, (2, 3, 4, 8, 16)), (20, (3, 4, 8, 16)), (16, (2, 3, 8))])
 def test_batched_plans_with_3bit_entries(M, widths):
-    # small plans: the kernel whose wavefronts split K (no layer holds a 2-bit copy) or the
-    # register-fed kernel in 64-row tiles; within tolerance of the oracle under patterns that move
+    # small plans, which the small-batch kernel serves; within tolerance of the oracle under patterns that move
     # the 3-bit entries around
     shapes = [(256, 1024), (100, 1408), (512, 4096), (64, 11008), (40, 128), (300, 4096)]
+    assert batch_serves([(N, K, widths) for N, K in shapes], M, own_x=True)
+    _batched_plan("bplan", shapes, M, widths)
+
+
+@pytest.mark.parametrize("M,widths", [(4, (3, 4, 8, 16)), (20, (3, 4, 8)), (16, (2, 3, 4)), (17, (2, 3))])
+def test_plans_of_many_small_entries_with_3bit_copies(M, widths):
+    # more than 64 entries: the kernel whose wavefronts split K, or, where a layer holds a 2-bit copy, the register-fed kernel in
+    # 64-row tiles
+    shapes = [(16, 1408), (40, 128), (33, 2176), (64, 640)] * 16 + [(17, 384), (100, 1152)]
+    assert not batch_serves([(N, K, widths) for N, K in shapes], M, own_x=True)
+    _batched_plan("many", shapes, M, widths)
+
+
+def _batched_plan(tag, shapes, M, widths):
     layers, xs, ys, xs_np, packs = [], [], [], [], []
     for i, (N, K) in enumerate(shapes):
-        w = synth.weight(0, "par3/bplan/w%d" % i, N, K, 0.02, outlier_p=0.001)
+        w = synth.weight(0, "par3/%s/w%d" % (tag, i), N, K, 0.02, outlier_p=0.001)
         layer, packed = make_layer(w, widths)
-        x = synth.activations(0, "par3/bplan/x%d/%d" % (i, M), M, K)
+        x = synth.activations(0, "par3/%s/x%d/%d" % (tag, i, M), M, K)
         layers.append(layer)
         packs.append((w, packed))
         xs_np.append(x)
