@@ -148,9 +148,11 @@ def _stream(stream):
     if stream is None:
         import torch
         # The current stream's handle without a Stream object around it, which took 2.9 us of a call (a 1 x 4096 -> 4096
-        # linear: 8.1 us a call with it, 5.4 without).  CUDA builds of torch have the two functions.
+        # linear: 8.1 us a call with it, 5.4 without).  The two functions are not public: a torch without them takes the public way.
         if torch.cuda.is_initialized():
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+            raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+            if raw and device:
+                return raw(device())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
