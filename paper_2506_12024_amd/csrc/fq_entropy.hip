@@ -7,7 +7,7 @@
 // workgroups per row, one to a piece of it, whose partials meet in a small static device array and are combined
 // by whichever workgroup arrives last (one launch either way; a single workgroup needs
 // 11 us for one 32000-entry pair, 32 of them 5.9).  Bound by HBM for many rows, by launch and
-// latency for few: 5 x 32000 6.1 us, 52 x 32000 8.2 (36 with a fence per partial and a ticket line shared by the rows).
+// latency for few: 5 x 32000 6.1 us, 52 x 32000 in half 8.1 (36 with a fence per partial and a ticket line shared by the rows).
 // Every lane keeps an online (running-max) partial
 //   m  = max a_i            S  = sum e^(a_i - m)
 //   U  = sum e^(a_i - m) (a_i - m)          D = sum e^(a_i - m) (a_i - b_i)

@@ -277,12 +277,12 @@ __global__ __launch_bounds__(THREADS) void lm_head_entropy_kernel(const uint16_t
     }
 }
 
-// Second launch (one workgroup): merges the workgroups' partials.  A separate launch because the
-// alternative, a ticket that lets the last workgroup do it, needs every workgroup to make its
-// partial visible to the other XCDs first, and that fence writes back an L2 per workgroup
-// (measured: 50 us for 1024 workgroups, more than the whole weight stream).
+// Second launch (one workgroup): merges the workgroups' partials.  Measured against a ticket that lets the last
+// workgroup do it behind a fence, which writes back an L2 per workgroup: 50 us for 1024 workgroups, more than the whole
+// weight stream.  A ticket without one (partials stored past the caches and acknowledged, as fq_entropy.hip hands its own
+// over) has not been measured here; what it could save is this launch, 3.8 to 4.6 us of a call.
 // One wavefront to a row of x, PER partials to a lane, all requested together; the maximum first, then the sums, in double
-// (4 x 1024 -> 8000: 3.4 us of a call of 12.8; 10.7 of 20.4 with one partial to each of 1024 threads, states merged pair by
+// (4 x 1024 -> 8000: 3.8 us of a call of 12.8; 10.4 of 20.4 with one partial to each of 1024 threads, states merged pair by
 // pair through the wavefront, LDS and once more).
 template <int PER>
 __global__ __launch_bounds__(64 * MAX_M) void lm_head_combine_kernel(int parts, int bank, float *__restrict__ H,

@@ -665,7 +665,8 @@ hipError_t fq_launch_w8a8(const FqLinearDesc &l, const void *xq, const float *sx
     // MFMAs instead of two (2048 x 28672, five rounds of the one against seven of the other: 1142 against
     // 1077 TOP/s), so the smaller one is taken only where its rounds (one workgroup per compute unit at a
     // time) cost at least an eighth less in all -- 2048 x 8192: 352 tiles of 192 are two rounds, 512
-    // tiles of 128 two rounds of two thirds the work (982 -> 1133 TOP/s).
+    // tiles of 128 two rounds of two thirds the work (982 -> 1133 TOP/s).  (The rates are from before a tile's end, which
+    // counts nowhere in this rule, became shorter.)
     int mt = MT_MAX;
     if (!per_row) {
         const long long t3 = (long long)((M + 191) / 192) * n_tiles, t2 = (long long)((M + 127) / 128) * n_tiles;

@@ -404,8 +404,11 @@ hipError_t launch(const Args &d, int segments, float *part, hipStream_t stream)
 }
 
 // Microseconds a call is expected to take, fitted to 9000 timings of forced plans (16 to 2048 tokens, 512 to 28672 rows, K
-// 128 to 28672; 10 and 12 % off on average, large tiles 9 and 11; the choice made from it costs 1 % over the best one; a
-// hand-over 1.2 more than fitted, for the host: a second launch).  A
+// 128 to 28672; 10 and 12 % off on average, large tiles 9 and 11; a hand-over 1.2 more than fitted, for the host: a second
+// launch).  The ends of the tiles of either size have become shorter since, and the constants are from before: over 246 calls of
+// those ranges, each under every plan, the choice takes 1.3 (groups) and 1.4 % (per row) more than the best one on average,
+// 86 % of them within 3 %, one in ten over 4 and the worst 13; few inputs are the worst of all, 1455 x 512 -> 22912 with one
+// scale per row 54.5 us in small tiles and 46.3 in the large ones.  A
 // round's end grows with its outputs: without that, and fitted from K = 1024 on, the model took three rounds of 192 x 128
 // tiles for two of 128 x 256 over few inputs (2048 x 128 .. 1536 -> 8192: 1.09 to 1.19 of the large tiles' time).
 struct Cost {
